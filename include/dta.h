@@ -233,7 +233,7 @@ int dta_tree_attn_bwd_stages(dta_tree_t* tree, const dta_attn_params_t* params, 
  * device memory: code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc.  Same arguments, results and bits as dta_tree_attn_bwd,
  * without the workspace: the scratch memory (row statistics, work-queue
- * counters, fp32 partial sums of split key tiles) is a device array of 160 MiB
+ * counters, fp32 partial sums of split key tiles) is a device array of 256 MiB
  * that the library holds on every GPU it runs on until the process ends.  The
  * call allocates and frees nothing, on the host side of HIP or on the device:
  *  - the tree's device metadata for this head configuration must already be
@@ -241,7 +241,7 @@ int dta_tree_attn_bwd_stages(dta_tree_t* tree, const dta_attn_params_t* params, 
  *    allocate, also resolves the scratch array's address on that device), else
  *    DTA_ERR_INVALID_ARG;
  *  - DTA_ERR_WORKSPACE, with a message on stderr, when
- *    dta_tree_attn_workspace_bytes(tree, params, 1) exceeds 160 MiB (trees of a
+ *    dta_tree_attn_workspace_bytes(tree, params, 1) exceeds 256 MiB (trees of a
  *    few hundred thousand tokens need 35 to 130 MiB; one whose long shared
  *    prefix is cut into many partial sums, like the 16K-token root of the deep
  *    benchmark tree with its 468 MiB, does not fit);

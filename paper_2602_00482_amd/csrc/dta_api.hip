@@ -26,22 +26,34 @@ size_t ticket_bytes(const dta_attn_params_t* p) {
   return round_up(2 * (size_t)p->n_kv_heads * sizeof(int), 256);
 }
 
-// delta plus, in bf16 mode, the rescaled lse, the ticket counters and the partial sums of split
-// key tiles (building the host schedule if this head configuration has not been seen yet)
-size_t bwd_workspace_bytes(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_params_t* p) {
-  size_t bytes = delta_bytes(tree, p);
-  if (p->dtype == DTA_BF16) {
-    bytes += delta_bytes(tree, p);   // lse in log2 units, same shape as delta
-    bytes += ticket_bytes(p);
-    try {
-      std::lock_guard<std::mutex> lock(tree->mu);
-      bytes += dta::partial_bytes(
-          dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads));
-    } catch (const std::bad_alloc&) {
-      return 0;
-    }
+// Backward workspace: delta; in bf16 mode the rescaled lse (same shape) and the ticket counters;
+// the partial sums of split key tiles
+size_t partial_offset(const dta_tree* tree, const dta_attn_params_t* p) {
+  return p->dtype == DTA_BF16 ? 2 * delta_bytes(tree, p) + ticket_bytes(p) : delta_bytes(tree, p);
+}
+
+// (builds the host schedule if this head configuration has not been seen yet); 0 when out of memory
+size_t bwd_workspace_bytes(dta_tree* tree, const dta_attn_params_t* p) {
+  dta::TileChoice tc;
+  if (dta::choose_tiles(p, &tc, tree->info.n_tokens) != DTA_OK) return 0;
+  try {
+    std::lock_guard<std::mutex> lock(tree->mu);
+    return partial_offset(tree, p) +
+           dta::partial_bytes(dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads,
+                                                p->n_q_heads / p->n_kv_heads, tc.q_rows));
+  } catch (const std::bad_alloc&) {
+    return 0;
   }
-  return bytes;
+}
+
+void set_workspace(dta::LaunchArgs& a, const dta_tree* tree, const dta_attn_params_t* p, void* workspace) {
+  char* ws = (char*)workspace;
+  a.delta = (float*)ws;
+  if (p->dtype == DTA_BF16) {
+    a.lse2 = (float*)(ws + delta_bytes(tree, p));
+    a.tickets = (int*)(ws + 2 * delta_bytes(tree, p));
+  }
+  a.partial = (float*)(ws + partial_offset(tree, p));
 }
 
 // Device metadata lives in blocks from a small pool of the library's own and is
@@ -226,7 +238,7 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
   if (!allocate_ok) {
     // a caller that must not allocate: everything has to be resident already
     // (dta_tree_attn_prepare on this device); look, do not build
-    const uint64_t key = dta::schedule_key(tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads);
+    const uint64_t key = dta::schedule_key(tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, tc.q_rows);
     auto it = tree->schedules.find(key);
     if (it == tree->schedules.end() || it->second.device != dev || tree->kend_device != dev ||
         !tree->last_use)
@@ -237,9 +249,9 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
   dta::Schedule* s;
   try {
     s = t_begin < 0
-            ? &dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads)
+            ? &dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, tc.q_rows)
             : &dta::get_segment_schedule(tree, tc.bm, tc.bn, p->n_kv_heads,
-                                         p->n_q_heads / p->n_kv_heads, t_begin, t_end);
+                                         p->n_q_heads / p->n_kv_heads, t_begin, t_end, tc.q_rows);
   } catch (const std::bad_alloc&) {
     return DTA_ERR_ALLOC;
   }
@@ -274,7 +286,6 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
     s->device = -1;
     if ((st = upload_parts(dev, us,
                            {part_of(s->q_tiles, &s->d_q_tiles), part_of(s->segs, &s->d_segs),
-                            part_of(s->kv_tiles, &s->d_kv_tiles),
                             part_of(s->kv_items, &s->d_kv_items),
                             part_of(s->kv_reduce, &s->d_kv_reduce)},
                            &s->d_blob, &s->d_blob_cap, t_begin < 0 ? nullptr : tree)) != DTA_OK)
@@ -336,16 +347,15 @@ void dta_tree_destroy(dta_tree_t* tree) {
 
 size_t dta_tree_attn_workspace_bytes(const dta_tree_t* tree, const dta_attn_params_t* params,
                                      int is_bwd) {
-  dta::TileChoice tc;
-  if (!tree || dta::choose_tiles(params, &tc) != DTA_OK) return 0;
+  if (!tree || dta::validate_params(params) != DTA_OK) return 0;
   if (!is_bwd) return params->dtype == DTA_BF16 ? ticket_bytes(params) : 0;
-  return bwd_workspace_bytes(const_cast<dta_tree*>(tree), tc, params);
+  return bwd_workspace_bytes(const_cast<dta_tree*>(tree), params);
 }
 
 int dta_tree_attn_prepare(dta_tree_t* tree, const dta_attn_params_t* params) {
   if (!tree) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc);
+  int st = dta::choose_tiles(params, &tc, tree->info.n_tokens);
   if (st != DTA_OK) return st;
   dta::Schedule* s = nullptr;
   if ((st = ensure_device(tree, tc, params, &s)) != DTA_OK) return st;
@@ -363,7 +373,7 @@ int dta_tree_attn_fwd(dta_tree_t* tree, const dta_attn_params_t* params, const v
                       size_t workspace_bytes, void* hip_stream) {
   if (!tree || !params) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc);
+  int st = dta::choose_tiles(params, &tc, tree->info.n_tokens);
   if (st != DTA_OK) return st;
   if (!q || !k || !v || !o || !lse) return DTA_ERR_INVALID_ARG;
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse))
@@ -406,9 +416,8 @@ int dta_tree_attn_bwd_stages(dta_tree_t* tree, const dta_attn_params_t* params, 
 namespace dta {
 
 size_t bwd_workspace_need(dta_tree* tree, const dta_attn_params_t* params) {
-  TileChoice tc;
-  if (!tree || choose_tiles(params, &tc) != DTA_OK) return 0;
-  return bwd_workspace_bytes(tree, tc, params);
+  if (!tree) return 0;
+  return bwd_workspace_bytes(tree, params);
 }
 
 int bwd_entry(dta_tree* tree, const dta_attn_params_t* params, const void* q, const void* k,
@@ -418,7 +427,7 @@ int bwd_entry(dta_tree* tree, const dta_attn_params_t* params, const void* q, co
   if (!tree || !params) return DTA_ERR_INVALID_ARG;
   if (stage_mask == 0 || (stage_mask & ~(uint32_t)DTA_BWD_ALL)) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc);
+  int st = dta::choose_tiles(params, &tc, tree->info.n_tokens);
   if (st != DTA_OK) return st;
   const bool want_dq = stage_mask & DTA_BWD_DQ, want_dkdv = stage_mask & DTA_BWD_DKDV;
   if (!q || !k || !v || !o || !lse || !d_o) return DTA_ERR_INVALID_ARG;
@@ -426,7 +435,7 @@ int bwd_entry(dta_tree* tree, const dta_attn_params_t* params, const void* q, co
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse) ||
       misaligned(d_o) || misaligned(dq) || misaligned(dk) || misaligned(dv))
     return DTA_ERR_INVALID_ARG;
-  if (!workspace || workspace_bytes < bwd_workspace_bytes(tree, tc, params) ||
+  if (!workspace || workspace_bytes < bwd_workspace_bytes(tree, params) ||
       ((uintptr_t)workspace & 255u))
     return DTA_ERR_WORKSPACE;
   dta::Schedule* s = nullptr;
@@ -446,10 +455,7 @@ int bwd_entry(dta_tree* tree, const dta_attn_params_t* params, const void* q, co
   a.dq = dq;
   a.dk = dk;
   a.dv = dv;
-  a.delta = (float*)workspace;
-  a.lse2 = (float*)((char*)workspace + delta_bytes(tree, params));
-  a.tickets = (int*)((char*)workspace + 2 * delta_bytes(tree, params));
-  a.partial = (float*)((char*)workspace + 2 * delta_bytes(tree, params) + ticket_bytes(params));
+  set_workspace(a, tree, params, workspace);
   a.stages = stage_mask;
   a.row_begin = 0;
   a.row_end = tree->info.n_tokens;
@@ -486,7 +492,7 @@ int dta_tree_attn_fwd_segment(dta_tree_t* tree, const dta_attn_params_t* params,
   (void)workspace_bytes;
   if (!tree || !params) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc);
+  int st = dta::choose_tiles(params, &tc, t_end - t_begin);
   if (st != DTA_OK) return st;
   if ((st = check_segment(tree, t_begin, t_end)) != DTA_OK) return st;
   if (!q || !k || !v || !o || !lse) return DTA_ERR_INVALID_ARG;
@@ -519,14 +525,14 @@ int dta_tree_attn_bwd_segment(dta_tree_t* tree, const dta_attn_params_t* params,
                               size_t workspace_bytes, void* hip_stream) {
   if (!tree || !params) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc);
+  int st = dta::choose_tiles(params, &tc, t_end - t_begin);
   if (st != DTA_OK) return st;
   if ((st = check_segment(tree, t_begin, t_end)) != DTA_OK) return st;
   if (!q || !k || !v || !o || !lse || !d_o || !dq || !dk_acc || !dv_acc) return DTA_ERR_INVALID_ARG;
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse) ||
       misaligned(d_o) || misaligned(dq) || misaligned(dk_acc) || misaligned(dv_acc))
     return DTA_ERR_INVALID_ARG;
-  if (!workspace || workspace_bytes < bwd_workspace_bytes(tree, tc, params) ||
+  if (!workspace || workspace_bytes < bwd_workspace_bytes(tree, params) ||
       ((uintptr_t)workspace & 255u))
     return DTA_ERR_WORKSPACE;
   dta::Schedule* s = nullptr;
@@ -546,10 +552,7 @@ int dta_tree_attn_bwd_segment(dta_tree_t* tree, const dta_attn_params_t* params,
   a.dq = dq;
   a.dk_acc = dk_acc;
   a.dv_acc = dv_acc;
-  a.delta = (float*)workspace;
-  a.lse2 = (float*)((char*)workspace + delta_bytes(tree, params));
-  a.tickets = (int*)((char*)workspace + 2 * delta_bytes(tree, params));
-  a.partial = (float*)((char*)workspace + 2 * delta_bytes(tree, params) + ticket_bytes(params));
+  set_workspace(a, tree, params, workspace);
   a.stages = DTA_BWD_ALL;
   a.row_begin = t_begin;
   a.row_end = t_end;

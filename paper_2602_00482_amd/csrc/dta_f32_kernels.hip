@@ -1,312 +1,710 @@
-// fp32 tree attention for gfx950: forward, dQ and dK/dV kernels that keep every
-// product, sum and exponential in fp32 (no matrix-core truncation), for callers
-// that need ~1e-6 relative accuracy.  Four lanes share one query (or key) row,
-// each holding a quarter of head_dim; keys (or queries) are streamed through LDS
-// and every lane group walks them one by one.
+// fp32 tree attention for gfx950: forward, dQ and dK/dV with every product, sum
+// and exponential in fp32, for callers that need ~1e-6 relative accuracy.
 //
 // What is computed follows the attention inside the paper's FWD / BWD
 // primitives (pseudocode appendix) for all segments of the tree at once: a
 // query sees key k iff  k <= t < kend[k]  in packed DFS coordinates.
+//
+// All products run on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fused
+// multiply-adds in fp32, nothing is rounded to a shorter type), twice the rate
+// of the vector ALU without packed arithmetic, and what bounds the kernels: a
+// 16x16x4 product holds a SIMD for 32 cycles and needs one operand of 256 bytes
+// from LDS, a quarter of what LDS delivers, so nothing else comes close.  A wave
+// owns 16 query rows (forward, dQ) or 16 keys (dK/dV): with 32 the stationary
+// operands and accumulators of dK/dV (four 32 x 128 matrices) would not fit in
+// 256 registers, and small trees would have half as many waves to spread.
+//   The scores of a tile come out with the streamed rows (keys, or queries) in
+// registers and the wave's own 16 in lanes: register v of lane group l / 16 is
+// streamed row 4 * (l / 16) + v, which is exactly the operand layout of the next
+// product with that row as the contraction index, so P and dS never move.
+//
+// Measured on MI355X (bound: 152 TFLOP/s, what a large fp32 library product reaches),
+// with four lanes per row on the vector ALU before, and now:
+//   4862 tokens (a prompt with 16 answers), 32/8 heads of 128:
+//     forward 1.51 -> 0.35 ms (93 TFLOP/s), dQ 2.38 -> 0.53 ms (93), dK/dV 13.6 -> 0.63 ms (103)
+//   384 tokens in 13 nodes, 4/4 heads of 64 (latency of a chain of dependent steps):
+//     forward 71 -> 11 us, dQ 64 -> 14 us, dK/dV 146 -> 20 us
+// A large launch's blocks are few rounds (1216 on 512 slots above), so what is left
+// is mostly the uneven end of the launch.
 #include <hip/hip_runtime.h>
 
 #include "dta_internal.h"
+#include "dta_mfma.h"
+#include "dta_tile_walk.h"
 
 namespace dta {
 namespace {
 
-constexpr int kRows = 64;   // rows (queries or keys) per block
-constexpr int kLanes = 4;   // lanes per row
-constexpr int kChunk = 32;  // streamed rows per LDS fill
+// D(16x16) += A(16x4) * B(4x16).  Lane l = (n = l % 16, g = l / 16):
+//   A: row n, k = g     B: column n, k = g     D: column n, row = 4*g + v, v = 0..3
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
 
-__device__ __forceinline__ float group_sum(float x) {
-  x += __shfl_xor(x, 1);
-  x += __shfl_xor(x, 2);
+// sum / max over the four lane groups that share a column
+__device__ __forceinline__ float column_sum(float x) {
+  x += __shfl_xor(x, 16);
+  x += __shfl_xor(x, 32);
   return x;
 }
+__device__ __forceinline__ float column_max(float x) {
+  x = fmaxf(x, __shfl_xor(x, 16));
+  return fmaxf(x, __shfl_xor(x, 32));
+}
 
-// Copies `n` rows of D floats (row stride `stride` floats) into LDS, all 256 threads.
-template <int D>
-__device__ __forceinline__ void stage_rows(float (*dst)[D], const float* src, size_t stride, int n) {
-  constexpr int V = D / 4;
-  for (int i = threadIdx.x; i < n * V; i += blockDim.x) {
-    int r = i / V, c = i % V;
-    reinterpret_cast<float4*>(dst[r])[c] =
-        *reinterpret_cast<const float4*>(src + (size_t)r * stride + 4 * c);
+// ---- 32-row tiles of HD floats filled by direct global-to-LDS loads -------------
+// One wave-wide 16-byte load fills 1 KB = kRowsPerGroup consecutive rows; groups
+// start 1056 bytes apart.  Matrix position x (0..31) uses row
+//   kRowsPerGroup * (x % kGroups) + x / kGroups
+// so that 8 consecutive positions lie in 8 different groups, 32 bytes of bank
+// offset apart: a 16-byte row read of 8 lanes touches 8 different bank quads.
+template <int HD>
+struct Rows32 {
+  static_assert(HD == 128 || HD == 64, "head_dim 64 or 128");
+  static constexpr int kRowsPerGroup = 256 / HD;
+  static constexpr int kGroups = 32 / kRowsPerGroup;
+  static constexpr int kPitch = 256 + 8;             // floats between groups
+  static constexpr int kTile = kGroups * kPitch;     // floats per tile
+  static constexpr int NB = HD / 16;                 // 16-wide output blocks; also float4 per lane and row
+
+  __device__ __forceinline__ static int row_of_pos(int x) {
+    return kRowsPerGroup * (x % kGroups) + x / kGroups;
+  }
+  // row of position 16*mb + 4*g + v
+  __device__ __forceinline__ static int row_of_acc(int mb, int g, int v) {
+    return HD == 128 ? 8 * g + 2 * v + mb : 16 * (g & 1) + 4 * v + (g >> 1) + 2 * mb;
+  }
+  // per-lane base of row operands: float4 j of position 16*mb + n is at
+  //   tile + row_lane_off() + 128 * mb + 16 * j      (columns 16*j + 4*g .. +3)
+  __device__ __forceinline__ static int row_lane_off() {
+    const int n = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+    return (n % kGroups) * kPitch + (n / kGroups) * HD + 4 * g;
+  }
+  // per-lane base of column operands: lane n owns columns NB*n .. NB*n + NB-1 (one per
+  // output block), of position 16*mb + 4*g + v:
+  //   tile + col_lane_off() + 128 * mb + kPitch * v
+  __device__ __forceinline__ static int col_lane_off() {
+    const int n = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
+    return ((4 * g) % kGroups) * kPitch + ((4 * g) / kGroups) * HD + NB * n;
+  }
+};
+
+// Starts the copy of ROWS rows of HD floats (row pitch stride_bytes, base uniform
+// over the block) into ROWS / 32 consecutive tiles; rows >= nvalid re-read row
+// nvalid - 1.  NW waves take part.  Completion: async_wait_all(), then a barrier.
+template <int HD, int ROWS, int NW>
+__device__ __forceinline__ void rows_async_load(float* tiles, const float* base, uint32_t stride_bytes,
+                                                int nvalid) {
+  using RL = Rows32<HD>;
+  constexpr int kGroupsAll = ROWS / RL::kRowsPerGroup, kLaneShift = HD == 128 ? 5 : 4;
+  static_assert(kGroupsAll % NW == 0, "every wave copies the same number of row groups");
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  const uint32_t tile_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)tiles;
+  const uint64_t base_bits = (uint64_t)(uintptr_t)base;
+  const uint32_t base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base_bits >> 32));
+  const uint32_t base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base_bits);
+  const uint64_t sbase = ((uint64_t)base_hi << 32) | (uint64_t)base_lo;
+#pragma unroll
+  for (int p = 0; p < kGroupsAll / NW; ++p) {
+    const int grp = w + NW * p;
+    const int row = min(RL::kRowsPerGroup * grp + (l >> kLaneShift), nvalid - 1);
+    const uint32_t voff = (uint32_t)row * stride_bytes + (l & ((1 << kLaneShift) - 1)) * 16;
+    const uint32_t lds_addr = __builtin_amdgcn_readfirstlane(tile_addr + grp * RL::kPitch * 4);
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(voff), "s"(sbase), "s"(lds_addr)
+                 : "memory");
   }
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void fwd_f32_kernel(const QTile* __restrict__ tiles,
-                                                      const KeySeg* __restrict__ segs,
-                                                      const int32_t* __restrict__ kend,
-                                                      const float* __restrict__ q,
-                                                      const float* __restrict__ k,
-                                                      const float* __restrict__ v,
-                                                      float* __restrict__ o, float* __restrict__ lse,
-                                                      int Hq, int Hkv, float scale) {
-  constexpr int DS = D / kLanes;
-  __shared__ float Ks[kChunk][D];
-  __shared__ float Vs[kChunk][D];
-  __shared__ int32_t kendS[kChunk];
-  const QTile tile = tiles[blockIdx.x];
-  const int h = blockIdx.y, g = h / (Hq / Hkv);
-  const int r = threadIdx.x / kLanes, j = threadIdx.x % kLanes;
-  const int t = tile.t0 + r;
-  const bool valid = t < tile.t1;
-  const int tc = valid ? t : tile.t1 - 1;
-
-  float qv[DS], acc[DS];
-  {
-    const float* qp = q + ((size_t)tc * Hq + h) * D + j * DS;
+// The KS wave groups of a block each hold a partial sum of N float4 per lane;
+// afterwards group 0 holds the total, added in group order.  `buf`: LDS of
+// (KS - 1) * R * N * 1 KB that nobody reads any more.  Called by every thread.
+template <int KS, int R, int N>
+__device__ __forceinline__ void sum_over_groups(f32x4* buf, int rw, int kg, f32x4 (&acc)[N]) {
+  if constexpr (KS > 1) {
+    const int l = threadIdx.x & 63;
+    __syncthreads();
+    if (kg > 0) {
 #pragma unroll
-    for (int i = 0; i < DS; ++i) { qv[i] = qp[i]; acc[i] = 0.f; }
-  }
-  float m = -INFINITY, l = 0.f;
-  const size_t kv_stride = (size_t)Hkv * D;
-
-  for (int si = tile.seg_begin; si <= tile.seg_end; ++si) {
-    int start, end, full;
-    if (si < tile.seg_end) { start = segs[si].start; end = segs[si].end; full = segs[si].full; }
-    else { start = tile.t0; end = tile.t1; full = 0; }   // the tile's own keys
-    for (int c0 = start; c0 < end; c0 += kChunk) {
-      const int n = min(kChunk, end - c0);
-      __syncthreads();
-      stage_rows<D>(Ks, k + (size_t)c0 * kv_stride + (size_t)g * D, kv_stride, n);
-      stage_rows<D>(Vs, v + (size_t)c0 * kv_stride + (size_t)g * D, kv_stride, n);
-      if (threadIdx.x < n) kendS[threadIdx.x] = kend[c0 + threadIdx.x];
-      __syncthreads();
-      for (int i = 0; i < n; ++i) {
-        float s = 0.f;
+      for (int i = 0; i < N; ++i) buf[(((kg - 1) * R + rw) * N + i) * 64 + l] = acc[i];
+    }
+    __syncthreads();
+    if (kg == 0) {
 #pragma unroll
-        for (int e = 0; e < DS; ++e) s = fmaf(qv[e], Ks[i][j * DS + e], s);
-        s = group_sum(s) * scale;
-        const bool vis = full || (c0 + i <= tc && tc < kendS[i]);
-        if (vis) {
-          const float mn = fmaxf(m, s);
-          const float a = expf(m - mn), p = expf(s - mn);
-          l = l * a + p;
+      for (int s = 0; s < KS - 1; ++s)
 #pragma unroll
-          for (int e = 0; e < DS; ++e) acc[e] = fmaf(acc[e], a, p * Vs[i][j * DS + e]);
-          m = mn;
-        }
-      }
+        for (int i = 0; i < N; ++i) acc[i] += buf[((s * R + rw) * N + i) * 64 + l];
     }
   }
-  if (valid) {
-    const float inv = 1.f / l;
-    float* op = o + ((size_t)t * Hq + h) * D + j * DS;
+}
+
+constexpr int kThreads = 512;   // forward and dQ blocks: 8 waves
+
+// Block = 8 waves = R row tiles (HB q heads of the group x 16-row blocks) x KS
+// groups.  The keys of the tile's root path are streamed in chunks of 32 * KS
+// keys, double-buffered in LDS; group kg of the block takes keys
+// [32*kg, 32*kg + 32) of every chunk and the groups' results are merged at the
+// end.  KS = 1: one K/V copy serves 8 row tiles, for launches that fill the chip.
+// KS = 4 / 2 (head_dim 64 / 128): a fourth / half of the rows per block and of the
+// steps per walk, for trees too small to fill it.
+template <int HD, int KS>
+__global__ __launch_bounds__(kThreads) void fwd_f32_kernel(
+    const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs, const int32_t* __restrict__ kend,
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    float* __restrict__ o, float* __restrict__ lse, int Hq, int Hkv, int HB, int hblocks, float scale) {
+  using RL = Rows32<HD>;
+  constexpr int NB = RL::NB, R = 8 / KS, CH = 32 * KS;
+  __shared__ __attribute__((aligned(1024))) float Ks[2][KS * RL::kTile];
+  __shared__ __attribute__((aligned(1024))) float Vs[2][KS * RL::kTile];
+  __shared__ __attribute__((aligned(16))) int32_t kendS[2][CH];
+  __shared__ float mlS[2][KS][R][16];
+
+  const int item = blockIdx.x / Hkv, g_kv = blockIdx.x % Hkv;
+  const QTile tile = tiles[item / hblocks];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  const int n16 = l & 15, lg = l >> 4;
+  const int rw = w % R, kg = w / R;
+  const int h = g_kv * (Hq / Hkv) + (item % hblocks) * HB + rw % HB;
+  const int row_base = tile.t0 + 16 * (rw / HB);
+  const int qrow = min(row_base + n16, tile.t1 - 1);
+
+  f32x4 Qr[NB];
+  {
+    const float* qp = q + ((size_t)qrow * Hq + h) * HD + 4 * lg;
 #pragma unroll
-    for (int i = 0; i < DS; ++i) op[i] = acc[i] * inv;
-    if (j == 0) lse[(size_t)t * Hq + h] = m + logf(l);
+    for (int j = 0; j < NB; ++j) Qr[j] = *reinterpret_cast<const f32x4*>(qp + 16 * j);
+  }
+  f32x4 O[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) O[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, lsum = 0.f;   // lsum: this lane's share of the row sum
+
+  const size_t kv_stride = (size_t)Hkv * HD;
+  const float* kbase = k + (size_t)g_kv * HD;
+  const float* vbase = v + (size_t)g_kv * HD;
+  const uint32_t kv_bytes = (uint32_t)kv_stride * 4;
+
+  KeyChunksT<CH> it;
+  it.init(segs, tile);
+  int c0, n, full;
+  bool have = it.next(c0, n, full);
+  auto issue = [&](int b) {
+    if ((!full || n < CH) && threadIdx.x < CH) {   // kendS is indexed by matrix position
+      const int row = 32 * (threadIdx.x >> 5) + RL::row_of_pos(threadIdx.x & 31);
+      kendS[b][threadIdx.x] = row >= n ? 0 : (full ? 0x7fffffff : kend[c0 + row]);
+    }
+    rows_async_load<HD, CH, 8>(Ks[b], kbase + (size_t)c0 * kv_stride, kv_bytes, n);
+    rows_async_load<HD, CH, 8>(Vs[b], vbase + (size_t)c0 * kv_stride, kv_bytes, n);
+  };
+  issue(0);
+  int buf = 0;
+  const int rlo = kg * RL::kTile + RL::row_lane_off(), clo = kg * RL::kTile + RL::col_lane_off();
+
+  while (have) {
+    async_wait_all();
+    __syncthreads();   // chunk `buf` has landed; everyone is done with the other buffer
+    const int k0 = c0 + 32 * kg, nk = n - 32 * kg;   // this group's keys
+    const bool need_mask = !full || nk < 32;
+    have = it.next(c0, n, full);
+    if (have) issue(buf ^ 1);
+    // nothing here, or keys that come after every row of this wave (own range only)
+    if (nk > 0 && !(need_mask && k0 > row_base + 15)) {
+      const float* Kt = Ks[buf] + rlo;
+      const float* Vt = Vs[buf] + clo;
+      f32x4 S[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const f32x4 a0 = *reinterpret_cast<const f32x4*>(Kt + 16 * j);
+        const f32x4 a1 = *reinterpret_cast<const f32x4*>(Kt + 128 + 16 * j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          S[0] = mfma16(a0[e], Qr[j][e], S[0]);
+          S[1] = mfma16(a1[e], Qr[j][e], S[1]);
+        }
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb) {
+        S[mb] *= scale;
+        if (need_mask) {
+          const int4 ke = *reinterpret_cast<const int4*>(&kendS[buf][32 * kg + 16 * mb + 4 * lg]);
+          const int kev[4] = {ke.x, ke.y, ke.z, ke.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            S[mb][e] = (k0 + RL::row_of_acc(mb, lg, e) <= qrow) & (qrow < kev[e]) ? S[mb][e] : -INFINITY;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[mb][e]);
+      }
+      const float mnew = fmaxf(m, column_max(mx));
+      const float mref = mnew == -INFINITY ? 0.f : mnew;
+      const float alpha = expf(m - mref);
+      m = mnew;
+      float ps = 0.f;
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          S[mb][e] = expf(S[mb][e] - mref);
+          ps += S[mb][e];
+        }
+      lsum = fmaf(lsum, alpha, ps);
+      if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) O[b] *= alpha;
+      }
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          f32x4 a[NB / 4];
+#pragma unroll
+          for (int x = 0; x < NB / 4; ++x)
+            a[x] = *reinterpret_cast<const f32x4*>(Vt + 128 * mb + RL::kPitch * e + 4 * x);
+#pragma unroll
+          for (int b = 0; b < NB; ++b) O[b] = mfma16(a[b >> 2][b & 3], S[mb][e], O[b]);
+        }
+    }
+    buf ^= 1;
+  }
+
+  float lt = column_sum(lsum);
+  if constexpr (KS > 1) {   // merge the groups: common maximum, then one sum
+    if (lg == 0) {
+      mlS[0][kg][rw][n16] = m;
+      mlS[1][kg][rw][n16] = lt;
+    }
+    __syncthreads();
+    float mall = mlS[0][0][rw][n16];
+#pragma unroll
+    for (int s = 1; s < KS; ++s) mall = fmaxf(mall, mlS[0][s][rw][n16]);
+    lt = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) lt = fmaf(expf(mlS[0][s][rw][n16] - mall), mlS[1][s][rw][n16], lt);
+    const float f = expf(m - mall);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) O[b] *= f;
+    m = mall;
+    sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&Ks[0][0]), rw, kg, O);
+  }
+  if (kg == 0 && row_base + n16 < tile.t1) {
+    const float inv = 1.f / lt;
+    float* op = o + ((size_t)qrow * Hq + h) * HD + NB * 4 * lg;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int x = 0; x < NB / 4; ++x) {
+        f32x4 r;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) r[b] = O[4 * x + b][e] * inv;
+        *reinterpret_cast<f32x4*>(op + NB * e + 4 * x) = r;
+      }
+    if (lg == 0) lse[(size_t)qrow * Hq + h] = m + logf(lt);
   }
 }
 
-// D[t,h] = dO[t,h] . O[t,h]
-template <int D>
+// D[t,h] = dO[t,h] . O[t,h], as a launch of its own: only when the delta stage is
+// asked for without dQ (otherwise the dQ launch computes it, in the same order).
+template <int HD>
 __global__ __launch_bounds__(256) void delta_f32_kernel(const float* __restrict__ o,
                                                         const float* __restrict__ d_o,
                                                         float* __restrict__ delta, size_t rows) {
-  constexpr int DS = D / kLanes;
-  size_t row = (size_t)blockIdx.x * kRows + threadIdx.x / kLanes;
-  int j = threadIdx.x % kLanes;
+  const size_t row = (size_t)blockIdx.x * 64 + threadIdx.x / 4;
+  const int g = threadIdx.x % 4;   // plays lane group g of the dQ kernel
   float s = 0.f;
   if (row < rows) {
-    const float* a = o + row * D + j * DS;
-    const float* b = d_o + row * D + j * DS;
+    const float* a = o + row * HD + 4 * g;
+    const float* b = d_o + row * HD + 4 * g;
 #pragma unroll
-    for (int i = 0; i < DS; ++i) s = fmaf(a[i], b[i], s);
+    for (int j = 0; j < HD / 16; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = fmaf(a[16 * j + e], b[16 * j + e], s);
   }
-  s = group_sum(s);
-  if (row < rows && j == 0) delta[row] = s;
+  s += __shfl_xor(s, 1);
+  s += __shfl_xor(s, 2);
+  if (row < rows && g == 0) delta[row] = s;
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void dq_f32_kernel(const QTile* __restrict__ tiles,
-                                                     const KeySeg* __restrict__ segs,
-                                                     const int32_t* __restrict__ kend,
-                                                     const float* __restrict__ q,
-                                                     const float* __restrict__ k,
-                                                     const float* __restrict__ v,
-                                                     const float* __restrict__ d_o,
-                                                     const float* __restrict__ lse,
-                                                     const float* __restrict__ delta,
-                                                     float* __restrict__ dq, int Hq, int Hkv,
-                                                     float scale) {
-  constexpr int DS = D / kLanes;
-  __shared__ float Ks[kChunk][D];
-  __shared__ float Vs[kChunk][D];
-  __shared__ int32_t kendS[kChunk];
-  const QTile tile = tiles[blockIdx.x];
-  const int h = blockIdx.y, g = h / (Hq / Hkv);
-  const int r = threadIdx.x / kLanes, j = threadIdx.x % kLanes;
-  const int t = tile.t0 + r;
-  const bool valid = t < tile.t1;
-  const int tc = valid ? t : tile.t1 - 1;
+// Same walk and block shapes as the forward kernel.  With o != nullptr the launch
+// also computes D for its rows and leaves it in `delta` for dK/dV.
+template <int HD, int KS>
+__global__ __launch_bounds__(kThreads) void dq_f32_kernel(
+    const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs, const int32_t* __restrict__ kend,
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    const float* __restrict__ d_o, const float* __restrict__ o, const float* __restrict__ lse,
+    float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, int HB, int hblocks, float scale) {
+  using RL = Rows32<HD>;
+  constexpr int NB = RL::NB, R = 8 / KS, CH = 32 * KS;
+  __shared__ __attribute__((aligned(1024))) float Ks[2][KS * RL::kTile];
+  __shared__ __attribute__((aligned(1024))) float Vs[2][KS * RL::kTile];
+  __shared__ __attribute__((aligned(16))) int32_t kendS[2][CH];
 
-  float qv[DS], dov[DS], acc[DS];
-  {
-    const size_t base = ((size_t)tc * Hq + h) * D + j * DS;
-#pragma unroll
-    for (int i = 0; i < DS; ++i) { qv[i] = q[base + i]; dov[i] = d_o[base + i]; acc[i] = 0.f; }
-  }
-  const float lse_t = lse[(size_t)tc * Hq + h], delta_t = delta[(size_t)tc * Hq + h];
-  const size_t kv_stride = (size_t)Hkv * D;
+  const int item = blockIdx.x / Hkv, g_kv = blockIdx.x % Hkv;
+  const QTile tile = tiles[item / hblocks];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  const int n16 = l & 15, lg = l >> 4;
+  const int rw = w % R, kg = w / R;
+  const int h = g_kv * (Hq / Hkv) + (item % hblocks) * HB + rw % HB;
+  const int row_base = tile.t0 + 16 * (rw / HB);
+  const int qrow = min(row_base + n16, tile.t1 - 1);
+  const size_t rh = (size_t)qrow * Hq + h;
 
-  for (int si = tile.seg_begin; si <= tile.seg_end; ++si) {
-    int start, end, full;
-    if (si < tile.seg_end) { start = segs[si].start; end = segs[si].end; full = segs[si].full; }
-    else { start = tile.t0; end = tile.t1; full = 0; }
-    for (int c0 = start; c0 < end; c0 += kChunk) {
-      const int n = min(kChunk, end - c0);
-      __syncthreads();
-      stage_rows<D>(Ks, k + (size_t)c0 * kv_stride + (size_t)g * D, kv_stride, n);
-      stage_rows<D>(Vs, v + (size_t)c0 * kv_stride + (size_t)g * D, kv_stride, n);
-      if (threadIdx.x < n) kendS[threadIdx.x] = kend[c0 + threadIdx.x];
-      __syncthreads();
-      for (int i = 0; i < n; ++i) {
-        float s = 0.f, dp = 0.f;
-#pragma unroll
-        for (int e = 0; e < DS; ++e) {
-          s = fmaf(qv[e], Ks[i][j * DS + e], s);
-          dp = fmaf(dov[e], Vs[i][j * DS + e], dp);
-        }
-        s = group_sum(s) * scale;
-        dp = group_sum(dp);
-        const bool vis = full || (c0 + i <= tc && tc < kendS[i]);
-        const float p = vis ? expf(s - lse_t) : 0.f;
-        const float ds = p * (dp - delta_t);
-#pragma unroll
-        for (int e = 0; e < DS; ++e) acc[e] = fmaf(ds, Ks[i][j * DS + e], acc[e]);
-      }
+  const size_t kv_stride = (size_t)Hkv * HD;
+  const float* kbase = k + (size_t)g_kv * HD;
+  const float* vbase = v + (size_t)g_kv * HD;
+  const uint32_t kv_bytes = (uint32_t)kv_stride * 4;
+
+  KeyChunksT<CH> it;
+  it.init(segs, tile);
+  int c0, n, full;
+  bool have = it.next(c0, n, full);
+  auto issue = [&](int b) {
+    if ((!full || n < CH) && threadIdx.x < CH) {
+      const int row = 32 * (threadIdx.x >> 5) + RL::row_of_pos(threadIdx.x & 31);
+      kendS[b][threadIdx.x] = row >= n ? 0 : (full ? 0x7fffffff : kend[c0 + row]);
     }
-  }
-  if (valid) {
-    float* op = dq + ((size_t)t * Hq + h) * D + j * DS;
-#pragma unroll
-    for (int i = 0; i < DS; ++i) op[i] = acc[i] * scale;
-  }
-}
+    rows_async_load<HD, CH, 8>(Ks[b], kbase + (size_t)c0 * kv_stride, kv_bytes, n);
+    rows_async_load<HD, CH, 8>(Vs[b], vbase + (size_t)c0 * kv_stride, kv_bytes, n);
+  };
+  issue(0);
 
-// One block owns kRows consecutive keys of one kv head and walks every query
-// row that can see any of them, for all q heads of the group, so each dK/dV
-// element is produced by exactly one lane group and written once.
-template <int D>
-__global__ __launch_bounds__(256) void dkdv_f32_kernel(const KvTile* __restrict__ tiles,
-                                                       const int32_t* __restrict__ kend,
-                                                       const float* __restrict__ q,
-                                                       const float* __restrict__ k,
-                                                       const float* __restrict__ v,
-                                                       const float* __restrict__ d_o,
-                                                       const float* __restrict__ lse,
-                                                       const float* __restrict__ delta,
-                                                       float* __restrict__ dk, float* __restrict__ dv,
-                                                       int accumulate, int Hq, int Hkv,
-                                                       float scale) {
-  constexpr int DS = D / kLanes;
-  __shared__ float Qs[kChunk][D];
-  __shared__ float dOs[kChunk][D];
-  __shared__ float lseS[kChunk], deltaS[kChunk];
-  const KvTile tile = tiles[blockIdx.x];
-  const int g = blockIdx.y, G = Hq / Hkv;
-  const int r = threadIdx.x / kLanes, j = threadIdx.x % kLanes;
-  const int kk = tile.k0 + r;
-  const bool valid = kk < tile.k1;
-  const int kc = valid ? kk : tile.k1 - 1;
-  const int my_kend = kend[kc];
-
-  float kv_[DS], vv[DS], dka[DS], dva[DS];
-  {
-    const size_t base = ((size_t)kc * Hkv + g) * D + j * DS;
+  f32x4 Qr[NB], dOr[NB];
 #pragma unroll
-    for (int i = 0; i < DS; ++i) { kv_[i] = k[base + i]; vv[i] = v[base + i]; dka[i] = 0.f; dva[i] = 0.f; }
+  for (int j = 0; j < NB; ++j) {
+    Qr[j] = *reinterpret_cast<const f32x4*>(q + rh * HD + 4 * lg + 16 * j);
+    dOr[j] = *reinterpret_cast<const f32x4*>(d_o + rh * HD + 4 * lg + 16 * j);
   }
-  const size_t q_stride = (size_t)Hq * D;
-
-  for (int hh = 0; hh < G; ++hh) {
-    const int h = g * G + hh;
-    for (int c0 = tile.q_begin; c0 < tile.q_end; c0 += kChunk) {
-      const int n = min(kChunk, tile.q_end - c0);
-      __syncthreads();
-      stage_rows<D>(Qs, q + (size_t)c0 * q_stride + (size_t)h * D, q_stride, n);
-      stage_rows<D>(dOs, d_o + (size_t)c0 * q_stride + (size_t)h * D, q_stride, n);
-      if (threadIdx.x < n) {
-        lseS[threadIdx.x] = lse[(size_t)(c0 + threadIdx.x) * Hq + h];
-        deltaS[threadIdx.x] = delta[(size_t)(c0 + threadIdx.x) * Hq + h];
-      }
-      __syncthreads();
-      for (int i = 0; i < n; ++i) {
-        const int t = c0 + i;
-        float s = 0.f, dp = 0.f;
+  float dlt;
+  if (o != nullptr) {
+    dlt = 0.f;
 #pragma unroll
-        for (int e = 0; e < DS; ++e) {
-          s = fmaf(Qs[i][j * DS + e], kv_[e], s);
-          dp = fmaf(dOs[i][j * DS + e], vv[e], dp);
-        }
-        s = group_sum(s) * scale;
-        dp = group_sum(dp);
-        const bool vis = kc <= t && t < my_kend;
-        const float p = vis ? expf(s - lseS[i]) : 0.f;
-        const float ds = p * (dp - deltaS[i]);
+    for (int j = 0; j < NB; ++j) {
+      const f32x4 ox = *reinterpret_cast<const f32x4*>(o + rh * HD + 4 * lg + 16 * j);
 #pragma unroll
-        for (int e = 0; e < DS; ++e) {
-          dva[e] = fmaf(p, dOs[i][j * DS + e], dva[e]);
-          dka[e] = fmaf(ds, Qs[i][j * DS + e], dka[e]);
-        }
-      }
+      for (int e = 0; e < 4; ++e) dlt = fmaf(ox[e], dOr[j][e], dlt);
     }
+    dlt = column_sum(dlt);
+    if (kg == 0 && lg == 0 && row_base + n16 < tile.t1) delta[rh] = dlt;
+  } else {
+    dlt = delta[rh];
   }
-  if (valid) {
-    const size_t base = ((size_t)kk * Hkv + g) * D + j * DS;
+  const float lse_t = lse[rh];
+  f32x4 dQ[NB];
 #pragma unroll
-    for (int i = 0; i < DS; ++i) {
-      // a segment call adds to the caller's accumulators (this lane group is the
-      // only owner of the key in the launch)
-      dk[base + i] = (accumulate ? dk[base + i] : 0.f) + dka[i] * scale;
-      dv[base + i] = (accumulate ? dv[base + i] : 0.f) + dva[i];
+  for (int b = 0; b < NB; ++b) dQ[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  int buf = 0;
+  const int rlo = kg * RL::kTile + RL::row_lane_off(), clo = kg * RL::kTile + RL::col_lane_off();
+  while (have) {
+    async_wait_all();
+    __syncthreads();
+    const int k0 = c0 + 32 * kg, nk = n - 32 * kg;
+    const bool need_mask = !full || nk < 32;
+    have = it.next(c0, n, full);
+    if (have) issue(buf ^ 1);
+    if (nk > 0 && !(need_mask && k0 > row_base + 15)) {
+      const float* Kt = Ks[buf] + rlo;
+      const float* Vt = Vs[buf] + rlo;
+      const float* Kc = Ks[buf] + clo;
+      f32x4 S[2], dP[2];
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb) S[mb] = dP[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+          const f32x4 ka = *reinterpret_cast<const f32x4*>(Kt + 128 * mb + 16 * j);
+          const f32x4 va = *reinterpret_cast<const f32x4*>(Vt + 128 * mb + 16 * j);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            S[mb] = mfma16(ka[e], Qr[j][e], S[mb]);
+            dP[mb] = mfma16(va[e], dOr[j][e], dP[mb]);
+          }
+        }
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) S[mb][e] = expf(fmaf(S[mb][e], scale, -lse_t));
+        if (need_mask) {
+          const int4 ke = *reinterpret_cast<const int4*>(&kendS[buf][32 * kg + 16 * mb + 4 * lg]);
+          const int kev[4] = {ke.x, ke.y, ke.z, ke.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            S[mb][e] = (k0 + RL::row_of_acc(mb, lg, e) <= qrow) & (qrow < kev[e]) ? S[mb][e] : 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) S[mb][e] *= dP[mb][e] - dlt;   // dS
+      }
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          f32x4 a[NB / 4];
+#pragma unroll
+          for (int x = 0; x < NB / 4; ++x)
+            a[x] = *reinterpret_cast<const f32x4*>(Kc + 128 * mb + RL::kPitch * e + 4 * x);
+#pragma unroll
+          for (int b = 0; b < NB; ++b) dQ[b] = mfma16(a[b >> 2][b & 3], S[mb][e], dQ[b]);
+        }
     }
+    buf ^= 1;
+  }
+
+  sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&Ks[0][0]), rw, kg, dQ);
+  if (kg == 0 && row_base + n16 < tile.t1) {
+    float* op = dq + rh * HD + NB * 4 * lg;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int x = 0; x < NB / 4; ++x) {
+        f32x4 r;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) r[b] = dQ[4 * x + b][e] * scale;
+        *reinterpret_cast<f32x4*>(op + NB * e + 4 * x) = r;
+      }
   }
 }
 
-template <int D>
+// Key-stationary: wave = 16 keys, K and V rows in registers; R key tiles x KS
+// groups per block.  Q and dO of the rows that can see the keys are streamed in
+// chunks of 32 * KS rows, q heads of the group innermost, last chunk first; group
+// qg takes rows [32*qg, 32*qg + 32) of every chunk.  KS = 1: four waves, two
+// blocks per CU.  KS = 4 / 2: eight waves, trees too small to fill the chip.
+// Long walks are cut into items that write partial sums, as in bf16 mode.
+template <int HD, int KS>
+__global__ __launch_bounds__(KS == 1 ? 256 : 512, KS == 1 ? 2 : 1) void dkdv_f32_kernel(
+    const KvItem* __restrict__ items, const int32_t* __restrict__ kend, const float* __restrict__ q,
+    const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ d_o,
+    const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dk,
+    float* __restrict__ dv, float* __restrict__ partial, int accumulate, int Hq, int Hkv, float scale) {
+  using RL = Rows32<HD>;
+  constexpr int NB = RL::NB, NW = KS == 1 ? 4 : 8, R = NW / KS, CH = 32 * KS, kKeys = 16 * R;
+  constexpr int kStat = CH < 64 ? 64 : CH;   // one wave-wide copy fills 64
+  __shared__ __attribute__((aligned(1024))) float Qs[2][KS * RL::kTile];
+  __shared__ __attribute__((aligned(1024))) float dOs[2][KS * RL::kTile];
+  __shared__ __attribute__((aligned(256))) float stat[2][2][kStat];   // [buffer][lse | delta][position]
+
+  const KvItem tile = items[blockIdx.x / Hkv];
+  const int g = blockIdx.x % Hkv, G = Hq / Hkv;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  const int n16 = l & 15, lg = l >> 4;
+  const int kw = w % R, qg = w / R;
+  const int kcol = tile.k0 + 16 * kw + n16;
+  const int kc = min(kcol, tile.k1 - 1);
+  const int my_kend = kcol < tile.k1 ? kend[kc] : 0;   // padded columns see nothing
+  // rows [wave_lo, wave_hi) are the only ones any of this wave's keys can see
+  int wave_hi = my_kend;
+#pragma unroll
+  for (int off = 8; off >= 1; off >>= 1) wave_hi = max(wave_hi, __shfl_xor(wave_hi, off));
+  wave_hi = __builtin_amdgcn_readfirstlane(wave_hi);
+  const int wave_lo = tile.k0 + 16 * kw;
+
+  const size_t q_stride = (size_t)Hq * HD;
+  const uint32_t q_bytes = (uint32_t)q_stride * 4;
+  const int n_chunks = (tile.q_end - tile.q_begin + CH - 1) / CH;
+  const int total = tile.it_end;
+  auto issue = [&](int it, int b) {
+    const int cq = it / G, h = g * G + (it - cq * G);
+    const int r0 = tile.q_begin + (n_chunks - 1 - cq) * CH;
+    const int nv = min(CH, tile.q_end - r0);
+    if (w < kStat / 64) {   // stat is indexed by matrix position
+      const int x = (64 * w + l) % CH;
+      const uint32_t off = (uint32_t)min(32 * (x >> 5) + RL::row_of_pos(x & 31), nv - 1) * (uint32_t)Hq;
+      row_async_load(&stat[b][0][64 * w], lse + (size_t)r0 * Hq + h, off);
+      row_async_load(&stat[b][1][64 * w], delta + (size_t)r0 * Hq + h, off);
+    }
+    rows_async_load<HD, CH, NW>(Qs[b], q + (size_t)r0 * q_stride + (size_t)h * HD, q_bytes, nv);
+    rows_async_load<HD, CH, NW>(dOs[b], d_o + (size_t)r0 * q_stride + (size_t)h * HD, q_bytes, nv);
+  };
+  if (tile.it_begin < total) issue(tile.it_begin, 0);
+
+  f32x4 Kr[NB], Vr[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    Kr[j] = *reinterpret_cast<const f32x4*>(k + ((size_t)kc * Hkv + g) * HD + 4 * lg + 16 * j);
+    Vr[j] = *reinterpret_cast<const f32x4*>(v + ((size_t)kc * Hkv + g) * HD + 4 * lg + 16 * j);
+  }
+  f32x4 acc[2 * NB];   // dK, dV
+#pragma unroll
+  for (int b = 0; b < 2 * NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int rlo = qg * RL::kTile + RL::row_lane_off(), clo = qg * RL::kTile + RL::col_lane_off();
+  int buf = 0;
+  for (int it = tile.it_begin; it < total; ++it) {
+    async_wait_all();
+    __syncthreads();
+    if (it + 1 < total) issue(it + 1, buf ^ 1);
+    const int c_lo = tile.q_begin + (n_chunks - 1 - it / G) * CH;
+    const int r0 = c_lo + 32 * qg;                                   // this group's rows
+    const int nr = min(32, tile.q_end - r0);
+    if (nr > 0 && r0 + nr > wave_lo && r0 < wave_hi) {
+      const bool need_mask = !(r0 >= tile.k1 && r0 + 32 <= tile.q_full_end);
+      const float* Qt = Qs[buf] + rlo;
+      const float* dOt = dOs[buf] + rlo;
+      const float* Qc = Qs[buf] + clo;
+      const float* dOc = dOs[buf] + clo;
+      // bounds of the visible rows of this lane's key, relative to r0
+      const int lo = kcol - r0, hi = min(my_kend - r0, nr);
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb) {
+        f32x4 S = {0.f, 0.f, 0.f, 0.f}, dP = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          const f32x4 qa = *reinterpret_cast<const f32x4*>(Qt + 128 * mb + 16 * j);
+          const f32x4 da = *reinterpret_cast<const f32x4*>(dOt + 128 * mb + 16 * j);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            S = mfma16(qa[e], Kr[j][e], S);
+            dP = mfma16(da[e], Vr[j][e], dP);
+          }
+        }
+        const f32x4 ls = *reinterpret_cast<const f32x4*>(&stat[buf][0][32 * qg + 16 * mb + 4 * lg]);
+        const f32x4 dl = *reinterpret_cast<const f32x4*>(&stat[buf][1][32 * qg + 16 * mb + 4 * lg]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float p = expf(fmaf(S[e], scale, -ls[e]));
+          if (need_mask) {
+            const int r = RL::row_of_acc(mb, lg, e);
+            p = (r >= lo) & (r < hi) ? p : 0.f;
+          }
+          S[e] = p;
+          dP[e] = p * (dP[e] - dl[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          f32x4 a[NB / 4], b[NB / 4];
+#pragma unroll
+          for (int x = 0; x < NB / 4; ++x) {
+            a[x] = *reinterpret_cast<const f32x4*>(Qc + 128 * mb + RL::kPitch * e + 4 * x);
+            b[x] = *reinterpret_cast<const f32x4*>(dOc + 128 * mb + RL::kPitch * e + 4 * x);
+          }
+#pragma unroll
+          for (int i = 0; i < NB; ++i) {
+            acc[i] = mfma16(a[i >> 2][i & 3], dP[e], acc[i]);
+            acc[NB + i] = mfma16(b[i >> 2][i & 3], S[e], acc[NB + i]);
+          }
+        }
+      }
+    }
+    buf ^= 1;
+  }
+
+  // (the LDS of both operands' buffers is one allocation only by declaration order: use each for its own half)
+  if constexpr (KS > 1) {
+    f32x4(&a)[NB] = *reinterpret_cast<f32x4(*)[NB]>(&acc[0]);
+    f32x4(&b)[NB] = *reinterpret_cast<f32x4(*)[NB]>(&acc[NB]);
+    sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&Qs[0][0]), kw, qg, a);
+    sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&dOs[0][0]), kw, qg, b);
+    if (qg != 0) return;
+  }
+  // lane (n16, lg) holds columns NB * (4*lg + e) + b of its key
+  const int key = 16 * kw + n16;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const float f = half == 0 ? scale : 1.f;
+    float* out = half == 0 ? dk : dv;
+    float* dst = tile.slot >= 0
+                     ? partial + ((size_t)tile.slot * Hkv + g) * (2 * kKeys * HD) + (size_t)(half * kKeys + key) * HD
+                     : out + ((size_t)kcol * Hkv + g) * HD;
+    if (tile.slot < 0 && kcol >= tile.k1) continue;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int x = 0; x < NB / 4; ++x) {
+        f32x4* p = reinterpret_cast<f32x4*>(dst + NB * (4 * lg + e) + 4 * x);
+        f32x4 r;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) r[b] = acc[half * NB + 4 * x + b][e];
+        if (tile.slot < 0) {
+          r *= f;
+          // a segment call adds to the caller's accumulators (this block is the only
+          // owner of the key in the launch)
+          if (accumulate) r += *p;
+        }
+        *p = r;
+      }
+  }
+}
+
+// Adds the partial sums of a split key tile in slot order and writes dK/dV.
+template <int HD>
+__global__ __launch_bounds__(256) void dkdv_reduce_f32_kernel(const KvReduce* __restrict__ red,
+                                                              const float* __restrict__ partial,
+                                                              float* __restrict__ dk,
+                                                              float* __restrict__ dv, int Hkv,
+                                                              float scale, int keys) {
+  // four blocks per (tile, kv head)
+  const KvReduce r = red[(blockIdx.x >> 2) / Hkv];
+  const int g = (blockIdx.x >> 2) % Hkv, n = (r.k1 - r.k0) * (HD / 4);
+  const size_t slot_stride = (size_t)Hkv * (2 * keys * HD);
+  const float* base = partial + ((size_t)r.first_slot * Hkv + g) * (2 * keys * HD);
+  for (int i = (blockIdx.x & 3) * 256 + threadIdx.x; i < n; i += 1024) {
+    f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
+    for (int p = 0; p < r.nparts; ++p) {
+      const float* src = base + (size_t)p * slot_stride + (size_t)4 * i;
+      sk += *reinterpret_cast<const f32x4*>(src);
+      sv += *reinterpret_cast<const f32x4*>(src + keys * HD);
+    }
+    const size_t o = ((size_t)(r.k0 + i / (HD / 4)) * Hkv + g) * HD + 4 * (i % (HD / 4));
+    *reinterpret_cast<f32x4*>(dk + o) = sk * scale;
+    *reinterpret_cast<f32x4*>(dv + o) = sv;
+  }
+}
+
+template <int HD>
 int fwd_impl(const LaunchArgs& a) {
   hipStream_t st = (hipStream_t)a.stream;
   clear_hip_error();
-  dim3 grid((unsigned)a.sched->q_tiles.size(), (unsigned)a.p.n_q_heads);
-  fwd_f32_kernel<D><<<grid, 256, 0, st>>>(a.sched->d_q_tiles, a.sched->d_segs, a.d_kend,
-                                          (const float*)a.q, (const float*)a.k, (const float*)a.v,
-                                          (float*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads,
-                                          a.p.softmax_scale);
+  const size_t blocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
+  if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
+  constexpr int kSplit = HD == 64 ? 4 : 2;
+  auto kernel = a.tc.split == 1 ? fwd_f32_kernel<HD, 1> : fwd_f32_kernel<HD, kSplit>;
+  kernel<<<(unsigned)blocks, kThreads, 0, st>>>(
+      a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
+      (const float*)a.v, (float*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
+      a.tc.hblocks, a.p.softmax_scale);
   return launch_status(__func__);
 }
 
-template <int D>
+template <int HD>
 int bwd_impl(const LaunchArgs& a) {
   hipStream_t st = (hipStream_t)a.stream;
   clear_hip_error();
   const size_t row0 = (size_t)a.row_begin * a.p.n_q_heads;
   const size_t rows = (size_t)(a.row_end - a.row_begin) * a.p.n_q_heads;
-  if (a.stages & DTA_BWD_DELTA) {
-    delta_f32_kernel<D><<<(unsigned)((rows + kRows - 1) / kRows), 256, 0, st>>>(
-        (const float*)a.o + row0 * D, (const float*)a.d_o + row0 * D, a.delta + row0, rows);
+  const size_t qblocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
+  const size_t kblocks = a.sched->kv_items.size() * (size_t)a.p.n_kv_heads;
+  if (qblocks == 0 || qblocks > 0x7fffffffu || kblocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
+  constexpr int kSplit = HD == 64 ? 4 : 2;
+  const bool fused_delta = (a.stages & DTA_BWD_DELTA) && (a.stages & DTA_BWD_DQ);
+  if ((a.stages & DTA_BWD_DELTA) && !fused_delta) {
+    delta_f32_kernel<HD><<<(unsigned)((rows + 63) / 64), 256, 0, st>>>(
+        (const float*)a.o + row0 * HD, (const float*)a.d_o + row0 * HD, a.delta + row0, rows);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
   if (a.stages & DTA_BWD_DQ) {
-    dim3 gq((unsigned)a.sched->q_tiles.size(), (unsigned)a.p.n_q_heads);
-    dq_f32_kernel<D><<<gq, 256, 0, st>>>(a.sched->d_q_tiles, a.sched->d_segs, a.d_kend,
-                                         (const float*)a.q, (const float*)a.k, (const float*)a.v,
-                                         (const float*)a.d_o, a.lse_in, a.delta, (float*)a.dq,
-                                         a.p.n_q_heads, a.p.n_kv_heads, a.p.softmax_scale);
+    auto kernel = a.tc.split == 1 ? dq_f32_kernel<HD, 1> : dq_f32_kernel<HD, kSplit>;
+    kernel<<<(unsigned)qblocks, kThreads, 0, st>>>(
+        a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
+        (const float*)a.v, (const float*)a.d_o, fused_delta ? (const float*)a.o : nullptr, a.lse_in,
+        a.delta, (float*)a.dq, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb, a.tc.hblocks, a.p.softmax_scale);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
   if (a.stages & DTA_BWD_DKDV) {
-    dim3 gk((unsigned)a.sched->kv_tiles.size(), (unsigned)a.p.n_kv_heads);
-    dkdv_f32_kernel<D><<<gk, 256, 0, st>>>(a.sched->d_kv_tiles, a.d_kend, (const float*)a.q,
-                                           (const float*)a.k, (const float*)a.v,
-                                           (const float*)a.d_o, a.lse_in, a.delta,
-                                           a.dk_acc ? a.dk_acc : (float*)a.dk,
-                                           a.dk_acc ? a.dv_acc : (float*)a.dv, a.dk_acc != nullptr,
-                                           a.p.n_q_heads, a.p.n_kv_heads, a.p.softmax_scale);
+    auto kernel = a.tc.split == 1 ? dkdv_f32_kernel<HD, 1> : dkdv_f32_kernel<HD, kSplit>;
+    kernel<<<(unsigned)kblocks, a.tc.split == 1 ? 256 : 512, 0, st>>>(
+        a.sched->d_kv_items, a.d_kend, (const float*)a.q, (const float*)a.k, (const float*)a.v,
+        (const float*)a.d_o, a.lse_in, a.delta, a.dk_acc ? a.dk_acc : (float*)a.dk,
+        a.dk_acc ? a.dv_acc : (float*)a.dv, a.partial, a.dk_acc != nullptr, a.p.n_q_heads,
+        a.p.n_kv_heads, a.p.softmax_scale);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
+    if (!a.sched->kv_reduce.empty()) {
+      dkdv_reduce_f32_kernel<HD><<<(unsigned)(a.sched->kv_reduce.size() * a.p.n_kv_heads * 4), 256, 0, st>>>(
+          a.sched->d_kv_reduce, a.partial, (float*)a.dk, (float*)a.dv, a.p.n_kv_heads, a.p.softmax_scale,
+          a.sched->kv_keys);
+      { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
+    }
   }
   return DTA_OK;
 }

@@ -48,9 +48,9 @@ struct KvTile {
   int32_t pad[3];
 };
 
-// One launch unit of the bf16 dK/dV kernel: key tile [k0, k1) and a slice
-// [it_begin, it_end) of its flattened (q head of the group, 64-row query chunk)
-// iteration space.  A tile whose walk is much longer than the average is cut
+// One launch unit of the dK/dV kernels: key tile [k0, k1) and a slice
+// [it_begin, it_end) of its flattened (query chunk of Schedule::q_rows rows, q head
+// of the group) iteration space.  A tile whose walk is much longer than the average is cut
 // into several items so that no block becomes the critical path; such items
 // write fp32 partial sums to workspace slot `slot` (>= 0) and a reduce launch
 // adds them in a fixed order.  slot < 0: the item covers the whole tile and
@@ -74,6 +74,7 @@ struct KvReduce {
 // dispatcher, which hands out blocks in index order, balances the CUs.
 struct Schedule {
   int bm = 0, bn = 0;
+  int q_rows = 64;   // query rows per step of a dK/dV walk
   int kv_keys = 0;   // keys per dK/dV tile in this schedule: bn, or 2*bn where the walks are long
   std::vector<QTile> q_tiles;
   std::vector<KeySeg> segs;
@@ -95,7 +96,6 @@ struct Schedule {
   size_t d_blob_cap = 0;
   QTile* d_q_tiles = nullptr;
   KeySeg* d_segs = nullptr;
-  KvTile* d_kv_tiles = nullptr;
   KvItem* d_kv_items = nullptr;
   KvReduce* d_kv_reduce = nullptr;
 };
@@ -144,17 +144,19 @@ constexpr int kNumCUs = 256;
 // Key tiles of 256 keys (eight-wave dK/dV blocks) for schedules of long walks.
 constexpr bool wide_key_tiles = true;
 
-// Key of a whole-tree schedule in dta_tree::schedules.
-inline uint64_t schedule_key(int bm, int bn, int hkv, int group) {
-  return ((uint64_t)bm << 48) | ((uint64_t)bn << 32) | ((uint64_t)hkv << 16) | (uint64_t)group;
+// Key of a whole-tree schedule in dta_tree::schedules (q_rows <= 128: a multiple of 32).
+inline uint64_t schedule_key(int bm, int bn, int hkv, int group, int q_rows) {
+  return ((uint64_t)bm << 48) | ((uint64_t)(q_rows / 32) << 44) | ((uint64_t)bn << 32) |
+         ((uint64_t)hkv << 16) | (uint64_t)group;
 }
-// Host: build (or fetch) the schedule for tile sizes (bm, bn).
-Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group);
+// Host: build (or fetch) the schedule for tile sizes (bm, bn) and dK/dV walks in
+// steps of q_rows query rows.
+Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q_rows = 64);
 // Same for a segment call on rows [t_begin, t_end), which must lie inside one
 // node's segment (checked by the caller): query tiles over the rows, key tiles
 // over the root path up to t_end, no split items.
 Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int group,
-                               int64_t t_begin, int64_t t_end);
+                               int64_t t_begin, int64_t t_end, int q_rows = 64);
 // Bytes of fp32 partial dK/dV sums the split items of a schedule need.
 size_t partial_bytes(const Schedule& s);
 
@@ -164,8 +166,12 @@ struct TileChoice {
   int bn;       // keys per dK/dV work item
   int hb;       // q heads of one kv group handled by one forward block
   int hblocks;  // blocks per (tile, kv head) = group size / hb
+  int q_rows;   // query rows per step of a dK/dV walk
+  int split;    // wave groups of a block that share out each streamed chunk (fp32 mode; 1 in bf16 mode)
 };
-int choose_tiles(const dta_attn_params_t* p, TileChoice* out);
+// rows: query rows of the launch (tokens of the tree or of the segment); a launch
+// too small to fill the chip may get other tiles.
+int choose_tiles(const dta_attn_params_t* p, TileChoice* out, int64_t rows = INT64_MAX);
 int validate_params(const dta_attn_params_t* p);
 
 struct LaunchArgs {

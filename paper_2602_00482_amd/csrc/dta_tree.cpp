@@ -183,8 +183,8 @@ size_t partial_bytes(const Schedule& s) {
   return (size_t)s.n_slots * (size_t)s.hkv * 2u * (size_t)s.kv_keys * 128u * sizeof(float);
 }
 
-Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group) {
-  const uint64_t key = schedule_key(bm, bn, hkv, group);
+Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q_rows) {
+  const uint64_t key = schedule_key(bm, bn, hkv, group, q_rows);
   auto it = tree->schedules.find(key);
   if (it != tree->schedules.end()) return it->second;
   // built aside and moved into the map when complete: an allocation failure half
@@ -192,6 +192,7 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group) {
   Schedule s;
   s.bm = bm;
   s.bn = bn;
+  s.q_rows = q_rows;
   s.hkv = hkv;
   s.group = group;
   const int64_t T = tree->info.n_tokens;
@@ -257,7 +258,7 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group) {
     s.kv_tiles.clear();
     s.bwd_tile_pairs = 0;
     s.kv_keys = keys;
-    constexpr int64_t kChunkRows = 64, kFixedSteps = 7;   // a block's prologue and epilogue cost about 7 walk steps
+    constexpr int64_t kFixedSteps = 7;   // a block's prologue and epilogue cost about 7 walk steps
     const int64_t INF = std::numeric_limits<int64_t>::max() / 4;
     std::vector<int64_t> best((size_t)T + 1, INF);
     std::vector<int32_t> from((size_t)T + 1, -1);
@@ -277,7 +278,7 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group) {
         mx = std::max(mx, off + tree->subtree_tokens[(size_t)u]);
         // the tile ends with this node, or after bn keys inside it
         const int64_t p = std::min(limit, off + tree->seg_len[(size_t)u]);
-        const int64_t c = base + kFixedSteps + (mx - q + kChunkRows - 1) / kChunkRows * group;
+        const int64_t c = base + kFixedSteps + (mx - q + q_rows - 1) / q_rows * group;
         if (c < best[(size_t)p]) {   // (on ties the earlier start, visited first, stays)
           best[(size_t)p] = c;
           from[(size_t)p] = (int32_t)q;
@@ -324,18 +325,20 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group) {
   // walks are cut four times finer (1/6 of a share): measured on the deep tree with its 128
   // root tiles of 17 344 steps per kv head, 3 % faster than uncut walks handed
   // out block by block, while the same queues over uncut walks are 2.5 % slower.
+  // (fp32 mode: a step is 32 rows at a sixteenth of the rate, several microseconds,
+  // so pieces may be as short as four steps before their partial sums cost more)
+  const int64_t min_piece = q_rows == 64 && bn == 128 ? 32 : 4;
   auto cut_items = [&](int64_t target_items) {
-    constexpr int kChunkRows = 64;
     s.kv_items.clear();
     s.kv_reduce.clear();
     s.n_slots = 0;
     s.kv_item_iters = 0;
     auto iters_of = [&](const KvTile& t) {
-      return (int64_t)((t.q_end - t.k0 + kChunkRows - 1) / kChunkRows) * group;
+      return (int64_t)((t.q_end - t.k0 + q_rows - 1) / q_rows) * group;
     };
     int64_t total = 0;
     for (const KvTile& t : s.kv_tiles) total += iters_of(t);
-    const int64_t target = std::max<int64_t>(32, (total * hkv + target_items - 1) / target_items);
+    const int64_t target = std::max<int64_t>(min_piece, (total * hkv + target_items - 1) / target_items);
     std::vector<int64_t> icost;
     for (const KvTile& t : s.kv_tiles) {
       const int64_t iters = iters_of(t);
@@ -374,7 +377,8 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group) {
     // finer pieces and would only pay for more partial sums)
     if (s.kv_queues && s.kv_item_iters > 384 * (int64_t)s.kv_items.size()) cut_items(resident * 6);
   };
-  cut_for(2 * (int64_t)kNumCUs);
+  if (min_piece == 32) cut_for(2 * (int64_t)kNumCUs);
+  else cut_items((q_rows == 32 ? 2 : 1) * (int64_t)kNumCUs * 3 / 2);   // fp32: four-wave blocks, eight when split
   constexpr int64_t kWideMinIters = 256;
   if (bn == 128 && wide_key_tiles && s.kv_item_iters > kWideMinIters * (int64_t)s.kv_tiles.size()) {
     // Long walks (256 steps per 128-key tile and more): tiles of 256 keys for the
@@ -393,8 +397,8 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group) {
 }
 
 Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int group,
-                               int64_t t_begin, int64_t t_end) {
-  const std::array<uint64_t, 3> key = {schedule_key(bm, bn, hkv, group), (uint64_t)t_begin,
+                               int64_t t_begin, int64_t t_end, int q_rows) {
+  const std::array<uint64_t, 3> key = {schedule_key(bm, bn, hkv, group, q_rows), (uint64_t)t_begin,
                                        (uint64_t)t_end};
   auto it = tree->segment_schedules.find(key);
   if (it != tree->segment_schedules.end()) {
@@ -405,6 +409,7 @@ Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int grou
   s.last_used = ++tree->use_counter;
   s.bm = bm;
   s.bn = bn;
+  s.q_rows = q_rows;
   s.kv_keys = bn;
   s.hkv = hkv;
   s.group = group;
@@ -462,9 +467,8 @@ Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int grou
   };
   add_tiles(t_begin, t_end, true);
   for (const KeySeg& ks : prefix) add_tiles(ks.start, ks.end, false);
-  constexpr int kChunkRows = 64;
   for (const KvTile& t : s.kv_tiles) {
-    const int64_t iters = (int64_t)((t.q_end - t.q_begin + kChunkRows - 1) / kChunkRows) * group;
+    const int64_t iters = (int64_t)((t.q_end - t.q_begin + q_rows - 1) / q_rows) * group;
     s.kv_items.push_back(KvItem{t.k0, t.k1, t.q_end, t.q_full_end, 0, (int32_t)iters, -1, t.q_begin});
     s.kv_item_iters += iters;
   }
@@ -500,15 +504,25 @@ int validate_params(const dta_attn_params_t* p) {
   return DTA_OK;
 }
 
-int choose_tiles(const dta_attn_params_t* p, TileChoice* out) {
+int choose_tiles(const dta_attn_params_t* p, TileChoice* out, int64_t rows) {
   int st = validate_params(p);
   if (st != DTA_OK) return st;
   int G = p->n_q_heads / p->n_kv_heads;
   if (p->dtype == DTA_F32) {
-    out->bm = 64;
-    out->bn = 64;
-    out->hb = 1;
-    out->hblocks = G;
+    // Eight waves of 16 rows: R row tiles (hb q heads x 16-row blocks) x `split`
+    // groups that share out the streamed keys.  A launch of fewer than 2048 waves
+    // of 16 rows leaves half of the chip's wave slots empty: there the walks are
+    // split instead.
+    const bool small = rows / 16 * p->n_q_heads < 2048;
+    out->split = !small ? 1 : p->head_dim == 64 ? 4 : 2;
+    const int R = 8 / out->split;
+    int hb = 1;
+    while (hb < R && G % (2 * hb) == 0) hb *= 2;
+    out->hb = hb;
+    out->hblocks = G / hb;
+    out->bm = 16 * (R / hb);
+    out->q_rows = 32 * out->split;
+    out->bn = out->split == 1 ? 64 : 16 * R;
   } else {
     // eight waves per block: hb q heads of the group x (8/hb) 32-row query blocks
     int hb = (G % 8 == 0) ? 8 : (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
@@ -516,6 +530,8 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out) {
     out->hblocks = G / hb;
     out->bm = 32 * (8 / hb);
     out->bn = 128;
+    out->q_rows = 64;
+    out->split = 1;
   }
   return DTA_OK;
 }
@@ -567,12 +583,12 @@ int dta_tree_schedule_info(dta_tree_t* tree, const dta_attn_params_t* params,
                            dta_schedule_info_t* out) {
   if (!tree || !out) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc);
+  int st = dta::choose_tiles(params, &tc, tree->info.n_tokens);
   if (st != DTA_OK) return st;
   try {
     std::lock_guard<std::mutex> lock(tree->mu);
     dta::Schedule& s = dta::get_schedule(tree, tc.bm, tc.bn, params->n_kv_heads,
-                                         params->n_q_heads / params->n_kv_heads);
+                                         params->n_q_heads / params->n_kv_heads, tc.q_rows);
     out->fwd_q_tile_tokens = tc.bm;
     out->fwd_work_items = (int64_t)s.q_tiles.size();
     out->fwd_tile_pairs = s.fwd_tile_pairs;
@@ -581,7 +597,7 @@ int dta_tree_schedule_info(dta_tree_t* tree, const dta_attn_params_t* params,
     out->bwd_tile_pairs = s.bwd_tile_pairs;
     out->metadata_bytes =
         (int64_t)(tree->token_kend.size() * sizeof(int32_t) + s.q_tiles.size() * sizeof(dta::QTile) +
-                  s.segs.size() * sizeof(dta::KeySeg) + s.kv_tiles.size() * sizeof(dta::KvTile) +
+                  s.segs.size() * sizeof(dta::KeySeg) +
                   s.kv_items.size() * sizeof(dta::KvItem) + s.kv_reduce.size() * sizeof(dta::KvReduce));
   } catch (const std::bad_alloc&) {
     return DTA_ERR_ALLOC;

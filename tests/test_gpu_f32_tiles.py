@@ -1,0 +1,40 @@
+"""fp32 kernels at the edges of their tiles: launches that fill the chip (one K/V
+copy for eight row tiles, dK/dV walks cut into partial sums) on ragged segments,
+and launches small enough for the blocks' wave groups to share out the streamed
+chunk, where some groups have no rows at all.  Whole tensors against the fp64
+oracle at the fp32 bar of the other parity tests (max|err| / max|ref| <= 1e-5)."""
+import math
+
+import numpy as np
+import pytest
+
+import paper_2602_00482_amd as dta
+from oracle import tree_direct as B
+from workloads import make_inputs_numpy
+from parity_util import rel_err, run_hip
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,seg", [
+    (32, 8, [517, 33, 64, 1, 129, 300, 31]),      # large launch, 4 heads x 2 row blocks of 16
+    (32, 2, [600, 15, 257, 96, 65]),              # 16 heads in 2 head blocks, 16-token tiles
+    (36, 12, [700, 47, 200, 1]),                  # group of 3: one head per block, 128-token tiles
+    (4, 2, [17, 1, 15, 16]),                      # small launch, walks shorter than one wave group's rows
+    (8, 1, [127, 128, 129, 33]),                  # small launch, edges of the 128-row chunk
+])
+def test_tiles_against_the_oracle(Hq, Hkv, seg, d):
+    parent = np.array([-1] + [0] * (len(seg) - 1), dtype=np.int32)
+    seg = np.array(seg, dtype=np.int32)
+    T, scale = int(seg.sum()), 1.0 / math.sqrt(d)
+    tree = dta.tree_build(parent, seg)
+    tile = tree.schedule_info(dta.AttnParams(Hq, Hkv, d, scale, dta.F32))["bwd_kv_tile_tokens"]
+    tree.destroy()
+    assert tile == (64 if Hq > 8 or d == 128 else 32), tile   # which form the launch takes
+    x = make_inputs_numpy(T, Hq, Hkv, d, 17, dtype="f32")
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32")
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
+    for name, ref in (("o", O), ("lse", LSE), ("dq", dQ), ("dk", dK), ("dv", dV)):
+        assert rel_err(got[name], ref) <= 1e-5, name
