@@ -35,12 +35,12 @@ size_t partial_offset(const dta_tree* tree, const dta_attn_params_t* p) {
 // (builds the host schedule if this head configuration has not been seen yet); 0 when out of memory
 size_t bwd_workspace_bytes(dta_tree* tree, const dta_attn_params_t* p) {
   dta::TileChoice tc;
-  if (dta::choose_tiles(p, &tc, tree->info.n_tokens) != DTA_OK) return 0;
+  if (dta::choose_tiles(p, &tc, dta::whole_tree(tree, true)) != DTA_OK) return 0;
   try {
     std::lock_guard<std::mutex> lock(tree->mu);
     return partial_offset(tree, p) +
            dta::partial_bytes(dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads,
-                                                p->n_q_heads / p->n_kv_heads, tc.q_rows));
+                                                p->n_q_heads / p->n_kv_heads, tc.walk));
   } catch (const std::bad_alloc&) {
     return 0;
   }
@@ -238,7 +238,7 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
   if (!allocate_ok) {
     // a caller that must not allocate: everything has to be resident already
     // (dta_tree_attn_prepare on this device); look, do not build
-    const uint64_t key = dta::schedule_key(tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, tc.q_rows);
+    const uint64_t key = dta::schedule_key(tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, tc.walk);
     auto it = tree->schedules.find(key);
     if (it == tree->schedules.end() || it->second.device != dev || tree->kend_device != dev ||
         !tree->last_use)
@@ -249,9 +249,9 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
   dta::Schedule* s;
   try {
     s = t_begin < 0
-            ? &dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, tc.q_rows)
+            ? &dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, tc.walk)
             : &dta::get_segment_schedule(tree, tc.bm, tc.bn, p->n_kv_heads,
-                                         p->n_q_heads / p->n_kv_heads, t_begin, t_end, tc.q_rows);
+                                         p->n_q_heads / p->n_kv_heads, t_begin, t_end, tc.walk);
   } catch (const std::bad_alloc&) {
     return DTA_ERR_ALLOC;
   }
@@ -354,11 +354,13 @@ size_t dta_tree_attn_workspace_bytes(const dta_tree_t* tree, const dta_attn_para
 
 int dta_tree_attn_prepare(dta_tree_t* tree, const dta_attn_params_t* params) {
   if (!tree) return DTA_ERR_INVALID_ARG;
-  dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc, tree->info.n_tokens);
-  if (st != DTA_OK) return st;
-  dta::Schedule* s = nullptr;
-  if ((st = ensure_device(tree, tc, params, &s)) != DTA_OK) return st;
+  for (const bool backward : {false, true}) {
+    dta::TileChoice tc;
+    int st = dta::choose_tiles(params, &tc, dta::whole_tree(tree, backward));
+    if (st != DTA_OK) return st;
+    dta::Schedule* s = nullptr;
+    if ((st = ensure_device(tree, tc, params, &s)) != DTA_OK) return st;
+  }
   // set-up for dta_tree_attn_bwd_noalloc: resolve this device's copy of the
   // library-held scratch array now, so that the call itself has nothing left to do
   int dev = -1;
@@ -373,7 +375,7 @@ int dta_tree_attn_fwd(dta_tree_t* tree, const dta_attn_params_t* params, const v
                       size_t workspace_bytes, void* hip_stream) {
   if (!tree || !params) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc, tree->info.n_tokens);
+  int st = dta::choose_tiles(params, &tc, dta::whole_tree(tree, false));
   if (st != DTA_OK) return st;
   if (!q || !k || !v || !o || !lse) return DTA_ERR_INVALID_ARG;
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse))
@@ -427,7 +429,7 @@ int bwd_entry(dta_tree* tree, const dta_attn_params_t* params, const void* q, co
   if (!tree || !params) return DTA_ERR_INVALID_ARG;
   if (stage_mask == 0 || (stage_mask & ~(uint32_t)DTA_BWD_ALL)) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc, tree->info.n_tokens);
+  int st = dta::choose_tiles(params, &tc, dta::whole_tree(tree, true));
   if (st != DTA_OK) return st;
   const bool want_dq = stage_mask & DTA_BWD_DQ, want_dkdv = stage_mask & DTA_BWD_DKDV;
   if (!q || !k || !v || !o || !lse || !d_o) return DTA_ERR_INVALID_ARG;
@@ -484,6 +486,16 @@ static int check_segment(const dta_tree* tree, int64_t t_begin, int64_t t_end) {
   return DTA_OK;
 }
 
+// tiles for rows [t_begin, t_end) of one node, which see its root path up to t_end
+static int segment_tiles(const dta_tree* tree, const dta_attn_params_t* p, int64_t t_begin, int64_t t_end,
+                         bool backward, dta::TileChoice* out) {
+  const int32_t u = tree->token_node[(size_t)t_begin];
+  return dta::choose_tiles(
+      p, out,
+      dta::CallShape{backward, true, t_end - t_begin,
+                     tree->node_start_depth[(size_t)u] + t_end - tree->node_offset[(size_t)u]});
+}
+
 int dta_tree_attn_fwd_segment(dta_tree_t* tree, const dta_attn_params_t* params, int64_t t_begin,
                               int64_t t_end, const void* q, const void* k, const void* v, void* o,
                               float* lse, void* workspace, size_t workspace_bytes,
@@ -492,9 +504,10 @@ int dta_tree_attn_fwd_segment(dta_tree_t* tree, const dta_attn_params_t* params,
   (void)workspace_bytes;
   if (!tree || !params) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc, t_end - t_begin);
+  int st = dta::validate_params(params);
   if (st != DTA_OK) return st;
   if ((st = check_segment(tree, t_begin, t_end)) != DTA_OK) return st;
+  if ((st = segment_tiles(tree, params, t_begin, t_end, false, &tc)) != DTA_OK) return st;
   if (!q || !k || !v || !o || !lse) return DTA_ERR_INVALID_ARG;
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse))
     return DTA_ERR_INVALID_ARG;
@@ -525,9 +538,10 @@ int dta_tree_attn_bwd_segment(dta_tree_t* tree, const dta_attn_params_t* params,
                               size_t workspace_bytes, void* hip_stream) {
   if (!tree || !params) return DTA_ERR_INVALID_ARG;
   dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc, t_end - t_begin);
+  int st = dta::validate_params(params);
   if (st != DTA_OK) return st;
   if ((st = check_segment(tree, t_begin, t_end)) != DTA_OK) return st;
+  if ((st = segment_tiles(tree, params, t_begin, t_end, true, &tc)) != DTA_OK) return st;
   if (!q || !k || !v || !o || !lse || !d_o || !dq || !dk_acc || !dv_acc) return DTA_ERR_INVALID_ARG;
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse) ||
       misaligned(d_o) || misaligned(dq) || misaligned(dk_acc) || misaligned(dv_acc))

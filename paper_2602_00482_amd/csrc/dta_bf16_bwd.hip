@@ -686,8 +686,11 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
   const size_t qblocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
   const size_t kblocks = a.sched->kv_items.size() * (size_t)a.p.n_kv_heads;
   if (qblocks == 0 || qblocks > 0x7fffffffu || kblocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
-  // the dQ launch computes the row statistics itself when both stages are asked for
-  const bool fused_delta = (a.stages & DTA_BWD_DELTA) && (a.stages & DTA_BWD_DQ);
+  // dQ and dK/dV both in the form for small launches: one launch does both
+  const bool one_launch =
+      a.tc.q_small && a.tc.k_small && (a.stages & DTA_BWD_DQ) && (a.stages & DTA_BWD_DKDV);
+  // otherwise the dQ launch computes the row statistics itself when both stages are asked for
+  const bool fused_delta = (a.stages & DTA_BWD_DELTA) && (a.stages & DTA_BWD_DQ) && !one_launch;
   if ((a.stages & DTA_BWD_DELTA) && !fused_delta) {
     constexpr size_t kDeltaRows = 256 / (HD / 8);   // rows per block of the delta kernel
     delta_bf16_kernel<HD><<<(unsigned)((rows + kDeltaRows - 1) / kDeltaRows), 256, 0, st>>>(
@@ -695,7 +698,13 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
         a.lse_in + row0, a.delta + row0, a.lse2 + row0, 1.f / a.p.softmax_scale, rows);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
-  if (a.stages & DTA_BWD_DQ) {
+  if (one_launch) {
+    const int ls = launch_bwd_bf16_small(a, DTA_BWD_DQ | DTA_BWD_DKDV, false);
+    if (ls != DTA_OK) return ls;
+  } else if ((a.stages & DTA_BWD_DQ) && a.tc.q_small) {
+    const int ls = launch_bwd_bf16_small(a, DTA_BWD_DQ, fused_delta);
+    if (ls != DTA_OK) return ls;
+  } else if (a.stages & DTA_BWD_DQ) {
     // Long blocks (at least 64 key chunks each on average) in at least 8 rounds:
     // blocks draw their item from queues, see the kernel.  Shorter blocks would
     // pay more for the draw (an atomic round trip before anything else can
@@ -726,7 +735,6 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
     // short items +0.6...+1.5 %, the 16 long answers and the deep tree +3...+5 %,
     // fewer than 8 rounds lose 1-2 % to the extra launch.
     const bool wide = a.sched->kv_keys == 256;   // tiles of 256 keys: eight waves, one block per CU
-    if (a.sched->kv_keys != 128 && !wide) return DTA_ERR_UNSUPPORTED;
     const size_t resident = (wide ? 1 : 2) * (size_t)kNumCUs;
     const bool queues = a.sched->kv_queues && a.dk_acc == nullptr;
     int* tickets = a.tickets + a.p.n_kv_heads;   // second half: this kernel's counters
@@ -734,12 +742,17 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
       zero_i32_kernel<<<1, 256, 0, st>>>(tickets, a.p.n_kv_heads);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     }
+    if (a.tc.k_small) {
+      const int ls = one_launch ? DTA_OK : launch_bwd_bf16_small(a, DTA_BWD_DKDV, false);
+      if (ls != DTA_OK) return ls;
+    } else {
     auto kernel = wide ? dkdv_bf16_kernel<HD, 8> : dkdv_bf16_kernel<HD, 4>;
     kernel<<<(unsigned)(queues ? resident : kblocks), wide ? 512 : 256, 0, st>>>(
         a.sched->d_kv_items, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
         (const uint16_t*)a.v, (const uint16_t*)a.d_o, a.lse2, a.delta, (uint16_t*)a.dk,
         (uint16_t*)a.dv, a.partial, a.dk_acc, a.dv_acc, a.p.n_q_heads, a.p.n_kv_heads,
         a.p.softmax_scale, queues ? tickets : nullptr, (int)a.sched->kv_items.size());
+    }
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     if (!a.sched->kv_reduce.empty()) {
       dkdv_reduce_kernel<HD><<<(unsigned)(a.sched->kv_reduce.size() * a.p.n_kv_heads * 8), 256, 0, st>>>(

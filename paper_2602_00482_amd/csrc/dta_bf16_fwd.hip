@@ -253,6 +253,7 @@ __global__ void zero_i32_kernel(int* __restrict__ p, int n) {
 int launch_fwd_bf16(const LaunchArgs& a) {
   hipStream_t st = (hipStream_t)a.stream;
   clear_hip_error();
+  if (a.tc.q_small) return launch_fwd_bf16_small(a);
   const size_t blocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
   if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
   // With a workspace for the counters and enough items, resident blocks draw the

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(
           const int kev[4] = {ke.x, ke.y, ke.z, ke.w};
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            S[mb][e] = (k0 + RL::row_of_acc(mb, lg, e) <= qrow) & (qrow < kev[e]) ? S[mb][e] : -INFINITY;
+            S[mb][e] = ((k0 + RL::row_of_acc(mb, lg, e) <= qrow) & (qrow < kev[e])) ? S[mb][e] : -INFINITY;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[mb][e]);
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(kThreads) void dq_f32_kernel(
           const int kev[4] = {ke.x, ke.y, ke.z, ke.w};
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            S[mb][e] = (k0 + RL::row_of_acc(mb, lg, e) <= qrow) & (qrow < kev[e]) ? S[mb][e] : 0.f;
+            S[mb][e] = ((k0 + RL::row_of_acc(mb, lg, e) <= qrow) & (qrow < kev[e])) ? S[mb][e] : 0.f;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) S[mb][e] *= dP[mb][e] - dlt;   // dS
@@ -468,8 +468,8 @@ __global__ __launch_bounds__(kThreads) void dq_f32_kernel(
 
 // Key-stationary: wave = 16 keys, K and V rows in registers; R key tiles x KS
 // groups per block.  Q and dO of the rows that can see the keys are streamed in
-// chunks of 32 * KS rows, q heads of the group innermost, last chunk first; group
-// qg takes rows [32*qg, 32*qg + 32) of every chunk.  KS = 1: four waves, two
+// iterations of 32 rows of one q head, heads innermost, last chunk first, KS
+// iterations per step, one per group.  KS = 1: four waves, two
 // blocks per CU.  KS = 4 / 2: eight waves, trees too small to fill the chip.
 // Long walks are cut into items that write partial sums, as in bf16 mode.
 template <int HD, int KS>
@@ -502,20 +502,26 @@ __global__ __launch_bounds__(KS == 1 ? 256 : 512, KS == 1 ? 2 : 1) void dkdv_f32
 
   const size_t q_stride = (size_t)Hq * HD;
   const uint32_t q_bytes = (uint32_t)q_stride * 4;
-  const int n_chunks = (tile.q_end - tile.q_begin + CH - 1) / CH;
+  const int n_chunks = (tile.q_end - tile.q_begin + 31) / 32;
   const int total = tile.it_end;
+  auto row_of_it = [&](int it) { return tile.q_begin + (n_chunks - 1 - it / G) * 32; };
+  // copies iterations it .. it + KS-1 into buffer b (beyond the last one: the last again, never computed on)
   auto issue = [&](int it, int b) {
-    const int cq = it / G, h = g * G + (it - cq * G);
-    const int r0 = tile.q_begin + (n_chunks - 1 - cq) * CH;
-    const int nv = min(CH, tile.q_end - r0);
-    if (w < kStat / 64) {   // stat is indexed by matrix position
-      const int x = (64 * w + l) % CH;
-      const uint32_t off = (uint32_t)min(32 * (x >> 5) + RL::row_of_pos(x & 31), nv - 1) * (uint32_t)Hq;
-      row_async_load(&stat[b][0][64 * w], lse + (size_t)r0 * Hq + h, off);
-      row_async_load(&stat[b][1][64 * w], delta + (size_t)r0 * Hq + h, off);
+    if (w < kStat / 64) {   // stat is indexed by matrix position; a wave-wide copy covers two iterations
+      const int r_base = row_of_it(min(it + 2 * w + 1, total - 1));
+      const int i = min(it + 2 * w + (KS == 1 ? 0 : l >> 5), total - 1), r0 = row_of_it(i);
+      const int row = min(RL::row_of_pos(l & 31), min(32, tile.q_end - r0) - 1);
+      const uint32_t off = (uint32_t)(r0 - r_base + row) * (uint32_t)Hq + (uint32_t)(i % G);
+      row_async_load(&stat[b][0][64 * w], lse + (size_t)r_base * Hq + g * G, off);
+      row_async_load(&stat[b][1][64 * w], delta + (size_t)r_base * Hq + g * G, off);
     }
-    rows_async_load<HD, CH, NW>(Qs[b], q + (size_t)r0 * q_stride + (size_t)h * HD, q_bytes, nv);
-    rows_async_load<HD, CH, NW>(dOs[b], d_o + (size_t)r0 * q_stride + (size_t)h * HD, q_bytes, nv);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int i = min(it + s, total - 1), r0 = row_of_it(i), nv = min(32, tile.q_end - r0);
+      const size_t at = (size_t)r0 * q_stride + (size_t)(g * G + i % G) * HD;
+      rows_async_load<HD, 32, NW>(&Qs[b][s * RL::kTile], q + at, q_bytes, nv);
+      rows_async_load<HD, 32, NW>(&dOs[b][s * RL::kTile], d_o + at, q_bytes, nv);
+    }
   };
   if (tile.it_begin < total) issue(tile.it_begin, 0);
 
@@ -531,14 +537,13 @@ __global__ __launch_bounds__(KS == 1 ? 256 : 512, KS == 1 ? 2 : 1) void dkdv_f32
 
   const int rlo = qg * RL::kTile + RL::row_lane_off(), clo = qg * RL::kTile + RL::col_lane_off();
   int buf = 0;
-  for (int it = tile.it_begin; it < total; ++it) {
+  for (int it = tile.it_begin; it < total; it += KS) {
     async_wait_all();
     __syncthreads();
-    if (it + 1 < total) issue(it + 1, buf ^ 1);
-    const int c_lo = tile.q_begin + (n_chunks - 1 - it / G) * CH;
-    const int r0 = c_lo + 32 * qg;                                   // this group's rows
+    if (it + KS < total) issue(it + KS, buf ^ 1);
+    const int r0 = row_of_it(min(it + qg, total - 1));   // this group's rows
     const int nr = min(32, tile.q_end - r0);
-    if (nr > 0 && r0 + nr > wave_lo && r0 < wave_hi) {
+    if (it + qg < total && r0 + nr > wave_lo && r0 < wave_hi) {
       const bool need_mask = !(r0 >= tile.k1 && r0 + 32 <= tile.q_full_end);
       const float* Qt = Qs[buf] + rlo;
       const float* dOt = dOs[buf] + rlo;
@@ -566,7 +571,7 @@ __global__ __launch_bounds__(KS == 1 ? 256 : 512, KS == 1 ? 2 : 1) void dkdv_f32
           float p = expf(fmaf(S[e], scale, -ls[e]));
           if (need_mask) {
             const int r = RL::row_of_acc(mb, lg, e);
-            p = (r >= lo) & (r < hi) ? p : 0.f;
+            p = ((r >= lo) & (r < hi)) ? p : 0.f;
           }
           S[e] = p;
           dP[e] = p * (dP[e] - dl[e]);
@@ -659,7 +664,7 @@ int fwd_impl(const LaunchArgs& a) {
   const size_t blocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
   if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
   constexpr int kSplit = HD == 64 ? 4 : 2;
-  auto kernel = a.tc.split == 1 ? fwd_f32_kernel<HD, 1> : fwd_f32_kernel<HD, kSplit>;
+  auto kernel = a.tc.q_small ? fwd_f32_kernel<HD, kSplit> : fwd_f32_kernel<HD, 1>;
   kernel<<<(unsigned)blocks, kThreads, 0, st>>>(
       a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
       (const float*)a.v, (float*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
@@ -684,7 +689,7 @@ int bwd_impl(const LaunchArgs& a) {
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
   if (a.stages & DTA_BWD_DQ) {
-    auto kernel = a.tc.split == 1 ? dq_f32_kernel<HD, 1> : dq_f32_kernel<HD, kSplit>;
+    auto kernel = a.tc.q_small ? dq_f32_kernel<HD, kSplit> : dq_f32_kernel<HD, 1>;
     kernel<<<(unsigned)qblocks, kThreads, 0, st>>>(
         a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
         (const float*)a.v, (const float*)a.d_o, fused_delta ? (const float*)a.o : nullptr, a.lse_in,
@@ -692,8 +697,8 @@ int bwd_impl(const LaunchArgs& a) {
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
   if (a.stages & DTA_BWD_DKDV) {
-    auto kernel = a.tc.split == 1 ? dkdv_f32_kernel<HD, 1> : dkdv_f32_kernel<HD, kSplit>;
-    kernel<<<(unsigned)kblocks, a.tc.split == 1 ? 256 : 512, 0, st>>>(
+    auto kernel = a.tc.k_small ? dkdv_f32_kernel<HD, kSplit> : dkdv_f32_kernel<HD, 1>;
+    kernel<<<(unsigned)kblocks, a.tc.k_small ? 512 : 256, 0, st>>>(
         a.sched->d_kv_items, a.d_kend, (const float*)a.q, (const float*)a.k, (const float*)a.v,
         (const float*)a.d_o, a.lse_in, a.delta, a.dk_acc ? a.dk_acc : (float*)a.dk,
         a.dk_acc ? a.dv_acc : (float*)a.dv, a.partial, a.dk_acc != nullptr, a.p.n_q_heads,

@@ -74,7 +74,7 @@ struct KvReduce {
 // dispatcher, which hands out blocks in index order, balances the CUs.
 struct Schedule {
   int bm = 0, bn = 0;
-  int q_rows = 64;   // query rows per step of a dK/dV walk
+  int q_rows = 64;   // query rows per iteration of a dK/dV walk
   int kv_keys = 0;   // keys per dK/dV tile in this schedule: bn, or 2*bn where the walks are long
   std::vector<QTile> q_tiles;
   std::vector<KeySeg> segs;
@@ -144,34 +144,48 @@ constexpr int kNumCUs = 256;
 // Key tiles of 256 keys (eight-wave dK/dV blocks) for schedules of long walks.
 constexpr bool wide_key_tiles = true;
 
-// Key of a whole-tree schedule in dta_tree::schedules (q_rows <= 128: a multiple of 32).
-inline uint64_t schedule_key(int bm, int bn, int hkv, int group, int q_rows) {
-  return ((uint64_t)bm << 48) | ((uint64_t)(q_rows / 32) << 44) | ((uint64_t)bn << 32) |
-         ((uint64_t)hkv << 16) | (uint64_t)group;
+// How a dK/dV kernel walks its query rows, as far as the schedule has to know.
+struct KvWalk {
+  int q_rows = 64;          // rows per iteration of the walk: 32 or 64
+  int min_piece = 32;       // shortest piece of a cut walk in iterations, a multiple of 4, at most 60
+  int resident = 512;       // blocks of the kernel that the chip holds
+};
+
+// Key of a whole-tree schedule in dta_tree::schedules.
+inline uint64_t schedule_key(int bm, int bn, int hkv, int group, const KvWalk& kw) {
+  return ((uint64_t)(kw.min_piece / 4) << 60) | ((uint64_t)bm << 48) | ((uint64_t)(kw.q_rows / 32) << 44) |
+         ((uint64_t)bn << 32) | ((uint64_t)hkv << 16) | (uint64_t)group;
 }
-// Host: build (or fetch) the schedule for tile sizes (bm, bn) and dK/dV walks in
-// steps of q_rows query rows.
-Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q_rows = 64);
+// Host: build (or fetch) the schedule for tile sizes (bm, bn).
+Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const KvWalk& kw = KvWalk());
 // Same for a segment call on rows [t_begin, t_end), which must lie inside one
 // node's segment (checked by the caller): query tiles over the rows, key tiles
 // over the root path up to t_end, no split items.
 Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int group,
-                               int64_t t_begin, int64_t t_end, int q_rows = 64);
+                               int64_t t_begin, int64_t t_end, const KvWalk& kw = KvWalk());
 // Bytes of fp32 partial dK/dV sums the split items of a schedule need.
 size_t partial_bytes(const Schedule& s);
 
 // Tile sizes the kernels use for a head configuration.
 struct TileChoice {
   int bm;       // query tokens per forward / dQ work item
-  int bn;       // keys per dK/dV work item
+  int bn;       // keys per dK/dV work item; 0: a forward call whose schedule needs no dK/dV part
   int hb;       // q heads of one kv group handled by one forward block
   int hblocks;  // blocks per (tile, kv head) = group size / hb
-  int q_rows;   // query rows per step of a dK/dV walk
-  int split;    // wave groups of a block that share out each streamed chunk (fp32 mode; 1 in bf16 mode)
+  KvWalk walk;
+  bool q_small, k_small;   // forward and dQ, dK/dV: the form for launches too small to fill the chip
 };
-// rows: query rows of the launch (tokens of the tree or of the segment); a launch
-// too small to fill the chip may get other tiles.
-int choose_tiles(const dta_attn_params_t* p, TileChoice* out, int64_t rows = INT64_MAX);
+// What a call covers: `rows` query rows and the `keys` they see (both the tokens of
+// the tree for a whole-tree call).
+struct CallShape {
+  bool backward = true;
+  bool segment = false;
+  int64_t rows = INT32_MAX, keys = INT32_MAX;
+};
+int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& call = CallShape());
+inline CallShape whole_tree(const dta_tree* tree, bool backward) {
+  return CallShape{backward, false, tree->info.n_tokens, tree->info.n_tokens};
+}
 int validate_params(const dta_attn_params_t* p);
 
 struct LaunchArgs {
@@ -220,6 +234,8 @@ int static_scratch(int dev, void** ptr, size_t* bytes);
 int launch_fwd_f32(const LaunchArgs& a);
 int launch_bwd_f32(const LaunchArgs& a);
 int launch_fwd_bf16(const LaunchArgs& a);
+int launch_fwd_bf16_small(const LaunchArgs& a);
+int launch_bwd_bf16_small(const LaunchArgs& a, uint32_t stages, bool fused_delta);
 int launch_bwd_bf16(const LaunchArgs& a);
 
 }  // namespace dta

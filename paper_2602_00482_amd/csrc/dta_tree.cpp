@@ -183,8 +183,9 @@ size_t partial_bytes(const Schedule& s) {
   return (size_t)s.n_slots * (size_t)s.hkv * 2u * (size_t)s.kv_keys * 128u * sizeof(float);
 }
 
-Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q_rows) {
-  const uint64_t key = schedule_key(bm, bn, hkv, group, q_rows);
+Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const KvWalk& kw) {
+  const uint64_t key = schedule_key(bm, bn, hkv, group, kw);
+  const int q_rows = kw.q_rows;
   auto it = tree->schedules.find(key);
   if (it != tree->schedules.end()) return it->second;
   // built aside and moved into the map when complete: an allocation failure half
@@ -309,6 +310,7 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q
     for (size_t i : by_cost) sorted.push_back(s.kv_tiles[i]);
     s.kv_tiles.swap(sorted);
   };
+  if (bn == 0) return tree->schedules.emplace(key, std::move(s)).first->second;   // query tiles only
   cut_key_tiles(bn);
 
   // ---- dK/dV launch items: cut the longest walks so that no block becomes the
@@ -325,9 +327,6 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q
   // walks are cut four times finer (1/6 of a share): measured on the deep tree with its 128
   // root tiles of 17 344 steps per kv head, 3 % faster than uncut walks handed
   // out block by block, while the same queues over uncut walks are 2.5 % slower.
-  // (fp32 mode: a step is 32 rows at a sixteenth of the rate, several microseconds,
-  // so pieces may be as short as four steps before their partial sums cost more)
-  const int64_t min_piece = q_rows == 64 && bn == 128 ? 32 : 4;
   auto cut_items = [&](int64_t target_items) {
     s.kv_items.clear();
     s.kv_reduce.clear();
@@ -338,7 +337,7 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q
     };
     int64_t total = 0;
     for (const KvTile& t : s.kv_tiles) total += iters_of(t);
-    const int64_t target = std::max<int64_t>(min_piece, (total * hkv + target_items - 1) / target_items);
+    const int64_t target = std::max<int64_t>(kw.min_piece, (total * hkv + target_items - 1) / target_items);
     std::vector<int64_t> icost;
     for (const KvTile& t : s.kv_tiles) {
       const int64_t iters = iters_of(t);
@@ -377,8 +376,8 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q
     // finer pieces and would only pay for more partial sums)
     if (s.kv_queues && s.kv_item_iters > 384 * (int64_t)s.kv_items.size()) cut_items(resident * 6);
   };
-  if (min_piece == 32) cut_for(2 * (int64_t)kNumCUs);
-  else cut_items((q_rows == 32 ? 2 : 1) * (int64_t)kNumCUs * 3 / 2);   // fp32: four-wave blocks, eight when split
+  if (bn == 128) cut_for(kw.resident);
+  else cut_items((int64_t)kw.resident * 3 / 2);
   constexpr int64_t kWideMinIters = 256;
   if (bn == 128 && wide_key_tiles && s.kv_item_iters > kWideMinIters * (int64_t)s.kv_tiles.size()) {
     // Long walks (256 steps per 128-key tile and more): tiles of 256 keys for the
@@ -397,8 +396,9 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, int q
 }
 
 Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int group,
-                               int64_t t_begin, int64_t t_end, int q_rows) {
-  const std::array<uint64_t, 3> key = {schedule_key(bm, bn, hkv, group, q_rows), (uint64_t)t_begin,
+                               int64_t t_begin, int64_t t_end, const KvWalk& kw) {
+  const int q_rows = kw.q_rows;
+  const std::array<uint64_t, 3> key = {schedule_key(bm, bn, hkv, group, kw), (uint64_t)t_begin,
                                        (uint64_t)t_end};
   auto it = tree->segment_schedules.find(key);
   if (it != tree->segment_schedules.end()) {
@@ -465,8 +465,10 @@ Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int grou
       s.bwd_tile_pairs += (t_end - qb) * bn;
     }
   };
-  add_tiles(t_begin, t_end, true);
-  for (const KeySeg& ks : prefix) add_tiles(ks.start, ks.end, false);
+  if (bn != 0) {   // 0: query tiles only
+    add_tiles(t_begin, t_end, true);
+    for (const KeySeg& ks : prefix) add_tiles(ks.start, ks.end, false);
+  }
   for (const KvTile& t : s.kv_tiles) {
     const int64_t iters = (int64_t)((t.q_end - t.q_begin + q_rows - 1) / q_rows) * group;
     s.kv_items.push_back(KvItem{t.k0, t.k1, t.q_end, t.q_full_end, 0, (int32_t)iters, -1, t.q_begin});
@@ -504,7 +506,32 @@ int validate_params(const dta_attn_params_t* p) {
   return DTA_OK;
 }
 
-int choose_tiles(const dta_attn_params_t* p, TileChoice* out, int64_t rows) {
+namespace {
+// Which bf16 calls take the form for launches too small to fill the chip
+// (dta_bf16_small.hip).  The unit is what a block of the other form holds one wave
+// (rows) or one block (keys) for; measured on MI355X, head_dim 128, in us, the
+// small form against the other one:
+//   forward   512 row tiles: 14.5 / 18.3 (32/8 heads), 15.2 / 28.7 (16/16);
+//             1024: 24.8 / 23.0 (32/8), 23.8 / 18.7 (64/8), 30.2 / 34.9 (16/16)
+//   backward of a tree, both kernels small (one launch) / both large:
+//             1536 row tiles: 82 / 120 (32/8), 122 / 122 (16/16), 148 / 160 (8/2);
+//             2048: 115 / 131, but 114 with only dK/dV small; 3072: dK/dV small 180 / 197 at
+//             192 key tiles, 247 / 236 at 256
+//   backward of a segment (whose dK/dV walks are never cut): 1600 rows under 2048 keys
+//             300 / 335 (32/8) and 570 / 609 (64/8); under 8192 keys 870 / 858 and 1680 / 1657
+void small_forms(const CallShape& c, int n_q_heads, int n_kv_heads, bool* q_small, bool* k_small) {
+  const int64_t row_tiles = c.rows / 32 * n_q_heads, key_tiles = c.keys / 128 * n_kv_heads;
+  if (!c.backward) {
+    *q_small = row_tiles < 900;
+    *k_small = false;
+    return;
+  }
+  *q_small = row_tiles < 1800 || (c.segment && row_tiles < 4000 && key_tiles < 350);
+  *k_small = *q_small || (!c.segment && key_tiles < 200);
+}
+}  // namespace
+
+int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& call) {
   int st = validate_params(p);
   if (st != DTA_OK) return st;
   int G = p->n_q_heads / p->n_kv_heads;
@@ -513,25 +540,42 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, int64_t rows) {
     // groups that share out the streamed keys.  A launch of fewer than 2048 waves
     // of 16 rows leaves half of the chip's wave slots empty: there the walks are
     // split instead.
-    const bool small = rows / 16 * p->n_q_heads < 2048;
-    out->split = !small ? 1 : p->head_dim == 64 ? 4 : 2;
-    const int R = 8 / out->split;
+    const bool small = call.rows / 16 * p->n_q_heads < 2048;
+    out->q_small = out->k_small = small;
+    const int split = !small ? 1 : p->head_dim == 64 ? 4 : 2;
+    const int R = 8 / split;
     int hb = 1;
     while (hb < R && G % (2 * hb) == 0) hb *= 2;
     out->hb = hb;
     out->hblocks = G / hb;
     out->bm = 16 * (R / hb);
-    out->q_rows = 32 * out->split;
-    out->bn = out->split == 1 ? 64 : 16 * R;
+    out->bn = small ? 16 * R : 64;
+    // an iteration takes a wave several microseconds, so cut walks may be short; four-wave blocks, eight when split
+    out->walk = KvWalk{32, 4 * split, small ? kNumCUs : 2 * kNumCUs};
   } else {
-    // eight waves per block: hb q heads of the group x (8/hb) 32-row query blocks
-    int hb = (G % 8 == 0) ? 8 : (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
-    out->hb = hb;
-    out->hblocks = G / hb;
-    out->bm = 32 * (8 / hb);
-    out->bn = 128;
-    out->q_rows = 64;
-    out->split = 1;
+    // eight waves per block: hb q heads of the group x (R/hb) 32-row query blocks,
+    // R = 8, or 2 where the launch has too few rows (see dta_bf16_small.hip)
+    auto rows_of = [&](bool small, int* heads) {
+      const int R = small ? 2 : 8;
+      *heads = 1;
+      while (*heads < R && G % (2 * *heads) == 0) *heads *= 2;
+      return 32 * (R / *heads);
+    };
+    small_forms(call, p->n_q_heads, p->n_kv_heads, &out->q_small, &out->k_small);
+    out->bm = rows_of(out->q_small, &out->hb);
+    out->hblocks = G / out->hb;
+    out->bn = out->k_small ? 64 : 128;
+    out->walk = out->k_small ? KvWalk{32, 32, kNumCUs} : KvWalk{64, 32, 2 * kNumCUs};
+    if (!call.backward) {
+      // the backward's schedule serves if its query tiles have the same size; otherwise a schedule of query tiles only
+      CallShape bwd = call;
+      bwd.backward = true;
+      TileChoice b;
+      choose_tiles(p, &b, bwd);
+      out->k_small = b.k_small;
+      out->bn = b.bm == out->bm ? b.bn : 0;
+      out->walk = b.bm == out->bm ? b.walk : KvWalk();
+    }
   }
   return DTA_OK;
 }
@@ -579,26 +623,31 @@ int dta_tree_layout(const dta_tree_t* tree, dta_tree_layout_t* out) {
   return DTA_OK;
 }
 
+static size_t schedule_bytes(const dta::Schedule& s) {
+  return s.q_tiles.size() * sizeof(dta::QTile) + s.segs.size() * sizeof(dta::KeySeg) +
+         s.kv_items.size() * sizeof(dta::KvItem) + s.kv_reduce.size() * sizeof(dta::KvReduce);
+}
+
 int dta_tree_schedule_info(dta_tree_t* tree, const dta_attn_params_t* params,
                            dta_schedule_info_t* out) {
   if (!tree || !out) return DTA_ERR_INVALID_ARG;
-  dta::TileChoice tc;
-  int st = dta::choose_tiles(params, &tc, tree->info.n_tokens);
+  dta::TileChoice tf, tb;
+  int st = dta::choose_tiles(params, &tf, dta::whole_tree(tree, false));
   if (st != DTA_OK) return st;
+  dta::choose_tiles(params, &tb, dta::whole_tree(tree, true));
   try {
     std::lock_guard<std::mutex> lock(tree->mu);
-    dta::Schedule& s = dta::get_schedule(tree, tc.bm, tc.bn, params->n_kv_heads,
-                                         params->n_q_heads / params->n_kv_heads, tc.q_rows);
-    out->fwd_q_tile_tokens = tc.bm;
-    out->fwd_work_items = (int64_t)s.q_tiles.size();
-    out->fwd_tile_pairs = s.fwd_tile_pairs;
-    out->bwd_kv_tile_tokens = s.kv_keys;
-    out->bwd_work_items = (int64_t)s.kv_items.size();
-    out->bwd_tile_pairs = s.bwd_tile_pairs;
-    out->metadata_bytes =
-        (int64_t)(tree->token_kend.size() * sizeof(int32_t) + s.q_tiles.size() * sizeof(dta::QTile) +
-                  s.segs.size() * sizeof(dta::KeySeg) +
-                  s.kv_items.size() * sizeof(dta::KvItem) + s.kv_reduce.size() * sizeof(dta::KvReduce));
+    const int group = params->n_q_heads / params->n_kv_heads;
+    const dta::Schedule& f = dta::get_schedule(tree, tf.bm, tf.bn, params->n_kv_heads, group, tf.walk);
+    const dta::Schedule& b = dta::get_schedule(tree, tb.bm, tb.bn, params->n_kv_heads, group, tb.walk);
+    out->fwd_q_tile_tokens = tf.bm;
+    out->fwd_work_items = (int64_t)f.q_tiles.size();
+    out->fwd_tile_pairs = f.fwd_tile_pairs;
+    out->bwd_kv_tile_tokens = b.kv_keys;
+    out->bwd_work_items = (int64_t)b.kv_items.size();
+    out->bwd_tile_pairs = b.bwd_tile_pairs;
+    out->metadata_bytes = (int64_t)(tree->token_kend.size() * sizeof(int32_t) + schedule_bytes(b) +
+                                    (&f == &b ? 0 : schedule_bytes(f)));
   } catch (const std::bad_alloc&) {
     return DTA_ERR_ALLOC;
   }

@@ -1,0 +1,52 @@
+"""bf16 launches on both sides of the size rules: few rows (or keys) take the form
+whose wave groups share out the streamed rows, many take the form that fills the
+chip.  Ragged segments at the edges of the 32-, 64- and 128-row tiles, whole
+tensors against the fp64 oracle at the bf16 bar (max|err| / max|ref| <= 1e-2)."""
+import math
+
+import numpy as np
+import pytest
+
+import paper_2602_00482_amd as dta
+from oracle import tree_direct as B
+from workloads import make_inputs_numpy
+from parity_util import rel_err, run_hip
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(seg, Hq, Hkv, d, key_tile):
+    parent = np.array([-1] + [0] * (len(seg) - 1), dtype=np.int32)
+    seg = np.array(seg, dtype=np.int32)
+    scale = 1.0 / math.sqrt(d)
+    tree = dta.tree_build(parent, seg)
+    got_tile = tree.schedule_info(dta.AttnParams(Hq, Hkv, d, scale, dta.BF16))["bwd_kv_tile_tokens"]
+    tree.destroy()
+    assert got_tile == key_tile, got_tile
+    x = make_inputs_numpy(int(seg.sum()), Hq, Hkv, d, 29, dtype="bf16")
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "bf16")
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
+    for name, ref in (("o", O), ("lse", LSE), ("dq", dQ), ("dk", dK), ("dv", dV)):
+        assert rel_err(got[name], ref) <= 1e-2, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,seg", [
+    (4, 2, [17, 1, 31, 33]),                # walks shorter than the groups' rows: some groups stay idle
+    (8, 1, [127, 128, 129, 1, 63]),         # eight heads: a step is four heads of one 32-row chunk
+    (3, 1, [65, 95, 32, 2]),                # odd group: iterations of two chunks in one step
+    (5, 5, [1, 64, 200, 31]),               # no grouping: a step is four chunks
+])
+def test_small_form(Hq, Hkv, seg, d):
+    _check(seg, Hq, Hkv, d, 64)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,seg", [
+    (96, 96, [300, 1, 63, 65, 129, 170]),   # no grouping: 256-token query tiles
+    (128, 64, [257, 33, 310, 95, 31]),       # group of two
+    (256, 64, [300, 127, 128, 129, 40]),    # group of four
+])
+def test_large_form(Hq, Hkv, seg, d):
+    _check(seg, Hq, Hkv, d, 128)
