@@ -286,6 +286,7 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
     s->device = -1;
     if ((st = upload_parts(dev, us,
                            {part_of(s->q_tiles, &s->d_q_tiles), part_of(s->segs, &s->d_segs),
+                            part_of(s->step_tiles, &s->d_step_tiles), part_of(s->steps, &s->d_steps),
                             part_of(s->kv_items, &s->d_kv_items),
                             part_of(s->kv_reduce, &s->d_kv_reduce)},
                            &s->d_blob, &s->d_blob_cap, t_begin < 0 ? nullptr : tree)) != DTA_OK)

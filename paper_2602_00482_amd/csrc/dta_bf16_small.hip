@@ -25,7 +25,6 @@
 
 #include "dta_internal.h"
 #include "dta_mfma.h"
-#include "dta_tile_walk.h"
 
 namespace dta {
 namespace {
@@ -76,9 +75,10 @@ __device__ __forceinline__ void subs_async_load(uint16_t* tiles, const uint16_t*
   for (int p = 0; p < 2 * TL::kGroups / 8; ++p) {
     const int t = p * 8 / TL::kGroups, grp = (w + 8 * p) % TL::kGroups;
     const int row = SubLayout<HD>::kRowsPerHalfGroup * grp + rr;
-    const int last = (l < 32 ? nv[2 * t] : nv[2 * t + 1]) - 1;
-    const uint32_t voff =
-        (l < 32 ? off[2 * t] : off[2 * t + 1]) + (uint32_t)min(row, last) * stride_bytes + piece;
+    // (the elements are read on their own: a choice between them would put the arrays in memory)
+    const int n0 = nv[2 * t], n1 = nv[2 * t + 1];
+    const uint32_t o0 = off[2 * t], o1 = off[2 * t + 1];
+    const uint32_t voff = (l < 32 ? o0 : o1) + (uint32_t)min(row, (l < 32 ? n0 : n1) - 1) * stride_bytes + piece;
     const uint32_t lds_addr =
         __builtin_amdgcn_readfirstlane(tile_addr + (t * TL::kTileElems + grp * kGroupPitch) * 2);
     asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
@@ -86,6 +86,15 @@ __device__ __forceinline__ void subs_async_load(uint16_t* tiles, const uint16_t*
                  : "v"(voff), "s"(sbase), "s"(lds_addr)
                  : "memory");
   }
+}
+
+// Records of the schedule are read through the scalar cache, whatever the block
+// stores in between.
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+template <typename V>
+__device__ __forceinline__ V scalar_load(const void* p) {
+  return *(const __attribute__((address_space(4))) V*)(uintptr_t)p;
 }
 
 // Adds the groups' accumulators of one row (key) tile: afterwards group b < DB holds
@@ -129,19 +138,34 @@ __device__ __forceinline__ float max_across_halves(float x) {
 }
 
 // What the forward and dQ kernels share: the block's item and its walk over the keys.
+// The host has cut the walk into steps (KeyStep: a piece of at most 32 keys for each
+// group); working the pieces out here, between the barrier and the first product of
+// every step, cost 6 % of a launch, more than the fuller steps give.  Measured over the
+// 1034 forward and 446 backward calls of a leaf-order plan over 446 short segments:
+// 13.4 -> 11.6 us a forward call, 18.7 -> 18.0 backward, against steps cut from one
+// interval each.
 template <int HD>
 struct KeyWalk {
   using TL = TileLayout<HD>;
-  QTile tile;
+  const KeyStep* steps;
+  int t1, at, end;    // next step to read ahead, end of the list
   int w, l, c, hh, rw, grp, g, h, row_base, qrow;
-  KeyChunksT<kStep> it;
-  int c0, n, full;
+  i32x8 step, next;   // the step copied last, the one after it: c0[0..3], n[0..3]
   bool have;
 
-  __device__ __forceinline__ void init(const QTile* tiles, const KeySeg* segs, int block, int Hq, int Hkv, int HB, int hblocks) {
+  __device__ __forceinline__ void init(const StepTile* tiles, const KeyStep* list, int block, int Hq, int Hkv, int HB,
+                                       int hblocks) {
     const int item = block / Hkv;
+    steps = list;
     g = block % Hkv;
-    tile = tiles[item / hblocks];
+    const i32x16 rec = scalar_load<i32x16>(tiles + item / hblocks);
+    const int t0 = rec[0];
+    t1 = rec[1];
+    at = rec[2];
+    end = rec[3];
+    step = i32x8{rec[8], rec[9], rec[10], rec[11], rec[12], rec[13], rec[14], rec[15]};
+    have = true;
+    read_ahead();
     w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     l = threadIdx.x & 63;
     c = l & 31;
@@ -149,34 +173,54 @@ struct KeyWalk {
     rw = w % kTiles;
     grp = w / kTiles;
     h = g * (Hq / Hkv) + (item % hblocks) * HB + rw % HB;
-    row_base = tile.t0 + 32 * (rw / HB);
-    qrow = min(row_base + c, tile.t1 - 1);
-    it.init(segs, tile);
-    have = it.next(c0, n, full);
+    row_base = t0 + 32 * (rw / HB);
+    qrow = min(row_base + c, t1 - 1);
   }
-  // copies the current chunk (c0, n, full) of K and V into tile pair b
+  __device__ __forceinline__ void read_ahead() {
+    if (at < end) next = scalar_load<i32x8>(steps + at);
+  }
+  // moves on to the next step; false at the end of the walk
+  __device__ __forceinline__ bool advance() {
+    if (at >= end) return false;
+    step = next;
+    ++at;
+    read_ahead();
+    return true;
+  }
+  // this group's piece of the step: first key, keys (may be none), every row sees every key
+  __device__ __forceinline__ void mine(int& k0, int& nk, bool& full) const {
+    k0 = grp == 0 ? step[0] : grp == 1 ? step[1] : grp == 2 ? step[2] : step[3];
+    const int n = grp == 0 ? step[4] : grp == 1 ? step[5] : grp == 2 ? step[6] : step[7];
+    nk = n & (kFullPiece - 1);
+    full = (n & kFullPiece) != 0;
+  }
+  // copies the step's pieces of K and V into tile pair b
   __device__ __forceinline__ void issue(uint16_t* Kd, uint16_t* Vd, int32_t* kendS, const int32_t* kend,
                                         const uint16_t* kbase, const uint16_t* vbase, uint32_t kv_bytes) {
-    if ((!full || n < kStep) && threadIdx.x < kStep) {   // kendS is indexed by matrix position
-      const int row = kSub * (threadIdx.x >> 5) + SubLayout<HD>::row_of_pos(threadIdx.x & 31);
-      kendS[threadIdx.x] = row >= n ? 0 : (full ? 0x7fffffff : kend[c0 + row]);
-    }
     uint32_t off[4];
     int nv[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {   // a sub-tile with no valid key re-reads the chunk's first row (finite data the mask hides)
-      off[s] = n > kSub * s ? (uint32_t)(kSub * s) * kv_bytes : 0u;
-      nv[s] = max(1, min(kSub, n - kSub * s));
+    for (int s = 0; s < 4; ++s) {   // (no piece: the first one's first row again, which nobody uses)
+      off[s] = (uint32_t)(step[s] - step[0]) * kv_bytes;
+      nv[s] = max(1, step[4 + s] & (kFullPiece - 1));
     }
-    const size_t at = (size_t)c0 * (kv_bytes / 2);
-    subs_async_load<HD>(Kd, kbase + at, kv_bytes, off, nv);
-    subs_async_load<HD>(Vd, vbase + at, kv_bytes, off, nv);
+    if ((step[4] & step[5] & step[6] & step[7] & kFullPiece) == 0 && w < kStep / 64) {
+      // kendS is indexed by matrix position; wave w fills sub-tiles 2w and 2w + 1
+      const int f0 = w == 0 ? step[0] : step[2], f1 = w == 0 ? step[1] : step[3];
+      const int n0 = w == 0 ? nv[0] : nv[2], n1 = w == 0 ? nv[1] : nv[3];
+      const int row = min(SubLayout<HD>::row_of_pos(l & 31), (l < 32 ? n0 : n1) - 1);
+      row_async_load(reinterpret_cast<float*>(kendS + 64 * w), reinterpret_cast<const float*>(kend + step[0]),
+                     (uint32_t)((l < 32 ? f0 : f1) - step[0] + row));
+    }
+    const size_t at0 = (size_t)step[0] * (kv_bytes / 2);
+    subs_async_load<HD>(Kd, kbase + at0, kv_bytes, off, nv);
+    subs_async_load<HD>(Vd, vbase + at0, kv_bytes, off, nv);
   }
 };
 
 template <int HD>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fwd_small_kernel(
-    const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs, const int32_t* __restrict__ kend,
+    const StepTile* __restrict__ tiles, const KeyStep* __restrict__ steps, const int32_t* __restrict__ kend,
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     uint16_t* __restrict__ o, float* __restrict__ lse, int Hq, int Hkv, int HB, int hblocks, float scale) {
   using TL = TileLayout<HD>;
@@ -190,7 +234,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   __shared__ float mS[kGroupsOfWaves][kTiles][32], lS[kGroupsOfWaves][kTiles][32];
 
   KeyWalk<HD> wk;
-  wk.init(tiles, segs, blockIdx.x, Hq, Hkv, HB, hblocks);
+  wk.init(tiles, steps, blockIdx.x, Hq, Hkv, HB, hblocks);
   const size_t kv_stride = (size_t)Hkv * HD;
   const uint16_t* kbase = k + (size_t)wk.g * HD;
   const uint16_t* vbase = v + (size_t)wk.g * HD;
@@ -223,10 +267,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   while (wk.have) {
     async_wait_all();
-    __syncthreads();   // chunk `buf` has landed; everyone is done with the other buffer
-    const int k0 = wk.c0 + kSub * grp, nk = wk.n - kSub * grp;   // this group's keys
-    const bool need_mask = !wk.full || nk < kSub;
-    wk.have = wk.it.next(wk.c0, wk.n, wk.full);
+    __syncthreads();   // step `buf` has landed; everyone is done with the other buffer
+    int k0, nk;   // this group's keys
+    bool full;
+    wk.mine(k0, nk, full);
+    const bool need_mask = !full || nk < kSub;
+    wk.have = wk.advance();
     if (wk.have) wk.issue(sm.K[buf ^ 1], sm.V[buf ^ 1], kendS[buf ^ 1], kend, kbase, vbase, kv_bytes);
     if (nk > 0) {
       const uint16_t* Kt = sm.K[buf] + rlo;
@@ -236,14 +282,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int e = 0; e < 16; ++e) S[e] = 0.f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) S = mfma32(tile_row8(Kt, 0, ks), Qr[ks], S);
-      if (need_mask) {
+      if (need_mask) {   // (kendS is only filled if some piece of the step is not full)
+        const int last = min(nk - 1, qrow - k0), no_end = full ? 0x7fffffff : 0;
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
           const int4 ke = *reinterpret_cast<const int4*>(&kendS[buf][kSub * grp + 8 * e4 + 4 * hh]);
           const int kev[4] = {ke.x, ke.y, ke.z, ke.w};
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const bool ok = (k0 + SubLayout<HD>::row_of_acc(4 * e4 + j, hh) <= qrow) & (qrow < kev[j]);
+            const bool ok = (SubLayout<HD>::row_of_acc(4 * e4 + j, hh) <= last) & (qrow < max(kev[j], no_end));
             S[4 * e4 + j] = ok ? S[4 * e4 + j] : -INFINITY;
           }
         }
@@ -302,7 +349,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   sum_over_groups<DB>(reinterpret_cast<float*>(&sm), O, wk.rw, grp, out);
   const float inv = 1.f / lt;
   const int token = wk.row_base + c;
-  if (token < wk.tile.t1) {
+  if (token < wk.t1) {
     if (grp < DB) {
       uint16_t* op = o + ((size_t)token * Hq + wk.h) * HD + 32 * grp + 4 * hh;
 #pragma unroll
@@ -319,8 +366,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
 // What a backward launch reads and writes.
 struct BwdArgs {
-  const QTile* tiles;
-  const KeySeg* segs;
+  const StepTile* tiles;
+  const KeyStep* steps;
   const KvItem* items;
   const int32_t* kend;
   const uint16_t *q, *k, *v, *d_o, *o;
@@ -356,7 +403,7 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD>& sm, int b
   auto& kendS = sm.kendS;
 
   KeyWalk<HD> wk;
-  wk.init(p.tiles, p.segs, block, Hq, Hkv, p.HB, p.hblocks);
+  wk.init(p.tiles, p.steps, block, Hq, Hkv, p.HB, p.hblocks);
   const size_t kv_stride = (size_t)Hkv * HD;
   const uint16_t* kbase = k + (size_t)wk.g * HD;
   const uint16_t* vbase = v + (size_t)wk.g * HD;
@@ -387,7 +434,7 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD>& sm, int b
     float d = (dpart[0] + dpart[1]) + (dpart[2] + dpart[3]);
     if constexpr (HD == 128) d += (dpart[KS - 4] + dpart[KS - 3]) + (dpart[KS - 2] + dpart[KS - 1]);
     ndlt = -d;
-    if (grp == 0 && hh == 0 && wk.row_base + c < wk.tile.t1) {
+    if (grp == 0 && hh == 0 && wk.row_base + c < wk.t1) {
       neg_delta[rh] = ndlt;
       neg_lse_s[rh] = -lse[rh] * (1.f / scale);
     }
@@ -406,9 +453,11 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD>& sm, int b
   while (wk.have) {
     async_wait_all();
     __syncthreads();
-    const int k0 = wk.c0 + kSub * grp, nk = wk.n - kSub * grp;
-    const bool need_mask = !wk.full || nk < kSub;
-    wk.have = wk.it.next(wk.c0, wk.n, wk.full);
+    int k0, nk;
+    bool full;
+    wk.mine(k0, nk, full);
+    const bool need_mask = !full || nk < kSub;
+    wk.have = wk.advance();
     if (wk.have) wk.issue(sm.K[buf ^ 1], sm.V[buf ^ 1], kendS[buf ^ 1], kend, kbase, vbase, kv_bytes);
     if (nk > 0) {
       const uint16_t* Kt = sm.K[buf] + rlo;
@@ -423,14 +472,15 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD>& sm, int b
       for (int ks = 0; ks < KS; ++ks) dP = mfma32(tile_row8(Vt, 0, ks), dOr[ks], dP);
 #pragma unroll
       for (int e = 0; e < 16; ++e) S[e] = __builtin_amdgcn_exp2f(S[e] * sc);
-      if (need_mask) {
+      if (need_mask) {   // (kendS is only filled if some piece of the step is not full)
+        const int last = min(nk - 1, qrow - k0), no_end = full ? 0x7fffffff : 0;
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
           const int4 ke = *reinterpret_cast<const int4*>(&kendS[buf][kSub * grp + 8 * e4 + 4 * hh]);
           const int kev[4] = {ke.x, ke.y, ke.z, ke.w};
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const bool ok = (k0 + SubLayout<HD>::row_of_acc(4 * e4 + j, hh) <= qrow) & (qrow < kev[j]);
+            const bool ok = (SubLayout<HD>::row_of_acc(4 * e4 + j, hh) <= last) & (qrow < max(kev[j], no_end));
             S[4 * e4 + j] = ok ? S[4 * e4 + j] : 0.f;
           }
         }
@@ -450,7 +500,7 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD>& sm, int b
   f32x16 out;
   sum_over_groups<DB>(reinterpret_cast<float*>(&sm), dQ, wk.rw, grp, out);
   const int token = wk.row_base + c;
-  if (grp < DB && token < wk.tile.t1) {
+  if (grp < DB && token < wk.t1) {
     uint16_t* op = dq + ((size_t)token * Hq + wk.h) * HD + 32 * grp + 4 * hh;
 #pragma unroll
     for (int v4 = 0; v4 < 4; ++v4) {
@@ -492,7 +542,11 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD>& sm, i
   const int Hq = p.Hq, Hkv = p.Hkv;
   const float scale = p.scale;
 
-  const KvItem tile = p.items[block / Hkv];
+  KvItem tile;
+  {
+    const i32x8 r = scalar_load<i32x8>(p.items + block / Hkv);
+    tile = KvItem{r[0], r[1], r[2], r[3], r[4], r[5], r[6], r[7]};
+  }
   const int g = block % Hkv, G = Hq / Hkv;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int c = l & 31, hh = l >> 5;
@@ -501,35 +555,56 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD>& sm, i
   const int kcol = tile.k0 + 32 * kt + c;
   const int kc = min(kcol, tile.k1 - 1);
   const int my_kend = kcol < tile.k1 ? kend[kc] : 0;   // padded columns see nothing
-  int wave_hi = my_kend;   // rows [wave_lo, wave_hi) are the only ones this wave's keys can see
-#pragma unroll
-  for (int off = 16; off >= 1; off >>= 1) wave_hi = max(wave_hi, __shfl_xor(wave_hi, off));
-  wave_hi = __builtin_amdgcn_readfirstlane(wave_hi);
-  const int wave_lo = tile.k0 + 32 * kt;
-
   const size_t q_stride = (size_t)Hq * HD;
   const uint32_t q_bytes = (uint32_t)q_stride * 2;
   const int n_chunks = (tile.q_end - tile.q_begin + kSub - 1) / kSub;
   const int total = tile.it_end;
-  auto row_of_it = [&](int it) { return tile.q_begin + (n_chunks - 1 - it / G) * kSub; };
-  // copies iterations it .. it+3 into buffer b (iterations >= total re-read the last one: never computed on)
-  auto issue = [&](int it, int b) {
+  // Iterations it .. it+3 of a step, `it` = chunk * G + head: their first rows and heads;
+  // iterations >= total repeat the last one (never computed on).  Kept up to date from
+  // step to step, without divisions.
+  int row[4], head[4];
+  {
+    const int chunk = tile.it_begin / G;
+    head[0] = tile.it_begin - chunk * G;
+    row[0] = tile.q_begin + (n_chunks - 1 - chunk) * kSub;
+  }
+  const int step_rows = kGroupsOfWaves / G * kSub, step_heads = kGroupsOfWaves % G;
+  auto fill = [&](int it) {   // iterations it+1 .. it+3 from the one at `it`
+#pragma unroll
+    for (int s = 1; s < 4; ++s) {
+      const bool wrap = head[s - 1] + 1 == G, stay = it + s >= total;
+      head[s] = stay ? head[s - 1] : wrap ? 0 : head[s - 1] + 1;
+      row[s] = stay || !wrap ? row[s - 1] : row[s - 1] - kSub;
+    }
+  };
+  auto advance = [&](int it) {   // to the step that begins with iteration `it` < total
+    head[0] += step_heads;
+    row[0] -= step_rows;
+    if (head[0] >= G) {
+      head[0] -= G;
+      row[0] -= kSub;
+    }
+    fill(it);
+  };
+  // copies the step's rows into buffer b
+  auto issue = [&](int b) {
     // rows of the last of the four iterations are the lowest: offsets from there are not negative
-    const int r_base = row_of_it(min(it + 3, total - 1));
+    const int r_base = row[3];
     const uint16_t* qb = q + (size_t)r_base * q_stride + (size_t)(g * G) * HD;
     const uint16_t* db = d_o + (size_t)r_base * q_stride + (size_t)(g * G) * HD;
     uint32_t off[4];
     int nv[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const int i = min(it + s, total - 1), r0 = row_of_it(i);
-      off[s] = (uint32_t)(r0 - r_base) * q_bytes + (uint32_t)(i % G) * (HD * 2);
-      nv[s] = min(kSub, tile.q_end - r0);
+      off[s] = (uint32_t)(row[s] - r_base) * q_bytes + (uint32_t)head[s] * (HD * 2);
+      nv[s] = min(kSub, tile.q_end - row[s]);
     }
     if (w < kStep / 64) {   // stat is indexed by matrix position; wave w fills sub-tiles 2w and 2w + 1
-      const int i = min(it + 2 * w + (l >> 5), total - 1), r0 = row_of_it(i);
-      const int row = min(SubLayout<HD>::row_of_pos(l & 31), min(kSub, tile.q_end - r0) - 1);
-      const uint32_t at = (uint32_t)(r0 - r_base + row) * (uint32_t)Hq + (uint32_t)(i % G);
+      const int r0 = w == 0 ? row[0] : row[2], r1 = w == 0 ? row[1] : row[3];
+      const int h0 = w == 0 ? head[0] : head[2], h1 = w == 0 ? head[1] : head[3];
+      const int n0 = w == 0 ? nv[0] : nv[2], n1 = w == 0 ? nv[1] : nv[3];
+      const int rr = min(SubLayout<HD>::row_of_pos(l & 31), (l < 32 ? n0 : n1) - 1);
+      const uint32_t at = (uint32_t)((l < 32 ? r0 : r1) - r_base + rr) * (uint32_t)Hq + (uint32_t)(l < 32 ? h0 : h1);
       const size_t sb = (size_t)r_base * Hq + (size_t)(g * G);
       row_async_load(&sm.stat[b][0][64 * w], neg_lse_s + sb, at);
       row_async_load(&sm.stat[b][1][64 * w], neg_delta + sb, at);
@@ -537,7 +612,8 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD>& sm, i
     subs_async_load<HD>(sm.Q[b], qb, q_bytes, off, nv);
     subs_async_load<HD>(sm.dO[b], db, q_bytes, off, nv);
   };
-  if (tile.it_begin < total) issue(tile.it_begin, 0);
+  fill(tile.it_begin);
+  issue(0);
 
   bf16x8 Kr[kRegK], Vr[kRegV];
   uint16_t* stash = &sm.stash[kt][0][l * 8];
@@ -569,13 +645,23 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD>& sm, i
   const int sub_off = (grp >> 1) * TL::kTileElems + 256 * (grp & 1);
   const int rlo = TL::row_lane_off() + sub_off, clo = TL::col_lane_off() + sub_off;
 
+  int wave_hi = my_kend;   // rows [wave_lo, wave_hi) are the only ones this wave's keys can see
+#pragma unroll
+  for (int off = 16; off >= 1; off >>= 1) wave_hi = max(wave_hi, __shfl_xor(wave_hi, off));
+  wave_hi = __builtin_amdgcn_readfirstlane(wave_hi);
+  const int wave_lo = tile.k0 + 32 * kt;
+
   int buf = 0;
   for (int it = tile.it_begin; it < total; it += kGroupsOfWaves) {
     async_wait_all();
     __syncthreads();   // step `buf` has landed (and, first time, the stash); everyone is done with the other buffer
-    if (it + kGroupsOfWaves < total) issue(it + kGroupsOfWaves, buf ^ 1);
     const int my_it = it + grp;
-    const int r0 = row_of_it(min(my_it, total - 1)), nv = min(kSub, tile.q_end - r0);
+    const int r0 = grp == 0 ? row[0] : grp == 1 ? row[1] : grp == 2 ? row[2] : row[3];
+    const int nv = min(kSub, tile.q_end - r0);
+    if (it + kGroupsOfWaves < total) {
+      advance(it + kGroupsOfWaves);
+      issue(buf ^ 1);
+    }
     if (my_it < total && r0 + nv > wave_lo && r0 < wave_hi) {
       const bool need_mask = !(r0 >= tile.k1 && r0 + kSub <= tile.q_full_end);
       const uint16_t* Qt = sm.Q[buf] + rlo;
@@ -710,7 +796,7 @@ int launch_fwd_bf16_small(const LaunchArgs& a) {
   if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
   auto kernel = a.p.head_dim == 128 ? fwd_small_kernel<128> : fwd_small_kernel<64>;
   kernel<<<(unsigned)blocks, kThreads, 0, (hipStream_t)a.stream>>>(
-      a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
+      a.sched->d_step_tiles, a.sched->d_steps, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
       (const uint16_t*)a.v, (uint16_t*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
       a.tc.hblocks, a.p.softmax_scale);
   return launch_status(__func__);
@@ -724,7 +810,7 @@ int launch_bwd_bf16_small(const LaunchArgs& a, uint32_t stages, bool fused_delta
   const size_t dq =
       stages & DTA_BWD_DQ ? a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks : 0;
   if (dq + dkdv == 0 || dq + dkdv > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
-  const BwdArgs p{a.sched->d_q_tiles, a.sched->d_segs, a.sched->d_kv_items, a.d_kend, (const uint16_t*)a.q,
+  const BwdArgs p{a.sched->d_step_tiles, a.sched->d_steps, a.sched->d_kv_items, a.d_kend, (const uint16_t*)a.q,
                   (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.d_o,
                   fused_delta ? (const uint16_t*)a.o : nullptr, a.lse_in, a.delta, a.lse2, (uint16_t*)a.dq,
                   (uint16_t*)a.dk, (uint16_t*)a.dv, a.partial, a.dk_acc, a.dv_acc, a.p.n_q_heads,

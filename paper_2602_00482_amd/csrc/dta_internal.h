@@ -34,6 +34,23 @@ struct QTile {
   KeySeg first;
 };
 
+// The walk of a query tile for the kernels whose four wave groups share out the keys:
+// steps of four pieces of at most 32 keys, one per group.  A piece ends with its key
+// interval and the step goes on with the next one, so where path segments are short
+// (a forest of 38-token segments) a tile takes 3.6 steps instead of the 5.4 of
+// steps cut from one interval each.  n = keys of the piece (0: none), + kFullPiece when
+// every query row of the tile sees all of them.
+constexpr int kFullPiece = 256;
+struct KeyStep {
+  int32_t c0[4], n[4];
+};
+// A query tile [t0, t1) with its first step; the others are steps[step_begin, step_end).
+struct StepTile {
+  int32_t t0, t1, step_begin, step_end;
+  int32_t pad[4];
+  KeyStep first;
+};
+
 // One dK/dV work item: BN consecutive packed keys [k0, k1).  The queries the
 // item walks are [q_begin, q_end): for a whole-tree launch q_begin = k0 and
 // these are exactly the rows that see at least one of the keys; a segment
@@ -78,6 +95,8 @@ struct Schedule {
   int kv_keys = 0;   // keys per dK/dV tile in this schedule: bn, or 2*bn where the walks are long
   std::vector<QTile> q_tiles;
   std::vector<KeySeg> segs;
+  std::vector<StepTile> step_tiles;   // the query tiles as steps (KvWalk::key_steps)
+  std::vector<KeyStep> steps;
   std::vector<KvTile> kv_tiles;
   int hkv = 0, group = 0;          // head configuration the item split was made for
   std::vector<KvItem> kv_items;
@@ -96,6 +115,8 @@ struct Schedule {
   size_t d_blob_cap = 0;
   QTile* d_q_tiles = nullptr;
   KeySeg* d_segs = nullptr;
+  StepTile* d_step_tiles = nullptr;
+  KeyStep* d_steps = nullptr;
   KvItem* d_kv_items = nullptr;
   KvReduce* d_kv_reduce = nullptr;
 };
@@ -144,16 +165,19 @@ constexpr int kNumCUs = 256;
 // Key tiles of 256 keys (eight-wave dK/dV blocks) for schedules of long walks.
 constexpr bool wide_key_tiles = true;
 
-// How a dK/dV kernel walks its query rows, as far as the schedule has to know.
+// How the kernels walk, as far as the schedule has to know: the dK/dV kernel its query
+// rows, and whether the query tiles are wanted as steps.
 struct KvWalk {
   int q_rows = 64;          // rows per iteration of the walk: 32 or 64
   int min_piece = 32;       // shortest piece of a cut walk in iterations, a multiple of 4, at most 60
   int resident = 512;       // blocks of the kernel that the chip holds
+  bool key_steps = false;   // query tiles as StepTile / KeyStep instead of QTile / KeySeg
 };
 
 // Key of a whole-tree schedule in dta_tree::schedules.
 inline uint64_t schedule_key(int bm, int bn, int hkv, int group, const KvWalk& kw) {
-  return ((uint64_t)(kw.min_piece / 4) << 60) | ((uint64_t)bm << 48) | ((uint64_t)(kw.q_rows / 32) << 44) |
+  return ((uint64_t)(kw.min_piece / 4) << 60) | ((uint64_t)bm << 48) | ((uint64_t)kw.key_steps << 46) |
+         ((uint64_t)(kw.q_rows / 32) << 44) |
          ((uint64_t)bn << 32) | ((uint64_t)hkv << 16) | (uint64_t)group;
 }
 // Host: build (or fetch) the schedule for tile sizes (bm, bn).

@@ -179,6 +179,48 @@ void fill_first_intervals(Schedule& s) {
 }
 }  // namespace
 
+namespace {
+// Cuts the walks of the query tiles into steps (KeyStep).  A step ends early when its
+// pieces would lie further apart than the kernels' 32-bit offsets reach.
+void cut_steps(Schedule& s) {
+  const int64_t reach = (int64_t)0xffffffff / ((int64_t)s.hkv * 256) - 32;   // keys; a K/V row is at most 256 bytes per head
+  for (const QTile& t : s.q_tiles) {
+    StepTile st{};
+    st.t0 = t.t0;
+    st.t1 = t.t1;
+    st.step_begin = (int32_t)s.steps.size();
+    KeyStep cur{};
+    int used = 0;
+    bool first = true;
+    auto flush = [&] {
+      if (used == 0) return;
+      for (; used < 4; ++used) {
+        cur.c0[used] = cur.c0[0];
+        cur.n[used] = kFullPiece;   // no keys
+      }
+      if (first) st.first = cur;
+      else s.steps.push_back(cur);
+      first = false;
+      used = 0;
+    };
+    auto add = [&](int32_t start, int32_t end, int32_t full) {
+      for (int32_t c = start; c < end; c += 32) {
+        if (used == 4 || (used > 0 && c - (int64_t)cur.c0[0] > reach)) flush();
+        cur.c0[used] = c;
+        cur.n[used] = std::min(32, end - c) + (full ? kFullPiece : 0);
+        ++used;
+      }
+    };
+    for (int32_t i = t.seg_begin; i < t.seg_end; ++i)
+      add(s.segs[(size_t)i].start, s.segs[(size_t)i].end, s.segs[(size_t)i].full);
+    add(t.t0, t.t1, 0);
+    flush();
+    st.step_end = (int32_t)s.steps.size();
+    s.step_tiles.push_back(st);
+  }
+}
+}  // namespace
+
 size_t partial_bytes(const Schedule& s) {
   return (size_t)s.n_slots * (size_t)s.hkv * 2u * (size_t)s.kv_keys * 128u * sizeof(float);
 }
@@ -245,6 +287,7 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const
     s.q_tiles.swap(sorted);
   }
   fill_first_intervals(s);
+  if (kw.key_steps) cut_steps(s);
 
   // ---- key tiles (dK/dV): runs of at most bn consecutive packed keys.  A block
   // walks the union of the query ranges of its keys, [k0, max kend), so a run that
@@ -453,6 +496,7 @@ Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int grou
   }
   std::reverse(s.q_tiles.begin(), s.q_tiles.end());   // the last tile sees the most keys
   fill_first_intervals(s);
+  if (kw.key_steps) cut_steps(s);
 
   // ---- key tiles: the prefix pieces (walk = all rows, no mask beyond padding),
   // then the rows themselves (causal)
@@ -566,15 +610,18 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
     out->hblocks = G / out->hb;
     out->bn = out->k_small ? 64 : 128;
     out->walk = out->k_small ? KvWalk{32, 32, kNumCUs} : KvWalk{64, 32, 2 * kNumCUs};
+    out->walk.key_steps = out->q_small;
     if (!call.backward) {
-      // the backward's schedule serves if its query tiles have the same size; otherwise a schedule of query tiles only
+      // the backward's schedule serves if its query tiles are the same; otherwise a schedule of query tiles only
       CallShape bwd = call;
       bwd.backward = true;
       TileChoice b;
       choose_tiles(p, &b, bwd);
       out->k_small = b.k_small;
-      out->bn = b.bm == out->bm ? b.bn : 0;
-      out->walk = b.bm == out->bm ? b.walk : KvWalk();
+      const bool same = b.bm == out->bm && b.q_small == out->q_small;
+      out->bn = same ? b.bn : 0;
+      out->walk = same ? b.walk : KvWalk();
+      out->walk.key_steps = out->q_small;
     }
   }
   return DTA_OK;
@@ -625,6 +672,7 @@ int dta_tree_layout(const dta_tree_t* tree, dta_tree_layout_t* out) {
 
 static size_t schedule_bytes(const dta::Schedule& s) {
   return s.q_tiles.size() * sizeof(dta::QTile) + s.segs.size() * sizeof(dta::KeySeg) +
+         s.step_tiles.size() * sizeof(dta::StepTile) + s.steps.size() * sizeof(dta::KeyStep) +
          s.kv_items.size() * sizeof(dta::KvItem) + s.kv_reduce.size() * sizeof(dta::KvReduce);
 }
 

@@ -15,8 +15,8 @@ from parity_util import rel_err, run_hip
 pytestmark = pytest.mark.gpu
 
 
-def _check(seg, Hq, Hkv, d, key_tile):
-    parent = np.array([-1] + [0] * (len(seg) - 1), dtype=np.int32)
+def _check(seg, Hq, Hkv, d, key_tile, parent=None):
+    parent = np.array([-1] + [0] * (len(seg) - 1) if parent is None else parent, dtype=np.int32)
     seg = np.array(seg, dtype=np.int32)
     scale = 1.0 / math.sqrt(d)
     tree = dta.tree_build(parent, seg)
@@ -50,3 +50,20 @@ def test_small_form(Hq, Hkv, seg, d):
 ])
 def test_large_form(Hq, Hkv, seg, d):
     _check(seg, Hq, Hkv, d, 128)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 1), (4, 2), (3, 3)])
+def test_small_form_path_of_many_short_intervals(Hq, Hkv, d):
+    """Every second node of the path is preceded by a leaf, so the path is 24 separate
+    key intervals of 1 to 70 tokens: steps made of up to four of them, full and ragged."""
+    lens = [1, 70, 31, 32, 33, 2, 64, 5, 3, 1, 65, 40, 7, 32, 9, 1, 1, 1, 30, 34, 96, 8, 63, 45]
+    parent, seg, tip = [], [], -1
+    for n in lens:
+        if tip >= 0:
+            parent.append(tip)   # a leaf between the tip and the next node of the path
+            seg.append(3)
+        parent.append(tip)
+        seg.append(n)
+        tip = len(seg) - 1
+    _check(seg, Hq, Hkv, d, 64, parent)
