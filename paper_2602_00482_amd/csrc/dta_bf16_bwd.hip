@@ -70,8 +70,9 @@ __global__ __launch_bounds__(256) void delta_bf16_kernel(const uint16_t* __restr
 constexpr int kDqThreads = 512;
 
 // Query-stationary dQ: 8 waves, each 32 query rows of one q head (same walk and
-// wave layout as the forward kernel).
-template <int HD>
+// wave layout as the forward kernel, kGroups = 2 included: 4 row tiles x 2 groups of
+// waves that take every other chunk).
+template <int HD, int kGroups = 1>
 __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
     const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs,
     const int32_t* __restrict__ kend, const uint16_t* __restrict__ q,
@@ -83,16 +84,22 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
   using TL = TileLayout<HD>;
   constexpr int kTileElems = TL::kTileElems, kHeadDim = HD;
   constexpr int KS = TL::kSteps;   // products per phase: k-steps over head_dim = 2 x output blocks
-  __shared__ __attribute__((aligned(1024))) uint16_t Ks[2][kTileElems];
-  __shared__ __attribute__((aligned(1024))) uint16_t Vs[2][kTileElems];
-  __shared__ __attribute__((aligned(16))) int32_t kendS[2][kKeyChunk];
+  struct Tiles {
+    uint16_t K[2][kGroups][kTileElems];
+    uint16_t V[2][kGroups][kTileElems];
+  };
+  __shared__ __attribute__((aligned(1024))) Tiles sm;
+  auto& Ks = sm.K;
+  auto& Vs = sm.V;
+  __shared__ __attribute__((aligned(16))) int32_t kendS[2][kGroups * kKeyChunk];
   // With head_dim 128 the last two k-steps of this wave's Q and dO operands live in
   // LDS instead of registers (each lane reads back what it wrote): with all 16 in
   // registers the kernel needs a few more than 256, and reloads from scratch
   // memory would wait for, i.e. serialise, the tile copies in flight.
   constexpr int kReg = HD == 128 ? 6 : KS;
   constexpr int kStash = KS - kReg;
-  __shared__ __attribute__((aligned(16))) uint16_t stashS[kDqThreads / 64][kStash ? 2 * kStash : 1][64 * 8];
+  // (two groups share a copy, so that four tiles per operand fit beside it)
+  __shared__ __attribute__((aligned(16))) uint16_t stashS[kDqThreads / 64 / kGroups][kStash ? 2 * kStash : 1][64 * 8];
 
   // Which (query tile, head block, kv head) this block works on.  tickets ==
   // nullptr: the block index says so.  Otherwise every block draws ONE item from
@@ -114,14 +121,15 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
   const int G = Hq / Hkv;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int c = l & 31, hh = l >> 5;
-  const int h = g * G + hblk * HB + (w % HB);
-  const int row_base = tile.t0 + 32 * (w / HB);
+  const int rw = w % (8 / kGroups), grp = kGroups == 1 ? 0 : __builtin_amdgcn_readfirstlane(w / (8 / kGroups));
+  const int h = g * G + hblk * HB + (rw % HB);
+  const int row_base = tile.t0 + 32 * (rw / HB);
   const float sc = scale * kLog2e;
 
   const int qrow = min(row_base + c, tile.t1 - 1);
   const size_t rh = (size_t)qrow * Hq + h;
   bf16x8 Qr[kReg], dOr[kReg];
-  uint16_t* stash = &stashS[w][0][l * 8];
+  uint16_t* stash = &stashS[rw][0][l * 8];
   // With o != nullptr this launch also does the work of delta_bf16_kernel for
   // its rows (every (row, q head) belongs to exactly one lane pair of one
   // block): D = dO . O, summed in that kernel's order so that the value is the
@@ -145,7 +153,7 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
       if (ks < kReg) {
         Qr[ks < kReg ? ks : 0] = qx;
         dOr[ks < kReg ? ks : 0] = dx;
-      } else {
+      } else if (grp == 0) {
         *reinterpret_cast<bf16x8*>(stash + (2 * (ks - kReg)) * 512) = qx;
         *reinterpret_cast<bf16x8*>(stash + (2 * (ks - kReg) + 1) * 512) = dx;
       }
@@ -171,7 +179,7 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
     float d = (dpart[0] + dpart[1]) + (dpart[2] + dpart[3]);
     if constexpr (HD == 128) d += (dpart[KS - 4] + dpart[KS - 3]) + (dpart[KS - 2] + dpart[KS - 1]);
     ndlt = -d;
-    if (hh == 0 && row_base + c < tile.t1) {
+    if (hh == 0 && grp == 0 && row_base + c < tile.t1) {
       neg_delta[rh] = ndlt;
       neg_lse_s[rh] = -lse[rh] * (1.f / scale);
     }
@@ -193,17 +201,28 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
   // chunk i lives in buffer i & 1 and is copied global -> LDS one iteration ahead
   KeyChunks it;
   it.init(segs, tile);
-  int c0, n, full;
-  bool have = it.next(c0, n, full);
+  int c0[kGroups], n[kGroups], full[kGroups];   // of the chunk(s) copied last; n = 0: none
+  auto next = [&] {
+    const bool some = it.next(c0[0], n[0], full[0]);
+    if constexpr (kGroups == 2)
+      if (!it.next(c0[1], n[1], full[1])) n[1] = 0;
+    return some;
+  };
+  bool have = next();
   auto issue = [&](int b) {
-    if (!full || n < kKeyChunk) {   // rare: a chunk that needs the visibility mask
-      if (threadIdx.x < kKeyChunk) {   // kendS is indexed by matrix position
-        const int row = TL::row_of_pos(threadIdx.x);
-        kendS[b][threadIdx.x] = row >= n ? 0 : (full ? 0x7fffffff : kend[c0 + row]);
+#pragma unroll
+    for (int gi = 0; gi < kGroups; ++gi) {
+      if (n[gi] == 0) continue;
+      if (!full[gi] || n[gi] < kKeyChunk) {   // rare: a chunk that needs the visibility mask
+        const int x = threadIdx.x - gi * kKeyChunk;
+        if (x >= 0 && x < kKeyChunk) {   // kendS is indexed by matrix position
+          const int row = TL::row_of_pos(x);
+          kendS[b][threadIdx.x] = row >= n[gi] ? 0 : (full[gi] ? 0x7fffffff : kend[c0[gi] + row]);
+        }
       }
+      tile_async_load<kDqThreads, HD>(Ks[b][gi], kbase + (size_t)c0[gi] * kv_stride, kv_bytes, n[gi]);
+      tile_async_load<kDqThreads, HD>(Vs[b][gi], vbase + (size_t)c0[gi] * kv_stride, kv_bytes, n[gi]);
     }
-    tile_async_load<kDqThreads, HD>(Ks[b], kbase + (size_t)c0 * kv_stride, kv_bytes, n);
-    tile_async_load<kDqThreads, HD>(Vs[b], vbase + (size_t)c0 * kv_stride, kv_bytes, n);
   };
   issue(0);
   int buf = 0;
@@ -212,13 +231,15 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
   while (have) {
     async_wait_all();
     __syncthreads();   // chunk `buf` has landed; everyone is done with the other buffer
-    const int cc0 = c0;
-    const bool need_mask = !full || n < kKeyChunk;
-    have = it.next(c0, n, full);
+    const int cc0 = kGroups == 1 || grp == 0 ? c0[0] : c0[kGroups - 1];
+    const int nn = kGroups == 1 || grp == 0 ? n[0] : n[kGroups - 1];
+    const bool need_mask = !(kGroups == 1 || grp == 0 ? full[0] : full[kGroups - 1]) || nn < kKeyChunk;
+    have = next();
     if (have) issue(buf ^ 1);
-    const uint16_t* Kt = Ks[buf] + rlo;
-    const uint16_t* Vt = Vs[buf] + rlo;
-    const uint16_t* Kc = Ks[buf] + clo;
+    if (kGroups == 2 && nn == 0) break;   // the walk's last step has a chunk for the first group only
+    const uint16_t* Kt = Ks[buf][grp] + rlo;
+    const uint16_t* Vt = Vs[buf][grp] + rlo;
+    const uint16_t* Kc = Ks[buf][grp] + clo;
 
     // The chunk's two 32-key halves as one sequence of 6 x KS matrix products (48
     // with head_dim 128) in six phases, in an issue order written out by hand (a scheduling barrier
@@ -281,7 +302,7 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
         if (need_mask) {   // uniform branch
 #pragma unroll
           for (int e4 = 0; e4 < 4; ++e4) {
-            const int4 ke = *reinterpret_cast<const int4*>(&kendS[buf][32 * mb + 8 * e4 + 4 * hh]);
+            const int4 ke = *reinterpret_cast<const int4*>(&kendS[buf][grp * kKeyChunk + 32 * mb + 8 * e4 + 4 * hh]);
             const int kev[4] = {ke.x, ke.y, ke.z, ke.w};
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
@@ -305,11 +326,37 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
     buf ^= 1;
   }
 
+  constexpr int kOut = TL::kBlocks / kGroups;   // 32-wide output blocks this wave stores, from block kOut * grp
+  if constexpr (kGroups == 2) {   // every group hands the other one its half of the blocks
+    f32x4* xs = reinterpret_cast<f32x4*>(&sm);
+    static_assert(sizeof(Tiles) >= 8 * kOut * 4 * 64 * sizeof(f32x4), "room for the exchange");
+    __syncthreads();   // everyone is done with the tiles
+#pragma unroll
+    for (int b = 0; b < kOut; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x16& x0 = dQ[b];
+        const f32x16& x1 = dQ[kOut + b];
+        xs[((w * kOut + b) * 4 + i) * 64 + l] =
+            grp == 0 ? f32x4{x1[4 * i], x1[4 * i + 1], x1[4 * i + 2], x1[4 * i + 3]}
+                     : f32x4{x0[4 * i], x0[4 * i + 1], x0[4 * i + 2], x0[4 * i + 3]};
+      }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < kOut; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4 x = xs[(((w ^ 4) * kOut + b) * 4 + i) * 64 + l];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          dQ[b][4 * i + e] = (grp == 0 ? dQ[b][4 * i + e] : dQ[kOut + b][4 * i + e]) + x[e];
+      }
+  }
   const int token = row_base + c;
   if (token < tile.t1) {
-    uint16_t* op = dq + ((size_t)token * Hq + h) * kHeadDim + 4 * hh;
+    uint16_t* op = dq + ((size_t)token * Hq + h) * kHeadDim + 32 * kOut * grp + 4 * hh;
 #pragma unroll
-    for (int dmb = 0; dmb < TL::kBlocks; ++dmb)
+    for (int dmb = 0; dmb < kOut; ++dmb)
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
         bf16x4 r;
@@ -710,13 +757,14 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
     // pay more for the draw (an atomic round trip before anything else can
     // start) than the balance between XCDs gives back.
     const size_t n_tiles = a.sched->q_tiles.size();
-    const bool draw = a.tickets != nullptr && qblocks >= 8 * (size_t)kNumCUs &&
+    const bool draw = !a.tc.q_split && a.tickets != nullptr && qblocks >= 8 * (size_t)kNumCUs &&
                       a.sched->fwd_chunks64 >= 64 * (int64_t)n_tiles && qblocks < 0x60000000u;
     if (draw) {
       zero_i32_kernel<<<1, 256, 0, st>>>(a.tickets, a.p.n_kv_heads);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     }
-    dq_bf16_kernel<HD><<<(unsigned)(draw ? qblocks + qblocks / 4 : qblocks), kDqThreads, 0, st>>>(
+    auto kernel = a.tc.q_split ? dq_bf16_kernel<HD, 2> : dq_bf16_kernel<HD>;
+    kernel<<<(unsigned)(draw ? qblocks + qblocks / 4 : qblocks), kDqThreads, 0, st>>>(
         a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
         (const uint16_t*)a.v, (const uint16_t*)a.d_o, a.lse_in,
         fused_delta ? (const uint16_t*)a.o : nullptr, a.delta, a.lse2, (uint16_t*)a.dq,

@@ -39,7 +39,11 @@ __device__ __forceinline__ float max_across_halves(float x) {
 // barrier, one round of bookkeeping and one online-softmax step per chunk, so
 // long key intervals run faster with 128, while every interval is padded to a
 // multiple of the chunk, so forests of short segments want 64.
-template <int kCh, int HD>
+//
+// kGroups = 2 (with kCh = 64): a block is 4 row tiles x 2 groups of waves, which take
+// every other chunk of the walk and are merged in LDS at the end: twice the blocks, each
+// half as long, for launches of so few rounds of blocks that the last one decides.
+template <int kCh, int HD, int kGroups = 1>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fwd_bf16_kernel(
     const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs,
     const int32_t* __restrict__ kend, const uint16_t* __restrict__ q,
@@ -47,11 +51,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     float* __restrict__ lse, int Hq, int Hkv, int HB, int hblocks, float scale,
     int* __restrict__ tickets, int n_items) {
   using TL = TileLayout<HD>;
-  constexpr int kSub = kCh / 64, kTileElems = TL::kTileElems, kHeadDim = HD;
+  static_assert(kGroups == 1 || kCh == 64, "a group takes one 64-row tile per step");
+  constexpr int kSub = kCh / 64, kTileElems = TL::kTileElems, kHeadDim = HD;   // kSub: LDS tiles per group
   constexpr int KS = TL::kSteps, DB = TL::kBlocks;   // k-steps over head_dim, 32-wide output blocks
-  __shared__ __attribute__((aligned(1024))) uint16_t Ks[2][kSub][kTileElems];
-  __shared__ __attribute__((aligned(1024))) uint16_t Vs[2][kSub][kTileElems];
-  __shared__ __attribute__((aligned(16))) int32_t kendS[2][kCh];
+  struct Tiles {
+    uint16_t K[2][kGroups * kSub][kTileElems];
+    uint16_t V[2][kGroups * kSub][kTileElems];
+  };
+  __shared__ __attribute__((aligned(1024))) Tiles sm;
+  auto& Ks = sm.K;
+  auto& Vs = sm.V;
+  __shared__ __attribute__((aligned(16))) int32_t kendS[2][kGroups * kCh];
   __shared__ int next_item[2];
 
   // tickets == nullptr: one (tile, kv head, head block) per block, from the block
@@ -68,8 +78,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int G = Hq / Hkv;
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int c = l & 31, hh = l >> 5;
-  const int h = g * G + hblk * HB + (w % HB);
-  const int row_base = tile.t0 + 32 * (w / HB);
+  const int rw = w % (8 / kGroups), grp = kGroups == 1 ? 0 : __builtin_amdgcn_readfirstlane(w / (8 / kGroups));
+  const int h = g * G + hblk * HB + (rw % HB);
+  const int row_base = tile.t0 + 32 * (rw / HB);
   // scores stay unscaled; the softmax scale (times log2 e) is folded into the
   // exponent.  A negative scale is moved into the sign of Q so that sc > 0.
   const float sc = fabsf(scale) * kLog2e;
@@ -104,23 +115,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // of its use, so one barrier per chunk is enough.
   KeyChunksT<kCh> it;
   it.init(segs, tile);
-  int c0, n, full;
-  bool have = it.next(c0, n, full);
+  int c0[kGroups], n[kGroups], full[kGroups];   // of the chunk(s) copied last; n = 0: none
+  auto next = [&] {
+    const bool some = it.next(c0[0], n[0], full[0]);
+    if constexpr (kGroups == 2)
+      if (!it.next(c0[1], n[1], full[1])) n[1] = 0;
+    return some;
+  };
+  bool have = next();
   auto issue = [&](int b) {
-    if (!full || n < kCh) {   // rare: a chunk that needs the visibility mask
-      if (threadIdx.x < kCh) {   // kendS is indexed by matrix position within each 64-key half
-        const int row = 64 * (threadIdx.x >> 6) + TL::row_of_pos(threadIdx.x & 63);
-        kendS[b][threadIdx.x] = row >= n ? 0 : (full ? 0x7fffffff : kend[c0 + row]);
-      }
-    }
 #pragma unroll
-    for (int sub = 0; sub < kSub; ++sub) {
-      // a half with no valid key re-reads the chunk's first row (finite data the mask hides)
-      const int nv = n - 64 * sub;
-      const int r0 = nv > 0 ? c0 + 64 * sub : c0;
-      const int nvalid = nv > 0 ? min(nv, 64) : 1;
-      tile_async_load<kThreads, HD>(Ks[b][sub], kbase + (size_t)r0 * kv_stride, kv_bytes, nvalid);
-      tile_async_load<kThreads, HD>(Vs[b][sub], vbase + (size_t)r0 * kv_stride, kv_bytes, nvalid);
+    for (int gi = 0; gi < kGroups; ++gi) {
+      if (n[gi] == 0) continue;
+      if (!full[gi] || n[gi] < kCh) {   // rare: a chunk that needs the visibility mask
+        const int x = threadIdx.x - gi * kCh;
+        if (x >= 0 && x < kCh) {   // kendS is indexed by matrix position within each 64-key half
+          const int row = 64 * (x >> 6) + TL::row_of_pos(x & 63);
+          kendS[b][threadIdx.x] = row >= n[gi] ? 0 : (full[gi] ? 0x7fffffff : kend[c0[gi] + row]);
+        }
+      }
+#pragma unroll
+      for (int sub = 0; sub < kSub; ++sub) {
+        // a half with no valid key re-reads the chunk's first row (finite data the mask hides)
+        const int nv = n[gi] - 64 * sub;
+        const int r0 = nv > 0 ? c0[gi] + 64 * sub : c0[gi];
+        const int nvalid = nv > 0 ? min(nv, 64) : 1;
+        tile_async_load<kThreads, HD>(Ks[b][gi * kSub + sub], kbase + (size_t)r0 * kv_stride, kv_bytes, nvalid);
+        tile_async_load<kThreads, HD>(Vs[b][gi * kSub + sub], vbase + (size_t)r0 * kv_stride, kv_bytes, nvalid);
+      }
     }
   };
   issue(0);
@@ -130,12 +152,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   while (have) {
     async_wait_all();
     __syncthreads();   // chunk `buf` has landed; everyone is done with the other buffer
-    const int cc0 = c0;
-    const bool need_mask = !full || n < kCh;
-    have = it.next(c0, n, full);
+    const int cc0 = kGroups == 1 || grp == 0 ? c0[0] : c0[kGroups - 1];
+    const int nn = kGroups == 1 || grp == 0 ? n[0] : n[kGroups - 1];
+    const bool need_mask = !(kGroups == 1 || grp == 0 ? full[0] : full[kGroups - 1]) || nn < kCh;
+    have = next();
     if (have) issue(buf ^ 1);
-    const uint16_t* Kt = Ks[buf][0] + rlo;
-    const uint16_t* Vt = Vs[buf][0] + clo;
+    if (kGroups == 2 && nn == 0) break;   // the walk's last step has a chunk for the first group only
+    const uint16_t* Kt = Ks[buf][grp * kSub] + rlo;
+    const uint16_t* Vt = Vs[buf][grp * kSub] + clo;
 
     // ---- S^T = K Q^T : 64 keys x 32 queries
     f32x16 S[2 * kSub];
@@ -162,7 +186,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
           const int kvl0 = 32 * mb + 8 * e4 + 4 * hh;
-          const int4 ke = *reinterpret_cast<const int4*>(&kendS[buf][kvl0]);
+          const int4 ke = *reinterpret_cast<const int4*>(&kendS[buf][grp * kCh + kvl0]);
           const int kev[4] = {ke.x, ke.y, ke.z, ke.w};
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -222,13 +246,52 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   // ---- normalise and store
   if (tickets != nullptr) queues.prefetch();
-  const float lt = lsum + __shfl_xor(lsum, 32);
+  float lt = lsum + __shfl_xor(lsum, 32);
+  constexpr int kOut = DB / kGroups;   // 32-wide output blocks this wave stores, from block kOut * grp
+  if constexpr (kGroups == 2) {
+    // common maximum and row sum, then every group hands the other one its half of the output blocks
+    __shared__ float mS[8][32], lS[8][32];
+    f32x4* xs = reinterpret_cast<f32x4*>(&sm);
+    static_assert(sizeof(Tiles) >= 8 * kOut * 4 * 64 * sizeof(f32x4), "room for the exchange");
+    if (hh == 0) {
+      mS[w][c] = m;
+      lS[w][c] = lt;
+    }
+    __syncthreads();   // everyone is done with the tiles, too
+    const float m2 = mS[w ^ 4][c], l2 = lS[w ^ 4][c], own = m;
+    m = fmaxf(own, m2);
+    const float f = __builtin_amdgcn_exp2f((own - m) * sc);
+    lt = lt * f + l2 * __builtin_amdgcn_exp2f((m2 - m) * sc);
+#pragma unroll
+    for (int dmb = 0; dmb < DB; ++dmb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) O[dmb][e] *= f;
+#pragma unroll
+    for (int b = 0; b < kOut; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x16& x0 = O[b];
+        const f32x16& x1 = O[kOut + b];
+        xs[((w * kOut + b) * 4 + i) * 64 + l] =
+              grp == 0 ? f32x4{x1[4 * i], x1[4 * i + 1], x1[4 * i + 2], x1[4 * i + 3]}
+                       : f32x4{x0[4 * i], x0[4 * i + 1], x0[4 * i + 2], x0[4 * i + 3]};
+      }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < kOut; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4 x = xs[(((w ^ 4) * kOut + b) * 4 + i) * 64 + l];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) O[b][4 * i + e] = (grp == 0 ? O[b][4 * i + e] : O[kOut + b][4 * i + e]) + x[e];
+      }
+  }
   const float inv = 1.f / lt;
   const int token = row_base + c;
   if (token < tile.t1) {
-    uint16_t* op = o + ((size_t)token * Hq + h) * kHeadDim + 4 * hh;
+    uint16_t* op = o + ((size_t)token * Hq + h) * kHeadDim + 32 * kOut * grp + 4 * hh;
 #pragma unroll
-    for (int dmb = 0; dmb < DB; ++dmb)
+    for (int dmb = 0; dmb < kOut; ++dmb)
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
         bf16x4 r;
@@ -236,7 +299,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int e = 0; e < 4; ++e) r[e] = (__bf16)(O[dmb][4 * v4 + e] * inv);
         *reinterpret_cast<bf16x4*>(op + 32 * dmb + 8 * v4) = r;
       }
-    if (hh == 0) lse[(size_t)token * Hq + h] = (m * sc + log2f(lt)) * kLn2;
+    if (hh == 0 && grp == 0) lse[(size_t)token * Hq + h] = (m * sc + log2f(lt)) * kLn2;
   }
   if (tickets == nullptr || !queues.draw(next_item, item_idx, g_idx, true)) break;
   }   // next item
@@ -254,11 +317,12 @@ int launch_fwd_bf16(const LaunchArgs& a) {
   hipStream_t st = (hipStream_t)a.stream;
   clear_hip_error();
   if (a.tc.q_small) return launch_fwd_bf16_small(a);
+  const bool split = a.tc.q_split;
   const size_t blocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
   if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
   // With a workspace for the counters and enough items, resident blocks draw the
   // items from per-head queues (see dta_queue.h); otherwise one block per item.
-  const bool queues = a.tickets != nullptr && blocks >= 8 * (size_t)kNumCUs;
+  const bool queues = !split && a.tickets != nullptr && blocks >= 8 * (size_t)kNumCUs;
   if (queues) {
     zero_i32_kernel<<<1, 256, 0, st>>>(a.tickets, a.p.n_kv_heads);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
@@ -267,7 +331,8 @@ int launch_fwd_bf16(const LaunchArgs& a) {
   // at most 6 % to the keys streamed (measured: 5 % faster at +0.5 %, 1.4 % faster
   // at +5.6 %, 2 % slower at +9.6 %)
   const bool wide = 2 * a.sched->fwd_chunks128 * 100 <= a.sched->fwd_chunks64 * 106;
-  auto kernel = a.p.head_dim == 128 ? (wide ? fwd_bf16_kernel<128, 128> : fwd_bf16_kernel<64, 128>)
+  auto kernel = split ? (a.p.head_dim == 128 ? fwd_bf16_kernel<64, 128, 2> : fwd_bf16_kernel<64, 64, 2>)
+                : a.p.head_dim == 128 ? (wide ? fwd_bf16_kernel<128, 128> : fwd_bf16_kernel<64, 128>)
                                     : (wide ? fwd_bf16_kernel<128, 64> : fwd_bf16_kernel<64, 64>);
   kernel<<<(unsigned)(queues ? (size_t)kNumCUs : blocks), kThreads, 0, st>>>(
       a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,

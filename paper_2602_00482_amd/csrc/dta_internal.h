@@ -198,6 +198,7 @@ struct TileChoice {
   int hblocks;  // blocks per (tile, kv head) = group size / hb
   KvWalk walk;
   bool q_small, k_small;   // forward and dQ, dK/dV: the form for launches too small to fill the chip
+  bool q_split;            // forward and dQ (bf16): the form for launches of a few rounds of blocks
 };
 // What a call covers: `rows` query rows and the `keys` they see (both the tokens of
 // the tree for a whole-tree call).

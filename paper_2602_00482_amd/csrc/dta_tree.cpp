@@ -551,27 +551,37 @@ int validate_params(const dta_attn_params_t* p) {
 }
 
 namespace {
-// Which bf16 calls take the form for launches too small to fill the chip
-// (dta_bf16_small.hip).  The unit is what a block of the other form holds one wave
-// (rows) or one block (keys) for; measured on MI355X, head_dim 128, in us, the
-// small form against the other one:
-//   forward   512 row tiles: 14.5 / 18.3 (32/8 heads), 15.2 / 28.7 (16/16);
-//             1024: 24.8 / 23.0 (32/8), 23.8 / 18.7 (64/8), 30.2 / 34.9 (16/16)
-//   backward of a tree, both kernels small (one launch) / both large:
-//             1536 row tiles: 82 / 120 (32/8), 122 / 122 (16/16), 148 / 160 (8/2);
-//             2048: 115 / 131, but 114 with only dK/dV small; 3072: dK/dV small 180 / 197 at
-//             192 key tiles, 247 / 236 at 256
-//   backward of a segment (whose dK/dV walks are never cut): 1600 rows under 2048 keys
-//             300 / 335 (32/8) and 570 / 609 (64/8); under 8192 keys 870 / 858 and 1680 / 1657
-void small_forms(const CallShape& c, int n_q_heads, int n_kv_heads, bool* q_small, bool* k_small) {
-  const int64_t row_tiles = c.rows / 32 * n_q_heads, key_tiles = c.keys / 128 * n_kv_heads;
+// Which form of the bf16 kernels a call takes.  Forward and dQ have three: blocks of 8
+// row tiles, blocks of 4 row tiles x 2 groups that share out the keys (split), blocks of
+// 2 x 4 (small, dta_bf16_small.hip); dK/dV has two.  The row tile is what a block of
+// 8 waves holds one wave for, so 2048 row tiles are one round of blocks on the 256 CUs
+// for the first form, 1024 for the second, 512 for the third; what shares out the keys
+// costs more per pair and gains where the other form's round would be left half empty.
+// Measured on MI355X, head_dim 128, in us, small / split / 8 row tiles:
+//   forward of a tree   500 row tiles 15 / 16 / 20 (32/8 heads), 15 / 21 / 32 (16/16);
+//             600: 20 / 16 / 20, 22 / 20 / 30; 1000: 25 / 21 / 26, 30 / 26 / 40;
+//             1200: 32 / 28 / 26, 41 / 35 / 37; 2400: 66 / 55 / 50
+//   forward of a segment under 1024 keys   500: 29 / 35 / 50; 1000: 58 / 45 / 63;
+//             2000: 124 / 87 / 93 (32/8), 100 / 72 / 71 (64/8), 170 / 123 / 137 (16/16);
+//             2500: 168 / 133 / 117
+//   backward of a tree   1600: 86 / 90 / 92 (32/8), 66 / 70 / 70 (64/8); 2000: 118 / 112 / 121,
+//             171 / 150 / 149 (16/16); 3000: 196 / 185 / 199, 298 / 251 / 272; 3500: 257 / 214 / 222;
+//             dQ alone at 4000: 163 / 133 / 130; head_dim 64, 2000: 80 / 77 / 70, 3500: 166 / 144 / 138
+//   dK/dV of a tree   3072 row tiles, small / large: 180 / 197 at 192 key tiles, 247 / 236 at 256
+//   backward of a segment (whose dK/dV walks are never cut)   1600 rows, small / 8 row tiles, under
+//             2048 keys 300 / 335 (32/8) and 570 / 609 (64/8), under 8192 keys 870 / 858 and 1680 / 1657;
+//             2000 row tiles under 1024 keys, 16/16: 418 / 386 / 412; 2500: 623 / 599 / 588
+void choose_forms(const CallShape& c, const dta_attn_params_t* p, TileChoice* out) {
+  const int64_t row_tiles = c.rows / 32 * p->n_q_heads, key_tiles = c.keys / 128 * p->n_kv_heads;
   if (!c.backward) {
-    *q_small = row_tiles < 900;
-    *k_small = false;
+    out->q_small = row_tiles <= 512;
+    out->q_split = !out->q_small && row_tiles <= (c.segment ? 2048 : 1024);
+    out->k_small = false;
     return;
   }
-  *q_small = row_tiles < 1800 || (c.segment && row_tiles < 4000 && key_tiles < 350);
-  *k_small = *q_small || (!c.segment && key_tiles < 200);
+  out->q_small = row_tiles < 1800 || (c.segment && row_tiles < 4000 && key_tiles < 350);
+  out->q_split = !out->q_small && (c.segment ? row_tiles <= 2048 : row_tiles < 3600 && p->head_dim == 128);
+  out->k_small = out->q_small || (!c.segment && key_tiles < 200);
 }
 }  // namespace
 
@@ -586,6 +596,7 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
     // split instead.
     const bool small = call.rows / 16 * p->n_q_heads < 2048;
     out->q_small = out->k_small = small;
+    out->q_split = false;
     const int split = !small ? 1 : p->head_dim == 64 ? 4 : 2;
     const int R = 8 / split;
     int hb = 1;
@@ -597,16 +608,12 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
     // an iteration takes a wave several microseconds, so cut walks may be short; four-wave blocks, eight when split
     out->walk = KvWalk{32, 4 * split, small ? kNumCUs : 2 * kNumCUs};
   } else {
-    // eight waves per block: hb q heads of the group x (R/hb) 32-row query blocks,
-    // R = 8, or 2 where the launch has too few rows (see dta_bf16_small.hip)
-    auto rows_of = [&](bool small, int* heads) {
-      const int R = small ? 2 : 8;
-      *heads = 1;
-      while (*heads < R && G % (2 * *heads) == 0) *heads *= 2;
-      return 32 * (R / *heads);
-    };
-    small_forms(call, p->n_q_heads, p->n_kv_heads, &out->q_small, &out->k_small);
-    out->bm = rows_of(out->q_small, &out->hb);
+    // eight waves per block: hb q heads of the group x (R/hb) 32-row query blocks
+    choose_forms(call, p, out);
+    const int R = out->q_small ? 2 : out->q_split ? 4 : 8;
+    out->hb = 1;
+    while (out->hb < R && G % (2 * out->hb) == 0) out->hb *= 2;
+    out->bm = 32 * (R / out->hb);
     out->hblocks = G / out->hb;
     out->bn = out->k_small ? 64 : 128;
     out->walk = out->k_small ? KvWalk{32, 32, kNumCUs} : KvWalk{64, 32, 2 * kNumCUs};

@@ -67,3 +67,43 @@ def test_small_form_path_of_many_short_intervals(Hq, Hkv, d):
         seg.append(n)
         tip = len(seg) - 1
     _check(seg, Hq, Hkv, d, 64, parent)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,seg", [
+    (30, 10, [257, 33, 310, 95, 31]),       # forward split (680 row tiles): one head per block, 128-token tiles
+    (40, 10, [300, 127, 128, 129, 40]),     # ... group of four, 32-token tiles
+    (120, 60, [257, 33, 310, 95, 31]),      # backward split at head_dim 128 (2722), group of two
+    (128, 16, [300, 1, 63, 65, 129, 170]),  # ... group of eight, two head blocks
+    (192, 96, [257, 33, 310, 95, 31]),      # blocks of 8 row tiles in both directions
+])
+def test_forms_between(Hq, Hkv, seg, d):
+    _check(seg, Hq, Hkv, d, 64 if Hq < 100 else 128 if Hkv > 32 else 64)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,rows", [(64, 64, 1000), (64, 64, 993), (48, 16, 700)])
+def test_split_segment(Hq, Hkv, rows, d):
+    """One segment of 1000 to 2000 row tiles under a ragged prompt, forward and backward,
+    against the whole-tree calls (the same pairs: both round P and dS to bf16 once)."""
+    import torch
+    parent, seg = np.array([-1, 0], dtype=np.int32), np.array([517, rows], dtype=np.int32)
+    T, scale = 517 + rows, 1.0 / math.sqrt(d)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    q, do = (torch.randn((T, Hq, d), generator=g, device="cuda").bfloat16() for _ in range(2))
+    k, v = (torch.randn((T, Hkv, d), generator=g, device="cuda").bfloat16() for _ in range(2))
+    p = dta.AttnParams(Hq, Hkv, d, scale, dta.BF16)
+    tree = dta.tree_build(parent, seg)
+    o, lse = dta.tree_attn_fwd(tree, p, q, k, v)
+    dq, dk, dv = dta.tree_attn_bwd(tree, p, q, k, v, o, lse, do)
+    o2, dq2 = torch.zeros_like(o), torch.zeros_like(dq)
+    lse2 = torch.zeros_like(lse)
+    dk2, dv2 = torch.zeros(k.shape, device="cuda"), torch.zeros(k.shape, device="cuda")
+    ws = torch.empty(max(256, dta.workspace_bytes(tree, p, True)), dtype=torch.uint8, device="cuda")
+    for t0, t1 in ((0, 517), (517, T)):
+        dta.tree_attn_fwd_segment(tree, p, t0, t1, q, k, v, o2, lse2)
+    for t0, t1 in ((517, T), (0, 517)):
+        dta.tree_attn_bwd_segment(tree, p, t0, t1, q, k, v, o2, lse2, do, dq2, dk2, dv2, ws)
+    for name, a, b in (("o", o2, o), ("lse", lse2, lse), ("dq", dq2, dq), ("dk", dk2, dk), ("dv", dv2, dv)):
+        assert rel_err(a.float().cpu().numpy(), b.float().cpu().numpy()) <= 1e-2, name
