@@ -23,7 +23,7 @@
 //   4862 tokens (a prompt with 16 answers), 32/8 heads of 128:
 //     forward 1.51 -> 0.35 ms (93 TFLOP/s), dQ 2.38 -> 0.53 ms (93), dK/dV 13.6 -> 0.63 ms (103)
 //   384 tokens in 13 nodes, 4/4 heads of 64 (latency of a chain of dependent steps):
-//     forward 71 -> 11 us, dQ 64 -> 14 us, dK/dV 146 -> 20 us
+//     forward 71 -> 11 us, dQ 64 and dK/dV 146 -> 17 us together (two launches)
 // A large launch's blocks are few rounds (1216 on 512 slots above), so what is left
 // is mostly the uneven end of the launch.
 #include <hip/hip_runtime.h>
@@ -139,22 +139,22 @@ __device__ __forceinline__ void sum_over_groups(f32x4* buf, int rw, int kg, f32x
   }
 }
 
-constexpr int kThreads = 512;   // forward and dQ blocks: 8 waves
-
-// Block = 8 waves = R row tiles (HB q heads of the group x 16-row blocks) x KS
+// Block = NW waves = R row tiles (HB q heads of the group x 16-row blocks) x KS
 // groups.  The keys of the tile's root path are streamed in chunks of 32 * KS
 // keys, double-buffered in LDS; group kg of the block takes keys
 // [32*kg, 32*kg + 32) of every chunk and the groups' results are merged at the
 // end.  KS = 1: one K/V copy serves 8 row tiles, for launches that fill the chip.
 // KS = 4 / 2 (head_dim 64 / 128): a fourth / half of the rows per block and of the
-// steps per walk, for trees too small to fill it.
-template <int HD, int KS>
-__global__ __launch_bounds__(kThreads) void fwd_f32_kernel(
+// steps per walk, for trees too small to fill it.  NW = 4 with KS > 1: half the row
+// tiles again, one wave per SIMD, for launches of so few blocks that a CU works on
+// one of them: what a step takes is the SIMD's products, and two waves have twice as many.
+template <int HD, int KS, int NW>
+__global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
     const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs, const int32_t* __restrict__ kend,
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     float* __restrict__ o, float* __restrict__ lse, int Hq, int Hkv, int HB, int hblocks, float scale) {
   using RL = Rows32<HD>;
-  constexpr int NB = RL::NB, R = 8 / KS, CH = 32 * KS;
+  constexpr int NB = RL::NB, R = NW / KS, CH = 32 * KS;
   __shared__ __attribute__((aligned(1024))) float Ks[2][KS * RL::kTile];
   __shared__ __attribute__((aligned(1024))) float Vs[2][KS * RL::kTile];
   __shared__ __attribute__((aligned(16))) int32_t kendS[2][CH];
@@ -194,8 +194,8 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(
       const int row = 32 * (threadIdx.x >> 5) + RL::row_of_pos(threadIdx.x & 31);
       kendS[b][threadIdx.x] = row >= n ? 0 : (full ? 0x7fffffff : kend[c0 + row]);
     }
-    rows_async_load<HD, CH, 8>(Ks[b], kbase + (size_t)c0 * kv_stride, kv_bytes, n);
-    rows_async_load<HD, CH, 8>(Vs[b], vbase + (size_t)c0 * kv_stride, kv_bytes, n);
+    rows_async_load<HD, CH, NW>(Ks[b], kbase + (size_t)c0 * kv_stride, kv_bytes, n);
+    rows_async_load<HD, CH, NW>(Vs[b], vbase + (size_t)c0 * kv_stride, kv_bytes, n);
   };
   issue(0);
   int buf = 0;
@@ -326,22 +326,45 @@ __global__ __launch_bounds__(256) void delta_f32_kernel(const float* __restrict_
   if (row < rows && g == 0) delta[row] = s;
 }
 
+// What the backward kernels read and write.
+struct BwdArgs {
+  const QTile* tiles;
+  const KeySeg* segs;
+  const KvItem* items;
+  const int32_t* kend;
+  const float *q, *k, *v, *d_o, *o, *lse;
+  float *delta, *dq, *dk, *dv, *partial;
+  int accumulate, Hq, Hkv, HB, hblocks;
+  float scale;
+  int dkdv_blocks;   // blocks [0, dkdv_blocks) of a launch of both do dK/dV, the rest dQ
+};
+
+template <int HD, int KS>
+struct DqSmem {
+  float K[2][KS * Rows32<HD>::kTile];
+  float V[2][KS * Rows32<HD>::kTile];
+  int32_t kendS[2][32 * KS];
+};
+
 // Same walk and block shapes as the forward kernel.  With o != nullptr the launch
 // also computes D for its rows and leaves it in `delta` for dK/dV.
-template <int HD, int KS>
-__global__ __launch_bounds__(kThreads) void dq_f32_kernel(
-    const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs, const int32_t* __restrict__ kend,
-    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
-    const float* __restrict__ d_o, const float* __restrict__ o, const float* __restrict__ lse,
-    float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, int HB, int hblocks, float scale) {
+template <int HD, int KS, int NW>
+__device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD, KS>& sm, int block) {
   using RL = Rows32<HD>;
-  constexpr int NB = RL::NB, R = 8 / KS, CH = 32 * KS;
-  __shared__ __attribute__((aligned(1024))) float Ks[2][KS * RL::kTile];
-  __shared__ __attribute__((aligned(1024))) float Vs[2][KS * RL::kTile];
-  __shared__ __attribute__((aligned(16))) int32_t kendS[2][CH];
+  constexpr int NB = RL::NB, R = NW / KS, CH = 32 * KS;
+  auto& Ks = sm.K;
+  auto& Vs = sm.V;
+  auto& kendS = sm.kendS;
+  const int32_t* __restrict__ kend = p.kend;
+  const float *__restrict__ q = p.q, *__restrict__ k = p.k, *__restrict__ v = p.v, *__restrict__ d_o = p.d_o;
+  const float *__restrict__ o = p.o, *__restrict__ lse = p.lse;
+  const KeySeg* __restrict__ segs = p.segs;
+  float *__restrict__ delta = p.delta, *__restrict__ dq = p.dq;
+  const int Hq = p.Hq, Hkv = p.Hkv, HB = p.HB, hblocks = p.hblocks;
+  const float scale = p.scale;
 
-  const int item = blockIdx.x / Hkv, g_kv = blockIdx.x % Hkv;
-  const QTile tile = tiles[item / hblocks];
+  const int item = block / Hkv, g_kv = block % Hkv;
+  const QTile tile = p.tiles[item / hblocks];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int n16 = l & 15, lg = l >> 4;
   const int rw = w % R, kg = w / R;
@@ -364,8 +387,8 @@ __global__ __launch_bounds__(kThreads) void dq_f32_kernel(
       const int row = 32 * (threadIdx.x >> 5) + RL::row_of_pos(threadIdx.x & 31);
       kendS[b][threadIdx.x] = row >= n ? 0 : (full ? 0x7fffffff : kend[c0 + row]);
     }
-    rows_async_load<HD, CH, 8>(Ks[b], kbase + (size_t)c0 * kv_stride, kv_bytes, n);
-    rows_async_load<HD, CH, 8>(Vs[b], vbase + (size_t)c0 * kv_stride, kv_bytes, n);
+    rows_async_load<HD, CH, NW>(Ks[b], kbase + (size_t)c0 * kv_stride, kv_bytes, n);
+    rows_async_load<HD, CH, NW>(Vs[b], vbase + (size_t)c0 * kv_stride, kv_bytes, n);
   };
   issue(0);
 
@@ -470,23 +493,33 @@ __global__ __launch_bounds__(kThreads) void dq_f32_kernel(
 // groups per block.  Q and dO of the rows that can see the keys are streamed in
 // iterations of 32 rows of one q head, heads innermost, last chunk first, KS
 // iterations per step, one per group.  KS = 1: four waves, two
-// blocks per CU.  KS = 4 / 2: eight waves, trees too small to fill the chip.
+// blocks per CU.  KS = 4 / 2: eight waves (NW = 4: four, see the forward kernel), trees too
+// small to fill the chip.
 // Long walks are cut into items that write partial sums, as in bf16 mode.
 template <int HD, int KS>
-__global__ __launch_bounds__(KS == 1 ? 256 : 512, KS == 1 ? 2 : 1) void dkdv_f32_kernel(
-    const KvItem* __restrict__ items, const int32_t* __restrict__ kend, const float* __restrict__ q,
-    const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ d_o,
-    const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ dk,
-    float* __restrict__ dv, float* __restrict__ partial, int accumulate, int Hq, int Hkv, float scale) {
-  using RL = Rows32<HD>;
-  constexpr int NB = RL::NB, NW = KS == 1 ? 4 : 8, R = NW / KS, CH = 32 * KS, kKeys = 16 * R;
-  constexpr int kStat = CH < 64 ? 64 : CH;   // one wave-wide copy fills 64
-  __shared__ __attribute__((aligned(1024))) float Qs[2][KS * RL::kTile];
-  __shared__ __attribute__((aligned(1024))) float dOs[2][KS * RL::kTile];
-  __shared__ __attribute__((aligned(256))) float stat[2][2][kStat];   // [buffer][lse | delta][position]
+struct DkdvSmem {
+  static constexpr int kStat = 32 * KS < 64 ? 64 : 32 * KS;   // one wave-wide copy fills 64
+  float Q[2][KS * Rows32<HD>::kTile];
+  float dO[2][KS * Rows32<HD>::kTile];
+  __attribute__((aligned(256))) float stat[2][2][kStat];   // [buffer][lse | delta][position]
+};
 
-  const KvItem tile = items[blockIdx.x / Hkv];
-  const int g = blockIdx.x % Hkv, G = Hq / Hkv;
+template <int HD, int KS, int NW>
+__device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD, KS>& sm, int block) {
+  using RL = Rows32<HD>;
+  constexpr int NB = RL::NB, R = NW / KS, kKeys = 16 * R, kStat = DkdvSmem<HD, KS>::kStat;
+  auto& Qs = sm.Q;
+  auto& dOs = sm.dO;
+  auto& stat = sm.stat;
+  const int32_t* __restrict__ kend = p.kend;
+  const float *__restrict__ q = p.q, *__restrict__ k = p.k, *__restrict__ v = p.v, *__restrict__ d_o = p.d_o;
+  const float *__restrict__ lse = p.lse, *__restrict__ delta = p.delta;
+  float *__restrict__ dk = p.dk, *__restrict__ dv = p.dv, *__restrict__ partial = p.partial;
+  const int accumulate = p.accumulate, Hq = p.Hq, Hkv = p.Hkv;
+  const float scale = p.scale;
+
+  const KvItem tile = p.items[block / Hkv];
+  const int g = block % Hkv, G = Hq / Hkv;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int n16 = l & 15, lg = l >> 4;
   const int kw = w % R, qg = w / R;
@@ -617,7 +650,7 @@ __global__ __launch_bounds__(KS == 1 ? 256 : 512, KS == 1 ? 2 : 1) void dkdv_f32
     for (int e = 0; e < 4; ++e)
 #pragma unroll
       for (int x = 0; x < NB / 4; ++x) {
-        f32x4* p = reinterpret_cast<f32x4*>(dst + NB * (4 * lg + e) + 4 * x);
+        f32x4* at = reinterpret_cast<f32x4*>(dst + NB * (4 * lg + e) + 4 * x);
         f32x4 r;
 #pragma unroll
         for (int b = 0; b < 4; ++b) r[b] = acc[half * NB + 4 * x + b][e];
@@ -625,11 +658,37 @@ __global__ __launch_bounds__(KS == 1 ? 256 : 512, KS == 1 ? 2 : 1) void dkdv_f32
           r *= f;
           // a segment call adds to the caller's accumulators (this block is the only
           // owner of the key in the launch)
-          if (accumulate) r += *p;
+          if (accumulate) r += *at;
         }
-        *p = r;
+        *at = r;
       }
   }
+}
+
+template <int HD, int KS, int NW>
+__global__ __launch_bounds__(64 * NW) void dq_f32_kernel(BwdArgs p) {
+  __shared__ __attribute__((aligned(1024))) DqSmem<HD, KS> sm;
+  dq_block<HD, KS, NW>(p, sm, blockIdx.x);
+}
+
+template <int HD, int KS, int NW>
+__global__ __launch_bounds__(64 * NW, KS == 1 ? 2 : 1) void dkdv_f32_kernel(BwdArgs p) {
+  __shared__ __attribute__((aligned(1024))) DkdvSmem<HD, KS> sm;
+  dkdv_block<HD, KS, NW>(p, sm, blockIdx.x);
+}
+
+// Both in one launch, after one of the delta kernel: neither fills the chip by itself,
+// and each is a few steps between a launch and its end.  Measured against dQ (which
+// then computes D) and dK/dV after each other: 256 row tiles of 16, 32/8 heads of 128,
+// 49 -> 35 us; 1000: 89 -> 85; 2000: 232 -> 208.
+template <int HD, int KS, int NW>
+__global__ __launch_bounds__(64 * NW, 1) void bwd_f32_kernel(BwdArgs p) {
+  __shared__ __attribute__((aligned(1024))) union {
+    DqSmem<HD, KS> dq;
+    DkdvSmem<HD, KS> dkdv;
+  } sm;
+  if ((int)blockIdx.x < p.dkdv_blocks) dkdv_block<HD, KS, NW>(p, sm.dkdv, blockIdx.x);
+  else dq_block<HD, KS, NW>(p, sm.dq, blockIdx.x - p.dkdv_blocks);
 }
 
 // Adds the partial sums of a split key tile in slot order and writes dK/dV.
@@ -664,8 +723,10 @@ int fwd_impl(const LaunchArgs& a) {
   const size_t blocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
   if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
   constexpr int kSplit = HD == 64 ? 4 : 2;
-  auto kernel = a.tc.q_small ? fwd_f32_kernel<HD, kSplit> : fwd_f32_kernel<HD, 1>;
-  kernel<<<(unsigned)blocks, kThreads, 0, st>>>(
+  auto kernel = a.tc.tiny      ? fwd_f32_kernel<HD, kSplit, 4>
+                : a.tc.q_small ? fwd_f32_kernel<HD, kSplit, 8>
+                               : fwd_f32_kernel<HD, 1, 8>;
+  kernel<<<(unsigned)blocks, a.tc.tiny ? 256 : 512, 0, st>>>(
       a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
       (const float*)a.v, (float*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
       a.tc.hblocks, a.p.softmax_scale);
@@ -682,28 +743,40 @@ int bwd_impl(const LaunchArgs& a) {
   const size_t kblocks = a.sched->kv_items.size() * (size_t)a.p.n_kv_heads;
   if (qblocks == 0 || qblocks > 0x7fffffffu || kblocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
   constexpr int kSplit = HD == 64 ? 4 : 2;
-  const bool fused_delta = (a.stages & DTA_BWD_DELTA) && (a.stages & DTA_BWD_DQ);
+  const bool one_launch = a.tc.q_small && (a.stages & DTA_BWD_DQ) && (a.stages & DTA_BWD_DKDV) &&
+                          qblocks + kblocks <= 0x7fffffffu;
+  // otherwise the dQ launch computes D itself when both stages are asked for
+  const bool fused_delta = (a.stages & DTA_BWD_DELTA) && (a.stages & DTA_BWD_DQ) && !one_launch;
   if ((a.stages & DTA_BWD_DELTA) && !fused_delta) {
     delta_f32_kernel<HD><<<(unsigned)((rows + 63) / 64), 256, 0, st>>>(
         (const float*)a.o + row0 * HD, (const float*)a.d_o + row0 * HD, a.delta + row0, rows);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
-  if (a.stages & DTA_BWD_DQ) {
-    auto kernel = a.tc.q_small ? dq_f32_kernel<HD, kSplit> : dq_f32_kernel<HD, 1>;
-    kernel<<<(unsigned)qblocks, kThreads, 0, st>>>(
-        a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
-        (const float*)a.v, (const float*)a.d_o, fused_delta ? (const float*)a.o : nullptr, a.lse_in,
-        a.delta, (float*)a.dq, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb, a.tc.hblocks, a.p.softmax_scale);
+  const BwdArgs args{a.sched->d_q_tiles, a.sched->d_segs, a.sched->d_kv_items, a.d_kend, (const float*)a.q,
+                     (const float*)a.k, (const float*)a.v, (const float*)a.d_o,
+                     fused_delta ? (const float*)a.o : nullptr, a.lse_in, a.delta, (float*)a.dq,
+                     a.dk_acc ? a.dk_acc : (float*)a.dk, a.dk_acc ? a.dv_acc : (float*)a.dv, a.partial,
+                     a.dk_acc != nullptr, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb, a.tc.hblocks,
+                     a.p.softmax_scale, (int)kblocks};
+  if (one_launch) {
+    auto kernel = a.tc.tiny ? bwd_f32_kernel<HD, kSplit, 4> : bwd_f32_kernel<HD, kSplit, 8>;
+    kernel<<<(unsigned)(qblocks + kblocks), a.tc.tiny ? 256 : 512, 0, st>>>(args);
+    { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
+  } else if (a.stages & DTA_BWD_DQ) {
+    auto kernel = a.tc.tiny      ? dq_f32_kernel<HD, kSplit, 4>
+                  : a.tc.q_small ? dq_f32_kernel<HD, kSplit, 8>
+                                 : dq_f32_kernel<HD, 1, 8>;
+    kernel<<<(unsigned)qblocks, a.tc.tiny ? 256 : 512, 0, st>>>(args);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
   if (a.stages & DTA_BWD_DKDV) {
-    auto kernel = a.tc.k_small ? dkdv_f32_kernel<HD, kSplit> : dkdv_f32_kernel<HD, 1>;
-    kernel<<<(unsigned)kblocks, a.tc.k_small ? 512 : 256, 0, st>>>(
-        a.sched->d_kv_items, a.d_kend, (const float*)a.q, (const float*)a.k, (const float*)a.v,
-        (const float*)a.d_o, a.lse_in, a.delta, a.dk_acc ? a.dk_acc : (float*)a.dk,
-        a.dk_acc ? a.dv_acc : (float*)a.dv, a.partial, a.dk_acc != nullptr, a.p.n_q_heads,
-        a.p.n_kv_heads, a.p.softmax_scale);
-    { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
+    if (!one_launch) {
+      auto kernel = a.tc.tiny      ? dkdv_f32_kernel<HD, kSplit, 4>
+                    : a.tc.k_small ? dkdv_f32_kernel<HD, kSplit, 8>
+                                   : dkdv_f32_kernel<HD, 1, 4>;
+      kernel<<<(unsigned)kblocks, a.tc.k_small && !a.tc.tiny ? 512 : 256, 0, st>>>(args);
+      { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
+    }
     if (!a.sched->kv_reduce.empty()) {
       dkdv_reduce_f32_kernel<HD><<<(unsigned)(a.sched->kv_reduce.size() * a.p.n_kv_heads * 4), 256, 0, st>>>(
           a.sched->d_kv_reduce, a.partial, (float*)a.dk, (float*)a.dv, a.p.n_kv_heads, a.p.softmax_scale,

@@ -199,6 +199,7 @@ struct TileChoice {
   KvWalk walk;
   bool q_small, k_small;   // forward and dQ, dK/dV: the form for launches too small to fill the chip
   bool q_split;            // forward and dQ (bf16): the form for launches of a few rounds of blocks
+  bool tiny;               // fp32: blocks of four waves, for launches of at most one block per CU
 };
 // What a call covers: `rows` query rows and the `keys` they see (both the tokens of
 // the tree for a whole-tree call).

@@ -593,12 +593,19 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
     // Eight waves of 16 rows: R row tiles (hb q heads x 16-row blocks) x `split`
     // groups that share out the streamed keys.  A launch of fewer than 2048 waves
     // of 16 rows leaves half of the chip's wave slots empty: there the walks are
-    // split instead.
-    const bool small = call.rows / 16 * p->n_q_heads < 2048;
+    // split instead.  Where even blocks of four waves are no more than the CUs, a
+    // block is four: one wave per SIMD.  Measured on MI355X, backward, four / eight waves,
+    // in us: 256 row tiles of 16, head_dim 128, 32/8 heads 35 / 53, 16/16 34 / 51; 512: 43 / 56,
+    // 56 / 63; head_dim 64, 8/2 heads, 256: 32 / 37.  Above, a CU gets two such blocks one after
+    // the other: 16/16 heads of 64, 256 row and 256 key blocks in one launch, 29 / 23.
+    const int64_t row_tiles = call.rows / 16 * p->n_q_heads;
+    const bool small = row_tiles < 2048;
     out->q_small = out->k_small = small;
     out->q_split = false;
     const int split = !small ? 1 : p->head_dim == 64 ? 4 : 2;
-    const int R = 8 / split;
+    const int64_t row_blocks = row_tiles * split / 4, key_blocks = call.keys / 16 * p->n_kv_heads * split / 4;
+    out->tiny = small && row_blocks <= kNumCUs && (p->head_dim == 128 || row_blocks + key_blocks <= kNumCUs * 4 / 3);
+    const int R = (out->tiny ? 4 : 8) / split;
     int hb = 1;
     while (hb < R && G % (2 * hb) == 0) hb *= 2;
     out->hb = hb;
@@ -610,6 +617,7 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
   } else {
     // eight waves per block: hb q heads of the group x (R/hb) 32-row query blocks
     choose_forms(call, p, out);
+    out->tiny = false;
     const int R = out->q_small ? 2 : out->q_split ? 4 : 8;
     out->hb = 1;
     while (out->hb < R && G % (2 * out->hb) == 0) out->hb *= 2;

@@ -21,8 +21,9 @@ pytestmark = pytest.mark.gpu
     (32, 8, [517, 33, 64, 1, 129, 300, 31]),      # large launch, 4 heads x 2 row blocks of 16
     (32, 2, [600, 15, 257, 96, 65]),              # 16 heads in 2 head blocks, 16-token tiles
     (36, 12, [700, 47, 200, 1]),                  # group of 3: one head per block, 128-token tiles
-    (4, 2, [17, 1, 15, 16]),                      # small launch, walks shorter than one wave group's rows
-    (8, 1, [127, 128, 129, 33]),                  # small launch, edges of the 128-row chunk
+    (4, 2, [17, 1, 15, 16]),                      # four-wave blocks, walks shorter than one wave group's rows
+    (8, 1, [127, 128, 129, 33]),                  # four-wave blocks, edges of the 128-row chunk
+    (16, 2, [300, 127, 128, 129, 33]),            # small launch in blocks of eight waves
 ])
 def test_tiles_against_the_oracle(Hq, Hkv, seg, d):
     parent = np.array([-1] + [0] * (len(seg) - 1), dtype=np.int32)
@@ -31,7 +32,8 @@ def test_tiles_against_the_oracle(Hq, Hkv, seg, d):
     tree = dta.tree_build(parent, seg)
     tile = tree.schedule_info(dta.AttnParams(Hq, Hkv, d, scale, dta.F32))["bwd_kv_tile_tokens"]
     tree.destroy()
-    assert tile == (64 if Hq > 8 or d == 128 else 32), tile   # which form the launch takes
+    # which form the launch takes: blocks that fill the chip, eight-wave and four-wave blocks of a small launch
+    assert tile == (64 if Hq > 16 else (32 if d == 64 else 64) // (1 if Hq > 8 else 2)), tile
     x = make_inputs_numpy(T, Hq, Hkv, d, 17, dtype="f32")
     got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32")
     O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
