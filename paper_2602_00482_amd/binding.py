@@ -214,13 +214,14 @@ def workspace_bytes(tree: Tree, params: AttnParams, is_bwd: bool) -> int:
     return int(load_library().dta_tree_attn_workspace_bytes(tree.handle, C.byref(params), int(is_bwd)))
 
 
+# (plain ints: the argtypes above turn them into pointers; a c_void_p object each would cost as much again)
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check_tree_tokens(tree, q):
@@ -240,8 +241,14 @@ def _check_workspace(workspace):
 def _check_tensor(t, name, shape, dtype):
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous CUDA tensor")
-    if tuple(t.shape) != tuple(shape) or t.dtype != dtype:
+    if t.shape != shape or t.dtype != dtype:
         raise ValueError(f"{name}: expected {tuple(shape)} {dtype}, got {tuple(t.shape)} {t.dtype}")
+
+
+def _shapes(T, params):
+    """(q heads, shape of q-like tensors, shape of k-like tensors) of T tokens."""
+    Hq, d = params.n_q_heads, params.head_dim
+    return Hq, (T, Hq, d), (T, params.n_kv_heads, d)
 
 
 def tree_attn_fwd(tree: Tree, params: AttnParams, q, k, v, o=None, lse=None, workspace=None):
@@ -250,21 +257,26 @@ def tree_attn_fwd(tree: Tree, params: AttnParams, q, k, v, o=None, lse=None, wor
     dt = torch.float32 if params.dtype == F32 else torch.bfloat16
     _check_tree_tokens(tree, q)
     T = q.shape[0]
-    _check_tensor(q, "q", (T, params.n_q_heads, params.head_dim), dt)
-    _check_tensor(k, "k", (T, params.n_kv_heads, params.head_dim), dt)
-    _check_tensor(v, "v", (T, params.n_kv_heads, params.head_dim), dt)
+    Hq, q_shape, kv_shape = _shapes(T, params)
+    _check_tensor(q, "q", q_shape, dt)
+    _check_tensor(k, "k", kv_shape, dt)
+    _check_tensor(v, "v", kv_shape, dt)
     if o is None:
         o = torch.empty_like(q)
+    else:
+        _check_tensor(o, "o", q_shape, dt)
     if lse is None:
-        lse = torch.empty((T, params.n_q_heads), dtype=torch.float32, device=q.device)
-    _check_tensor(o, "o", q.shape, dt)
-    _check_tensor(lse, "lse", (T, params.n_q_heads), torch.float32)
+        lse = q.new_empty((T, Hq), dtype=torch.float32)
+    else:
+        _check_tensor(lse, "lse", (T, Hq), torch.float32)
     if workspace is None:
         need = workspace_bytes(tree, params, False)
         if need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    _check_workspace(workspace)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+            workspace = q.new_empty(need, dtype=torch.uint8)
+        ws_bytes = need
+    else:
+        _check_workspace(workspace)
+        ws_bytes = workspace.numel() * workspace.element_size()
     st = load_library().dta_tree_attn_fwd(tree.handle, C.byref(params), _ptr(q), _ptr(k), _ptr(v),
                                           _ptr(o), _ptr(lse), _ptr(workspace), ws_bytes, _stream())
     _check(st, "dta_tree_attn_fwd")
@@ -282,23 +294,31 @@ def tree_attn_bwd(tree: Tree, params: AttnParams, q, k, v, o, lse, d_o, dq=None,
     dt = torch.float32 if params.dtype == F32 else torch.bfloat16
     _check_tree_tokens(tree, q)
     T = q.shape[0]
-    _check_tensor(q, "q", (T, params.n_q_heads, params.head_dim), dt)
-    _check_tensor(k, "k", (T, params.n_kv_heads, params.head_dim), dt)
-    _check_tensor(v, "v", (T, params.n_kv_heads, params.head_dim), dt)
-    _check_tensor(o, "o", q.shape, dt)
-    _check_tensor(d_o, "d_o", q.shape, dt)
-    _check_tensor(lse, "lse", (T, params.n_q_heads), torch.float32)
-    dq = torch.empty_like(q) if dq is None else dq
-    dk = torch.empty_like(k) if dk is None else dk
-    dv = torch.empty_like(v) if dv is None else dv
-    _check_tensor(dq, "dq", q.shape, dt)
-    _check_tensor(dk, "dk", k.shape, dt)
-    _check_tensor(dv, "dv", v.shape, dt)
+    Hq, q_shape, kv_shape = _shapes(T, params)
+    _check_tensor(q, "q", q_shape, dt)
+    _check_tensor(k, "k", kv_shape, dt)
+    _check_tensor(v, "v", kv_shape, dt)
+    _check_tensor(o, "o", q_shape, dt)
+    _check_tensor(d_o, "d_o", q_shape, dt)
+    _check_tensor(lse, "lse", (T, Hq), torch.float32)
+    if dq is None:
+        dq = torch.empty_like(q)
+    else:
+        _check_tensor(dq, "dq", q_shape, dt)
+    if dk is None:
+        dk = torch.empty_like(k)
+    else:
+        _check_tensor(dk, "dk", kv_shape, dt)
+    if dv is None:
+        dv = torch.empty_like(v)
+    else:
+        _check_tensor(dv, "dv", kv_shape, dt)
     if workspace is None:
-        need = workspace_bytes(tree, params, True)
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
-    _check_workspace(workspace)
-    ws_bytes = workspace.numel() * workspace.element_size()
+        ws_bytes = max(workspace_bytes(tree, params, True), 256)
+        workspace = q.new_empty(ws_bytes, dtype=torch.uint8)
+    else:
+        _check_workspace(workspace)
+        ws_bytes = workspace.numel() * workspace.element_size()
     lib = load_library()
     args = (tree.handle, C.byref(params), _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(d_o),
             _ptr(dq), _ptr(dk), _ptr(dv), _ptr(workspace), ws_bytes, _stream())
@@ -336,14 +356,15 @@ def tree_attn_fwd_segment(tree: Tree, params: AttnParams, t_begin: int, t_end: i
     dt = torch.float32 if params.dtype == F32 else torch.bfloat16
     _check_tree_tokens(tree, q)
     T = q.shape[0]
-    _check_tensor(q, "q", (T, params.n_q_heads, params.head_dim), dt)
-    _check_tensor(k, "k", (T, params.n_kv_heads, params.head_dim), dt)
-    _check_tensor(v, "v", (T, params.n_kv_heads, params.head_dim), dt)
-    _check_tensor(o, "o", q.shape, dt)
-    _check_tensor(lse, "lse", (T, params.n_q_heads), torch.float32)
+    Hq, q_shape, kv_shape = _shapes(T, params)
+    _check_tensor(q, "q", q_shape, dt)
+    _check_tensor(k, "k", kv_shape, dt)
+    _check_tensor(v, "v", kv_shape, dt)
+    _check_tensor(o, "o", q_shape, dt)
+    _check_tensor(lse, "lse", (T, Hq), torch.float32)
     st = load_library().dta_tree_attn_fwd_segment(tree.handle, C.byref(params), int(t_begin), int(t_end),
                                                   _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
-                                                  C.c_void_p(0), 0, _stream())
+                                                  None, 0, _stream())
     _check(st, "dta_tree_attn_fwd_segment")
 
 
@@ -355,15 +376,16 @@ def tree_attn_bwd_segment(tree: Tree, params: AttnParams, t_begin: int, t_end: i
     dt = torch.float32 if params.dtype == F32 else torch.bfloat16
     _check_tree_tokens(tree, q)
     T = q.shape[0]
-    _check_tensor(q, "q", (T, params.n_q_heads, params.head_dim), dt)
-    _check_tensor(k, "k", (T, params.n_kv_heads, params.head_dim), dt)
-    _check_tensor(v, "v", (T, params.n_kv_heads, params.head_dim), dt)
-    _check_tensor(o, "o", q.shape, dt)
-    _check_tensor(d_o, "d_o", q.shape, dt)
-    _check_tensor(lse, "lse", (T, params.n_q_heads), torch.float32)
-    _check_tensor(dq, "dq", q.shape, dt)
-    _check_tensor(dk_acc, "dk_acc", k.shape, torch.float32)
-    _check_tensor(dv_acc, "dv_acc", v.shape, torch.float32)
+    Hq, q_shape, kv_shape = _shapes(T, params)
+    _check_tensor(q, "q", q_shape, dt)
+    _check_tensor(k, "k", kv_shape, dt)
+    _check_tensor(v, "v", kv_shape, dt)
+    _check_tensor(o, "o", q_shape, dt)
+    _check_tensor(d_o, "d_o", q_shape, dt)
+    _check_tensor(lse, "lse", (T, Hq), torch.float32)
+    _check_tensor(dq, "dq", q_shape, dt)
+    _check_tensor(dk_acc, "dk_acc", kv_shape, torch.float32)
+    _check_tensor(dv_acc, "dv_acc", kv_shape, torch.float32)
     _check_workspace(workspace)
     ws_bytes = workspace.numel() * workspace.element_size()
     st = load_library().dta_tree_attn_bwd_segment(tree.handle, C.byref(params), int(t_begin), int(t_end),
