@@ -297,11 +297,21 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
   return DTA_OK;
 }
 
-// After a launch on `stream` that reads the tree's device copies.
-int mark_use(dta_tree* tree, void* stream, int launch_result) {
+// Runs a call's launches, which read the tree's device copies, and has the tree's event
+// complete after them: attached to the last launch where the launcher does that,
+// recorded otherwise (always while the stream is being captured: there the event has to
+// become part of the graph).
+int launch_and_mark(dta_tree* tree, dta::LaunchArgs& a, int (*launcher)(const dta::LaunchArgs&)) {
+  void* const stream = a.stream;
+  hipStreamCaptureStatus capture;
+  bool recorded = false;
+  if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) (void)hipGetLastError();
+  else if (capture == hipStreamCaptureStatusNone) a.done_event = tree->last_use;
+  a.done_recorded = &recorded;
+  const int launch_result = launcher(a);
   if (launch_result != DTA_OK) return launch_result;
   std::lock_guard<std::mutex> lock(tree->mu);
-  if (hipEventRecord((hipEvent_t)tree->last_use, (hipStream_t)stream) != hipSuccess) {
+  if (!recorded && hipEventRecord((hipEvent_t)tree->last_use, (hipStream_t)stream) != hipSuccess) {
     (void)hipGetLastError();
     return DTA_ERR_HIP;
   }
@@ -402,8 +412,7 @@ int dta_tree_attn_fwd(dta_tree_t* tree, const dta_attn_params_t* params, const v
   a.row_begin = 0;
   a.row_end = tree->info.n_tokens;
   a.stream = hip_stream;
-  return mark_use(tree, hip_stream,
-                  params->dtype == DTA_F32 ? dta::launch_fwd_f32(a) : dta::launch_fwd_bf16(a));
+  return launch_and_mark(tree, a, params->dtype == DTA_F32 ? dta::launch_fwd_f32 : dta::launch_fwd_bf16);
 }
 
 int dta_tree_attn_bwd_stages(dta_tree_t* tree, const dta_attn_params_t* params, const void* q,
@@ -463,8 +472,7 @@ int bwd_entry(dta_tree* tree, const dta_attn_params_t* params, const void* q, co
   a.row_begin = 0;
   a.row_end = tree->info.n_tokens;
   a.stream = hip_stream;
-  return mark_use(tree, hip_stream,
-                  params->dtype == DTA_F32 ? dta::launch_bwd_f32(a) : dta::launch_bwd_bf16(a));
+  return launch_and_mark(tree, a, params->dtype == DTA_F32 ? dta::launch_bwd_f32 : dta::launch_bwd_bf16);
 }
 
 }  // namespace dta
@@ -528,8 +536,7 @@ int dta_tree_attn_fwd_segment(dta_tree_t* tree, const dta_attn_params_t* params,
   a.row_begin = t_begin;
   a.row_end = t_end;
   a.stream = hip_stream;
-  return mark_use(tree, hip_stream,
-                  params->dtype == DTA_F32 ? dta::launch_fwd_f32(a) : dta::launch_fwd_bf16(a));
+  return launch_and_mark(tree, a, params->dtype == DTA_F32 ? dta::launch_fwd_f32 : dta::launch_fwd_bf16);
 }
 
 int dta_tree_attn_bwd_segment(dta_tree_t* tree, const dta_attn_params_t* params, int64_t t_begin,
@@ -572,8 +579,7 @@ int dta_tree_attn_bwd_segment(dta_tree_t* tree, const dta_attn_params_t* params,
   a.row_begin = t_begin;
   a.row_end = t_end;
   a.stream = hip_stream;
-  return mark_use(tree, hip_stream,
-                  params->dtype == DTA_F32 ? dta::launch_bwd_f32(a) : dta::launch_bwd_bf16(a));
+  return launch_and_mark(tree, a, params->dtype == DTA_F32 ? dta::launch_bwd_f32 : dta::launch_bwd_bf16);
 }
 
 }  // extern "C"

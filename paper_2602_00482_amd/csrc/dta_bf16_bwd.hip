@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "dta_internal.h"
+#include "dta_launch.h"
 #include "dta_mfma.h"
 #include "dta_queue.h"
 #include "dta_tile_walk.h"
@@ -795,7 +796,7 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
       if (ls != DTA_OK) return ls;
     } else {
     auto kernel = wide ? dkdv_bf16_kernel<HD, 8> : dkdv_bf16_kernel<HD, 4>;
-    kernel<<<(unsigned)(queues ? resident : kblocks), wide ? 512 : 256, 0, st>>>(
+    launch(a, a.sched->kv_reduce.empty(), kernel, queues ? resident : kblocks, wide ? 512 : 256,
         a.sched->d_kv_items, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
         (const uint16_t*)a.v, (const uint16_t*)a.d_o, a.lse2, a.delta, (uint16_t*)a.dk,
         (uint16_t*)a.dv, a.partial, a.dk_acc, a.dv_acc, a.p.n_q_heads, a.p.n_kv_heads,
@@ -803,7 +804,7 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
     }
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     if (!a.sched->kv_reduce.empty()) {
-      dkdv_reduce_kernel<HD><<<(unsigned)(a.sched->kv_reduce.size() * a.p.n_kv_heads * 8), 256, 0, st>>>(
+      launch(a, true, dkdv_reduce_kernel<HD>, a.sched->kv_reduce.size() * a.p.n_kv_heads * 8, 256,
           a.sched->d_kv_reduce, a.partial, (uint16_t*)a.dk, (uint16_t*)a.dv, a.p.n_kv_heads,
           a.p.softmax_scale, a.sched->kv_keys);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }

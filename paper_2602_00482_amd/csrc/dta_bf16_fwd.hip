@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dta_internal.h"
+#include "dta_launch.h"
 #include "dta_mfma.h"
 #include "dta_queue.h"
 #include "dta_tile_walk.h"
@@ -334,7 +335,7 @@ int launch_fwd_bf16(const LaunchArgs& a) {
   auto kernel = split ? (a.p.head_dim == 128 ? fwd_bf16_kernel<64, 128, 2> : fwd_bf16_kernel<64, 64, 2>)
                 : a.p.head_dim == 128 ? (wide ? fwd_bf16_kernel<128, 128> : fwd_bf16_kernel<64, 128>)
                                     : (wide ? fwd_bf16_kernel<128, 64> : fwd_bf16_kernel<64, 64>);
-  kernel<<<(unsigned)(queues ? (size_t)kNumCUs : blocks), kThreads, 0, st>>>(
+  launch(a, true, kernel, queues ? (size_t)kNumCUs : blocks, kThreads,
       a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
       (const uint16_t*)a.v, (uint16_t*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
       a.tc.hblocks, a.p.softmax_scale, queues ? a.tickets : nullptr,

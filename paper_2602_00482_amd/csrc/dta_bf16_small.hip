@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dta_internal.h"
+#include "dta_launch.h"
 #include "dta_mfma.h"
 
 namespace dta {
@@ -795,7 +796,7 @@ int launch_fwd_bf16_small(const LaunchArgs& a) {
   const size_t blocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
   if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
   auto kernel = a.p.head_dim == 128 ? fwd_small_kernel<128> : fwd_small_kernel<64>;
-  kernel<<<(unsigned)blocks, kThreads, 0, (hipStream_t)a.stream>>>(
+  launch(a, true, kernel, blocks, kThreads,
       a.sched->d_step_tiles, a.sched->d_steps, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
       (const uint16_t*)a.v, (uint16_t*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
       a.tc.hblocks, a.p.softmax_scale);
@@ -816,7 +817,7 @@ int launch_bwd_bf16_small(const LaunchArgs& a, uint32_t stages, bool fused_delta
                   (uint16_t*)a.dk, (uint16_t*)a.dv, a.partial, a.dk_acc, a.dv_acc, a.p.n_q_heads,
                   a.p.n_kv_heads, a.tc.hb, a.tc.hblocks, a.p.softmax_scale, (int)dkdv};
   auto kernel = a.p.head_dim == 128 ? bwd_small_kernel<128> : bwd_small_kernel<64>;
-  kernel<<<(unsigned)(dq + dkdv), kThreads, 0, (hipStream_t)a.stream>>>(p);
+  launch(a, dkdv != 0 && a.sched->kv_reduce.empty(), kernel, dq + dkdv, kThreads, p);
   return launch_status(__func__);
 }
 

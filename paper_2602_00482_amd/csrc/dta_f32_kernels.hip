@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dta_internal.h"
+#include "dta_launch.h"
 #include "dta_mfma.h"
 #include "dta_tile_walk.h"
 
@@ -726,7 +727,7 @@ int fwd_impl(const LaunchArgs& a) {
   auto kernel = a.tc.tiny      ? fwd_f32_kernel<HD, kSplit, 4>
                 : a.tc.q_small ? fwd_f32_kernel<HD, kSplit, 8>
                                : fwd_f32_kernel<HD, 1, 8>;
-  kernel<<<(unsigned)blocks, a.tc.tiny ? 256 : 512, 0, st>>>(
+  launch(a, true, kernel, blocks, a.tc.tiny ? 256 : 512,
       a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
       (const float*)a.v, (float*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
       a.tc.hblocks, a.p.softmax_scale);
@@ -760,7 +761,7 @@ int bwd_impl(const LaunchArgs& a) {
                      a.p.softmax_scale, (int)kblocks};
   if (one_launch) {
     auto kernel = a.tc.tiny ? bwd_f32_kernel<HD, kSplit, 4> : bwd_f32_kernel<HD, kSplit, 8>;
-    kernel<<<(unsigned)(qblocks + kblocks), a.tc.tiny ? 256 : 512, 0, st>>>(args);
+    launch(a, a.sched->kv_reduce.empty(), kernel, qblocks + kblocks, a.tc.tiny ? 256 : 512, args);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   } else if (a.stages & DTA_BWD_DQ) {
     auto kernel = a.tc.tiny      ? dq_f32_kernel<HD, kSplit, 4>
@@ -774,11 +775,11 @@ int bwd_impl(const LaunchArgs& a) {
       auto kernel = a.tc.tiny      ? dkdv_f32_kernel<HD, kSplit, 4>
                     : a.tc.k_small ? dkdv_f32_kernel<HD, kSplit, 8>
                                    : dkdv_f32_kernel<HD, 1, 4>;
-      kernel<<<(unsigned)kblocks, a.tc.k_small && !a.tc.tiny ? 512 : 256, 0, st>>>(args);
+      launch(a, a.sched->kv_reduce.empty(), kernel, kblocks, a.tc.k_small && !a.tc.tiny ? 512 : 256, args);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     }
     if (!a.sched->kv_reduce.empty()) {
-      dkdv_reduce_f32_kernel<HD><<<(unsigned)(a.sched->kv_reduce.size() * a.p.n_kv_heads * 4), 256, 0, st>>>(
+      launch(a, true, dkdv_reduce_f32_kernel<HD>, a.sched->kv_reduce.size() * a.p.n_kv_heads * 4, 256,
           a.sched->d_kv_reduce, a.partial, (float*)a.dk, (float*)a.dv, a.p.n_kv_heads, a.p.softmax_scale,
           a.sched->kv_keys);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }

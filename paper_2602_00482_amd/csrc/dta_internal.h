@@ -234,6 +234,10 @@ struct LaunchArgs {
   float *dk_acc, *dv_acc;
   uint32_t stages;  // backward stages to launch (DTA_BWD_*)
   void* stream;
+  // event (hipEvent_t) the call's last launch may attach to itself, and whether it has;
+  // null: the entry point records it afterwards
+  void* done_event;
+  bool* done_recorded;
 };
 
 // HIP keeps the last error of earlier, unrelated runtime calls of this thread
