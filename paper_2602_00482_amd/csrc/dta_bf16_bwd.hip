@@ -85,13 +85,8 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
   using TL = TileLayout<HD>;
   constexpr int kTileElems = TL::kTileElems, kHeadDim = HD;
   constexpr int KS = TL::kSteps;   // products per phase: k-steps over head_dim = 2 x output blocks
-  struct Tiles {
-    uint16_t K[2][kGroups][kTileElems];
-    uint16_t V[2][kGroups][kTileElems];
-  };
-  __shared__ __attribute__((aligned(1024))) Tiles sm;
-  auto& Ks = sm.K;
-  auto& Vs = sm.V;
+  __shared__ __attribute__((aligned(1024))) uint16_t Ks[2][kGroups][kTileElems];
+  __shared__ __attribute__((aligned(1024))) uint16_t Vs[2][kGroups][kTileElems];
   __shared__ __attribute__((aligned(16))) int32_t kendS[2][kGroups * kKeyChunk];
   // With head_dim 128 the last two k-steps of this wave's Q and dO operands live in
   // LDS instead of registers (each lane reads back what it wrote): with all 16 in
@@ -215,10 +210,12 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
     for (int gi = 0; gi < kGroups; ++gi) {
       if (n[gi] == 0) continue;
       if (!full[gi] || n[gi] < kKeyChunk) {   // rare: a chunk that needs the visibility mask
-        const int x = threadIdx.x - gi * kKeyChunk;
-        if (x >= 0 && x < kKeyChunk) {   // kendS is indexed by matrix position
+        unsigned tid = threadIdx.x;   // (opaque, so that no address made from it is kept over the loop, in scratch memory)
+        asm volatile("" : "+v"(tid));
+        const unsigned x = tid - gi * kKeyChunk;
+        if (x < kKeyChunk) {   // kendS is indexed by matrix position
           const int row = TL::row_of_pos(x);
-          kendS[b][threadIdx.x] = row >= n[gi] ? 0 : (full[gi] ? 0x7fffffff : kend[c0[gi] + row]);
+          kendS[b][tid] = row >= n[gi] ? 0 : (full[gi] ? 0x7fffffff : kend[c0[gi] + row]);
         }
       }
       tile_async_load<kDqThreads, HD>(Ks[b][gi], kbase + (size_t)c0[gi] * kv_stride, kv_bytes, n[gi]);
@@ -329,8 +326,8 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
 
   constexpr int kOut = TL::kBlocks / kGroups;   // 32-wide output blocks this wave stores, from block kOut * grp
   if constexpr (kGroups == 2) {   // every group hands the other one its half of the blocks
-    f32x4* xs = reinterpret_cast<f32x4*>(&sm);
-    static_assert(sizeof(Tiles) >= 8 * kOut * 4 * 64 * sizeof(f32x4), "room for the exchange");
+    f32x4* xs = reinterpret_cast<f32x4*>(&Ks[0][0][0]);
+    static_assert(sizeof(Ks) >= 8 * kOut * 4 * 64 * sizeof(f32x4), "room for the exchange");
     __syncthreads();   // everyone is done with the tiles
 #pragma unroll
     for (int b = 0; b < kOut; ++b)

@@ -55,13 +55,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   static_assert(kGroups == 1 || kCh == 64, "a group takes one 64-row tile per step");
   constexpr int kSub = kCh / 64, kTileElems = TL::kTileElems, kHeadDim = HD;   // kSub: LDS tiles per group
   constexpr int KS = TL::kSteps, DB = TL::kBlocks;   // k-steps over head_dim, 32-wide output blocks
-  struct Tiles {
-    uint16_t K[2][kGroups * kSub][kTileElems];
-    uint16_t V[2][kGroups * kSub][kTileElems];
-  };
-  __shared__ __attribute__((aligned(1024))) Tiles sm;
-  auto& Ks = sm.K;
-  auto& Vs = sm.V;
+  __shared__ __attribute__((aligned(1024))) uint16_t Ks[2][kGroups * kSub][kTileElems];
+  __shared__ __attribute__((aligned(1024))) uint16_t Vs[2][kGroups * kSub][kTileElems];
   __shared__ __attribute__((aligned(16))) int32_t kendS[2][kGroups * kCh];
   __shared__ int next_item[2];
 
@@ -129,8 +124,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int gi = 0; gi < kGroups; ++gi) {
       if (n[gi] == 0) continue;
       if (!full[gi] || n[gi] < kCh) {   // rare: a chunk that needs the visibility mask
-        const int x = threadIdx.x - gi * kCh;
-        if (x >= 0 && x < kCh) {   // kendS is indexed by matrix position within each 64-key half
+        const unsigned x = threadIdx.x - gi * kCh;
+        if (x < kCh) {   // kendS is indexed by matrix position within each 64-key half
           const int row = 64 * (x >> 6) + TL::row_of_pos(x & 63);
           kendS[b][threadIdx.x] = row >= n[gi] ? 0 : (full[gi] ? 0x7fffffff : kend[c0[gi] + row]);
         }
@@ -252,8 +247,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   if constexpr (kGroups == 2) {
     // common maximum and row sum, then every group hands the other one its half of the output blocks
     __shared__ float mS[8][32], lS[8][32];
-    f32x4* xs = reinterpret_cast<f32x4*>(&sm);
-    static_assert(sizeof(Tiles) >= 8 * kOut * 4 * 64 * sizeof(f32x4), "room for the exchange");
+    f32x4* xs = reinterpret_cast<f32x4*>(&Ks[0][0][0]);
+    static_assert(sizeof(Ks) >= 8 * kOut * 4 * 64 * sizeof(f32x4), "room for the exchange");
     if (hh == 0) {
       mS[w][c] = m;
       lS[w][c] = lt;
