@@ -287,6 +287,7 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
     if ((st = upload_parts(dev, us,
                            {part_of(s->q_tiles, &s->d_q_tiles), part_of(s->segs, &s->d_segs),
                             part_of(s->step_tiles, &s->d_step_tiles), part_of(s->steps, &s->d_steps),
+                            part_of(s->fwd.q_tiles, &s->fwd.d_q_tiles), part_of(s->fwd.segs, &s->fwd.d_segs),
                             part_of(s->kv_items, &s->d_kv_items),
                             part_of(s->kv_reduce, &s->d_kv_reduce)},
                            &s->d_blob, &s->d_blob_cap, t_begin < 0 ? nullptr : tree)) != DTA_OK)
@@ -365,13 +366,11 @@ size_t dta_tree_attn_workspace_bytes(const dta_tree_t* tree, const dta_attn_para
 
 int dta_tree_attn_prepare(dta_tree_t* tree, const dta_attn_params_t* params) {
   if (!tree) return DTA_ERR_INVALID_ARG;
-  for (const bool backward : {false, true}) {
-    dta::TileChoice tc;
-    int st = dta::choose_tiles(params, &tc, dta::whole_tree(tree, backward));
-    if (st != DTA_OK) return st;
-    dta::Schedule* s = nullptr;
-    if ((st = ensure_device(tree, tc, params, &s)) != DTA_OK) return st;
-  }
+  dta::TileChoice tc;   // (the schedule of either direction serves both)
+  int st = dta::choose_tiles(params, &tc, dta::whole_tree(tree, true));
+  if (st != DTA_OK) return st;
+  dta::Schedule* s = nullptr;
+  if ((st = ensure_device(tree, tc, params, &s)) != DTA_OK) return st;
   // set-up for dta_tree_attn_bwd_noalloc: resolve this device's copy of the
   // library-held scratch array now, so that the call itself has nothing left to do
   int dev = -1;

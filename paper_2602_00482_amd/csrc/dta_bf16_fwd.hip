@@ -314,7 +314,8 @@ int launch_fwd_bf16(const LaunchArgs& a) {
   clear_hip_error();
   if (a.tc.q_small) return launch_fwd_bf16_small(a);
   const bool split = a.tc.q_split;
-  const size_t blocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
+  const QueryTiles& qt = a.sched->forward_tiles();
+  const size_t blocks = qt.q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
   if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
   // With a workspace for the counters and enough items, resident blocks draw the
   // items from per-head queues (see dta_queue.h); otherwise one block per item.
@@ -326,15 +327,15 @@ int launch_fwd_bf16(const LaunchArgs& a) {
   // chunk size: 128 keys when padding every key interval to 128 instead of 64 adds
   // at most 6 % to the keys streamed (measured: 5 % faster at +0.5 %, 1.4 % faster
   // at +5.6 %, 2 % slower at +9.6 %)
-  const bool wide = 2 * a.sched->fwd_chunks128 * 100 <= a.sched->fwd_chunks64 * 106;
+  const bool wide = 2 * qt.fwd_chunks128 * 100 <= qt.fwd_chunks64 * 106;
   auto kernel = split ? (a.p.head_dim == 128 ? fwd_bf16_kernel<64, 128, 2> : fwd_bf16_kernel<64, 64, 2>)
                 : a.p.head_dim == 128 ? (wide ? fwd_bf16_kernel<128, 128> : fwd_bf16_kernel<64, 128>)
                                     : (wide ? fwd_bf16_kernel<128, 64> : fwd_bf16_kernel<64, 64>);
   launch(a, true, kernel, queues ? (size_t)kNumCUs : blocks, kThreads,
-      a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
+      qt.d_q_tiles, qt.d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
       (const uint16_t*)a.v, (uint16_t*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
       a.tc.hblocks, a.p.softmax_scale, queues ? a.tickets : nullptr,
-      (int)(a.sched->q_tiles.size() * (size_t)a.tc.hblocks));
+      (int)(qt.q_tiles.size() * (size_t)a.tc.hblocks));
   return launch_status(__func__);
 }
 

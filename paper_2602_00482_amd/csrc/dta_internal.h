@@ -86,17 +86,32 @@ struct KvReduce {
   int32_t first_slot, nparts;
 };
 
-// Tile schedule for one (BM, BN) choice: host vectors, and device copies made on
-// first use.  Work items are stored longest first so that the hardware block
-// dispatcher, which hands out blocks in index order, balances the CUs.
-struct Schedule {
-  int bm = 0, bn = 0;
-  int q_rows = 64;   // query rows per iteration of a dK/dV walk
-  int kv_keys = 0;   // keys per dK/dV tile in this schedule: bn, or 2*bn where the walks are long
+// The query tiles of a schedule, longest walk first.
+struct QueryTiles {
   std::vector<QTile> q_tiles;
   std::vector<KeySeg> segs;
   std::vector<StepTile> step_tiles;   // the query tiles as steps (KvWalk::key_steps)
   std::vector<KeyStep> steps;
+  int64_t fwd_tile_pairs = 0;
+  // chunks the query tiles stream when every key interval is cut into pieces of 64 / 128 keys
+  int64_t fwd_chunks64 = 0, fwd_chunks128 = 0;
+  // device copies, in the schedule's allocation
+  QTile* d_q_tiles = nullptr;
+  KeySeg* d_segs = nullptr;
+  StepTile* d_step_tiles = nullptr;
+  KeyStep* d_steps = nullptr;
+};
+// Tile schedule for one (BM, BN) choice: host vectors, and device copies made on
+// first use.  Work items are stored longest first so that the hardware block
+// dispatcher, which hands out blocks in index order, balances the CUs.
+// One schedule serves both directions of a head configuration: the first call of either
+// makes everything the other one needs resident.  Its own query tiles are dQ's, and the
+// forward's too unless that takes another tile size (`fwd`).
+struct Schedule : QueryTiles {
+  int bm = 0, bn = 0;
+  int q_rows = 64;   // query rows per iteration of a dK/dV walk
+  int kv_keys = 0;   // keys per dK/dV tile in this schedule: bn, or 2*bn where the walks are long
+  QueryTiles fwd;    // the forward's query tiles where they are not dQ's (KvWalk::fwd_bm)
   std::vector<KvTile> kv_tiles;
   int hkv = 0, group = 0;          // head configuration the item split was made for
   std::vector<KvItem> kv_items;
@@ -104,21 +119,17 @@ struct Schedule {
   int64_t n_slots = 0;
   int64_t kv_item_iters = 0;       // sum over kv_items of (it_end - it_begin)
   bool kv_queues = false;          // the dK/dV launch runs as resident blocks drawing items from queues
-  int64_t fwd_tile_pairs = 0, bwd_tile_pairs = 0;
-  // chunks the query tiles stream when every key interval is cut into pieces of 64 / 128 keys
-  int64_t fwd_chunks64 = 0, fwd_chunks128 = 0;
+  int64_t bwd_tile_pairs = 0;
   // device copies: one allocation (d_blob, owned, released with the tree) that
   // the typed pointers below point into
   uint64_t last_used = 0;   // segment schedules: the tree's use counter at the latest call
   int device = -1;
   void* d_blob = nullptr;
   size_t d_blob_cap = 0;
-  QTile* d_q_tiles = nullptr;
-  KeySeg* d_segs = nullptr;
-  StepTile* d_step_tiles = nullptr;
-  KeyStep* d_steps = nullptr;
   KvItem* d_kv_items = nullptr;
   KvReduce* d_kv_reduce = nullptr;
+
+  const QueryTiles& forward_tiles() const { return fwd.q_tiles.empty() ? *this : fwd; }
 };
 
 }  // namespace dta
@@ -166,18 +177,20 @@ constexpr int kNumCUs = 256;
 constexpr bool wide_key_tiles = true;
 
 // How the kernels walk, as far as the schedule has to know: the dK/dV kernel its query
-// rows, and whether the query tiles are wanted as steps.
+// rows, whether the query tiles are wanted as steps, and what tiles the forward wants.
 struct KvWalk {
   int q_rows = 64;          // rows per iteration of the walk: 32 or 64
   int min_piece = 32;       // shortest piece of a cut walk in iterations, a multiple of 4, at most 60
   int resident = 512;       // blocks of the kernel that the chip holds
-  bool key_steps = false;   // query tiles as StepTile / KeyStep instead of QTile / KeySeg
+  bool key_steps = false;   // query tiles as StepTile / KeyStep beside QTile / KeySeg
+  int fwd_bm = 0;           // query tokens per forward tile; 0: dQ's tiles
 };
 
 // Key of a whole-tree schedule in dta_tree::schedules.
 inline uint64_t schedule_key(int bm, int bn, int hkv, int group, const KvWalk& kw) {
-  return ((uint64_t)(kw.min_piece / 4) << 60) | ((uint64_t)bm << 48) | ((uint64_t)kw.key_steps << 46) |
-         ((uint64_t)(kw.q_rows / 32) << 44) |
+  // (query tiles are 16 to 256 tokens, multiples of 16)
+  return ((uint64_t)(kw.min_piece / 4) << 60) | ((uint64_t)(kw.fwd_bm / 16) << 54) | ((uint64_t)(bm / 16) << 48) |
+         ((uint64_t)kw.key_steps << 46) | ((uint64_t)(kw.q_rows / 32) << 44) |
          ((uint64_t)bn << 32) | ((uint64_t)hkv << 16) | (uint64_t)group;
 }
 // Host: build (or fetch) the schedule for tile sizes (bm, bn).
@@ -192,9 +205,9 @@ size_t partial_bytes(const Schedule& s);
 
 // Tile sizes the kernels use for a head configuration.
 struct TileChoice {
-  int bm;       // query tokens per forward / dQ work item
-  int bn;       // keys per dK/dV work item; 0: a forward call whose schedule needs no dK/dV part
-  int hb;       // q heads of one kv group handled by one forward block
+  int bm;       // query tokens per dQ work item, and per forward one unless walk.fwd_bm is set
+  int bn;       // keys per dK/dV work item
+  int hb;       // q heads of one kv group handled by one forward (backward call: dQ) block
   int hblocks;  // blocks per (tile, kv head) = group size / hb
   KvWalk walk;
   bool q_small, k_small;   // forward and dQ, dK/dV: the form for launches too small to fill the chip

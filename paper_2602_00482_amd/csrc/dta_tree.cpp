@@ -162,7 +162,7 @@ int64_t order_key(int64_t cost) {
 // mask with kend[] wherever a key interval is not visible to every row.
 namespace {
 // adds the chunks a query tile streams, for both chunk sizes of the forward kernel
-void count_chunks(Schedule& s, const QTile& qt) {
+void count_chunks(QueryTiles& s, const QTile& qt) {
   auto add = [&](int64_t len) {
     s.fwd_chunks64 += (len + 63) / 64;
     s.fwd_chunks128 += (len + 127) / 128;
@@ -174,7 +174,7 @@ void count_chunks(Schedule& s, const QTile& qt) {
 
 namespace {
 // copies each tile's first key interval into its record
-void fill_first_intervals(Schedule& s) {
+void fill_first_intervals(QueryTiles& s) {
   for (QTile& t : s.q_tiles)
     t.first = t.seg_begin < t.seg_end ? s.segs[(size_t)t.seg_begin] : KeySeg{t.t0, t.t0, 0, 0};
 }
@@ -183,8 +183,8 @@ void fill_first_intervals(Schedule& s) {
 namespace {
 // Cuts the walks of the query tiles into steps (KeyStep).  A step ends early when its
 // pieces would lie further apart than the kernels' 32-bit offsets reach.
-void cut_steps(Schedule& s) {
-  const int64_t reach = (int64_t)0xffffffff / ((int64_t)s.hkv * 256) - 32;   // keys; a K/V row is at most 256 bytes per head
+void cut_steps(QueryTiles& s, int hkv) {
+  const int64_t reach = (int64_t)0xffffffff / ((int64_t)hkv * 256) - 32;   // keys; a K/V row is at most 256 bytes per head
   for (const QTile& t : s.q_tiles) {
     StepTile st{};
     st.t0 = t.t0;
@@ -226,23 +226,11 @@ size_t partial_bytes(const Schedule& s) {
   return (size_t)s.n_slots * (size_t)s.hkv * 2u * (size_t)s.kv_keys * 128u * sizeof(float);
 }
 
-Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const KvWalk& kw) {
-  const uint64_t key = schedule_key(bm, bn, hkv, group, kw);
-  const int q_rows = kw.q_rows;
-  auto it = tree->schedules.find(key);
-  if (it != tree->schedules.end()) return it->second;
-  // built aside and moved into the map when complete: an allocation failure half
-  // way must not leave a partial schedule behind that a later call would use
-  Schedule s;
-  s.bm = bm;
-  s.bn = bn;
-  s.q_rows = q_rows;
-  s.hkv = hkv;
-  s.group = group;
+namespace {
+// query tiles of bm tokens over the whole tree
+void cut_query_tiles(const dta_tree* tree, int bm, QueryTiles& s) {
   const int64_t T = tree->info.n_tokens;
   const auto& parent = tree->parent;
-
-  // ---- query tiles (forward and dQ)
   std::vector<int64_t> cost;
   std::vector<int32_t> path;
   for (int64_t t0 = 0; t0 < T; t0 += bm) {
@@ -288,7 +276,29 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const
     s.q_tiles.swap(sorted);
   }
   fill_first_intervals(s);
-  if (kw.key_steps) cut_steps(s);
+}
+}  // namespace
+
+Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const KvWalk& kw) {
+  const uint64_t key = schedule_key(bm, bn, hkv, group, kw);
+  const int q_rows = kw.q_rows;
+  auto it = tree->schedules.find(key);
+  if (it != tree->schedules.end()) return it->second;
+  // built aside and moved into the map when complete: an allocation failure half
+  // way must not leave a partial schedule behind that a later call would use
+  Schedule s;
+  s.bm = bm;
+  s.bn = bn;
+  s.q_rows = q_rows;
+  s.hkv = hkv;
+  s.group = group;
+  const int64_t T = tree->info.n_tokens;
+  std::vector<int64_t> cost;
+
+  // ---- query tiles (dQ and forward)
+  cut_query_tiles(tree, bm, s);
+  if (kw.key_steps) cut_steps(s, hkv);
+  if (kw.fwd_bm != 0) cut_query_tiles(tree, kw.fwd_bm, s.fwd);
 
   // ---- key tiles (dK/dV): runs of at most bn consecutive packed keys.  A block
   // walks the union of the query ranges of its keys, [k0, max kend), so a run that
@@ -361,7 +371,6 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const
     if (q_rows == 32) cut_key_tiles_at(keys, std::integral_constant<int, 32>{});
     else cut_key_tiles_at(keys, std::integral_constant<int, 64>{});
   };
-  if (bn == 0) return tree->schedules.emplace(key, std::move(s)).first->second;   // query tiles only
   cut_key_tiles(bn);
 
   // ---- dK/dV launch items: cut the longest walks so that no block becomes the
@@ -486,25 +495,29 @@ Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int grou
   for (const KeySeg& ks : prefix) prefix_keys += ks.end - ks.start;
 
   // ---- query tiles over the rows; a tile also sees the rows before it
-  for (int64_t t0 = t_begin; t0 < t_end; t0 += bm) {
-    const int64_t t1 = std::min<int64_t>(t_end, t0 + bm);
-    QTile qt;
-    qt.t0 = (int32_t)t0;
-    qt.t1 = (int32_t)t1;
-    qt.seg_begin = (int32_t)s.segs.size();
-    for (const KeySeg& ks : prefix) s.segs.push_back(ks);
-    if (t0 > t_begin) {
-      if (!prefix.empty() && s.segs.back().end == t_begin) s.segs.back().end = (int32_t)t0;
-      else s.segs.push_back(KeySeg{(int32_t)t_begin, (int32_t)t0, 1, 0});
+  auto cut_rows = [&](int tokens, QueryTiles& qs) {
+    for (int64_t t0 = t_begin; t0 < t_end; t0 += tokens) {
+      const int64_t t1 = std::min<int64_t>(t_end, t0 + tokens);
+      QTile qt;
+      qt.t0 = (int32_t)t0;
+      qt.t1 = (int32_t)t1;
+      qt.seg_begin = (int32_t)qs.segs.size();
+      for (const KeySeg& ks : prefix) qs.segs.push_back(ks);
+      if (t0 > t_begin) {
+        if (!prefix.empty() && qs.segs.back().end == t_begin) qs.segs.back().end = (int32_t)t0;
+        else qs.segs.push_back(KeySeg{(int32_t)t_begin, (int32_t)t0, 1, 0});
+      }
+      qt.seg_end = (int32_t)qs.segs.size();
+      qs.q_tiles.push_back(qt);
+      qs.fwd_tile_pairs += (prefix_keys + (t1 - t_begin)) * tokens;
+      count_chunks(qs, qt);
     }
-    qt.seg_end = (int32_t)s.segs.size();
-    s.q_tiles.push_back(qt);
-    s.fwd_tile_pairs += (prefix_keys + (t1 - t_begin)) * bm;
-    count_chunks(s, qt);
-  }
-  std::reverse(s.q_tiles.begin(), s.q_tiles.end());   // the last tile sees the most keys
-  fill_first_intervals(s);
-  if (kw.key_steps) cut_steps(s);
+    std::reverse(qs.q_tiles.begin(), qs.q_tiles.end());   // the last tile sees the most keys
+    fill_first_intervals(qs);
+  };
+  cut_rows(bm, s);
+  if (kw.key_steps) cut_steps(s, hkv);
+  if (kw.fwd_bm != 0) cut_rows(kw.fwd_bm, s.fwd);
 
   // ---- key tiles: the prefix pieces (walk = all rows, no mask beyond padding),
   // then the rows themselves (causal)
@@ -517,10 +530,8 @@ Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int grou
       s.bwd_tile_pairs += (t_end - qb) * bn;
     }
   };
-  if (bn != 0) {   // 0: query tiles only
-    add_tiles(t_begin, t_end, true);
-    for (const KeySeg& ks : prefix) add_tiles(ks.start, ks.end, false);
-  }
+  add_tiles(t_begin, t_end, true);
+  for (const KeySeg& ks : prefix) add_tiles(ks.start, ks.end, false);
   for (const KvTile& t : s.kv_tiles) {
     const int64_t iters = (int64_t)((t.q_end - t.q_begin + q_rows - 1) / q_rows) * group;
     s.kv_items.push_back(KvItem{t.k0, t.k1, t.q_end, t.q_full_end, 0, (int32_t)iters, -1, t.q_begin});
@@ -624,28 +635,28 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
     out->walk = KvWalk{32, 4 * split, small ? kNumCUs : 2 * kNumCUs};
   } else {
     // eight waves per block: hb q heads of the group x (R/hb) 32-row query blocks
-    choose_forms(call, p, out);
-    out->tiny = false;
-    const int R = out->q_small ? 2 : out->q_split ? 4 : 8;
-    out->hb = 1;
-    while (out->hb < R && G % (2 * out->hb) == 0) out->hb *= 2;
-    out->bm = 32 * (R / out->hb);
-    out->hblocks = G / out->hb;
-    out->bn = out->k_small ? 64 : 128;
-    out->walk = out->k_small ? KvWalk{32, 32, kNumCUs} : KvWalk{64, 32, 2 * kNumCUs};
-    out->walk.key_steps = out->q_small;
-    if (!call.backward) {
-      // the backward's schedule serves if its query tiles are the same; otherwise a schedule of query tiles only
-      CallShape bwd = call;
-      bwd.backward = true;
-      TileChoice b;
-      choose_tiles(p, &b, bwd);
-      out->k_small = b.k_small;
-      const bool same = b.bm == out->bm && b.q_small == out->q_small;
-      out->bn = same ? b.bn : 0;
-      out->walk = same ? b.walk : KvWalk();
-      out->walk.key_steps = out->q_small;
-    }
+    TileChoice f{}, b{};
+    auto choose = [&](bool backward, TileChoice* t) {
+      CallShape c = call;
+      c.backward = backward;
+      choose_forms(c, p, t);
+      const int R = t->q_small ? 2 : t->q_split ? 4 : 8;
+      t->hb = 1;
+      while (t->hb < R && G % (2 * t->hb) == 0) t->hb *= 2;
+      t->hblocks = G / t->hb;
+      return 32 * (R / t->hb);
+    };
+    const int fwd_bm = choose(false, &f);
+    b.bm = choose(true, &b);
+    b.bn = b.k_small ? 64 : 128;
+    b.walk = b.k_small ? KvWalk{32, 32, kNumCUs} : KvWalk{64, 32, 2 * kNumCUs};
+    // (a launch small enough for the forward's steps is small for dQ too, and then the tiles are the same)
+    b.walk.key_steps = b.q_small;
+    b.walk.fwd_bm = fwd_bm == b.bm ? 0 : fwd_bm;
+    f.bm = b.bm;
+    f.bn = b.bn;
+    f.walk = b.walk;
+    *out = call.backward ? b : f;
   }
   return DTA_OK;
 }
@@ -694,31 +705,29 @@ int dta_tree_layout(const dta_tree_t* tree, dta_tree_layout_t* out) {
 }
 
 static size_t schedule_bytes(const dta::Schedule& s) {
-  return s.q_tiles.size() * sizeof(dta::QTile) + s.segs.size() * sizeof(dta::KeySeg) +
-         s.step_tiles.size() * sizeof(dta::StepTile) + s.steps.size() * sizeof(dta::KeyStep) +
+  return (s.q_tiles.size() + s.fwd.q_tiles.size()) * sizeof(dta::QTile) +
+         (s.segs.size() + s.fwd.segs.size()) * sizeof(dta::KeySeg) + s.step_tiles.size() * sizeof(dta::StepTile) + s.steps.size() * sizeof(dta::KeyStep) +
          s.kv_items.size() * sizeof(dta::KvItem) + s.kv_reduce.size() * sizeof(dta::KvReduce);
 }
 
 int dta_tree_schedule_info(dta_tree_t* tree, const dta_attn_params_t* params,
                            dta_schedule_info_t* out) {
   if (!tree || !out) return DTA_ERR_INVALID_ARG;
-  dta::TileChoice tf, tb;
-  int st = dta::choose_tiles(params, &tf, dta::whole_tree(tree, false));
+  dta::TileChoice tc;
+  int st = dta::choose_tiles(params, &tc, dta::whole_tree(tree, true));
   if (st != DTA_OK) return st;
-  dta::choose_tiles(params, &tb, dta::whole_tree(tree, true));
   try {
     std::lock_guard<std::mutex> lock(tree->mu);
     const int group = params->n_q_heads / params->n_kv_heads;
-    const dta::Schedule& f = dta::get_schedule(tree, tf.bm, tf.bn, params->n_kv_heads, group, tf.walk);
-    const dta::Schedule& b = dta::get_schedule(tree, tb.bm, tb.bn, params->n_kv_heads, group, tb.walk);
-    out->fwd_q_tile_tokens = tf.bm;
+    const dta::Schedule& b = dta::get_schedule(tree, tc.bm, tc.bn, params->n_kv_heads, group, tc.walk);
+    const dta::QueryTiles& f = b.forward_tiles();
+    out->fwd_q_tile_tokens = tc.walk.fwd_bm != 0 ? tc.walk.fwd_bm : tc.bm;
     out->fwd_work_items = (int64_t)f.q_tiles.size();
     out->fwd_tile_pairs = f.fwd_tile_pairs;
     out->bwd_kv_tile_tokens = b.kv_keys;
     out->bwd_work_items = (int64_t)b.kv_items.size();
     out->bwd_tile_pairs = b.bwd_tile_pairs;
-    out->metadata_bytes = (int64_t)(tree->token_kend.size() * sizeof(int32_t) + schedule_bytes(b) +
-                                    (&f == &b ? 0 : schedule_bytes(f)));
+    out->metadata_bytes = (int64_t)(tree->token_kend.size() * sizeof(int32_t) + schedule_bytes(b));
   } catch (const std::bad_alloc&) {
     return DTA_ERR_ALLOC;
   }

@@ -229,3 +229,32 @@ def test_more_segment_ranges_than_the_schedule_cache_holds():
     tree.destroy()
     assert float((lse - lse_ref).abs().max()) <= 1e-5
     assert float((o.double() - o_ref.double()).abs().max() / o_ref.double().abs().max()) <= 1e-2
+
+
+@pytest.mark.parametrize("Hq,Hkv,seg", [
+    (32, 8, [300, 200, 378]),     # forward split, backward small, the same query tiles
+    (8, 8, [1200, 900, 1457]),    # ... on query tiles of 128 and of 64 tokens
+    (8, 8, [1500, 1600, 1300]),   # forward in blocks of eight row tiles
+])
+def test_the_first_call_leaves_nothing_to_allocate_for_the_other_direction(Hq, Hkv, seg):
+    """An eager forward on a tree that was not prepared, then the backward under
+    stream capture, where an upload (its wait for the library's own stream) would be an
+    error; every replay must give the eager backward's bits."""
+    parent = np.array([-1] + [0] * (len(seg) - 1), dtype=np.int32)
+    x, t, tree, p, _ = _setup(parent, np.array(seg, dtype=np.int32), Hq, Hkv, 128, "bf16", seed=31)
+    ws = torch.empty(dta.workspace_bytes(tree, p, True), dtype=torch.uint8, device="cuda")
+    dq, dk, dv = torch.empty_like(t["q"]), torch.empty_like(t["k"]), torch.empty_like(t["v"])
+    o, lse = dta.tree_attn_fwd(tree, p, t["q"], t["k"], t["v"])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dta.tree_attn_bwd(tree, p, t["q"], t["k"], t["v"], o, lse, t["do"], dq, dk, dv, ws)
+    ref = dta.tree_attn_bwd(tree, p, t["q"], t["k"], t["v"], o, lse, t["do"])
+    for _ in range(3):
+        for a in (dq, dk, dv):
+            a.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(ref, (dq, dk, dv)):
+            assert torch.equal(a, b)
+    tree.destroy()
