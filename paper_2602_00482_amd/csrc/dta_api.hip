@@ -498,10 +498,10 @@ static int check_segment(const dta_tree* tree, int64_t t_begin, int64_t t_end) {
 static int segment_tiles(const dta_tree* tree, const dta_attn_params_t* p, int64_t t_begin, int64_t t_end,
                          bool backward, dta::TileChoice* out) {
   const int32_t u = tree->token_node[(size_t)t_begin];
+  const int64_t rows = t_end - t_begin;
+  const int64_t keys = tree->node_start_depth[(size_t)u] + t_end - tree->node_offset[(size_t)u];
   return dta::choose_tiles(
-      p, out,
-      dta::CallShape{backward, true, t_end - t_begin,
-                     tree->node_start_depth[(size_t)u] + t_end - tree->node_offset[(size_t)u]});
+      p, out, dta::CallShape{backward, true, rows, keys, rows * (keys - rows) + rows * (rows + 1) / 2});
 }
 
 int dta_tree_attn_fwd_segment(dta_tree_t* tree, const dta_attn_params_t* params, int64_t t_begin,

@@ -214,16 +214,16 @@ struct TileChoice {
   bool q_split;            // forward and dQ (bf16): the form for launches of a few rounds of blocks
   bool tiny;               // fp32: blocks of four waves, for launches of at most one block per CU
 };
-// What a call covers: `rows` query rows and the `keys` they see (both the tokens of
-// the tree for a whole-tree call).
+// What a call covers: `rows` query rows, the `keys` they see (both the tokens of
+// the tree for a whole-tree call) and the (row, visible key) pairs of one head.
 struct CallShape {
   bool backward = true;
   bool segment = false;
-  int64_t rows = INT32_MAX, keys = INT32_MAX;
+  int64_t rows = INT32_MAX, keys = INT32_MAX, pairs = INT64_MAX;
 };
 int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& call = CallShape());
 inline CallShape whole_tree(const dta_tree* tree, bool backward) {
-  return CallShape{backward, false, tree->info.n_tokens, tree->info.n_tokens};
+  return CallShape{backward, false, tree->info.n_tokens, tree->info.n_tokens, tree->info.unique_pairs};
 }
 int validate_params(const dta_attn_params_t* p);
 

@@ -583,24 +583,57 @@ namespace {
 //   forward of a segment under 1024 keys   500: 29 / 35 / 50; 1000: 58 / 45 / 63;
 //             2000: 124 / 87 / 93 (32/8), 100 / 72 / 71 (64/8), 170 / 123 / 137 (16/16);
 //             2500: 168 / 133 / 117
-//   backward of a tree   1600: 86 / 90 / 92 (32/8), 66 / 70 / 70 (64/8); 2000: 118 / 112 / 121,
-//             171 / 150 / 149 (16/16); 3000: 196 / 185 / 199, 298 / 251 / 272; 3500: 257 / 214 / 222;
-//             dQ alone at 4000: 163 / 133 / 130; head_dim 64, 2000: 80 / 77 / 70, 3500: 166 / 144 / 138
-//   dK/dV of a tree   3072 row tiles, small / large: 180 / 197 at 192 key tiles, 247 / 236 at 256
+//             Above 1024 row tiles the split form has blocks left for a second round, which takes as long as the
+//             first where the rows see mostly what lies before them: 1100, 16/1 heads, 2200 rows after 512 keys
+//             68 / 52 / 74, 2048: 118 / 91 / 108, 8192: 327 / 281 / 245, 16 384: 598 / 532 / 431; 1500, 32/8, 1500 rows
+//             after 512 66 / 50 / 61, 2048: 117 / 98 / 93, 8192: 325 / 288 / 238; 2000, 4/4, 16 000 rows after
+//             8192 753 / 544 / 603, 16 384: 1108 / 809 / 832
+//   backward of a tree (4 row tiles x 2 with the large dK/dV)   1600: 86 / 90 / 92 (32/8), 66 / 70 / 70
+//             (64/8); 2000: 118 / 112 / 121, 171 / 150 / 149 (16/16); 3000: 196 / 185 / 199, 298 / 251 / 272;
+//             3500: 257 / 214 / 222; dQ alone at 4000: 163 / 133 / 130; head_dim 64, 2000: 80 / 77 / 70,
+//             3500: 166 / 144 / 138.  Below 1800 the small form loses where its blocks are many rounds:
+//             with few heads per group, 400 key tiles, a prompt with answers 135 / 126 / 123 (16/16),
+//             195 / 181 / 177 (8/8), short segments 114 / 99 / 99, at 300 key tiles 101 / 130 / 131 and
+//             92 / 94 / 96; and where few heads walk far, 1600, a prompt with answers 605 / 578 / 551 (2/1,
+//             25 600 tokens), one segment 1270 / 1179 / 1406, while 4/1, 12 800 tokens, has 323 / 360 / 342
+//   dK/dV of a tree, small / large   the walks are cut, so few key tiles fill the chip as well if their walks
+//             are long: what decides is the work.  In walk steps of the small form per CU (2^21 pairs each),
+//             1800 row tiles and more: 19 91 / 117 (16/1), 76 / 79 (32/8); 44 142 / 164 (16/1), 135 / 121 (32/8);
+//             69 192 / 212 (16/2), 190 / 190 (64/8); 82 229 / 276 (16/1); 100 295 / 294 (16/1); 125 333 / 332
+//             (32/2); 138 348 / 300 (8/2); 156 418 / 365 (16/2), 410 / 370 (64/8); 313 785 / 655 (32/4);
+//             625 1555 / 1269 (16/1); 1250 3196 / 2648 (32/2); at and above 200 key tiles only the large form is taken
 //   backward of a segment (whose dK/dV walks are never cut)   1600 rows, small / 8 row tiles, under
-//             2048 keys 300 / 335 (32/8) and 570 / 609 (64/8), under 8192 keys 870 / 858 and 1680 / 1657;
-//             2000 row tiles under 1024 keys, 16/16: 418 / 386 / 412; 2500: 623 / 599 / 588
+//             2048 keys 300 / 335 (32/8) and 570 / 609 (64/8); 2000 row tiles under 1024 keys, 16/16:
+//             418 / 386 / 412; 2500: 623 / 599 / 588.  The large dK/dV takes what its longest walk takes, with
+//             one block per CU up to 256 key tiles and two up to 512; the small one takes the sum of its walks.
+//             So the small form wins while many walks are short or many slots empty, and loses where most
+//             rows see a full round of key tiles.  1790 row tiles, 16/1 heads, key tiles seen by the average
+//             row: 86 1226 / 2048 / 2070, 236 3227 / 2843 / 2795, 336 4638 / 4239 / 4132, 436 5993 / 4924 / 4771;
+//             64/8: 217 467 / 574 / 599 (2100 row tiles), 222 411 / 387 / 393, 422 733 / 645 / 645.
+//             Blocks of 4 row tiles are one round up to 1024 row tiles, of 8 up to 2048: 16/1, 450 key tiles,
+//             500 row tiles 1706 / 1759 / 2472, 800: 2953 / 2270 / 2933, 1200: 3860 / 4037 / 3619; 250 key tiles,
+//             2100: 3546 / 3754 / 3956, 2600: 4549 / 4170 / 4425, 3000: 5225 / 4683 / 4755, 3900: 6553 / 6215 / 5975
 void choose_forms(const CallShape& c, const dta_attn_params_t* p, TileChoice* out) {
   const int64_t row_tiles = c.rows / 32 * p->n_q_heads, key_tiles = c.keys / 128 * p->n_kv_heads;
   if (!c.backward) {
     out->q_small = row_tiles <= 512;
-    out->q_split = !out->q_small && row_tiles <= (c.segment ? 2048 : 1024);
+    out->q_split = !out->q_small && (row_tiles <= 1024 || (c.segment && row_tiles <= 2048 && c.keys <= 2 * c.rows));
     out->k_small = false;
     return;
   }
-  out->q_small = row_tiles < 1800 || (c.segment && row_tiles < 4000 && key_tiles < 350);
-  out->q_split = !out->q_small && (c.segment ? row_tiles <= 2048 : row_tiles < 3600 && p->head_dim == 128);
-  out->k_small = out->q_small || (!c.segment && key_tiles < 200);
+  if (c.segment) {
+    const double seen = (double)c.pairs / (double)c.rows * p->n_kv_heads / 128;   // key tiles seen by the average row
+    const bool k_full = seen >= 280 || (key_tiles <= 256 && seen >= 218);   // the large dK/dV fills its rounds
+    const bool q_full = (row_tiles >= 600 && row_tiles < 1800) || row_tiles >= 2900;   // ... and the large or split dQ
+    out->q_small = (row_tiles < 1800 || (row_tiles < 4000 && key_tiles < 350)) && !(k_full && q_full);
+    out->q_split = !out->q_small && (row_tiles <= 1024 || (row_tiles >= 1800 && row_tiles <= 2048));
+    out->k_small = out->q_small;
+    return;
+  }
+  const double work = (double)c.pairs * p->n_q_heads / (1 << 21);   // walk steps of the small dK/dV per CU
+  out->q_small = row_tiles < 1800 && key_tiles < 380 && (row_tiles < 1000 || work <= 128);
+  out->q_split = !out->q_small && row_tiles < (p->head_dim == 128 ? 3600 : 1800);
+  out->k_small = out->q_small || (key_tiles < 200 && work <= 100);
 }
 }  // namespace
 

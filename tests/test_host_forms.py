@@ -1,0 +1,118 @@
+"""Which form of the kernels a call takes (CPU): the rules of dta_tree.cpp at the sizes
+where the forms' measured times cross, through the schedule the library reports and
+through a small driver around choose_tiles for what it does not report."""
+import os
+import shutil
+import subprocess
+import tempfile
+
+import numpy as np
+import pytest
+
+import paper_2602_00482_amd as dta
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2602_00482_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def forms():
+    """forms(calls) -> [(q form, dK/dV form, dQ tile, key tile, forward tile where it differs)]"""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    out = os.path.join(tempfile.mkdtemp(prefix="dta_forms_"), "driver")
+    cmd = [gxx, "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-static-libubsan",
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(ROOT, "tests", "host_forms", "driver.cpp"),
+           os.path.join(CSRC, "dta_tree.cpp"), "-o", out]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+
+    def run(calls):
+        text = "".join(" ".join(str(int(x)) for x in c) + "\n" for c in calls)
+        res = subprocess.run([out], input=text, capture_output=True, text=True, timeout=60)
+        assert res.returncode == 0, res.stderr
+        got = [l.split() for l in res.stdout.splitlines()]
+        assert len(got) == len(calls)
+        return [(q, k, int(bm), int(bn), int(fb)) for q, k, bm, bn, fb in got]
+
+    yield run
+    shutil.rmtree(os.path.dirname(out), ignore_errors=True)
+
+
+def tree_call(parent, seg, Hq, Hkv, d, dtype, backward):
+    tree = dta.tree_build(np.asarray(parent, dtype=np.int32), np.asarray(seg, dtype=np.int32))
+    info = tree.info()
+    tree.destroy()
+    T = info["n_tokens"]
+    return Hq, Hkv, d, dtype, backward, 0, T, T, info["unique_pairs"]
+
+
+def segment_call(Hq, Hkv, d, backward, before, rows):
+    """`rows` rows after `before` tokens of their root path"""
+    return Hq, Hkv, d, dta.BF16, backward, 1, rows, before + rows, before * rows + rows * (rows + 1) // 2
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,tokens,small", [
+    (16, 1, 2560, True), (16, 1, 12800, False), (16, 1, 24000, False),
+    (16, 2, 2560, True), (16, 2, 9600, False), (32, 2, 6400, False), (64, 8, 1600, True), (64, 8, 3100, False),
+])
+def test_dkdv_tiles_of_a_tree_follow_the_work_of_the_walks(Hq, Hkv, tokens, small, d):
+    """One segment: few key tiles, long walks.  The form for launches that leave the chip
+    empty (64-key tiles) is 10-30 % slower there once the cut walks fill it."""
+    tree = dta.tree_build(np.array([-1], dtype=np.int32), np.array([tokens], dtype=np.int32))
+    tile = tree.schedule_info(dta.AttnParams(Hq, Hkv, d, 0.1, dta.BF16))["bwd_kv_tile_tokens"]
+    tree.destroy()
+    assert (tile == 64) == small, tile
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_forms_of_segment_calls(forms, d):
+    backward = [   # heads, tokens before, rows, dQ form, dK/dV form
+        (16, 1, 9220, 3580, "small", "small"),      # 86 key tiles seen by the average row
+        (16, 1, 28420, 3580, "large", "large"),     # 236 of 250
+        (16, 1, 54000, 1600, "split", "large"),     # 428, 800 row tiles
+        (16, 1, 54000, 600, "small", "small"),      # ... 300 row tiles
+        (16, 1, 54000, 3580, "large", "large"),
+        (32, 8, 16384, 512, "small", "small"),      # 512 row tiles, a 16K prompt
+        (32, 8, 16384, 1024, "split", "large"),     # 1024
+        (32, 8, 16384, 1536, "large", "large"),     # 1536
+        (64, 8, 2000, 1000, "small", "small"),      # 2000 row tiles, 156 key tiles seen
+        (64, 8, 4000, 1000, "small", "small"),      # 281 seen, but blocks of 8 row tiles would be a round and a bit
+        (64, 8, 4000, 1600, "large", "large"),      # 300 seen, 3200 row tiles
+        (16, 8, 420, 3580, "small", "small"),       # mostly its own causal half
+    ]
+    got = forms([segment_call(Hq, Hkv, d, 1, before, rows) for Hq, Hkv, before, rows, _, _ in backward])
+    for g, c in zip(got, backward):
+        assert g[:2] == c[4:], (g, c)
+    forward = [   # heads, tokens before, rows, form
+        (16, 1, 16384, 1000, "small"), (16, 1, 16384, 2000, "split"), (16, 1, 16384, 2200, "large"),
+        (16, 1, 2048, 2200, "split"), (32, 8, 2048, 1500, "large"), (32, 8, 512, 1500, "split"), (4, 4, 8192, 16000, "split"),
+        (16, 1, 512, 5000, "large"),
+    ]
+    got = forms([segment_call(Hq, Hkv, d, 0, before, rows) for Hq, Hkv, before, rows, _ in forward])
+    for g, c in zip(got, forward):
+        assert g[0] == c[4], (g, c)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("segment", [0, 1])
+def test_one_schedule_serves_both_directions(forms, segment, d):
+    """The choices of a forward and of a backward call of the same rows describe one schedule, and a
+    forward that walks steps finds them there: its tiles are then dQ's."""
+    rng = np.random.default_rng(3)
+    shapes = []
+    for _ in range(400):
+        hkv = int(rng.choice([1, 2, 3, 8, 16]))
+        hq = hkv * int(rng.choice([1, 2, 3, 4, 5, 8, 16]))
+        rows = int(np.exp(rng.uniform(0, np.log(40000))))
+        keys = rows + (int(np.exp(rng.uniform(0, np.log(40000)))) if segment else 0)
+        pairs = rows * (keys - rows) + rows * (rows + 1) // 2
+        shapes.append((hq, hkv, d, int(rng.choice([dta.F32, dta.BF16])), segment, rows, keys, pairs))
+    f = forms([s[:4] + (0,) + s[4:] for s in shapes])
+    b = forms([s[:4] + (1,) + s[4:] for s in shapes])
+    for s, x, y in zip(shapes, f, b):
+        assert x[2:] == y[2:], (s, x, y)
+        if x[0] in ("small", "tiny"):
+            assert y[0] in ("small", "tiny") and x[4] == 0, (s, x, y)
