@@ -286,7 +286,11 @@ int dta_tree_attn_bwd_noalloc(dta_tree_t* tree, const dta_attn_params_t* params,
  * that add into the same accumulators must not overlap (same stream, or
  * ordered by events); within a call every key has one owner, so results are
  * bit-reproducible for a fixed sequence of calls.  o, lse: the forward results
- * of the rows.  workspace: as for dta_tree_attn_bwd (same size).
+ * of the rows.  workspace: as for dta_tree_attn_bwd; one of that size serves,
+ * but only its row statistics are used, so these calls accept any of at least
+ *   round256(4 * T * n_q_heads) bytes in fp32 mode,
+ *   2 * round256(4 * T * n_q_heads) + round256(8 * n_kv_heads) bytes in bf16 mode
+ * (round256: up to a multiple of 256; T: tokens of the whole tree).
  */
 int dta_tree_attn_fwd_segment(dta_tree_t* tree, const dta_attn_params_t* params, int64_t t_begin,
                               int64_t t_end, const void* q, const void* k, const void* v, void* o,

@@ -38,9 +38,9 @@ size_t bwd_workspace_bytes(dta_tree* tree, const dta_attn_params_t* p) {
   if (dta::choose_tiles(p, &tc, dta::whole_tree(tree, true)) != DTA_OK) return 0;
   try {
     std::lock_guard<std::mutex> lock(tree->mu);
-    return partial_offset(tree, p) +
-           dta::partial_bytes(dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads,
-                                                p->n_q_heads / p->n_kv_heads, tc.walk));
+    const dta::Schedule& s =
+        dta::get_schedule(tree, tc.bm, tc.bn, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, tc.walk);
+    return partial_offset(tree, p) + dta::partial_bytes(s, p->head_dim);
   } catch (const std::bad_alloc&) {
     return 0;
   }
@@ -553,7 +553,8 @@ int dta_tree_attn_bwd_segment(dta_tree_t* tree, const dta_attn_params_t* params,
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o) || misaligned(lse) ||
       misaligned(d_o) || misaligned(dq) || misaligned(dk_acc) || misaligned(dv_acc))
     return DTA_ERR_INVALID_ARG;
-  if (!workspace || workspace_bytes < bwd_workspace_bytes(tree, params) ||
+  // (no walk of a segment call is cut: the part before the partial sums is all it uses)
+  if (!workspace || workspace_bytes < partial_offset(tree, params) ||
       ((uintptr_t)workspace & 255u))
     return DTA_ERR_WORKSPACE;
   dta::Schedule* s = nullptr;

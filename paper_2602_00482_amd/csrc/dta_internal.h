@@ -201,7 +201,7 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const
 Schedule& get_segment_schedule(dta_tree* tree, int bm, int bn, int hkv, int group,
                                int64_t t_begin, int64_t t_end, const KvWalk& kw = KvWalk());
 // Bytes of fp32 partial dK/dV sums the split items of a schedule need.
-size_t partial_bytes(const Schedule& s);
+size_t partial_bytes(const Schedule& s, int head_dim);
 
 // Tile sizes the kernels use for a head configuration.
 struct TileChoice {

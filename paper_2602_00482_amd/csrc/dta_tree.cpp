@@ -222,8 +222,8 @@ void cut_steps(QueryTiles& s, int hkv) {
 }
 }  // namespace
 
-size_t partial_bytes(const Schedule& s) {
-  return (size_t)s.n_slots * (size_t)s.hkv * 2u * (size_t)s.kv_keys * 128u * sizeof(float);
+size_t partial_bytes(const Schedule& s, int head_dim) {
+  return (size_t)s.n_slots * (size_t)s.hkv * 2u * (size_t)s.kv_keys * (size_t)head_dim * sizeof(float);
 }
 
 namespace {

@@ -282,3 +282,39 @@ def test_plan_captured_in_a_graph_replays_to_the_eager_result():
             assert torch.equal(x, w), rep
     del graph
     tree.destroy()
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [("f32", 8, 2, 64), ("f32", 16, 4, 128), ("bf16", 8, 2, 128), ("bf16", 8, 2, 64)])
+def test_backward_segment_needs_the_row_statistics_only(dtype, Hq, Hkv, d):
+    """A tree whose whole-tree backward cuts walks into partial sums: the segment calls run
+    on a workspace without room for them, write nothing behind it and refuse a smaller one."""
+    parent, seg = np.array([-1, 0, 0, 0], dtype=np.int32), np.array([700, 400, 90, 333], dtype=np.int32)
+    T = int(seg.sum())
+    rows = -(-4 * T * Hq // 256) * 256
+    need = rows if dtype == "f32" else 2 * rows + -(-8 * Hkv // 256) * 256
+    x = make_inputs_numpy(T, Hq, Hkv, d, 12, dtype=dtype)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    t = {n: torch.from_numpy(a).cuda().to(tdt).contiguous() for n, a in x.items()}
+    tree = dta.tree_build(parent, seg)
+    p = dta.AttnParams(Hq, Hkv, d, 1.0 / math.sqrt(d), dta.F32 if dtype == "f32" else dta.BF16)
+    full = dta.workspace_bytes(tree, p, True)
+    assert full > need
+    o, lse = dta.tree_attn_fwd(tree, p, t["q"], t["k"], t["v"])
+    raw = torch.full((full,), 0xA5, dtype=torch.uint8, device="cuda")
+    res = []
+    for ws in (raw[:need], torch.empty(full, dtype=torch.uint8, device="cuda")):
+        dq = torch.zeros_like(t["q"])
+        dk, dv = (torch.zeros((T, Hkv, d), dtype=torch.float32, device="cuda") for _ in range(2))
+        for u in (3, 2, 1, 0):
+            t1 = int(seg[:u + 1].sum())
+            dta.tree_attn_bwd_segment(tree, p, t1 - int(seg[u]), t1, t["q"], t["k"], t["v"], o, lse, t["do"], dq,
+                                      dk, dv, ws)
+        torch.cuda.synchronize()
+        res.append((dq, dk, dv))
+    assert bool((raw[need:] == 0xA5).all())
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+    with pytest.raises(dta.DtaError) as err:
+        dta.tree_attn_bwd_segment(tree, p, 0, 700, t["q"], t["k"], t["v"], o, lse, t["do"], *res[0], raw[:need - 256])
+    assert err.value.status == -6
+    tree.destroy()
