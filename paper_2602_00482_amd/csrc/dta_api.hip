@@ -301,7 +301,8 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
 // Runs a call's launches, which read the tree's device copies, and has the tree's event
 // complete after them: attached to the last launch where the launcher does that,
 // recorded otherwise (always while the stream is being captured: there the event has to
-// become part of the graph).
+// become part of the graph).  Under the tree's lock, like every other use of the event:
+// calls of other threads on the tree attach it, and uploads into recycled blocks wait for it.
 int launch_and_mark(dta_tree* tree, dta::LaunchArgs& a, int (*launcher)(const dta::LaunchArgs&)) {
   void* const stream = a.stream;
   hipStreamCaptureStatus capture;
@@ -309,9 +310,9 @@ int launch_and_mark(dta_tree* tree, dta::LaunchArgs& a, int (*launcher)(const dt
   if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) (void)hipGetLastError();
   else if (capture == hipStreamCaptureStatusNone) a.done_event = tree->last_use;
   a.done_recorded = &recorded;
+  std::lock_guard<std::mutex> lock(tree->mu);
   const int launch_result = launcher(a);
   if (launch_result != DTA_OK) return launch_result;
-  std::lock_guard<std::mutex> lock(tree->mu);
   if (!recorded && hipEventRecord((hipEvent_t)tree->last_use, (hipStream_t)stream) != hipSuccess) {
     (void)hipGetLastError();
     return DTA_ERR_HIP;

@@ -258,3 +258,91 @@ def test_the_first_call_leaves_nothing_to_allocate_for_the_other_direction(Hq, H
         for a, b in zip(ref, (dq, dk, dv)):
             assert torch.equal(a, b)
     tree.destroy()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+def test_one_tree_from_two_threads(dtype, d):
+    """Two host threads, each on its own stream with its own outputs and workspace, issue
+    whole-tree and segment calls on one tree at the same time; both must get the bits that
+    one thread alone gets."""
+    import threading
+    rng = np.random.default_rng(44)
+    parent, seg = random_tree(rng, 20, 200, n_roots=2)
+    Hq, Hkv = 8, 2
+    x, t, tree, p, _ = _setup(parent, seg, Hq, Hkv, d, dtype, seed=9)
+    T = int(seg.sum())
+    off = tree.layout()["node_offset"]
+    ranges = [(int(off[u]), int(off[u] + seg[u])) for u in range(len(seg))]
+    ws_bytes = max(256, dta.workspace_bytes(tree, p, True))
+    torch.cuda.synchronize()
+    results = {}
+
+    def work(who, rounds):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+                for _ in range(rounds):
+                    o, lse = dta.tree_attn_fwd(tree, p, t["q"], t["k"], t["v"])
+                    grads = dta.tree_attn_bwd(tree, p, t["q"], t["k"], t["v"], o, lse, t["do"], workspace=ws)
+                    o2, lse2, dq2 = torch.zeros_like(o), torch.zeros_like(lse), torch.zeros_like(o)
+                    dk2, dv2 = (torch.zeros((T, Hkv, d), dtype=torch.float32, device="cuda") for _ in range(2))
+                    for t0, t1 in ranges:
+                        dta.tree_attn_fwd_segment(tree, p, t0, t1, t["q"], t["k"], t["v"], o2, lse2)
+                    for t0, t1 in reversed(ranges):
+                        dta.tree_attn_bwd_segment(tree, p, t0, t1, t["q"], t["k"], t["v"], o2, lse2, t["do"], dq2,
+                                                  dk2, dv2, ws)
+                torch.cuda.current_stream().synchronize()
+                results[who] = [a.cpu() for a in (o, lse, *grads, o2, lse2, dq2, dk2, dv2)]
+        except Exception as e:   # shown by the assertion below
+            results[who] = e
+
+    work("alone", 1)
+    threads = [threading.Thread(target=work, args=(i, 4)) for i in range(2)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    tree.destroy()
+    for i in range(2):
+        assert isinstance(results[i], list), results[i]
+        for a, b in zip(results["alone"], results[i]):
+            assert torch.equal(a, b)
+
+
+def test_the_metadata_of_a_destroyed_tree_is_not_reused_before_its_launches_ran():
+    """Calls on a tree wait in the stream behind some 100 ms of other work; the tree is
+    destroyed and trees of the same size class are prepared meanwhile.  The event that
+    rides on the call's last kernel must keep its blocks until the kernels have run."""
+    a_seg, b_seg = [300, 64, 200, 130, 90], [90, 130, 200, 64, 300]
+    parent = np.array([-1, 0, 0, 0, 0], dtype=np.int32)
+    for dtype, Hq, Hkv, d in (("bf16", 8, 2, 128), ("bf16", 64, 32, 128), ("f32", 8, 2, 64)):
+        outs = []
+        for busy in (False, True):
+            x, t, tree, p, _ = _setup(parent, np.array(a_seg, dtype=np.int32), Hq, Hkv, d, dtype, seed=21)
+            ws = torch.empty(dta.workspace_bytes(tree, p, True), dtype=torch.uint8, device="cuda")
+            tree.prepare(p)
+            w = torch.ones((8192, 8192), device="cuda")
+            o, lse = torch.empty_like(t["q"]), torch.empty((sum(a_seg), Hq), device="cuda")
+            dq, dk, dv = torch.empty_like(t["q"]), torch.empty_like(t["k"]), torch.empty_like(t["v"])
+            torch.cuda.synchronize()
+            if busy:
+                ahead = torch.cuda.Event()
+                for _ in range(12):
+                    w @ w
+                ahead.record()
+            dta.tree_attn_fwd(tree, p, t["q"], t["k"], t["v"], o, lse)
+            dta.tree_attn_bwd(tree, p, t["q"], t["k"], t["v"], o, lse, t["do"], dq, dk, dv, ws)
+            tree.destroy()
+            if busy:
+                others = []
+                for _ in range(4):
+                    other = dta.tree_build(parent, np.array(b_seg, dtype=np.int32))
+                    other.prepare(p)
+                    others.append(other)
+                assert not ahead.query()      # the calls had not begun when the other trees were uploaded
+            torch.cuda.synchronize()
+            outs.append([a.clone() for a in (o, lse, dq, dk, dv)])
+        for other in others:
+            other.destroy()
+        for a, b in zip(*outs):
+            assert torch.equal(a, b)
