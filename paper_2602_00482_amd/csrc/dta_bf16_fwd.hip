@@ -256,8 +256,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     __syncthreads();   // everyone is done with the tiles, too
     const float m2 = mS[w ^ 4][c], l2 = lS[w ^ 4][c], own = m;
     m = fmaxf(own, m2);
-    const float f = __builtin_amdgcn_exp2f((own - m) * sc);
-    lt = lt * f + l2 * __builtin_amdgcn_exp2f((m2 - m) * sc);
+    const float mref = m == -INFINITY ? 0.f : m;   // (every score of the row may be -inf)
+    const float f = __builtin_amdgcn_exp2f((own - mref) * sc);
+    lt = lt * f + l2 * __builtin_amdgcn_exp2f((m2 - mref) * sc);
 #pragma unroll
     for (int dmb = 0; dmb < DB; ++dmb)
 #pragma unroll

@@ -337,11 +337,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   float mall = mS[0][wk.rw][c];
 #pragma unroll
   for (int s = 1; s < kGroupsOfWaves; ++s) mall = fmaxf(mall, mS[s][wk.rw][c]);
+  const float mref = mall == -INFINITY ? 0.f : mall;   // (every score of the row may be -inf)
   lt = 0.f;
 #pragma unroll
   for (int s = 0; s < kGroupsOfWaves; ++s)
-    lt = fmaf(__builtin_amdgcn_exp2f((mS[s][wk.rw][c] - mall) * sc), lS[s][wk.rw][c], lt);
-  const float f = __builtin_amdgcn_exp2f((m - mall) * sc);
+    lt = fmaf(__builtin_amdgcn_exp2f((mS[s][wk.rw][c] - mref) * sc), lS[s][wk.rw][c], lt);
+  const float f = __builtin_amdgcn_exp2f((m - mref) * sc);
 #pragma unroll
   for (int dmb = 0; dmb < DB; ++dmb)
 #pragma unroll

@@ -280,10 +280,11 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
     float mall = mlS[0][0][rw][n16];
 #pragma unroll
     for (int s = 1; s < KS; ++s) mall = fmaxf(mall, mlS[0][s][rw][n16]);
+    const float mref = mall == -INFINITY ? 0.f : mall;   // (every score of the row may be -inf)
     lt = 0.f;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) lt = fmaf(expf(mlS[0][s][rw][n16] - mall), mlS[1][s][rw][n16], lt);
-    const float f = expf(m - mall);
+    for (int s = 0; s < KS; ++s) lt = fmaf(expf(mlS[0][s][rw][n16] - mref), mlS[1][s][rw][n16], lt);
+    const float f = expf(m - mref);
 #pragma unroll
     for (int b = 0; b < NB; ++b) O[b] *= f;
     m = mall;

@@ -107,3 +107,32 @@ def test_split_segment(Hq, Hkv, rows, d):
         dta.tree_attn_bwd_segment(tree, p, t0, t1, q, k, v, o2, lse2, do, dq2, dk2, dv2, ws)
     for name, a, b in (("o", o2, o), ("lse", lse2, lse), ("dq", dq2, dq), ("dk", dk2, dk), ("dv", dv2, dv)):
         assert rel_err(a.float().cpu().numpy(), b.float().cpu().numpy()) <= 1e-2, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype,Hq,Hkv,n", [
+    ("bf16", 4, 2, 300),         # small form
+    ("bf16", 40, 10, 500),       # split forward (600 row tiles)
+    ("bf16", 128, 32, 500),      # blocks of 8 row tiles
+    ("f32", 4, 2, 300), ("f32", 64, 16, 600),
+])
+def test_a_row_of_infinite_scores(dtype, Hq, Hkv, n, d):
+    """One query row whose scores are all -inf (a -inf element against positive keys): its LSE is
+    -inf and its output NaN in every form, and no other row changes."""
+    import torch
+    parent, seg = np.array([-1, 0, 0], dtype=np.int32), np.array([n // 2, n // 4 + 3, n - n // 2 - n // 4 - 3], dtype=np.int32)
+    x = make_inputs_numpy(n, Hq, Hkv, d, 41, dtype=dtype)
+    x["k"][:, :, 7] = np.abs(x["k"][:, :, 7]) + 0.5
+    kind = torch.float32 if dtype == "f32" else torch.bfloat16
+    p = dta.AttnParams(Hq, Hkv, d, 1.0 / math.sqrt(d), dta.F32 if dtype == "f32" else dta.BF16)
+    tree = dta.tree_build(parent, seg)
+    t = {k: torch.from_numpy(a).cuda().to(kind) for k, a in x.items()}
+    ref = dta.tree_attn_fwd(tree, p, t["q"], t["k"], t["v"])
+    row = n - 20
+    t["q"][row, :, 7] = -float("inf")
+    o, lse = dta.tree_attn_fwd(tree, p, t["q"], t["k"], t["v"])
+    torch.cuda.synchronize()
+    tree.destroy()
+    assert bool((lse[row] == -float("inf")).all()) and bool(torch.isnan(o[row]).all())
+    keep = torch.arange(n, device="cuda") != row
+    assert torch.equal(o[keep], ref[0][keep]) and torch.equal(lse[keep], ref[1][keep])
