@@ -290,8 +290,58 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
     m = mall;
     sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&Ks[0][0]), rw, kg, O);
   }
-  if (kg == 0 && row_base + n16 < tile.t1) {
-    const float inv = 1.f / lt;
+  if (kg != 0) return;
+  const float inv = 1.f / lt;
+  {
+    // The products above multiply the V rows of masked keys by 0, which is NaN where such a
+    // row is not finite: a row's output must not depend on keys it does not see.  Rows with a
+    // finite sum and an output that is not finite are worked out again, key by key.
+    float t = 0.f;
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t = fmaf(O[b][e], 0.f, t);
+    const bool spoilt = column_sum(t) != 0.f && lt - lt == 0.f;   // (NaN compares unequal)
+    if (__builtin_amdgcn_ballot_w64(spoilt) != 0) {
+      f32x4 acc[NB];   // columns 16 * j + 4 * lg .. + 3, as Qr
+#pragma unroll
+      for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int si = tile.seg_begin; si <= tile.seg_end; ++si) {
+        const bool own = si == tile.seg_end;
+        const int start = own ? tile.t0 : segs[si].start, end = own ? tile.t1 : segs[si].end;
+        const bool all = !own && segs[si].full;
+#pragma unroll 1
+        for (int key = start; key < end; ++key) {
+          const size_t at = (size_t)key * kv_stride + 4 * lg;
+          float s = 0.f;
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            const f32x4 kx = *reinterpret_cast<const f32x4*>(kbase + at + 16 * j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = fmaf(kx[e], Qr[j][e], s);
+          }
+          s = column_sum(s) * scale;
+          if (all || (key <= qrow && qrow < kend[key])) {
+            const float w = expf(s - m) * inv;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+              const f32x4 vx = *reinterpret_cast<const f32x4*>(vbase + at + 16 * j);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(w, vx[e], acc[j][e]);
+            }
+          }
+        }
+      }
+      if (spoilt && row_base + n16 < tile.t1) {
+        float* op = o + ((size_t)qrow * Hq + h) * HD + 4 * lg;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) *reinterpret_cast<f32x4*>(op + 16 * j) = acc[j];
+        if (lg == 0) lse[(size_t)qrow * Hq + h] = m + logf(lt);
+        return;
+      }
+    }
+  }
+  if (row_base + n16 < tile.t1) {
     float* op = o + ((size_t)qrow * Hq + h) * HD + NB * 4 * lg;
 #pragma unroll
     for (int e = 0; e < 4; ++e)

@@ -40,3 +40,39 @@ def test_tiles_against_the_oracle(Hq, Hkv, seg, d):
     dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
     for name, ref in (("o", O), ("lse", LSE), ("dq", dQ), ("dk", dK), ("dv", dV)):
         assert rel_err(got[name], ref) <= 1e-5, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(128, 128), (126, 42), (128, 32), (16, 4), (2, 1)])
+def test_rows_do_not_depend_on_keys_they_do_not_see(Hq, Hkv, d):
+    """K and V rows that are not finite, of a leaf and of the last token of another one: O and LSE
+    of every row that sees none of them are those of finite inputs, in tiles that mix
+    the leaves and in the causal tile of a segment call; rows that see them have NaN."""
+    import torch
+    parent = np.array([-1, 0, 0, 0, 3, 0], dtype=np.int32)
+    seg = np.array([70, 33, 21, 50, 64, 77], dtype=np.int32)
+    T, scale = int(seg.sum()), 1.0 / math.sqrt(d)
+    off = np.concatenate([[0], np.cumsum(seg)])
+    x = make_inputs_numpy(T, Hq, Hkv, d, 23, dtype="f32")
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    clean = np.ones(T, dtype=bool)
+    clean[off[2]:off[3]] = False        # node 2
+    clean[T - 1] = False                # last token of node 5
+    for r in (*range(off[2], off[3]), T - 1):
+        x["v"][r, :, 0], x["v"][r, :, d // 2 + 1], x["v"][r, :, d - 1] = np.nan, np.inf, -np.inf
+        x["k"][r, :, 1] = np.inf if r % 2 else np.nan
+    t = {n: torch.from_numpy(a).cuda() for n, a in x.items()}
+    p = dta.AttnParams(Hq, Hkv, d, scale, dta.F32)
+    tree = dta.tree_build(parent, seg)
+    o, lse = dta.tree_attn_fwd(tree, p, t["q"], t["k"], t["v"])
+    o2, lse2 = torch.zeros_like(o), torch.zeros_like(lse)
+    for u in range(len(seg)):
+        dta.tree_attn_fwd_segment(tree, p, int(off[u]), int(off[u + 1]), t["q"], t["k"], t["v"], o2, lse2)
+    torch.cuda.synchronize()
+    tree.destroy()
+    for got in ((o, lse), (o2, lse2)):
+        for name, a, ref in zip(("o", "lse"), got, (O, LSE)):
+            a = a.double().cpu().numpy()
+            assert np.isfinite(a[clean]).all(), name
+            assert rel_err(a[clean], ref[clean]) <= 1e-5, name
+            assert np.isnan(a[~clean]).any(axis=tuple(range(1, a.ndim))).all() or name == "lse", name
