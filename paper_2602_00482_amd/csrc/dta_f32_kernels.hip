@@ -18,10 +18,16 @@
 // streamed row 4 * (l / 16) + v, which is exactly the operand layout of the next
 // product with that row as the contraction index, so P and dS never move.
 //
+//   Products that contract over head_dim sum its two halves apart: one chain of
+// head_dim / 4 instructions rounds more than the chains per quarter of head_dim that
+// four lanes per row had (relative errors of O and dQ against 64 bits, 4862 tokens below:
+// 4.3e-7 and 5.4e-7 there, 4.8e-7 and 6.0e-7 in one chain, 3.8e-7 and 5.1e-7 in two).
+// It costs 1 to 2 % of each kernel, and quarters cost dQ 4 %.
+//
 // Measured on MI355X (bound: 152 TFLOP/s, what a large fp32 library product reaches),
 // with four lanes per row on the vector ALU before, and now:
 //   4862 tokens (a prompt with 16 answers), 32/8 heads of 128:
-//     forward 1.51 -> 0.35 ms (93 TFLOP/s), dQ 2.38 -> 0.53 ms (93), dK/dV 13.6 -> 0.63 ms (103)
+//     forward 1.51 -> 0.36 ms (90 TFLOP/s), dQ 2.38 -> 0.54 ms (92), dK/dV 13.6 -> 0.65 ms (101)
 //   384 tokens in 13 nodes, 4/4 heads of 64 (latency of a chain of dependent steps):
 //     forward 71 -> 11 us, dQ 64 and dK/dV 146 -> 17 us together (two launches)
 // A large launch's blocks are few rounds (1216 on 512 slots above), so what is left
@@ -213,17 +219,19 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
     if (nk > 0 && !(need_mask && k0 > row_base + 15)) {
       const float* Kt = Ks[buf] + rlo;
       const float* Vt = Vs[buf] + clo;
-      f32x4 S[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+      f32x4 Sh[2][2] = {};   // sums over each half of head_dim: shorter chains of roundings
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         const f32x4 a0 = *reinterpret_cast<const f32x4*>(Kt + 16 * j);
         const f32x4 a1 = *reinterpret_cast<const f32x4*>(Kt + 128 + 16 * j);
+        f32x4(&c)[2] = Sh[j / (NB / 2)];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          S[0] = mfma16(a0[e], Qr[j][e], S[0]);
-          S[1] = mfma16(a1[e], Qr[j][e], S[1]);
+          c[0] = mfma16(a0[e], Qr[j][e], c[0]);
+          c[1] = mfma16(a1[e], Qr[j][e], c[1]);
         }
       }
+      f32x4 S[2] = {Sh[0][0] + Sh[1][0], Sh[0][1] + Sh[1][1]};
       float mx = -INFINITY;
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb) {
@@ -482,9 +490,7 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD, KS>& sm, i
       const float* Kt = Ks[buf] + rlo;
       const float* Vt = Vs[buf] + rlo;
       const float* Kc = Ks[buf] + clo;
-      f32x4 S[2], dP[2];
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) S[mb] = dP[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      f32x4 Sh[2][2] = {}, dPh[2][2] = {};   // over each half of head_dim, as in the forward kernel
 #pragma unroll
       for (int j = 0; j < NB; ++j)
 #pragma unroll
@@ -493,10 +499,13 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD, KS>& sm, i
           const f32x4 va = *reinterpret_cast<const f32x4*>(Vt + 128 * mb + 16 * j);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            S[mb] = mfma16(ka[e], Qr[j][e], S[mb]);
-            dP[mb] = mfma16(va[e], dOr[j][e], dP[mb]);
+            f32x4 &c = Sh[j / (NB / 2)][mb], &dc = dPh[j / (NB / 2)][mb];
+            c = mfma16(ka[e], Qr[j][e], c);
+            dc = mfma16(va[e], dOr[j][e], dc);
           }
         }
+      f32x4 S[2] = {Sh[0][0] + Sh[1][0], Sh[0][1] + Sh[1][1]};
+      const f32x4 dP[2] = {dPh[0][0] + dPh[1][0], dPh[0][1] + dPh[1][1]};
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb) {
 #pragma unroll
@@ -638,17 +647,19 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD, KS>& s
       const int lo = kcol - r0, hi = min(my_kend - r0, nr);
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb) {
-        f32x4 S = {0.f, 0.f, 0.f, 0.f}, dP = {0.f, 0.f, 0.f, 0.f};
+        f32x4 Sh[2] = {}, dPh[2] = {};   // over each half of head_dim, as in the forward kernel
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
           const f32x4 qa = *reinterpret_cast<const f32x4*>(Qt + 128 * mb + 16 * j);
           const f32x4 da = *reinterpret_cast<const f32x4*>(dOt + 128 * mb + 16 * j);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            S = mfma16(qa[e], Kr[j][e], S);
-            dP = mfma16(da[e], Vr[j][e], dP);
+            f32x4 &c = Sh[j / (NB / 2)], &dc = dPh[j / (NB / 2)];
+            c = mfma16(qa[e], Kr[j][e], c);
+            dc = mfma16(da[e], Vr[j][e], dc);
           }
         }
+        f32x4 S = Sh[0] + Sh[1], dP = dPh[0] + dPh[1];
         const f32x4 ls = *reinterpret_cast<const f32x4*>(&stat[buf][0][32 * qg + 16 * mb + 4 * lg]);
         const f32x4 dl = *reinterpret_cast<const f32x4*>(&stat[buf][1][32 * qg + 16 * mb + 4 * lg]);
 #pragma unroll

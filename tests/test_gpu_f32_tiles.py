@@ -76,3 +76,23 @@ def test_rows_do_not_depend_on_keys_they_do_not_see(Hq, Hkv, d):
             assert np.isfinite(a[clean]).all(), name
             assert rel_err(a[clean], ref[clean]) <= 1e-5, name
             assert np.isnan(a[~clean]).any(axis=tuple(range(1, a.ndim))).all() or name == "lse", name
+
+
+@pytest.mark.parametrize("Hq,Hkv,limit_o,limit_dq", [(8, 2, 3.65e-7, 4.82e-7), (64, 16, 3.64e-7, 4.79e-7)])
+def test_rounding_errors_of_the_products(Hq, Hkv, limit_o, limit_dq):
+    """Relative 2-norm errors against 64 bits, head_dim 128: no larger than those of one
+    fused multiply-add chain per quarter of head_dim (four lanes per row on the vector ALU),
+    which are the limits here (measured: a small launch, and one that fills the chip).  A product that sums
+    head_dim in one chain exceeds them by 5 to 16 %."""
+    rng = np.random.default_rng(77)
+    seg = np.array([300] + [int(n) for n in rng.integers(60, 300, size=7)], dtype=np.int32)
+    parent = np.array([-1] + [0] * 7, dtype=np.int32)
+    T, d = int(seg.sum()), 128
+    scale = 1.0 / math.sqrt(d)
+    x = make_inputs_numpy(T, Hq, Hkv, d, 5, dtype="f32")
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32")
+    O, _ = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    dQ, _, _ = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
+    err = [float(np.linalg.norm(got[n] - ref) / np.linalg.norm(ref)) for n, ref in (("o", O), ("dq", dQ))]
+    print(f"T={T} {Hq}/{Hkv}: o {err[0]:.4e} dq {err[1]:.4e}", flush=True)
+    assert err[0] <= limit_o and err[1] <= limit_dq, err
