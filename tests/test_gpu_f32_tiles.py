@@ -10,7 +10,7 @@ import pytest
 
 import paper_2602_00482_amd as dta
 from oracle import tree_direct as B
-from workloads import make_inputs_numpy
+from workloads import make_inputs_numpy, random_tree
 from parity_util import rel_err, run_hip
 
 pytestmark = pytest.mark.gpu
@@ -96,3 +96,18 @@ def test_rounding_errors_of_the_products(Hq, Hkv, limit_o, limit_dq):
     err = [float(np.linalg.norm(got[n] - ref) / np.linalg.norm(ref)) for n, ref in (("o", O), ("dq", dQ))]
     print(f"T={T} {Hq}/{Hkv}: o {err[0]:.4e} dq {err[1]:.4e}", flush=True)
     assert err[0] <= limit_o and err[1] <= limit_dq, err
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,sign", [(32, 32, 1), (36, 12, -1), (32, 8, 1), (48, 3, -1)])
+def test_forests_in_launches_that_fill_the_chip(Hq, Hkv, sign, d):
+    """Tiles that straddle many short nodes, groups of 1, 3, 4 and 16, a negative scale."""
+    parent, seg = random_tree(np.random.default_rng(55), 30, 80, n_roots=3)
+    T, scale = int(seg.sum()), sign / math.sqrt(d)
+    assert T // 16 * Hq >= 2048
+    x = make_inputs_numpy(T, Hq, Hkv, d, 62, dtype="f32")
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32")
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
+    for name, ref in (("o", O), ("lse", LSE), ("dq", dQ), ("dk", dK), ("dv", dV)):
+        assert rel_err(got[name], ref) <= 1e-5, name

@@ -9,7 +9,7 @@ import pytest
 
 import paper_2602_00482_amd as dta
 from oracle import tree_direct as B
-from workloads import make_inputs_numpy
+from workloads import chain_tree, make_inputs_numpy, random_tree
 from parity_util import rel_err, run_hip
 
 pytestmark = pytest.mark.gpu
@@ -44,9 +44,9 @@ def test_small_form(Hq, Hkv, seg, d):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Hq,Hkv,seg", [
-    (96, 96, [300, 1, 63, 65, 129, 170]),   # no grouping: 256-token query tiles
-    (128, 64, [257, 33, 310, 95, 31]),       # group of two
-    (256, 64, [300, 127, 128, 129, 40]),    # group of four
+    (96, 96, [300, 1, 63, 65, 129, 170]),   # no grouping: 256-token query tiles, dQ of head_dim 128 split (128 tokens)
+    (128, 64, [257, 33, 310, 95, 31]),       # group of two, dQ of head_dim 128 split
+    (256, 64, [300, 127, 128, 129, 40]),    # group of four, blocks of 8 row tiles in both directions
 ])
 def test_large_form(Hq, Hkv, seg, d):
     _check(seg, Hq, Hkv, d, 128)
@@ -71,9 +71,9 @@ def test_small_form_path_of_many_short_intervals(Hq, Hkv, d):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Hq,Hkv,seg", [
-    (30, 10, [257, 33, 310, 95, 31]),       # forward split (680 row tiles): one head per block, 128-token tiles
+    (30, 10, [257, 33, 310, 95, 31]),       # forward split (660 row tiles): one head per block, 128-token tiles
     (40, 10, [300, 127, 128, 129, 40]),     # ... group of four, 32-token tiles
-    (120, 60, [257, 33, 310, 95, 31]),      # backward split at head_dim 128 (2722), group of two
+    (120, 60, [257, 33, 310, 95, 31]),      # backward split at head_dim 128 (2640), group of two
     (128, 16, [300, 1, 63, 65, 129, 170]),  # ... group of eight, two head blocks
     (192, 96, [257, 33, 310, 95, 31]),      # blocks of 8 row tiles in both directions
 ])
@@ -136,3 +136,81 @@ def test_a_row_of_infinite_scores(dtype, Hq, Hkv, n, d):
     assert bool((lse[row] == -float("inf")).all()) and bool(torch.isnan(o[row]).all())
     keep = torch.arange(n, device="cuda") != row
     assert torch.equal(o[keep], ref[0][keep]) and torch.equal(lse[keep], ref[1][keep])
+
+
+def _forest():
+    return random_tree(np.random.default_rng(55), 30, 80, n_roots=3)   # 1275 tokens
+
+
+# (tree, Hq, Hkv, sign of the softmax scale; forms of forward, dQ at head_dim 64 and 128, dK/dV).  That these
+# sizes take these forms is checked without a GPU by test_host_forms.py.
+FORMS = [
+    (_forest, 96, 96, -1, "large", "large", "large", "large"),
+    (_forest, 120, 40, 1, "large", "large", "large", "large"),      # groups of 3, 5 and 16
+    (_forest, 120, 24, -1, "large", "large", "large", "large"),
+    (_forest, 384, 24, 1, "large", "large", "large", "large"),
+    (_forest, 72, 24, -1, "large", "large", "split", "large"),
+    (_forest, 80, 16, 1, "large", "large", "split", "small"),
+    (_forest, 64, 4, -1, "large", "large", "split", "small"),
+    (_forest, 44, 44, 1, "large", "split", "split", "large"),
+    (_forest, 24, 8, -1, "split", "small", "small", "small"),
+    (_forest, 25, 5, 1, "split", "small", "small", "small"),
+    (_forest, 16, 1, -1, "split", "small", "small", "small"),
+    (_forest, 12, 4, -1, "small", "small", "small", "small"),
+    (lambda: (np.array([-1] * 5), np.array([3, 70, 1, 64, 65])), 640, 320, 1, "large", "large", "large", "large"),
+    (lambda: chain_tree([300, 37, 64, 128]), 256, 64, 1, "large", "large", "large", "large"),
+]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tree,Hq,Hkv,sign", [f[:4] for f in FORMS])
+def test_forests_in_every_form(tree, Hq, Hkv, sign, d):
+    """Forests whose tiles straddle many short nodes, degenerate trees, odd and large groups
+    and a negative scale in the forms that small trees no longer reach."""
+    parent, seg = tree()
+    T, scale = int(np.sum(seg)), sign / math.sqrt(d)
+    x = make_inputs_numpy(T, Hq, Hkv, d, 61, dtype="bf16")
+    got = run_hip(np.asarray(parent, dtype=np.int32), np.asarray(seg, dtype=np.int32), x, Hq, Hkv, d, scale, "bf16")
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
+    for name, ref in (("o", O), ("lse", LSE), ("dq", dQ), ("dk", dK), ("dv", dV)):
+        assert rel_err(got[name], ref) <= 1e-2, name
+
+
+# (dtype, Hq, Hkv, d; forms of dQ and dK/dV) on 3848 tokens
+STAGED = [("bf16", 64, 16, 128, "large", "large"), ("bf16", 64, 16, 64, "large", "large"),
+          ("bf16", 24, 6, 128, "split", "small"), ("bf16", 24, 12, 128, "split", "large"), ("f32", 16, 4, 128, "large", "large"),
+          ("f32", 16, 4, 64, "large", "large")]
+
+
+def staged_tree():
+    return random_tree(np.random.default_rng(5), 25, 300, n_roots=2)
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [s[:4] for s in STAGED])
+def test_stages_one_by_one_give_the_bits_of_one_call(dtype, Hq, Hkv, d):
+    """The delta stage as a launch of its own, or inside the dQ launch, in the split form and in
+    the forms that fill the chip (the small ones: test_gpu_api.py)."""
+    import torch
+    parent, seg = staged_tree()
+    T = int(seg.sum())
+    kind = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(8)
+    q, do = (torch.randn((T, Hq, d), generator=g, device="cuda").to(kind) for _ in range(2))
+    k, v = (torch.randn((T, Hkv, d), generator=g, device="cuda").to(kind) for _ in range(2))
+    p = dta.AttnParams(Hq, Hkv, d, 1.0 / math.sqrt(d), dta.F32 if dtype == "f32" else dta.BF16)
+    tree = dta.tree_build(parent, seg)
+    o, lse = dta.tree_attn_fwd(tree, p, q, k, v)
+    ref = dta.tree_attn_bwd(tree, p, q, k, v, o, lse, do)
+    ws = torch.empty(dta.workspace_bytes(tree, p, True), dtype=torch.uint8, device="cuda")
+    for stages in ((dta.BWD_DELTA, dta.BWD_DKDV, dta.BWD_DQ), (dta.BWD_DELTA | dta.BWD_DQ, dta.BWD_DKDV),
+                   (dta.BWD_DELTA | dta.BWD_DKDV, dta.BWD_DQ), (dta.BWD_DELTA, dta.BWD_DQ | dta.BWD_DKDV)):
+        ws.fill_(0xff)
+        out = [torch.full_like(a, float("nan")) for a in ref]
+        for st in stages:
+            dta.tree_attn_bwd(tree, p, q, k, v, o, lse, do, *out, ws, stages=st)
+        torch.cuda.synchronize()
+        for a, b in zip(ref, out):
+            assert torch.equal(a, b), stages
+    tree.destroy()

@@ -116,3 +116,15 @@ def test_one_schedule_serves_both_directions(forms, segment, d):
         assert x[2:] == y[2:], (s, x, y)
         if x[0] in ("small", "tiny"):
             assert y[0] in ("small", "tiny") and x[4] == 0, (s, x, y)
+
+
+def test_the_gpu_tests_reach_the_forms_they_name(forms):
+    import test_gpu_launch_forms as G
+    for tree, Hq, Hkv, _, fwd, dq64, dq128, dkdv in G.FORMS:
+        for d, dq in ((64, dq64), (128, dq128)):
+            parent, seg = tree()
+            f, b = forms([tree_call(parent, seg, Hq, Hkv, d, dta.BF16, way) for way in (0, 1)])
+            assert (f[0], b[0], b[1]) == (fwd, dq, dkdv), (Hq, Hkv, d, f, b)
+    for dtype, Hq, Hkv, d, dq, dkdv in G.STAGED:
+        b = forms([tree_call(*G.staged_tree(), Hq, Hkv, d, dta.F32 if dtype == "f32" else dta.BF16, 1)])[0]
+        assert b[:2] == (dq, dkdv), (dtype, Hq, Hkv, d, b)
