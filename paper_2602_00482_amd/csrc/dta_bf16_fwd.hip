@@ -26,16 +26,6 @@ namespace {
 
 constexpr int kThreads = 512;
 
-// max over both halves of the wave: lane l gets max(x[l], x[l ^ 32]).  The
-// lane-half swap (v_permlane32_swap: upper 32 lanes of the first operand <->
-// lower 32 lanes of the second) runs in the vector ALU, without the LDS round
-// trip of a shuffle.
-__device__ __forceinline__ float max_across_halves(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 // kCh = keys per streamed chunk (one or two 64-row LDS tiles per operand): one
 // barrier, one round of bookkeeping and one online-softmax step per chunk, so
 // long key intervals run faster with 128, while every interval is padded to a

@@ -131,13 +131,6 @@ __device__ __forceinline__ void sum_over_groups(float* buf, const f32x16 (&x)[DB
     }
 }
 
-// max over both halves of the wave (lane l gets max(x[l], x[l ^ 32]))
-__device__ __forceinline__ float max_across_halves(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
 // What the forward and dQ kernels share: the block's item and its walk over the keys.
 // The host has cut the walk into steps (KeyStep: a piece of at most 32 keys for each
 // group); working the pieces out here, between the barrier and the first product of

@@ -41,6 +41,15 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& x, int s) {
   return r;
 }
 
+// max over both halves of the wave: lane l gets max(x[l], x[l ^ 32]).  The
+// lane-half swap (v_permlane32_swap: upper 32 lanes of the first operand <->
+// lower 32 lanes of the second) runs in the vector ALU, without the LDS round
+// trip of a shuffle.
+__device__ __forceinline__ float max_across_halves(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
 // ---- tiles filled by direct global-to-LDS loads -------------------------------
 // A tile is 64 rows (keys or query rows) of HD bf16, HD = 128 or 64.  A wave's
