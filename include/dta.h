@@ -19,14 +19,17 @@
  *    synchronise it.  The first attention call on a tree (or an explicit
  *    dta_tree_attn_prepare) allocates and uploads the tree's device metadata
  *    (into a block of the library's own pool, by a copy on a stream the library owns; the call
- *    waits for that copy only, never for the caller's streams); later calls
- *    allocate nothing;
+ *    waits for that copy only, never for the caller's streams); later calls for
+ *    that head configuration, of either direction, allocate nothing.  A segment
+ *    call does the same at the first call, of either direction, on its rows;
  *  - tensors are dense row-major [T, H, head_dim] with T = unique tree tokens in
  *    the packed DFS order defined by dta_tree_build;
  *  - a tree may be used from several host threads (its lazily built schedules are
- *    guarded); every attention call also records an event on its stream, which
- *    is how dta_tree_destroy knows when the device copies are free, so a tree
- *    must outlive any captured graph that replays calls made on it.
+ *    guarded, and so are its calls' launches); with every attention call an event
+ *    of the tree completes after the call's last kernel (attached to that kernel,
+ *    or recorded behind it), which is how dta_tree_destroy knows when the device
+ *    copies are free, so a tree must outlive any captured graph that replays
+ *    calls made on it.
  */
 #ifndef DTA_H_
 #define DTA_H_
@@ -203,7 +206,8 @@ int dta_tree_attn_fwd(dta_tree_t* tree, const dta_attn_params_t* params, const v
  *        OVERWRITTEN (each element written exactly once, no atomics).
  *   workspace : device, >= dta_tree_attn_workspace_bytes(tree, params, 1)
  * As for the forward, the first call for a head configuration may build the
- * schedule and allocate / upload the tree's device metadata.
+ * schedule and allocate / upload the tree's device metadata (one schedule serves
+ * both directions, so a forward call has done so).
  */
 int dta_tree_attn_bwd(dta_tree_t* tree, const dta_attn_params_t* params, const void* q,
                       const void* k, const void* v, const void* o, const float* lse,
@@ -216,10 +220,12 @@ int dta_tree_attn_bwd(dta_tree_t* tree, const dta_attn_params_t* params, const v
  * launches one by one.  dta_tree_attn_bwd equals DTA_BWD_ALL.  DTA_BWD_DQ and
  * DTA_BWD_DKDV read what DTA_BWD_DELTA leaves in the workspace (the D values
  * and, in bf16 mode, lse rescaled for the kernels), so the delta stage must have
- * run on the same workspace, o, lse, d_o and softmax_scale before them.  In
- * bf16 mode a call that asks for DTA_BWD_DELTA and DTA_BWD_DQ together computes
- * D inside the dQ launch (no separate pass over o and d_o) and leaves the same
- * values in the workspace; results do not depend on how the stages are grouped.
+ * run on the same workspace, o, lse, d_o and softmax_scale before them.  A call
+ * that asks for DTA_BWD_DELTA and DTA_BWD_DQ together computes D inside the dQ
+ * launch (no separate pass over o and d_o) and leaves the same values in the
+ * workspace, except where dQ and dK/dV share one launch (all three stages on a
+ * small tree): there, and without DTA_BWD_DQ, D is a launch of its own.  Results
+ * do not depend on how the stages are grouped.
  * Outputs of stages that are not selected are not touched (and may be NULL).
  */
 enum { DTA_BWD_DELTA = 1, DTA_BWD_DQ = 2, DTA_BWD_DKDV = 4, DTA_BWD_ALL = 7 };

@@ -8,8 +8,8 @@
 // groups: the groups share out the rows streamed through LDS, 32 each per step, and
 // their results are added in LDS at the end.  Against the forms for large launches
 // (8 row tiles, or 4 key tiles, walking 64 rows per step) a launch has 4 (dK/dV: 2)
-// times as many blocks and each walks a half (dK/dV: an eighth) as many steps, at
-// the price of fewer tiles per copied row.
+// times as many blocks and each walks half as many steps, at the price of fewer
+// tiles per copied row.
 //
 // The same launch does dQ and dK/dV: each alone is a few steps between a launch and
 // its end, and together they fill the chip better.

@@ -364,8 +364,9 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
   }
 }
 
-// D[t,h] = dO[t,h] . O[t,h], as a launch of its own: only when the delta stage is
-// asked for without dQ (otherwise the dQ launch computes it, in the same order).
+// D[t,h] = dO[t,h] . O[t,h], as a launch of its own: before a launch that does dQ and
+// dK/dV together, and when the delta stage is asked for without dQ (otherwise the dQ
+// launch computes it, in the same order).
 template <int HD>
 __global__ __launch_bounds__(256) void delta_f32_kernel(const float* __restrict__ o,
                                                         const float* __restrict__ d_o,

@@ -155,8 +155,8 @@ struct dta_tree {
   int32_t* d_token_kend = nullptr;
   size_t d_kend_cap = 0;
   int kend_device = -1;
-  void* last_use = nullptr;   // hipEvent_t recorded after every launch that reads the device copies
-  bool used = false;          // last_use has been recorded at least once
+  void* last_use = nullptr;   // hipEvent_t that completes after the last launch that reads the device copies
+  bool used = false;          // last_use has been recorded or attached at least once
   std::mutex mu;
 };
 
