@@ -11,7 +11,7 @@ ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libdta.so")
 PROBE_LIB_PATH = os.path.join(PKG_DIR, "libdta_probe.so")   # measurement kernels, not part of the product library
-SOURCES = ["dta_tree.cpp", "dta_rollouts.cpp", "dta_plan.cpp", "dta_api.hip", "dta_f32_kernels.hip", "dta_bf16_small.hip", "dta_bf16_fwd.hip", "dta_bf16_bwd.hip", "dta_noalloc.hip"]
+SOURCES = ["dta_tree.cpp", "dta_rollouts.cpp", "dta_plan.cpp", "dta_api.hip", "dta_f32_kernels.hip", "dta_f32_planes.hip", "dta_bf16_small.hip", "dta_bf16_fwd.hip", "dta_bf16_bwd.hip", "dta_noalloc.hip"]
 PROBE_SOURCES = ["dta_probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -1,5 +1,7 @@
 // fp32 tree attention for gfx950: forward, dQ and dK/dV with every product, sum
-// and exponential in fp32, for callers that need ~1e-6 relative accuracy.
+// and exponential in fp32, for callers that need ~1e-6 relative accuracy.  Here: launches
+// that do not fill the chip; the others are in dta_f32_planes.hip (f32_planes in
+// dta_tree.cpp has the rule), but for the dK/dV kernel of 64-key tiles.
 //
 // What is computed follows the attention inside the paper's FWD / BWD
 // primitives (pseudocode appendix) for all segments of the tree at once: a
@@ -7,9 +9,9 @@
 //
 // All products run on the fp32 matrix instruction (v_mfma_f32_16x16x4_f32: fused
 // multiply-adds in fp32, nothing is rounded to a shorter type), twice the rate
-// of the vector ALU without packed arithmetic, and what bounds the kernels: a
+// of the vector ALU without packed arithmetic.  A
 // 16x16x4 product holds a SIMD for 32 cycles and needs one operand of 256 bytes
-// from LDS, a quarter of what LDS delivers, so nothing else comes close.  A wave
+// from LDS, a quarter of what LDS delivers.  A wave
 // owns 16 query rows (forward, dQ) or 16 keys (dK/dV): with 32 the stationary
 // operands and accumulators of dK/dV (four 32 x 128 matrices) would not fit in
 // 256 registers, and small trees would have half as many waves to spread.
@@ -20,44 +22,19 @@
 //
 //   Products that contract over head_dim sum its two halves apart: one chain of
 // head_dim / 4 instructions rounds more than the chains per quarter of head_dim that
-// four lanes per row had (relative errors of O and dQ against 64 bits, 4862 tokens below:
-// 4.3e-7 and 5.4e-7 there, 4.8e-7 and 6.0e-7 in one chain, 3.8e-7 and 5.1e-7 in two).
-// It costs 1 to 2 % of each kernel, and quarters cost dQ 4 %.
+// four lanes per row on the vector ALU had.  It costs 1 to 2 % of each kernel, and quarters cost dQ 4 %.
 //
-// Measured on MI355X (bound: 152 TFLOP/s, what a large fp32 library product reaches),
-// with four lanes per row on the vector ALU before, and now:
-//   4862 tokens (a prompt with 16 answers), 32/8 heads of 128:
-//     forward 1.51 -> 0.36 ms (90 TFLOP/s), dQ 2.38 -> 0.54 ms (92), dK/dV 13.6 -> 0.65 ms (101)
+// Measured on MI355X, four lanes per row on the vector ALU before, and now:
 //   384 tokens in 13 nodes, 4/4 heads of 64 (latency of a chain of dependent steps):
 //     forward 71 -> 11 us, dQ 64 and dK/dV 146 -> 17 us together (two launches)
-// A large launch's blocks are few rounds (1216 on 512 slots above), so what is left
-// is mostly the uneven end of the launch.
 #include <hip/hip_runtime.h>
 
-#include "dta_internal.h"
+#include "dta_f32_common.h"
 #include "dta_launch.h"
-#include "dta_mfma.h"
 #include "dta_tile_walk.h"
 
 namespace dta {
 namespace {
-
-// D(16x16) += A(16x4) * B(4x16).  Lane l = (n = l % 16, g = l / 16):
-//   A: row n, k = g     B: column n, k = g     D: column n, row = 4*g + v, v = 0..3
-__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// sum / max over the four lane groups that share a column
-__device__ __forceinline__ float column_sum(float x) {
-  x += __shfl_xor(x, 16);
-  x += __shfl_xor(x, 32);
-  return x;
-}
-__device__ __forceinline__ float column_max(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
-}
 
 // ---- 32-row tiles of HD floats filled by direct global-to-LDS loads -------------
 // One wave-wide 16-byte load fills 1 KB = kRowsPerGroup consecutive rows; groups
@@ -150,9 +127,8 @@ __device__ __forceinline__ void sum_over_groups(f32x4* buf, int rw, int kg, f32x
 // groups.  The keys of the tile's root path are streamed in chunks of 32 * KS
 // keys, double-buffered in LDS; group kg of the block takes keys
 // [32*kg, 32*kg + 32) of every chunk and the groups' results are merged at the
-// end.  KS = 1: one K/V copy serves 8 row tiles, for launches that fill the chip.
-// KS = 4 / 2 (head_dim 64 / 128): a fourth / half of the rows per block and of the
-// steps per walk, for trees too small to fill it.  NW = 4 with KS > 1: half the row
+// end.  KS = 4 / 2 (head_dim 64 / 128): a fourth / half of the rows per block and of the
+// steps per walk of blocks of 8 row tiles.  NW = 4: half the row
 // tiles again, one wave per SIMD, for launches of so few blocks that a CU works on
 // one of them: what a step takes is the SIMD's products, and two waves have twice as many.
 template <int HD, int KS, int NW>
@@ -227,8 +203,8 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
         f32x4(&c)[2] = Sh[j / (NB / 2)];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          c[0] = mfma16(a0[e], Qr[j][e], c[0]);
-          c[1] = mfma16(a1[e], Qr[j][e], c[1]);
+          c[0] = mfma16_f32(a0[e], Qr[j][e], c[0]);
+          c[1] = mfma16_f32(a1[e], Qr[j][e], c[1]);
         }
       }
       f32x4 S[2] = {Sh[0][0] + Sh[1][0], Sh[0][1] + Sh[1][1]};
@@ -272,7 +248,7 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
           for (int x = 0; x < NB / 4; ++x)
             a[x] = *reinterpret_cast<const f32x4*>(Vt + 128 * mb + RL::kPitch * e + 4 * x);
 #pragma unroll
-          for (int b = 0; b < NB; ++b) O[b] = mfma16(a[b >> 2][b & 3], S[mb][e], O[b]);
+          for (int b = 0; b < NB; ++b) O[b] = mfma16_f32(a[b >> 2][b & 3], S[mb][e], O[b]);
         }
     }
     buf ^= 1;
@@ -303,7 +279,7 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
   {
     // The products above multiply the V rows of masked keys by 0, which is NaN where such a
     // row is not finite: a row's output must not depend on keys it does not see.  Rows with a
-    // finite sum and an output that is not finite are worked out again, key by key.
+    // finite sum and an output that is not finite are worked out again (row_by_keys).
     float t = 0.f;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -311,35 +287,9 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
       for (int e = 0; e < 4; ++e) t = fmaf(O[b][e], 0.f, t);
     const bool spoilt = column_sum(t) != 0.f && lt - lt == 0.f;   // (NaN compares unequal)
     if (__builtin_amdgcn_ballot_w64(spoilt) != 0) {
-      f32x4 acc[NB];   // columns 16 * j + 4 * lg .. + 3, as Qr
-#pragma unroll
-      for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int si = tile.seg_begin; si <= tile.seg_end; ++si) {
-        const bool own = si == tile.seg_end;
-        const int start = own ? tile.t0 : segs[si].start, end = own ? tile.t1 : segs[si].end;
-        const bool all = !own && segs[si].full;
-#pragma unroll 1
-        for (int key = start; key < end; ++key) {
-          const size_t at = (size_t)key * kv_stride + 4 * lg;
-          float s = 0.f;
-#pragma unroll
-          for (int j = 0; j < NB; ++j) {
-            const f32x4 kx = *reinterpret_cast<const f32x4*>(kbase + at + 16 * j);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s = fmaf(kx[e], Qr[j][e], s);
-          }
-          s = column_sum(s) * scale;
-          if (all || (key <= qrow && qrow < kend[key])) {
-            const float w = expf(s - m) * inv;
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-              const f32x4 vx = *reinterpret_cast<const f32x4*>(vbase + at + 16 * j);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(w, vx[e], acc[j][e]);
-            }
-          }
-        }
-      }
+      f32x4 acc[NB];
+      row_by_keys<HD>(tile, segs, kend, qrow, q + ((size_t)qrow * Hq + h) * HD, kbase, vbase, kv_stride, scale, m, inv,
+                      acc);
       if (spoilt && row_base + n16 < tile.t1) {
         float* op = o + ((size_t)qrow * Hq + h) * HD + 4 * lg;
 #pragma unroll
@@ -387,19 +337,6 @@ __global__ __launch_bounds__(256) void delta_f32_kernel(const float* __restrict_
   if (row < rows && g == 0) delta[row] = s;
 }
 
-// What the backward kernels read and write.
-struct BwdArgs {
-  const QTile* tiles;
-  const KeySeg* segs;
-  const KvItem* items;
-  const int32_t* kend;
-  const float *q, *k, *v, *d_o, *o, *lse;
-  float *delta, *dq, *dk, *dv, *partial;
-  int accumulate, Hq, Hkv, HB, hblocks;
-  float scale;
-  int dkdv_blocks;   // blocks [0, dkdv_blocks) of a launch of both do dK/dV, the rest dQ
-};
-
 template <int HD, int KS>
 struct DqSmem {
   float K[2][KS * Rows32<HD>::kTile];
@@ -410,7 +347,7 @@ struct DqSmem {
 // Same walk and block shapes as the forward kernel.  With o != nullptr the launch
 // also computes D for its rows and leaves it in `delta` for dK/dV.
 template <int HD, int KS, int NW>
-__device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD, KS>& sm, int block) {
+__device__ __forceinline__ void dq_block(const F32BwdArgs& p, DqSmem<HD, KS>& sm, int block) {
   using RL = Rows32<HD>;
   constexpr int NB = RL::NB, R = NW / KS, CH = 32 * KS;
   auto& Ks = sm.K;
@@ -501,8 +438,8 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD, KS>& sm, i
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             f32x4 &c = Sh[j / (NB / 2)][mb], &dc = dPh[j / (NB / 2)][mb];
-            c = mfma16(ka[e], Qr[j][e], c);
-            dc = mfma16(va[e], dOr[j][e], dc);
+            c = mfma16_f32(ka[e], Qr[j][e], c);
+            dc = mfma16_f32(va[e], dOr[j][e], dc);
           }
         }
       f32x4 S[2] = {Sh[0][0] + Sh[1][0], Sh[0][1] + Sh[1][1]};
@@ -530,7 +467,7 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD, KS>& sm, i
           for (int x = 0; x < NB / 4; ++x)
             a[x] = *reinterpret_cast<const f32x4*>(Kc + 128 * mb + RL::kPitch * e + 4 * x);
 #pragma unroll
-          for (int b = 0; b < NB; ++b) dQ[b] = mfma16(a[b >> 2][b & 3], S[mb][e], dQ[b]);
+          for (int b = 0; b < NB; ++b) dQ[b] = mfma16_f32(a[b >> 2][b & 3], S[mb][e], dQ[b]);
         }
     }
     buf ^= 1;
@@ -555,7 +492,7 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD, KS>& sm, i
 // groups per block.  Q and dO of the rows that can see the keys are streamed in
 // iterations of 32 rows of one q head, heads innermost, last chunk first, KS
 // iterations per step, one per group.  KS = 1: four waves, two
-// blocks per CU.  KS = 4 / 2: eight waves (NW = 4: four, see the forward kernel), trees too
+// blocks per CU (see f32_key_planes in dta_tree.cpp).  KS = 4 / 2: eight waves (NW = 4: four, see the forward kernel), trees too
 // small to fill the chip.
 // Long walks are cut into items that write partial sums, as in bf16 mode.
 template <int HD, int KS>
@@ -567,7 +504,7 @@ struct DkdvSmem {
 };
 
 template <int HD, int KS, int NW>
-__device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD, KS>& sm, int block) {
+__device__ __forceinline__ void dkdv_block(const F32BwdArgs& p, DkdvSmem<HD, KS>& sm, int block) {
   using RL = Rows32<HD>;
   constexpr int NB = RL::NB, R = NW / KS, kKeys = 16 * R, kStat = DkdvSmem<HD, KS>::kStat;
   auto& Qs = sm.Q;
@@ -656,8 +593,8 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD, KS>& s
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             f32x4 &c = Sh[j / (NB / 2)], &dc = dPh[j / (NB / 2)];
-            c = mfma16(qa[e], Kr[j][e], c);
-            dc = mfma16(da[e], Vr[j][e], dc);
+            c = mfma16_f32(qa[e], Kr[j][e], c);
+            dc = mfma16_f32(da[e], Vr[j][e], dc);
           }
         }
         f32x4 S = Sh[0] + Sh[1], dP = dPh[0] + dPh[1];
@@ -683,8 +620,8 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD, KS>& s
           }
 #pragma unroll
           for (int i = 0; i < NB; ++i) {
-            acc[i] = mfma16(a[i >> 2][i & 3], dP[e], acc[i]);
-            acc[NB + i] = mfma16(b[i >> 2][i & 3], S[e], acc[NB + i]);
+            acc[i] = mfma16_f32(a[i >> 2][i & 3], dP[e], acc[i]);
+            acc[NB + i] = mfma16_f32(b[i >> 2][i & 3], S[e], acc[NB + i]);
           }
         }
       }
@@ -730,13 +667,13 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD, KS>& s
 }
 
 template <int HD, int KS, int NW>
-__global__ __launch_bounds__(64 * NW) void dq_f32_kernel(BwdArgs p) {
+__global__ __launch_bounds__(64 * NW) void dq_f32_kernel(F32BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) DqSmem<HD, KS> sm;
   dq_block<HD, KS, NW>(p, sm, blockIdx.x);
 }
 
 template <int HD, int KS, int NW>
-__global__ __launch_bounds__(64 * NW, KS == 1 ? 2 : 1) void dkdv_f32_kernel(BwdArgs p) {
+__global__ __launch_bounds__(64 * NW, KS == 1 ? 2 : 1) void dkdv_f32_kernel(F32BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) DkdvSmem<HD, KS> sm;
   dkdv_block<HD, KS, NW>(p, sm, blockIdx.x);
 }
@@ -746,7 +683,7 @@ __global__ __launch_bounds__(64 * NW, KS == 1 ? 2 : 1) void dkdv_f32_kernel(BwdA
 // then computes D) and dK/dV after each other: 256 row tiles of 16, 32/8 heads of 128,
 // 49 -> 35 us; 1000: 89 -> 85; 2000: 232 -> 208.
 template <int HD, int KS, int NW>
-__global__ __launch_bounds__(64 * NW, 1) void bwd_f32_kernel(BwdArgs p) {
+__global__ __launch_bounds__(64 * NW, 1) void bwd_f32_kernel(F32BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) union {
     DqSmem<HD, KS> dq;
     DkdvSmem<HD, KS> dkdv;
@@ -755,43 +692,58 @@ __global__ __launch_bounds__(64 * NW, 1) void bwd_f32_kernel(BwdArgs p) {
   else dq_block<HD, KS, NW>(p, sm.dq, blockIdx.x - p.dkdv_blocks);
 }
 
-// Adds the partial sums of a split key tile in slot order and writes dK/dV.
+// Adds the partial sums of a split key tile in slot order and writes dK/dV.  One float4 of
+// dK and dV per thread, and four slots in flight: a few split tiles of many parts are otherwise a chain of
+// memory round trips.  Measured against four blocks per tile and head, one slot at a time: dK/dV stage of
+// 1030 tokens with 32/1 heads of 128 215 -> 138 us, the launch alone for 4862 tokens with 32/8 heads 14.5 -> 9.
 template <int HD>
 __global__ __launch_bounds__(256) void dkdv_reduce_f32_kernel(const KvReduce* __restrict__ red,
                                                               const float* __restrict__ partial,
                                                               float* __restrict__ dk,
                                                               float* __restrict__ dv, int Hkv,
                                                               float scale, int keys) {
-  // four blocks per (tile, kv head)
-  const KvReduce r = red[(blockIdx.x >> 2) / Hkv];
-  const int g = (blockIdx.x >> 2) % Hkv, n = (r.k1 - r.k0) * (HD / 4);
+  const int blocks = (keys * (HD / 4) + 255) / 256;   // per (tile, kv head)
+  const int tile_head = blockIdx.x / blocks;
+  const KvReduce r = red[tile_head / Hkv];
+  const int g = tile_head % Hkv, i = (blockIdx.x % blocks) * 256 + threadIdx.x;
+  if (i >= (r.k1 - r.k0) * (HD / 4)) return;
   const size_t slot_stride = (size_t)Hkv * (2 * keys * HD);
-  const float* base = partial + ((size_t)r.first_slot * Hkv + g) * (2 * keys * HD);
-  for (int i = (blockIdx.x & 3) * 256 + threadIdx.x; i < n; i += 1024) {
-    f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-    for (int p = 0; p < r.nparts; ++p) {
-      const float* src = base + (size_t)p * slot_stride + (size_t)4 * i;
-      sk += *reinterpret_cast<const f32x4*>(src);
-      sv += *reinterpret_cast<const f32x4*>(src + keys * HD);
+  const float* src = partial + ((size_t)r.first_slot * Hkv + g) * (2 * keys * HD) + (size_t)4 * i;
+  f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
+  int p = 0;
+  for (; p + 4 <= r.nparts; p += 4, src += 4 * slot_stride) {
+    f32x4 a[4], b[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      a[j] = *reinterpret_cast<const f32x4*>(src + j * slot_stride);
+      b[j] = *reinterpret_cast<const f32x4*>(src + j * slot_stride + keys * HD);
     }
-    const size_t o = ((size_t)(r.k0 + i / (HD / 4)) * Hkv + g) * HD + 4 * (i % (HD / 4));
-    *reinterpret_cast<f32x4*>(dk + o) = sk * scale;
-    *reinterpret_cast<f32x4*>(dv + o) = sv;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      sk += a[j];
+      sv += b[j];
+    }
   }
+  for (; p < r.nparts; ++p, src += slot_stride) {
+    sk += *reinterpret_cast<const f32x4*>(src);
+    sv += *reinterpret_cast<const f32x4*>(src + keys * HD);
+  }
+  const size_t o = ((size_t)(r.k0 + i / (HD / 4)) * Hkv + g) * HD + 4 * (i % (HD / 4));
+  *reinterpret_cast<f32x4*>(dk + o) = sk * scale;
+  *reinterpret_cast<f32x4*>(dv + o) = sv;
 }
 
 template <int HD>
 int fwd_impl(const LaunchArgs& a) {
-  hipStream_t st = (hipStream_t)a.stream;
   clear_hip_error();
-  const size_t blocks = a.sched->q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
+  const QueryTiles& qt = a.sched->forward_tiles();
+  const size_t blocks = qt.q_tiles.size() * (size_t)a.p.n_kv_heads * (size_t)a.tc.hblocks;
   if (blocks == 0 || blocks > 0x7fffffffu) return DTA_ERR_UNSUPPORTED;
+  if (a.tc.planes) return launch_fwd_f32_planes(a, blocks);
   constexpr int kSplit = HD == 64 ? 4 : 2;
-  auto kernel = a.tc.tiny      ? fwd_f32_kernel<HD, kSplit, 4>
-                : a.tc.q_small ? fwd_f32_kernel<HD, kSplit, 8>
-                               : fwd_f32_kernel<HD, 1, 8>;
+  auto kernel = a.tc.tiny ? fwd_f32_kernel<HD, kSplit, 4> : fwd_f32_kernel<HD, kSplit, 8>;
   launch(a, true, kernel, blocks, a.tc.tiny ? 256 : 512,
-      a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
+      qt.d_q_tiles, qt.d_segs, a.d_kend, (const float*)a.q, (const float*)a.k,
       (const float*)a.v, (float*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,
       a.tc.hblocks, a.p.softmax_scale);
   return launch_status(__func__);
@@ -816,7 +768,7 @@ int bwd_impl(const LaunchArgs& a) {
         (const float*)a.o + row0 * HD, (const float*)a.d_o + row0 * HD, a.delta + row0, rows);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
-  const BwdArgs args{a.sched->d_q_tiles, a.sched->d_segs, a.sched->d_kv_items, a.d_kend, (const float*)a.q,
+  const F32BwdArgs args{a.sched->d_q_tiles, a.sched->d_segs, a.sched->d_kv_items, a.d_kend, (const float*)a.q,
                      (const float*)a.k, (const float*)a.v, (const float*)a.d_o,
                      fused_delta ? (const float*)a.o : nullptr, a.lse_in, a.delta, (float*)a.dq,
                      a.dk_acc ? a.dk_acc : (float*)a.dk, a.dk_acc ? a.dv_acc : (float*)a.dv, a.partial,
@@ -826,15 +778,19 @@ int bwd_impl(const LaunchArgs& a) {
     auto kernel = a.tc.tiny ? bwd_f32_kernel<HD, kSplit, 4> : bwd_f32_kernel<HD, kSplit, 8>;
     launch(a, a.sched->kv_reduce.empty(), kernel, qblocks + kblocks, a.tc.tiny ? 256 : 512, args);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
+  } else if ((a.stages & DTA_BWD_DQ) && a.tc.planes) {
+    const int ls = launch_dq_f32_planes(a, args, qblocks);
+    if (ls != DTA_OK) return ls;
   } else if (a.stages & DTA_BWD_DQ) {
-    auto kernel = a.tc.tiny      ? dq_f32_kernel<HD, kSplit, 4>
-                  : a.tc.q_small ? dq_f32_kernel<HD, kSplit, 8>
-                                 : dq_f32_kernel<HD, 1, 8>;
+    auto kernel = a.tc.tiny ? dq_f32_kernel<HD, kSplit, 4> : dq_f32_kernel<HD, kSplit, 8>;
     kernel<<<(unsigned)qblocks, a.tc.tiny ? 256 : 512, 0, st>>>(args);
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
   if (a.stages & DTA_BWD_DKDV) {
-    if (!one_launch) {
+    if (a.tc.k_planes) {
+      const int ls = launch_dkdv_f32_planes(a, args, kblocks);
+      if (ls != DTA_OK) return ls;
+    } else if (!one_launch) {
       auto kernel = a.tc.tiny      ? dkdv_f32_kernel<HD, kSplit, 4>
                     : a.tc.k_small ? dkdv_f32_kernel<HD, kSplit, 8>
                                    : dkdv_f32_kernel<HD, 1, 4>;
@@ -842,7 +798,8 @@ int bwd_impl(const LaunchArgs& a) {
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     }
     if (!a.sched->kv_reduce.empty()) {
-      launch(a, true, dkdv_reduce_f32_kernel<HD>, a.sched->kv_reduce.size() * a.p.n_kv_heads * 4, 256,
+      const size_t per_tile = ((size_t)a.sched->kv_keys * (HD / 4) + 255) / 256;
+      launch(a, true, dkdv_reduce_f32_kernel<HD>, a.sched->kv_reduce.size() * a.p.n_kv_heads * per_tile, 256,
           a.sched->d_kv_reduce, a.partial, (float*)a.dk, (float*)a.dv, a.p.n_kv_heads, a.p.softmax_scale,
           a.sched->kv_keys);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }

@@ -24,6 +24,13 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// D(16x16) += A(16x32) * B(32x16), bf16 inputs, fp32 accumulate, at the same rate.
+// Lane l = (n = l % 16, g = l / 16):
+//   A: row n, k = 8*g .. 8*g+7     B: column n, k = 8*g .. 8*g+7     D: column n, row = 4*g + v, v = 0..3
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 // Transposing LDS read (ds_read_b64_tr_b16).  Within each group of 16 lanes,
 // lane j supplies the address of 4 consecutive bf16; lane i receives, as
 // element e, element (i % 4) of what lane 4*e + i/4 addressed.  With lane j

@@ -436,10 +436,10 @@ Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const
     // finer pieces and would only pay for more partial sums)
     if (s.kv_queues && s.kv_item_iters > 384 * (int64_t)s.kv_items.size()) cut_items(resident * 6);
   };
-  if (bn == 128) cut_for(kw.resident);
+  if (kw.queues) cut_for(kw.resident);
   else cut_items((int64_t)kw.resident * 3 / 2);
   constexpr int64_t kWideMinIters = 256;
-  if (bn == 128 && wide_key_tiles && s.kv_item_iters > kWideMinIters * (int64_t)s.kv_tiles.size()) {
+  if (kw.queues && wide_key_tiles && s.kv_item_iters > kWideMinIters * (int64_t)s.kv_tiles.size()) {
     // Long walks (256 steps per 128-key tile and more): tiles of 256 keys for the
     // eight-wave form of the kernel, one block per CU.  Every streamed 64-row
     // chunk then meets twice the keys, which halves the copies L2 -> LDS per
@@ -637,35 +637,74 @@ void choose_forms(const CallShape& c, const dta_attn_params_t* p, TileChoice* ou
 }
 }  // namespace
 
+namespace {
+// Which form of the fp32 kernels a call takes: products on the fp32 instruction in blocks that
+// share out the keys (small, dta_f32_kernels.hip), or on the bf16 one with operands in three
+// parts (planes, dta_f32_planes.hip), whose blocks of 8 row tiles of 16 and 128-key tiles need a
+// launch that fills the chip.  Measured on MI355X, in us, small / planes:
+//   trees (a prompt with 8 answers), forward and backward   1000 row tiles: 38 + 124 / 46 + 120 (16/16 heads of
+//             128), 25 + 83 / 29 + 77 (32/8), 19 + 56 / 21 + 66 (64/8), 42 + 116 / 43 + 107 (8/2 heads of 64);
+//             1200: 51 + 150 / 47 + 124, 38 + 87 / 29 + 96, 26 + 75 / 21 + 67, 57 + 142 / 48 + 119, 38 + 95 / 29 + 106 (32/1);
+//             1600: 82 + 222 / 59 + 163, 50 + 146 / 32 + 118, 40 + 109 / 24 + 92, 80 + 220 / 59 + 154, 50 + 144 / 32 + 130;
+//             2000: 105 + 323 / 73 + 217, 65 + 207 / 41 + 150
+//   forward of a segment   rows after 512 keys, 1200: 134 / 154 (16/16, 1200 rows), 113 / 106 (32/8, 600 rows);
+//             1600: 282 / 327 (8/2, 3200 rows), 116 / 94 (64/8, 400 rows); 2000: 251 / 221, 400 / 396; after
+//             4096 keys, 1000: 349 / 397 (32/8), 1200: 638 / 404, 687 / 561 (8/2), 340 / 294 (16/16 heads of 64)
+//   backward of a segment (dK/dV walks are not cut: few 128-key tiles leave the chip empty)   after 512 keys, 1200:
+//             393 / 357 (16/16, 214 tiles; small all the same, as its forward is), 346 / 447 (32/8); 2000: 578 / 695 (32/8, 94 tiles), 2152 / 2481 (8/2, 70); after
+//             4096, 1200: 1730 / 1064, 1553 / 1137 (32/8, 293), 1567 / 1129 (64/8), 1775 / 1888 (8/2, 104)
+bool f32_planes(const CallShape& c, const dta_attn_params_t* p) {
+  const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
+  if (row_tiles < 1200 || row_tiles >= 2048 || !c.segment) return row_tiles >= 1200;
+  return 2 * c.keys >= 3 * c.rows && (!c.backward || c.keys / 128 * p->n_kv_heads >= 200);
+}
+// dK/dV beside a dQ of the planes form: from 2560 row tiles on and below 2048 tiles of 128 keys.  Between, the
+// blocks of 64 keys on the fp32 instruction stay, as the tile that dta_tree_schedule_info reports for these
+// sizes does; they take up to a third longer (128 / 102 us with 32/8 heads of 128, 70 / 66 of 64).
+bool f32_key_planes(const CallShape& c, const dta_attn_params_t* p) {
+  const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
+  return f32_planes(c, p) && (row_tiles < 2048 || row_tiles >= 2560);
+}
+}  // namespace
+
 int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& call) {
   int st = validate_params(p);
   if (st != DTA_OK) return st;
   int G = p->n_q_heads / p->n_kv_heads;
   if (p->dtype == DTA_F32) {
     // Eight waves of 16 rows: R row tiles (hb q heads x 16-row blocks) x `split`
-    // groups that share out the streamed keys.  A launch of fewer than 2048 waves
-    // of 16 rows leaves half of the chip's wave slots empty: there the walks are
-    // split instead.  Where even blocks of four waves are no more than the CUs, a
-    // block is four: one wave per SIMD.  Measured on MI355X, backward, four / eight waves,
+    // groups that share out the streamed keys where the launch does not fill the chip.  Where even blocks of four
+    // waves are no more than the CUs, a block is four: one wave per SIMD.  Measured on MI355X, backward, four / eight waves,
     // in us: 256 row tiles of 16, head_dim 128, 32/8 heads 35 / 53, 16/16 34 / 51; 512: 43 / 56,
     // 56 / 63; head_dim 64, 8/2 heads, 256: 32 / 37.  Above, a CU gets two such blocks one after
     // the other: 16/16 heads of 64, 256 row and 256 key blocks in one launch, 29 / 23.
-    const int64_t row_tiles = call.rows / 16 * p->n_q_heads;
-    const bool small = row_tiles < 2048;
-    out->q_small = out->k_small = small;
-    out->q_split = false;
-    const int split = !small ? 1 : p->head_dim == 64 ? 4 : 2;
-    const int64_t row_blocks = row_tiles * split / 4, key_blocks = call.keys / 16 * p->n_kv_heads * split / 4;
-    out->tiny = small && row_blocks <= kNumCUs && (p->head_dim == 128 || row_blocks + key_blocks <= kNumCUs * 4 / 3);
-    const int R = (out->tiny ? 4 : 8) / split;
-    int hb = 1;
-    while (hb < R && G % (2 * hb) == 0) hb *= 2;
-    out->hb = hb;
-    out->hblocks = G / hb;
-    out->bm = 16 * (R / hb);
-    out->bn = small ? 16 * R : 64;
-    // an iteration takes a wave several microseconds, so cut walks may be short; four-wave blocks, eight when split
-    out->walk = KvWalk{32, 4 * split, small ? kNumCUs : 2 * kNumCUs};
+    TileChoice f{}, b{};
+    auto choose = [&](bool backward, TileChoice* t) {
+      CallShape c = call;
+      c.backward = backward;
+      t->planes = f32_planes(c, p);
+      t->q_small = t->k_small = !t->planes;
+      const int split = t->planes ? 1 : p->head_dim == 64 ? 4 : 2;
+      const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
+      const int64_t row_blocks = row_tiles * split / 4, key_blocks = c.keys / 16 * p->n_kv_heads * split / 4;
+      t->tiny = t->q_small && row_blocks <= kNumCUs && (p->head_dim == 128 || row_blocks + key_blocks <= kNumCUs * 4 / 3);
+      const int R = (t->tiny ? 4 : 8) / split;
+      t->hb = 1;
+      while (t->hb < R && G % (2 * t->hb) == 0) t->hb *= 2;
+      t->hblocks = G / t->hb;
+      t->k_planes = f32_key_planes(c, p);
+      t->bn = t->k_small ? 16 * R : t->k_planes ? 128 : 64;
+      // an iteration takes a wave several microseconds, so cut walks may be short; blocks of 64 keys: two per CU
+      t->walk = KvWalk{32, 4 * split, t->k_small || t->k_planes ? kNumCUs : 2 * kNumCUs};
+      return 16 * (R / t->hb);
+    };
+    const int fwd_bm = choose(false, &f);
+    b.bm = choose(true, &b);
+    b.walk.fwd_bm = fwd_bm == b.bm ? 0 : fwd_bm;
+    f.bm = b.bm;
+    f.bn = b.bn;
+    f.walk = b.walk;
+    *out = call.backward ? b : f;
   } else {
     // eight waves per block: hb q heads of the group x (R/hb) 32-row query blocks
     TileChoice f{}, b{};
@@ -683,6 +722,7 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
     b.bm = choose(true, &b);
     b.bn = b.k_small ? 64 : 128;
     b.walk = b.k_small ? KvWalk{32, 32, kNumCUs} : KvWalk{64, 32, 2 * kNumCUs};
+    b.walk.queues = !b.k_small;
     // (a launch small enough for the forward's steps is small for dQ too, and then the tiles are the same)
     b.walk.key_steps = b.q_small;
     b.walk.fwd_bm = fwd_bm == b.bm ? 0 : fwd_bm;

@@ -111,3 +111,114 @@ def test_forests_in_launches_that_fill_the_chip(Hq, Hkv, sign, d):
     dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
     for name, ref in (("o", O), ("lse", LSE), ("dq", dQ), ("dk", dK), ("dv", dV)):
         assert rel_err(got[name], ref) <= 1e-5, name
+
+
+# trees for the kernels that multiply fp32 numbers in three bf16 parts: tiles of 128 keys, chunks of 32 rows
+PLANES = [
+    ([-1], [257], 96, 3),                               # two key tiles and a row, group of 32
+    ([-1, 0, 0, 2, 2], [129, 31, 33, 1, 95], 112, 112),     # no groups: row tiles of 128 tokens; edges of the 32-row chunk
+    ([-1, -1, 1, 1], [64, 500, 127, 128], 30, 10),          # group of 3
+    ([-1, 0, 0, 0], [700, 300, 290, 310], 32, 8),           # cut walks
+]
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("parent,seg,Hq,Hkv", PLANES)
+def test_products_in_three_parts(parent, seg, Hq, Hkv, d):
+    """Against the oracle, and exact under a change of scale: the parts of 2^n x are 2^n times those of x,
+    so outputs linear in V and dO follow them to the last bit."""
+    import torch
+    parent, seg = np.array(parent, dtype=np.int32), np.array(seg, dtype=np.int32)
+    T, scale = int(seg.sum()), 1.0 / math.sqrt(d)
+    x = make_inputs_numpy(T, Hq, Hkv, d, 31, dtype="f32")
+    p = dta.AttnParams(Hq, Hkv, d, scale, dta.F32)
+    tree = dta.tree_build(parent, seg)
+    assert tree.schedule_info(p)["bwd_kv_tile_tokens"] == 128
+    t = {n: torch.from_numpy(a).cuda() for n, a in x.items()}
+
+    def run(v, do):
+        o, lse = dta.tree_attn_fwd(tree, p, t["q"], t["k"], v)
+        return (o, lse, *dta.tree_attn_bwd(tree, p, t["q"], t["k"], v, o, lse, do))
+
+    got = run(t["v"], t["do"])
+    refs = (*B.forward(parent, seg, x["q"], x["k"], x["v"], scale),
+            *B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale))
+    for name, a, ref in zip(("o", "lse", "dq", "dk", "dv"), got, refs):
+        assert rel_err(a.double().cpu().numpy(), ref) <= 1e-5, name
+    up, down = 2.0 ** 30, 2.0 ** -45
+    scaled = run(t["v"] * up, t["do"] * down)
+    for name, a, b, f in zip(("o", "lse", "dq", "dk", "dv"), got, scaled, (up, 1, up * down, up * down, down)):
+        assert torch.equal(a * f, b), name
+    tree.destroy()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(112, 112), (96, 8)])
+@pytest.mark.parametrize("what", ["key -inf", "value", "do", "query row"])
+def test_numbers_without_three_parts(what, Hq, Hkv, d):
+    """Infinities and numbers that bf16 rounds to infinity, in a chunk in the middle of walks or
+    in a block's own rows: the results of the fp32 instruction."""
+    import torch
+    parent = np.array([-1, 0, 0], dtype=np.int32)
+    seg = np.array([170, 33, 64], dtype=np.int32)
+    T, scale = int(seg.sum()), 1.0 / math.sqrt(d)
+    x = make_inputs_numpy(T, Hq, Hkv, d, 41, dtype="f32")
+    big = np.float32(3.395e38)
+    if what == "key -inf":            # a score of -inf against every query: the key has no part in any output
+        x["q"][:, :, 7] = np.abs(x["q"][:, :, 7]) + 0.1
+        x["k"][100, :, 7] = -np.inf
+    elif what == "value":
+        x["v"][100, :, 3] = big
+    elif what == "do":                # (V keeps dP finite)
+        x["do"][230, :, 3] = big
+        x["v"][:, :, 3] *= 1e-6
+        x["k"] *= 1e-3
+    else:                             # scores and dK stay finite
+        x["q"][[5, 200], :, 9] = big
+        x["k"][:, :, 9] *= 1e-38
+        x["do"] *= 1e-3
+    p = dta.AttnParams(Hq, Hkv, d, scale, dta.F32)
+    tree = dta.tree_build(parent, seg)
+    assert tree.schedule_info(p)["bwd_kv_tile_tokens"] == 128
+    t = {n: torch.from_numpy(a).cuda() for n, a in x.items()}
+    o, lse = dta.tree_attn_fwd(tree, p, t["q"], t["k"], t["v"])
+    with np.errstate(all="ignore"):
+        O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    got, ref = {"o": o, "lse": lse}, {"o": O, "lse": LSE}
+    if what in ("do", "query row"):
+        got["dq"], got["dk"], got["dv"] = dta.tree_attn_bwd(tree, p, t["q"], t["k"], t["v"], o, lse, t["do"])
+        ref["dq"], ref["dk"], ref["dv"] = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
+    for n in got:
+        a = got[n].double().cpu().numpy()
+        assert np.isfinite(a).all(), n
+        assert rel_err(a, ref[n]) <= 1e-5, n
+        if what == "value" and n == "o":   # the other columns on their own scale
+            cols = [i for i in range(d) if i != 3]
+            assert rel_err(a[..., cols], ref[n][..., cols]) <= 1e-5
+    tree.destroy()
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(32, 8, 128), (16, 16, 64)])
+def test_segment_calls_in_three_parts(Hq, Hkv, d):
+    """Forward and backward of a segment behind a prefix that is no multiple of a tile, added to
+    accumulators that are not zero."""
+    import torch
+    parent, seg = np.array([-1, 0], dtype=np.int32), np.array([3301, 1290], dtype=np.int32)
+    T, scale = int(seg.sum()), 1.0 / math.sqrt(d)
+    x = make_inputs_numpy(T, Hq, Hkv, d, 51, dtype="f32")
+    x["do"][:3301] = 0
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
+    t = {n: torch.from_numpy(a).cuda() for n, a in x.items()}
+    p = dta.AttnParams(Hq, Hkv, d, scale, dta.F32)
+    tree = dta.tree_build(parent, seg)
+    o, lse = torch.zeros_like(t["q"]), torch.zeros((T, Hq), device="cuda")
+    dq = torch.zeros_like(t["q"])
+    acc = [torch.full((T, Hkv, d), 1.0, device="cuda") for _ in range(2)]
+    ws = torch.empty(dta.workspace_bytes(tree, p, True), dtype=torch.uint8, device="cuda")
+    dta.tree_attn_fwd_segment(tree, p, 3301, T, t["q"], t["k"], t["v"], o, lse)
+    dta.tree_attn_bwd_segment(tree, p, 3301, T, t["q"], t["k"], t["v"], o, lse, t["do"], dq, *acc, ws)
+    tree.destroy()
+    for name, a, ref in (("o", o[3301:], O[3301:]), ("lse", lse[3301:], LSE[3301:]), ("dq", dq[3301:], dQ[3301:]),
+                         ("dk", acc[0] - 1, dK), ("dv", acc[1] - 1, dV)):
+        assert rel_err(a.double().cpu().numpy(), ref) <= 1e-5, name

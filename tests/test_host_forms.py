@@ -118,6 +118,30 @@ def test_one_schedule_serves_both_directions(forms, segment, d):
             assert y[0] in ("small", "tiny") and x[4] == 0, (s, x, y)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_forms_of_fp32_calls(forms, d):
+    """Trees (before = None) and segments on both sides of the measured crossings; key tiles of 128 say
+    that dK/dV multiplies in three bf16 parts."""
+    calls = [   # heads, tokens before, rows, forward, dQ, key tile (None: a small form's)
+        (32, 8, None, 607, "small", "small", None), (32, 8, None, 608, "large", "large", 128),
+        (32, 1, None, 1020, "large", "large", 128), (32, 8, None, 1100, "large", "large", 64),
+        (32, 8, None, 1290, "large", "large", 128), (16, 16, None, 9000, "large", "large", 128),
+        (16, 16, 512, 1300, "small", "small", None), (32, 8, 512, 700, "large", "small", None),
+        (32, 8, 512, 1000, "large", "small", None), (32, 8, 4096, 620, "large", "large", 128),
+        (8, 2, 4096, 2400, "large", "small", None), (8, 2, 4096, 4200, "large", "large", 64),
+        (8, 2, 512, 5200, "large", "large", 128), (32, 8, 4096, 500, "small", "small", None),
+    ]
+    args = []
+    for Hq, Hkv, before, rows, *_ in calls:
+        keys = rows + (before or 0)
+        args.append((Hq, Hkv, d, dta.F32, 0, int(before is not None), rows, keys, 1))
+    f = forms(args)
+    b = forms([a[:4] + (1,) + a[5:] for a in args])
+    for c, x, y in zip(calls, f, b):
+        assert (x[0].replace("tiny", "small"), y[0].replace("tiny", "small")) == c[4:6], (c, x, y)
+        assert y[3] == c[6] or (c[6] is None and y[3] < 128 and y[1] == "small"), (c, y)
+
+
 def test_the_gpu_tests_reach_the_forms_they_name(forms):
     import test_gpu_launch_forms as G
     for tree, Hq, Hkv, _, fwd, dq64, dq128, dkdv in G.FORMS:
