@@ -683,39 +683,50 @@ __global__ void zero_i32_kernel(int* __restrict__ p, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
-// Adds the partial sums of a split key tile in slot order and writes dK/dV.
+// Adds the partial sums of a split key tile in slot order and writes dK/dV.  Four elements of dK and of
+// dV per thread, and four slots in flight: a few split tiles of many parts are otherwise a chain of
+// memory round trips.  Measured against eight blocks per tile and head, one slot at a time: 6.3 -> 4.1 us for 2455 tokens
+// with 32/8 heads of 128 (answers of 32-256 tokens).
 template <int HD>
 __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const KvReduce* __restrict__ red,
                                                           const float* __restrict__ partial,
                                                           uint16_t* __restrict__ dk,
                                                           uint16_t* __restrict__ dv, int Hkv,
-                                                          float scale, int kKvTile) {
-  // 8 blocks per (tile, kv head), an eighth of the tile's kKvTile keys each, so that even a handful of split
-  // tiles fills the chip
-  const int sub = blockIdx.x & 7;
-  const KvReduce r = red[(blockIdx.x >> 3) / Hkv];
+                                                          float scale, int keys) {
   constexpr int kHeadDim = HD;
-  const int g = (blockIdx.x >> 3) % Hkv;
-  const size_t slot_stride = (size_t)Hkv * (2 * kKvTile * kHeadDim);
-  const float* base = partial + ((size_t)r.first_slot * Hkv + g) * (2 * kKvTile * kHeadDim);
-  const int key_lo = sub * (kKvTile / 8), key_hi = min(r.k1 - r.k0, key_lo + kKvTile / 8);
-  for (int i = key_lo * (kHeadDim / 4) + threadIdx.x; i < key_hi * (kHeadDim / 4); i += blockDim.x) {
-    const int key = i / (kHeadDim / 4), d4 = i % (kHeadDim / 4);
-    f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-    for (int p = 0; p < r.nparts; ++p) {
-      const float* src = base + (size_t)p * slot_stride + (size_t)key * kHeadDim + 4 * d4;
-      const f32x4 a = *reinterpret_cast<const f32x4*>(src);
-      const f32x4 b = *reinterpret_cast<const f32x4*>(src + kKvTile * kHeadDim);
+  const int blocks = keys * (kHeadDim / 4) / 256;   // per (tile, kv head)
+  const int tile_head = blockIdx.x / blocks;
+  const KvReduce r = red[tile_head / Hkv];
+  const int g = tile_head % Hkv, i = (blockIdx.x % blocks) * 256 + threadIdx.x;
+  const int key = i / (kHeadDim / 4), d4 = i % (kHeadDim / 4);
+  if (key >= r.k1 - r.k0) return;
+  const size_t slot_stride = (size_t)Hkv * (2 * keys * kHeadDim);
+  const float* src = partial + ((size_t)r.first_slot * Hkv + g) * (2 * keys * kHeadDim) + (size_t)4 * i;
+  f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
+  int p = 0;
+  for (; p + 4 <= r.nparts; p += 4, src += 4 * slot_stride) {
+    f32x4 a[4], b[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { sk[e] += a[e]; sv[e] += b[e]; }
+    for (int j = 0; j < 4; ++j) {
+      a[j] = *reinterpret_cast<const f32x4*>(src + j * slot_stride);
+      b[j] = *reinterpret_cast<const f32x4*>(src + j * slot_stride + keys * kHeadDim);
     }
-    bf16x4 rk, rv;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { rk[e] = (__bf16)(sk[e] * scale); rv[e] = (__bf16)sv[e]; }
-    const size_t o = ((size_t)(r.k0 + key) * Hkv + g) * kHeadDim + 4 * d4;
-    *reinterpret_cast<bf16x4*>(dk + o) = rk;
-    *reinterpret_cast<bf16x4*>(dv + o) = rv;
+    for (int j = 0; j < 4; ++j) {
+      sk += a[j];
+      sv += b[j];
+    }
   }
+  for (; p < r.nparts; ++p, src += slot_stride) {
+    sk += *reinterpret_cast<const f32x4*>(src);
+    sv += *reinterpret_cast<const f32x4*>(src + keys * kHeadDim);
+  }
+  bf16x4 rk, rv;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { rk[e] = (__bf16)(sk[e] * scale); rv[e] = (__bf16)sv[e]; }
+  const size_t o = ((size_t)(r.k0 + key) * Hkv + g) * kHeadDim + 4 * d4;
+  *reinterpret_cast<bf16x4*>(dk + o) = rk;
+  *reinterpret_cast<bf16x4*>(dv + o) = rv;
 }
 
 }  // namespace
@@ -801,7 +812,8 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
     }
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     if (!a.sched->kv_reduce.empty()) {
-      launch(a, true, dkdv_reduce_kernel<HD>, a.sched->kv_reduce.size() * a.p.n_kv_heads * 8, 256,
+      const size_t per_tile = (size_t)a.sched->kv_keys * (HD / 4) / 256;   // (tiles are multiples of 64 keys)
+      launch(a, true, dkdv_reduce_kernel<HD>, a.sched->kv_reduce.size() * a.p.n_kv_heads * per_tile, 256,
           a.sched->d_kv_reduce, a.partial, (uint16_t*)a.dk, (uint16_t*)a.dv, a.p.n_kv_heads,
           a.p.softmax_scale, a.sched->kv_keys);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
