@@ -263,8 +263,11 @@ int ensure_device(dta_tree* tree, const dta::TileChoice& tc, const dta_attn_para
   hipStream_t us;
   if ((st = upload_stream(dev, &us)) != DTA_OK) return st;
   if (!tree->last_use) {
+    // (No system-scope fence: the event orders uses of the tree's device copies, which kernels only read,
+    // and nothing else.  With the fence the launch it is attached to ends 2 us later: backward segment calls of 37 rows
+    // on average take 24.2 us one after another, 22.2 without.)
     hipEvent_t ev;
-    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
       (void)hipGetLastError();
       return DTA_ERR_HIP;
     }
