@@ -72,8 +72,8 @@ constexpr int kDqThreads = 512;
 
 // Query-stationary dQ: 8 waves, each 32 query rows of one q head (same walk and
 // wave layout as the forward kernel, kGroups = 2 included: 4 row tiles x 2 groups of
-// waves that take every other chunk).
-template <int HD, int kGroups = 1>
+// waves that take every other chunk; kSkip as there).
+template <int HD, int kGroups = 1, bool kSkip = false>
 __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
     const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs,
     const int32_t* __restrict__ kend, const uint16_t* __restrict__ q,
@@ -235,6 +235,12 @@ __global__ __launch_bounds__(kDqThreads) void dq_bf16_kernel(
     have = next();
     if (have) issue(buf ^ 1);
     if (kGroups == 2 && nn == 0) break;   // the walk's last step has a chunk for the first group only
+    if constexpr (kSkip) {
+      if (need_mask && !wave_sees<1, HD>(kendS[buf], cc0, row_base)) {
+        buf ^= 1;
+        continue;
+      }
+    }
     const uint16_t* Kt = Ks[buf][grp] + rlo;
     const uint16_t* Vt = Vs[buf][grp] + rlo;
     const uint16_t* Kc = Ks[buf][grp] + clo;
@@ -772,7 +778,11 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
       zero_i32_kernel<<<1, 256, 0, st>>>(a.tickets, a.p.n_kv_heads);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     }
-    auto kernel = a.tc.q_split ? dq_bf16_kernel<HD, 2> : dq_bf16_kernel<HD>;
+    // Waves leave out masked chunks that none of their rows sees, with head_dim 64 where that is worth the branch, as
+    // in the forward kernel.  Measured, without / with: two-answer pairs, 16/16 heads of 128 721 / 662 us, of 64 (pass of
+    // dQ) 267 / 257; multi-turn agents, 32/8 heads of 128 7250 / 7220, of 64 4210 / 4250.  (Blocks of two groups lose 7 %.)
+    const bool skip = HD == 128 || (a.tc.hb <= 2 && 10 * a.sched->fwd_masked64 > 3 * a.sched->fwd_chunks64);
+    auto kernel = a.tc.q_split ? dq_bf16_kernel<HD, 2> : skip ? dq_bf16_kernel<HD, 1, true> : dq_bf16_kernel<HD, 1, HD == 128>;
     kernel<<<(unsigned)(draw ? qblocks + qblocks / 4 : qblocks), kDqThreads, 0, st>>>(
         a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
         (const uint16_t*)a.v, (const uint16_t*)a.d_o, a.lse_in,

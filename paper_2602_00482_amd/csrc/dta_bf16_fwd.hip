@@ -34,7 +34,12 @@ constexpr int kThreads = 512;
 // kGroups = 2 (with kCh = 64): a block is 4 row tiles x 2 groups of waves, which take
 // every other chunk of the walk and are merged in LDS at the end: twice the blocks, each
 // half as long, for launches of so few rounds of blocks that the last one decides.
-template <int kCh, int HD, int kGroups = 1>
+//
+// kSkip: a wave leaves out masked chunks of which none of its 32 rows sees a key (what comes after
+// them, or belongs to a neighbouring node that shares the tile).  For tiles of 128 tokens and more (at most two q heads
+// of a group per block), whose row blocks see different keys, where masked chunks are many; the branch itself
+// costs the schedule of the loop 1 to 3 %.
+template <int kCh, int HD, int kGroups = 1, bool kSkip = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fwd_bf16_kernel(
     const QTile* __restrict__ tiles, const KeySeg* __restrict__ segs,
     const int32_t* __restrict__ kend, const uint16_t* __restrict__ q,
@@ -43,6 +48,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     int* __restrict__ tickets, int n_items) {
   using TL = TileLayout<HD>;
   static_assert(kGroups == 1 || kCh == 64, "a group takes one 64-row tile per step");
+  static_assert(kGroups == 1 || !kSkip, "kSkip: for blocks of 8 row tiles");
   constexpr int kSub = kCh / 64, kTileElems = TL::kTileElems, kHeadDim = HD;   // kSub: LDS tiles per group
   constexpr int KS = TL::kSteps, DB = TL::kBlocks;   // k-steps over head_dim, 32-wide output blocks
   __shared__ __attribute__((aligned(1024))) uint16_t Ks[2][kGroups * kSub][kTileElems];
@@ -144,6 +150,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     have = next();
     if (have) issue(buf ^ 1);
     if (kGroups == 2 && nn == 0) break;   // the walk's last step has a chunk for the first group only
+    if constexpr (kSkip) {
+      if (need_mask && !wave_sees<kSub, HD>(kendS[buf], cc0, row_base)) {
+        buf ^= 1;
+        continue;
+      }
+    }
     const uint16_t* Kt = Ks[buf][grp * kSub] + rlo;
     const uint16_t* Vt = Vs[buf][grp * kSub] + clo;
 
@@ -319,9 +331,16 @@ int launch_fwd_bf16(const LaunchArgs& a) {
   // at most 6 % to the keys streamed (measured: 5 % faster at +0.5 %, 1.4 % faster
   // at +5.6 %, 2 % slower at +9.6 %)
   const bool wide = 2 * qt.fwd_chunks128 * 100 <= qt.fwd_chunks64 * 106;
+  // kSkip where more than 30 % of the chunks are masked.  Measured, without / with, by share of masked chunks: 16/16
+  // heads of 128, 79 % 319 / 295 us (short answers), 40 % 333 / 319 (pairs), 36 % 1476 / 1402, 15 % 80.0 / 81.4, 6 %
+  // 344 / 348; 8/4 heads, 61 % 129 / 117, 23 % 154.5 / 156.3, 20 % 650.5 / 651.2, 3 % 203 / 208
+  const bool skip = a.tc.hb <= 2 && 10 * qt.fwd_masked64 > 3 * qt.fwd_chunks64;
   auto kernel = split ? (a.p.head_dim == 128 ? fwd_bf16_kernel<64, 128, 2> : fwd_bf16_kernel<64, 64, 2>)
-                : a.p.head_dim == 128 ? (wide ? fwd_bf16_kernel<128, 128> : fwd_bf16_kernel<64, 128>)
-                                    : (wide ? fwd_bf16_kernel<128, 64> : fwd_bf16_kernel<64, 64>);
+                : a.p.head_dim == 128
+                    ? (skip ? (wide ? fwd_bf16_kernel<128, 128, 1, true> : fwd_bf16_kernel<64, 128, 1, true>)
+                            : (wide ? fwd_bf16_kernel<128, 128> : fwd_bf16_kernel<64, 128>))
+                    : (skip ? (wide ? fwd_bf16_kernel<128, 64, 1, true> : fwd_bf16_kernel<64, 64, 1, true>)
+                            : (wide ? fwd_bf16_kernel<128, 64> : fwd_bf16_kernel<64, 64>));
   launch(a, true, kernel, queues ? (size_t)kNumCUs : blocks, kThreads,
       qt.d_q_tiles, qt.d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
       (const uint16_t*)a.v, (uint16_t*)a.o_out, a.lse_out, a.p.n_q_heads, a.p.n_kv_heads, a.tc.hb,

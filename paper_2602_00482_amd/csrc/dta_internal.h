@@ -95,6 +95,7 @@ struct QueryTiles {
   int64_t fwd_tile_pairs = 0;
   // chunks the query tiles stream when every key interval is cut into pieces of 64 / 128 keys
   int64_t fwd_chunks64 = 0, fwd_chunks128 = 0;
+  int64_t fwd_masked64 = 0;   // ... of 64, those that need the visibility mask
   // device copies, in the schedule's allocation
   QTile* d_q_tiles = nullptr;
   KeySeg* d_segs = nullptr;

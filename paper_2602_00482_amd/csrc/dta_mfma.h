@@ -189,6 +189,20 @@ __device__ __forceinline__ void async_wait_all() {
   asm volatile("" ::: "memory");
 }
 
+// Whether any of the 32 rows from row_lo sees a key of a masked chunk of 64 * kSub keys from c0: `ends` holds the
+// keys' ends of visibility by matrix position (0 for padding).  Uniform over the wave.
+template <int kSub, int HD>
+__device__ __forceinline__ bool wave_sees(const int32_t* ends, int c0, int row_lo) {
+  unsigned l = threadIdx.x;   // (opaque, so that no lane value made from it is kept over the loop)
+  asm volatile("" : "+v"(l));
+  l &= 63;
+  bool any = false;
+#pragma unroll
+  for (int sub = 0; sub < kSub; ++sub)
+    any |= (c0 + 64 * sub + TileLayout<HD>::row_of_pos(l) <= row_lo + 31) & (ends[64 * sub + l] > row_lo);
+  return __builtin_amdgcn_ballot_w64(any) != 0;
+}
+
 // Reads at a lane pointer made from TileLayout<HD>::row_lane_off() / col_lane_off().
 __device__ __forceinline__ bf16x8 tile_row8(const uint16_t* lane_ptr, int mb, int ks) {
   return *reinterpret_cast<const bf16x8*>(lane_ptr + 256 * mb + 16 * ks);

@@ -163,12 +163,14 @@ int64_t order_key(int64_t cost) {
 namespace {
 // adds the chunks a query tile streams, for both chunk sizes of the forward kernel
 void count_chunks(QueryTiles& s, const QTile& qt) {
-  auto add = [&](int64_t len) {
+  auto add = [&](int64_t len, bool full) {
     s.fwd_chunks64 += (len + 63) / 64;
     s.fwd_chunks128 += (len + 127) / 128;
+    if (!full) s.fwd_masked64 += (len + 63) / 64;
   };
-  for (int32_t i = qt.seg_begin; i < qt.seg_end; ++i) add(s.segs[(size_t)i].end - s.segs[(size_t)i].start);
-  add(qt.t1 - qt.t0);
+  for (int32_t i = qt.seg_begin; i < qt.seg_end; ++i)
+    add(s.segs[(size_t)i].end - s.segs[(size_t)i].start, s.segs[(size_t)i].full != 0);
+  add(qt.t1 - qt.t0, false);
 }
 }  // namespace
 

@@ -159,6 +159,8 @@ FORMS = [
     (_forest, 12, 4, -1, "small", "small", "small", "small"),
     (lambda: (np.array([-1] * 5), np.array([3, 70, 1, 64, 65])), 640, 320, 1, "large", "large", "large", "large"),
     (lambda: chain_tree([300, 37, 64, 128]), 256, 64, 1, "large", "large", "large", "large"),
+    # tiles of 256 tokens across two answers: waves leave out chunks of 128 and 64 keys
+    (lambda: (np.array([-1, 0, 0]), np.array([500, 640, 511])), 72, 72, 1, "large", "large", "large", "large"),
 ]
 
 
