@@ -733,13 +733,26 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD>& sm, i
     buf ^= 1;
   }
 
+  // A segment call adds to the caller's accumulators (this block is the only owner of these keys in the
+  // launch): what they hold is read while the groups' sums are added.  Read after each sum it is 2 us
+  // of the 4 between a walk and its end, of 13 us a block lives on short segments.
+  const int col0 = 32 * grp + 4 * hh;
+  const size_t base = ((size_t)kcol * Hkv + g) * HD + col0;
+  const bool adds = dk_acc != nullptr && tile.slot < 0 && grp < DB && kcol < tile.k1;
+  f32x4 old[2][4];
+  if (adds) {
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4)
+        old[half][v4] = *reinterpret_cast<const f32x4*>((half == 0 ? dk_acc : dv_acc) + base + 8 * v4);
+  }
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     f32x16 out;
     sum_over_groups<DB>(reinterpret_cast<float*>(&sm), half == 0 ? dK : dV, kt, grp, out);
     if (grp >= DB) continue;
     const float f = half == 0 ? scale : 1.f;
-    const int col0 = 32 * grp + 4 * hh;
     if (tile.slot >= 0) {   // one of several items of this key tile: fp32 partial sums
       float* dst = p.partial + ((size_t)tile.slot * Hkv + g) * (2 * kKeys * HD) +
                  (size_t)(half * kKeys + 32 * kt + c) * HD + col0;
@@ -748,12 +761,11 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD>& sm, i
         *reinterpret_cast<f32x4*>(dst + 8 * v4) =
             f32x4{out[4 * v4], out[4 * v4 + 1], out[4 * v4 + 2], out[4 * v4 + 3]};
     } else if (kcol < tile.k1) {
-      const size_t base = ((size_t)kcol * Hkv + g) * HD + col0;
-      if (dk_acc != nullptr) {   // segment call: this block is the only owner of these keys in this launch
+      if (adds) {
         float* dst = (half == 0 ? dk_acc : dv_acc) + base;
 #pragma unroll
         for (int v4 = 0; v4 < 4; ++v4) {
-          f32x4 r = *reinterpret_cast<const f32x4*>(dst + 8 * v4);
+          f32x4 r = old[half][v4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) r[e] += out[4 * v4 + e] * f;
           *reinterpret_cast<f32x4*>(dst + 8 * v4) = r;
