@@ -266,16 +266,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     bool full;
     wk.mine(k0, nk, full);
     const bool need_mask = !full || nk < kSub;
+    const uint16_t* Kt = sm.K[buf] + rlo;
+    const uint16_t* Vt = sm.V[buf] + clo;
+    bf16x8 a[KS];   // (read before the copies are issued, whose addresses take a while to work out)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) a[ks] = tile_row8(Kt, 0, ks);
     wk.have = wk.advance();
     if (wk.have) wk.issue(sm.K[buf ^ 1], sm.V[buf ^ 1], kendS[buf ^ 1], kend, kbase, vbase, kv_bytes);
     if (nk > 0) {
-      const uint16_t* Kt = sm.K[buf] + rlo;
-      const uint16_t* Vt = sm.V[buf] + clo;
       f32x16 S;
 #pragma unroll
       for (int e = 0; e < 16; ++e) S[e] = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) S = mfma32(tile_row8(Kt, 0, ks), Qr[ks], S);
+      for (int ks = 0; ks < KS; ++ks) S = mfma32(a[ks], Qr[ks], S);
       if (need_mask) {   // (kendS is only filled if some piece of the step is not full)
         const int last = min(nk - 1, qrow - k0), no_end = full ? 0x7fffffff : 0;
 #pragma unroll
@@ -452,17 +455,20 @@ __device__ __forceinline__ void dq_block(const BwdArgs& p, DqSmem<HD>& sm, int b
     bool full;
     wk.mine(k0, nk, full);
     const bool need_mask = !full || nk < kSub;
+    const uint16_t* Kt = sm.K[buf] + rlo;
+    const uint16_t* Vt = sm.V[buf] + rlo;
+    const uint16_t* Kc = sm.K[buf] + clo;
+    bf16x8 a[KS];   // (read before the copies are issued, as in the forward kernel)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) a[ks] = tile_row8(Kt, 0, ks);
     wk.have = wk.advance();
     if (wk.have) wk.issue(sm.K[buf ^ 1], sm.V[buf ^ 1], kendS[buf ^ 1], kend, kbase, vbase, kv_bytes);
     if (nk > 0) {
-      const uint16_t* Kt = sm.K[buf] + rlo;
-      const uint16_t* Vt = sm.V[buf] + rlo;
-      const uint16_t* Kc = sm.K[buf] + clo;
       f32x16 S, dP;
 #pragma unroll
       for (int e = 0; e < 16; ++e) { S[e] = nlse; dP[e] = ndlt; }
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) S = mfma32(tile_row8(Kt, 0, ks), Qr[ks], S);
+      for (int ks = 0; ks < KS; ++ks) S = mfma32(a[ks], Qr[ks], S);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) dP = mfma32(tile_row8(Vt, 0, ks), dOr[ks], dP);
 #pragma unroll
@@ -653,30 +659,36 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD>& sm, i
     const int my_it = it + grp;
     const int r0 = grp == 0 ? row[0] : grp == 1 ? row[1] : grp == 2 ? row[2] : row[3];
     const int nv = min(kSub, tile.q_end - r0);
+    const uint16_t* Qt = sm.Q[buf] + rlo;
+    const uint16_t* dOt = sm.dO[buf] + rlo;
+    const uint16_t* Qc = sm.Q[buf] + clo;
+    const uint16_t* dOc = sm.dO[buf] + clo;
+    const float* stat = &sm.stat[buf][0][kSub * grp + 4 * hh];
+    // operand reads run two products ahead (the first ones before the copies are issued, as in the forward
+    // kernel); the barriers bound their registers
+    constexpr int kAhead = 2;
+    bf16x8 a[KS];
+#pragma unroll
+    for (int ks = 0; ks < kAhead; ++ks) a[ks] = tile_row8(Qt, 0, ks);
+    f32x16 S, dP;
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) {
+      const f32x4 ls = *reinterpret_cast<const f32x4*>(stat + 8 * e4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) S[4 * e4 + j] = ls[j];
+    }
     if (it + kGroupsOfWaves < total) {
       advance(it + kGroupsOfWaves);
       issue(buf ^ 1);
     }
     if (my_it < total && r0 + nv > wave_lo && r0 < wave_hi) {
       const bool need_mask = !(r0 >= tile.k1 && r0 + kSub <= tile.q_full_end);
-      const uint16_t* Qt = sm.Q[buf] + rlo;
-      const uint16_t* dOt = sm.dO[buf] + rlo;
-      const uint16_t* Qc = sm.Q[buf] + clo;
-      const uint16_t* dOc = sm.dO[buf] + clo;
-      const float* stat = &sm.stat[buf][0][kSub * grp + 4 * hh];
-      f32x16 S, dP;
 #pragma unroll
       for (int e4 = 0; e4 < 4; ++e4) {
-        const f32x4 ls = *reinterpret_cast<const f32x4*>(stat + 8 * e4);
         const f32x4 dl = *reinterpret_cast<const f32x4*>(stat + kStep + 8 * e4);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { S[4 * e4 + j] = ls[j]; dP[4 * e4 + j] = dl[j]; }
+        for (int j = 0; j < 4; ++j) dP[4 * e4 + j] = dl[j];
       }
-      // operand reads run two products ahead; the barriers bound their registers
-      constexpr int kAhead = 2;
-      bf16x8 a[KS];
-#pragma unroll
-      for (int ks = 0; ks < kAhead; ++ks) a[ks] = tile_row8(Qt, 0, ks);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         if (ks + kAhead < KS) a[ks + kAhead] = tile_row8(Qt, 0, ks + kAhead);
