@@ -13,6 +13,7 @@ import numpy as np
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdta.so")
 _lib = None
+_torch_calls = None
 
 F32, BF16 = 0, 1
 
@@ -137,9 +138,27 @@ def load_library():
     return lib
 
 
+def _calls():
+    """dta_torch.so: the attention calls on plain torch tensors, made without the
+    interpreter between their parts.  Its functions return None where they do not
+    know an argument; the wrappers below then make the call, or raise the error."""
+    global _torch_calls
+    if _torch_calls is None:
+        import torch  # noqa: F401  (its libraries have to be there first)
+        load_library()
+        from . import dta_torch
+        _torch_calls = dta_torch
+    return _torch_calls
+
+
 def _check(status: int, where: str):
     if status != 0:
         raise DtaError(status, where)
+
+
+def _known(tree, params):
+    """Handle of the tree if the compiled calls may read it and the parameters."""
+    return type(tree) is Tree and type(params) is AttnParams and tree._h is not None and tree._h.value
 
 
 class Tree:
@@ -253,6 +272,13 @@ def _shapes(T, params):
 
 def tree_attn_fwd(tree: Tree, params: AttnParams, q, k, v, o=None, lse=None, workspace=None):
     """dta_tree_attn_fwd on torch's current stream.  Returns (o, lse)."""
+    h = _known(tree, params)
+    if h:
+        res = _calls().fwd(h, C.addressof(params), tree.n_tokens, q, k, v, o, lse, workspace)
+        if type(res) is tuple:
+            return res
+        if res is not None:
+            _check(res, "dta_tree_attn_fwd")
     import torch
     dt = torch.float32 if params.dtype == F32 else torch.bfloat16
     _check_tree_tokens(tree, q)
@@ -290,6 +316,13 @@ def tree_attn_bwd(tree: Tree, params: AttnParams, q, k, v, o, lse, d_o, dq=None,
                   workspace=None, stages: int = BWD_ALL):
     """dta_tree_attn_bwd (or dta_tree_attn_bwd_stages when `stages` selects a
     subset) on torch's current stream.  Returns (dq, dk, dv)."""
+    h = stages == BWD_ALL and _known(tree, params)
+    if h:
+        res = _calls().bwd(h, C.addressof(params), tree.n_tokens, q, k, v, o, lse, d_o, dq, dk, dv, workspace)
+        if type(res) is tuple:
+            return res
+        if res is not None:
+            _check(res, "dta_tree_attn_bwd")
     import torch
     dt = torch.float32 if params.dtype == F32 else torch.bfloat16
     _check_tree_tokens(tree, q)
@@ -352,6 +385,11 @@ def tree_attn_bwd_noalloc(tree: Tree, params: AttnParams, q, k, v, o, lse, d_o, 
 def tree_attn_fwd_segment(tree: Tree, params: AttnParams, t_begin: int, t_end: int, q, k, v, o, lse):
     """dta_tree_attn_fwd_segment on torch's current stream: fills rows
     [t_begin, t_end) of the full-size o and lse."""
+    h = _known(tree, params)
+    if h:
+        st = _calls().fwd_segment(h, C.addressof(params), tree.n_tokens, t_begin, t_end, q, k, v, o, lse)
+        if st is not None:
+            return _check(st, "dta_tree_attn_fwd_segment")
     import torch
     dt = torch.float32 if params.dtype == F32 else torch.bfloat16
     _check_tree_tokens(tree, q)
@@ -372,6 +410,12 @@ def tree_attn_bwd_segment(tree: Tree, params: AttnParams, t_begin: int, t_end: i
                           dq, dk_acc, dv_acc, workspace):
     """dta_tree_attn_bwd_segment on torch's current stream: writes rows
     [t_begin, t_end) of dq and adds into the fp32 accumulators dk_acc, dv_acc."""
+    h = _known(tree, params)
+    if h:
+        st = _calls().bwd_segment(h, C.addressof(params), tree.n_tokens, t_begin, t_end, q, k, v, o, lse, d_o,
+                                  dq, dk_acc, dv_acc, workspace)
+        if st is not None:
+            return _check(st, "dta_tree_attn_bwd_segment")
     import torch
     dt = torch.float32 if params.dtype == F32 else torch.bfloat16
     _check_tree_tokens(tree, q)

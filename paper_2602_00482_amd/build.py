@@ -1,9 +1,11 @@
-"""Builds libdta.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc."""
+"""Builds libdta.so (HIP kernels + C ABI) in-tree for gfx950 with hipcc, and dta_torch.so (its calls on torch
+tensors, host code only) with the C++ compiler."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -13,6 +15,7 @@ LIB_PATH = os.path.join(PKG_DIR, "libdta.so")
 PROBE_LIB_PATH = os.path.join(PKG_DIR, "libdta_probe.so")   # measurement kernels, not part of the product library
 SOURCES = ["dta_tree.cpp", "dta_rollouts.cpp", "dta_plan.cpp", "dta_api.hip", "dta_f32_kernels.hip", "dta_f32_planes.hip", "dta_bf16_small.hip", "dta_bf16_fwd.hip", "dta_bf16_bwd.hip", "dta_noalloc.hip"]
 PROBE_SOURCES = ["dta_probe.hip"]
+TORCH_PATH = os.path.join(PKG_DIR, "dta_torch.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-x", "hip",
@@ -34,16 +37,39 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _compile_torch() -> str:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    obj = os.path.join(CSRC, "dta_torch.o")
+    inc = [f for d in include_paths("cuda") + [sysconfig.get_paths()["include"]] for f in ("-isystem", d)]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+           "-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, "dta_torch.cpp"), "-o", obj]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("compiling dta_torch.cpp failed:\n" + res.stderr)
+    return obj
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link libdta.so and libdta_probe.so; returns the
+    """Compile every source and link libdta.so, libdta_probe.so and dta_torch.so; returns the
     path of libdta.so."""
     with ThreadPoolExecutor(max_workers=8) as pool:
+        torch_obj = pool.submit(_compile_torch)
         objs = list(pool.map(lambda s: _compile(s, verbose), SOURCES + PROBE_SOURCES))
     for out, group in ((LIB_PATH, objs[:len(SOURCES)]), (PROBE_LIB_PATH, objs[len(SOURCES):])):
         cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *group, "-o", out]
         res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError("link failed:\n" + res.stderr)
+    import torch
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    # libdta.so beside it; torch's own libraries are loaded by the `import torch` that comes first
+    cmd = [os.environ.get("CXX", "g++"), "-shared", "-fPIC", torch_obj.result(), "-o", TORCH_PATH, "-L", PKG_DIR, "-l:libdta.so",
+           "-Wl,-rpath,$ORIGIN", "-L", torch_lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("link failed:\n" + res.stderr)
     return LIB_PATH
 
 
@@ -51,7 +77,7 @@ def _stale() -> bool:
     """True when a source or header is newer than the built library (work-list
     records are shared between separately compiled host and device objects, so a
     half-rebuilt or outdated library must never be loaded)."""
-    built = min(os.path.getmtime(LIB_PATH), os.path.getmtime(PROBE_LIB_PATH))
+    built = min(os.path.getmtime(f) for f in (LIB_PATH, PROBE_LIB_PATH, TORCH_PATH))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith((".hip", ".cpp", ".h"))]
     deps += [os.path.join(ROOT, "include", h) for h in ("dta.h", "dta_probe.h")]
     return any(os.path.getmtime(d) > built for d in deps)
@@ -61,7 +87,7 @@ def ensure_built() -> str:
     """Build if no library is there or a source is newer than it (tests, the smoke
     run and the benchmark call this).  On a machine without the compiler a library
     that is there is used as it is."""
-    if not (os.path.exists(LIB_PATH) and os.path.exists(PROBE_LIB_PATH)):
+    if not all(os.path.exists(f) for f in (LIB_PATH, PROBE_LIB_PATH, TORCH_PATH)):
         return build()
     if _stale() and os.path.exists(HIPCC):
         return build()
