@@ -1,4 +1,5 @@
-"""ctypes binding for include/dta.h: argument marshalling only.
+"""Binding for include/dta.h: argument marshalling only, with ctypes, and for
+the attention calls on plain torch tensors in C++ (csrc/dta_torch.cpp).
 
 Function names mirror the C ABI (dta_tree_build -> tree_build, ...).  Tensors
 are torch tensors used purely as device memory; the current torch stream is

@@ -17,7 +17,10 @@
 // Measured on MI355X, head_dim 128, against the other forms (dta_tree.cpp has the
 // rule that chooses and more figures): forward of 512 tokens, 32/8 heads, 18.3 -> 14.5 us,
 // backward 100 -> 34; a 192-row segment under 2048 keys, 64/8 heads, forward 67 -> 35 us,
-// backward 147 -> 75; under 8192 keys forward 204 -> 98, backward 401 -> 236.  What is left
+// backward 147 -> 75; under 8192 keys forward 204 -> 98, backward 401 -> 236.  With a step's first
+// operands read before the next step's copies are issued, and a segment's accumulators read while the groups' sums
+// are added, the calls of a leaf-order plan (short segments) take 11.0 us forward (11.3 before) and 14.6 us
+// backward (17.1).  What is left
 // is about 7 us from launch to store and 1.3 us per step of 128 streamed rows, a
 // third of the matrix rate: one wave's chain of products, softmax, products, with
 // only one other wave on its SIMD.
