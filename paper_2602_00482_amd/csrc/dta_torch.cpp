@@ -16,6 +16,8 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cxxabi.h>
+
 #include <algorithm>
 
 #include "dta.h"
@@ -77,7 +79,8 @@ struct Unlocked {
   PyThreadState* state = PyEval_SaveThread();
   Unlocked() = default;
   Unlocked(const Unlocked&) = delete;
-  ~Unlocked() { PyEval_RestoreThread(state); }
+  // (a thread that asks for the lock after the interpreter has ended is unwound from here)
+  ~Unlocked() noexcept(false) { PyEval_RestoreThread(state); }
 };
 
 // The caller's output (its object is returned), or a new tensor.
@@ -107,6 +110,8 @@ template <class Body>
 PyObject* guarded(Body body) {
   try {
     return body();
+  } catch (abi::__forced_unwind&) {
+    throw;
   } catch (...) {
     PyErr_Clear();
     Py_RETURN_NONE;
