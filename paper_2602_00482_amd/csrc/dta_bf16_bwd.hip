@@ -615,12 +615,12 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void dkdv_bf16_kernel(
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    // Half a chunk (32 consecutive rows) that none of this wave's keys can see contributes nothing (wave-uniform).
-    // Against whole chunks of rows that lie four apart in the halves: two-answer pairs, 16/16 heads 745 -> 707 us, a
-    // prompt with 16 answers 985 -> 960, multi-turn agents 9681 -> 9547, the mixed forest 20.1 -> 19.9 ms.
-    auto seen = [&](int mq) { return r0 + min(32 * mq + 32, nv) > wave_lo && r0 + 32 * mq < wave_hi && 32 * mq < nv; };
-    if (seen(0)) half(std::integral_constant<int, 0>{});
-    if (seen(1)) half(std::integral_constant<int, 1>{});
+    // a chunk none of this wave's keys can see contributes nothing (wave-uniform)
+    const bool wave_sees = r0 + nv > wave_lo && r0 < wave_hi;
+    if (wave_sees) {
+      half(std::integral_constant<int, 0>{});
+      half(std::integral_constant<int, 1>{});
+    }
   };
   for (int it = tile.it_begin; it < total; it += 2) {
     step(it, std::integral_constant<int, 0>{});

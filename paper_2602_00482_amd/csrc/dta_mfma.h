@@ -61,14 +61,12 @@ __device__ __forceinline__ float max_across_halves(float x) {
 // ---- tiles filled by direct global-to-LDS loads -------------------------------
 // A tile is 64 rows (keys or query rows) of HD bf16, HD = 128 or 64.  A wave's
 // 16-byte direct loads land in 1 KB of consecutive LDS = 4 rows of 128 (8 rows of
-// 64) bf16, so padding is only possible between such groups of rows.  Half of a group's
-// rows come from the tile's first 32 rows, half from the others.  Bank
+// 64) bf16, so padding is only possible between such groups of rows.  Bank
 // conflicts are avoided by choosing WHICH tile row each matrix position uses: the
 // matrix products only need keys (or query rows) to sit at consistent positions,
 // not in order.  With sigma(y) = 4 * (y & 3) + (y >> 2), position x (0..63) uses
 //     HD = 128:  group sigma(x & 15),      row (x >> 4) of the group's 4
 //     HD = 64 :  group sigma(x & 15) & 7,  row (sigma(x & 15) >> 3) + 2 * (x >> 4) of its 8
-// (so that 32-position block mb is the tile's rows 32 * mb .. + 31, and can be left out by itself)
 // and group g starts at g * 1040 bytes.  Then the 16 lanes of one pass of a
 // 16-byte row read touch 16 different 16-byte bank offsets, the 4 rows of one pass
 // of a transposing read (32 lanes: 4 rows x 64 bytes) sit 64 bytes of bank offset
@@ -88,14 +86,14 @@ struct TileLayout {
   static constexpr int kBlocks = HD / 32;                   // 32-wide output blocks along HD
 
   __device__ __forceinline__ static int row_of_pos(int x) {
-    const int s = sigma16(x & 15), i = (x >> 4) & 1;
-    return 32 * (x >> 5) + (HD == 128 ? 2 * s + i : 4 * (s & 7) + (s >> 3) + 2 * i);
+    const int s = sigma16(x & 15);
+    return HD == 128 ? 4 * s + (x >> 4) : 8 * (s & 7) + (s >> 3) + 2 * (x >> 4);
   }
   // For lane half hh, accumulator value e (0..15) of 32-position block mb holds
   // position 32*mb + 8*(e/4) + 4*hh + e%4, i.e. tile row
   __device__ __forceinline__ static constexpr int row_of_acc(int mb, int e, int hh) {
-    return 32 * mb + (HD == 128 ? 8 * (e & 3) + 4 * ((e >> 2) & 1) + 2 * hh + (e >> 3)
-                                : 16 * (e & 1) + 8 * ((e >> 2) & 1) + 4 * hh + ((e >> 1) & 1) + 2 * (e >> 3));
+    return HD == 128 ? 16 * (e & 3) + 8 * ((e >> 2) & 1) + 4 * hh + 2 * mb + (e >> 3)
+                     : 32 * (e & 1) + 16 * ((e >> 2) & 1) + 8 * hh + ((e >> 1) & 1) + 4 * mb + 2 * (e >> 3);
   }
   // element offset of position x's row inside a tile
   __device__ __forceinline__ static int pos_off(int x) {
@@ -140,19 +138,17 @@ __device__ __forceinline__ void tile_async_load(uint16_t* tile, const uint16_t* 
   const uint32_t base_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base_bits >> 32));
   const uint32_t base_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base_bits);
   const uint64_t sbase = ((uint64_t)base_hi << 32) | (uint64_t)base_lo;
-  // lane part of the address for a full tile: row (l >> kRowShift) of a group, half of them from the tile's rows
-  // 32 .., 16-byte piece l & kPieceMask
-  constexpr int kHalfGroup = TL::kRowsPerGroup / 2;
-  const int lane_row = (l >> kRowShift) % kHalfGroup + 32 * ((l >> kRowShift) / kHalfGroup);
-  const uint32_t lane_off = (uint32_t)lane_row * stride_bytes + (l & kPieceMask) * 16;
+  // lane part of the address for a full tile: row (l >> kRowShift) of a group, 16-byte piece l & kPieceMask
+  const uint32_t lane_off = (uint32_t)(l >> kRowShift) * stride_bytes + (l & kPieceMask) * 16;
 #pragma unroll
   for (int p = 0; p < TL::kGroups / NW; ++p) {
     const int grp = w + NW * p;
-    uint64_t gbase = sbase + (uint64_t)(kHalfGroup * grp) * stride_bytes;   // scalar
+    uint64_t gbase = sbase + (uint64_t)(TL::kRowsPerGroup * grp) * stride_bytes;   // scalar
     uint32_t voff = lane_off;
     if (nvalid < 64) {   // ragged tail of an interval (uniform branch)
       gbase = sbase;
-      voff = (uint32_t)min(kHalfGroup * grp + lane_row, nvalid - 1) * stride_bytes + (l & kPieceMask) * 16;
+      voff = (uint32_t)min(TL::kRowsPerGroup * grp + (l >> kRowShift), nvalid - 1) * stride_bytes +
+             (l & kPieceMask) * 16;
     }
     // Written as inline assembly on purpose: for the builtin form the compiler
     // drains every outstanding load before the next LDS read, which would undo

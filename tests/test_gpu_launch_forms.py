@@ -161,7 +161,7 @@ FORMS = [
     (lambda: chain_tree([300, 37, 64, 128]), 256, 64, 1, "large", "large", "large", "large"),
     # tiles of 256 tokens across two answers: waves leave out chunks of 128 and 64 keys
     (lambda: (np.array([-1, 0, 0]), np.array([500, 640, 511])), 72, 72, 1, "large", "large", "large", "large"),
-    # answers that end at and beside 32 rows: waves of dK/dV leave out either half of a chunk
+    # answers that end at and beside 32 rows
     (lambda: (np.array([-1] + [0] * 8), np.array([96, 31, 33, 32, 1, 65, 97, 64, 30])), 384, 192, -1,
      "large", "large", "large", "large"),
 ]
