@@ -782,7 +782,7 @@ __device__ __forceinline__ void dkdv_block(const BwdArgs& p, DkdvSmem<HD>& sm, i
         for (int v4 = 0; v4 < 4; ++v4) {
           f32x4 r = old[half][v4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) r[e] += out[4 * v4 + e] * f;
+          for (int e = 0; e < 4; ++e) r[e] = fmaf(out[4 * v4 + e], f, r[e]);   // (one rounding)
           *reinterpret_cast<f32x4*>(dst + 8 * v4) = r;
         }
       } else {

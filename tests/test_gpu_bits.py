@@ -19,6 +19,9 @@ CASES = {   # name: parent, seg_len, q heads, kv heads, head_dim
     "chain": ([-1, 0, 1, 2], [300, 37, 64, 128], 256, 64, 128),
     "two groups": ([-1, 0, 0], [700, 500, 311], 32, 8, 128),
     "long walks": ([-1, 0, 0], [4500, 700, 811], 16, 2, 64),
+    # the executors' calls, a push and a pop per node
+    "segments small": ([-1, 0, 0], [70, 33, 5], 8, 2, 128),
+    "segments": ([-1, 0, 0], [1100, 700, 33], 32, 8, 128),
 }
 
 
@@ -31,8 +34,19 @@ def digests(name):
     q, k, v, do = (torch.from_numpy(x[n]).cuda().to(torch.bfloat16) for n in ("q", "k", "v", "do"))
     p = dta.AttnParams(Hq, Hkv, d, 1.0 / math.sqrt(d), dta.BF16)
     tree = dta.tree_build(np.array(parent, dtype=np.int32), np.array(seg, dtype=np.int32))
-    o, lse = dta.tree_attn_fwd(tree, p, q, k, v)
-    out = (o, lse, *dta.tree_attn_bwd(tree, p, q, k, v, o, lse, do))
+    if name.startswith("segments"):
+        o, lse, dq = torch.zeros_like(q), torch.zeros(q.shape[:2], device="cuda"), torch.zeros_like(q)
+        acc = [torch.zeros(k.shape, device="cuda") for _ in range(2)]
+        ws = torch.empty(dta.workspace_bytes(tree, p, True), dtype=torch.uint8, device="cuda")
+        ends = np.cumsum(seg)
+        for n, end in zip(seg, ends):
+            dta.tree_attn_fwd_segment(tree, p, int(end - n), int(end), q, k, v, o, lse)
+        for n, end in zip(seg[::-1], ends[::-1]):
+            dta.tree_attn_bwd_segment(tree, p, int(end - n), int(end), q, k, v, o, lse, do, dq, *acc, ws)
+        out = (o, lse, dq, *acc)
+    else:
+        o, lse = dta.tree_attn_fwd(tree, p, q, k, v)
+        out = (o, lse, *dta.tree_attn_bwd(tree, p, q, k, v, o, lse, do))
     torch.cuda.synchronize()
     tree.destroy()
     return [hashlib.sha256(t.contiguous().view(torch.uint8).cpu().numpy().tobytes()).hexdigest()[:16] for t in out]
