@@ -139,8 +139,8 @@ template <int HD>
 struct OwnRows {
   using PT = PlaneTile<HD>;
   bf16x8 p[kPlanes][PT::KS];
-  // `row`: this lane's row; false if it has no planes (see kNoPlanes)
-  __device__ __forceinline__ bool load(const float* row) {
+  // `row`: this lane's row, times `sign` (1 or -1); false if it has no planes (see kNoPlanes)
+  __device__ __forceinline__ bool load(const float* row, float sign = 1.f) {
     const int lg = (threadIdx.x >> 4) & 3;
     float big = 0.f;
 #pragma unroll
@@ -148,7 +148,7 @@ struct OwnRows {
       Frag f[kPlanes];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const f32x4 x = *reinterpret_cast<const f32x4*>(row + PT::k_off(lg) + 8 * ks + 4 * i);
+        const f32x4 x = *reinterpret_cast<const f32x4*>(row + PT::k_off(lg) + 8 * ks + 4 * i) * sign;
 #pragma unroll
         for (int e = 0; e < 4; e += 2) {
           uint32_t s[kPlanes];
@@ -463,10 +463,11 @@ struct Walk {
   __device__ __forceinline__ bool mine() const { return row_base + n16 < tile.t1; }
 };
 
-// The online softmax of a chunk, in powers of two: S, scaled by softmax_scale * log2 e, becomes the
-// probabilities relative to the running maximum m.
+// The online softmax of a chunk: S becomes the probabilities relative to the running maximum m.  Both are
+// products of q and k, not scaled yet: only differences are multiplied by `scale2` (> 0, softmax_scale times log2 e),
+// so that its rounding does not grow with the scores, and LSE is one rounding from m.
 template <int DB>
-__device__ __forceinline__ void softmax_step(f32x4 (&S)[2], float& m, float& lsum, f32x4 (&O)[DB]) {
+__device__ __forceinline__ void softmax_step(f32x4 (&S)[2], float& m, float& lsum, f32x4 (&O)[DB], float scale2) {
   float mx = -INFINITY;
 #pragma unroll
   for (int b = 0; b < 2; ++b)
@@ -474,14 +475,14 @@ __device__ __forceinline__ void softmax_step(f32x4 (&S)[2], float& m, float& lsu
     for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[b][e]);
   const float mnew = fmaxf(m, column_max4(mx));
   const float mref = mnew == -INFINITY ? 0.f : mnew;
-  const float alpha = __builtin_amdgcn_exp2f(m - mref);
+  const float alpha = __builtin_amdgcn_exp2f((m - mref) * scale2);
   m = mnew;
   float ps = 0.f;
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      S[b][e] = __builtin_amdgcn_exp2f(S[b][e] - mref);
+      S[b][e] = __builtin_amdgcn_exp2f((S[b][e] - mref) * scale2);
       ps += S[b][e];
     }
   lsum = fmaf(lsum, alpha, ps);
@@ -510,12 +511,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   f32x4 O[DB];
 #pragma unroll
   for (int b = 0; b < DB; ++b) O[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float scale2 = scale * kLog2e;
-  float m = -INFINITY, lsum = 0.f;   // (m: of the scores times log2 e); lsum: this lane's share of the row sum
+  // (a negative scale is a negative Q: the maximum is then that of the scaled scores, too)
+  const float sign = scale < 0.f ? -1.f : 1.f, scale2 = fabsf(scale) * kLog2e;
+  float m = -INFINITY, lsum = 0.f;   // lsum: this lane's share of the row sum
   bool q_planes;   // (a row without planes spoils its own column only; it is worked out at the end)
   {
     OwnRows<HD> Q;
-    q_planes = Q.load(q + at * HD);
+    q_planes = Q.load(q + at * HD, sign);
     async_wait_all();
     __syncthreads();   // (big[] is clear)
     wk.copy_ends(kendS[0], kend, wk.cur);
@@ -554,10 +556,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         if (__builtin_amdgcn_readfirstlane(big) != 0) break;   // the whole block goes on below
         sp.finish(sm, step + 1);
         go_on();
-#pragma unroll
-        for (int b = 0; b < 2; ++b) S[b] *= scale2;
         if (wk.cur.masked()) wk.mask(S, wk.cur, kendS[buf], -INFINITY);
-        softmax_step<DB>(S, m, lsum, O);
+        softmax_step<DB>(S, m, lsum, O, scale2);
         Frag f[kPlanes];
 #pragma unroll
         for (int t = 0; t < 4; ++t) split_piece(S, f, t);
@@ -582,9 +582,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
       f32x4 S[2];
       slow_dot<HD>(S, wk.keys(wk.cur), wk.kv_stride, wk.cur.n, q + at * HD);
 #pragma unroll
-      for (int b = 0; b < 2; ++b) S[b] *= scale2;
+      for (int b = 0; b < 2; ++b) S[b] *= sign;
       wk.mask_slow(S, wk.cur, kend, -INFINITY);
-      softmax_step<DB>(S, m, lsum, O);
+      softmax_step<DB>(S, m, lsum, O, scale2);
       slow_apply<HD>(O, wk.values(wk.cur), wk.kv_stride, wk.cur.n, S);
     }
     if (!wk.have_nxt) break;
@@ -592,7 +592,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     wk.have_nxt = wk.advance(wk.nxt);
   }
 done:
-  float lt = column_sum(lsum), m_e = fmaf(m, kLn2, m * kLn2Low);   // (m_e: m of the scores themselves)
+  float lt = column_sum(lsum), m_e = m * fabsf(scale);   // (m_e: m of the scaled scores)
   if (__builtin_amdgcn_ballot_w64(!q_planes) != 0) {
     float m1 = -INFINITY, l1 = 0.f;
     scores_by_keys<HD>(wk.tile, segs, kend, wk.qrow, q + at * HD, wk.kbase, wk.kv_stride, scale, [&](int, float s) {
@@ -606,10 +606,8 @@ done:
     }
   }
   const float inv = 1.f / lt;
-  if (wk.mine() && wk.lg == 0) {   // (every score of the row may be -infinity: m is then, and the sum 0)
-    const float by_two = fmaf(m, kLn2, fmaf(m, kLn2Low, logf(lt)));
-    lse[at] = q_planes && lt != 0.f ? by_two : m_e + logf(lt);
-  }
+  if (wk.mine() && wk.lg == 0)   // (every score of the row may be -infinity: m is then, the sum is 0, and LSE -infinity)
+    lse[at] = q_planes ? fmaf(m, fabsf(scale), logf(lt)) : m_e + logf(lt);
   float t = 0.f;
 #pragma unroll
   for (int b = 0; b < DB; ++b) {

@@ -8,6 +8,7 @@
 // range [k, kend[k]) where kend[k] is the end of the subtree of k's node, which
 // is what the kernels use as their visibility mask.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <limits>
 #include <new>
@@ -655,7 +656,11 @@ namespace {
 //   backward of a segment (dK/dV walks are not cut: few 128-key tiles leave the chip empty)   after 512 keys, 1200:
 //             393 / 357 (16/16, 214 tiles; small all the same, as its forward is), 346 / 447 (32/8); 2000: 578 / 695 (32/8, 94 tiles), 2152 / 2481 (8/2, 70); after
 //             4096, 1200: 1730 / 1064, 1553 / 1137 (32/8, 293), 1567 / 1129 (64/8), 1775 / 1888 (8/2, 104)
+// (The planes' softmax multiplies by |softmax_scale| log2 e, which has to be a normal number: scales beyond 2^100 or
+// below 2^-100 stay on the fp32 instruction.)
 bool f32_planes(const CallShape& c, const dta_attn_params_t* p) {
+  const float scale = std::fabs(p->softmax_scale);
+  if (!(scale >= 0x1p-100f && scale <= 0x1p100f)) return false;
   const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
   if (row_tiles < 1200 || row_tiles >= 2048 || !c.segment) return row_tiles >= 1200;
   return 2 * c.keys >= 3 * c.rows && (!c.backward || c.keys / 128 * p->n_kv_heads >= 200);

@@ -222,3 +222,40 @@ def test_segment_calls_in_three_parts(Hq, Hkv, d):
     for name, a, ref in (("o", o[3301:], O[3301:]), ("lse", lse[3301:], LSE[3301:]), ("dq", dq[3301:], dQ[3301:]),
                          ("dk", acc[0] - 1, dK), ("dv", acc[1] - 1, dV)):
         assert rel_err(a.double().cpu().numpy(), ref) <= 1e-5, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (112, 112), (96, 8)])
+def test_a_row_whose_only_key_is_infinite(Hq, Hkv, d):
+    """Key 0 has a -inf element against positive queries: every score of row 0 is -inf, though its own
+    numbers are finite.  Its LSE is -inf and its output NaN; other rows leave the key out."""
+    import torch
+    parent, seg = np.array([-1, 0, 0], dtype=np.int32), np.array([170, 33, 64], dtype=np.int32)
+    T, scale = int(seg.sum()), 1.0 / math.sqrt(d)
+    x = make_inputs_numpy(T, Hq, Hkv, d, 41, dtype="f32")
+    x["q"][:, :, 7] = np.abs(x["q"][:, :, 7]) + 0.1
+    x["k"][0, :, 7] = -np.inf
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32", backward=False)
+    assert (got["lse"][0] == -np.inf).all() and np.isnan(got["o"][0]).all()
+    with np.errstate(all="ignore"):
+        O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    assert np.isfinite(got["lse"][1:]).all() and np.isfinite(got["o"][1:]).all()
+    assert rel_err(got["lse"][1:], LSE[1:]) <= 1e-5 and rel_err(got["o"][1:], O[1:]) <= 1e-5
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale", [3e38, -2e30, 1e-37])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (112, 112)])
+def test_scales_at_the_ends_of_the_range(Hq, Hkv, scale, d):
+    """Scores of ordinary size from a scale near fp32's largest or smallest number."""
+    parent, seg = np.array([-1, 0, 0], dtype=np.int32), np.array([170, 33, 64], dtype=np.int32)
+    x = make_inputs_numpy(int(seg.sum()), Hq, Hkv, d, 43, dtype="f32")
+    f = np.float32(math.sqrt(1 / math.sqrt(d) / abs(scale)))   # q . k scale is that of N(0,1) inputs
+    x["q"] *= f
+    x["k"] *= f
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32")
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    assert rel_err(got["o"], O) <= 1e-5 and rel_err(got["lse"], LSE) <= 1e-5
+    dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
+    for name, ref in (("dq", dQ), ("dk", dK), ("dv", dV)):
+        assert rel_err(got[name], ref) <= 1e-5, name
