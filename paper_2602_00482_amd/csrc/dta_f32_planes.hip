@@ -234,25 +234,38 @@ __device__ __forceinline__ void dot(f32x4 (&S)[2], Pair (&ring)[kRing], const ui
   for (int b = 0; b < 2; ++b) S[b] = c0[b] + c1[b];
 }
 
-// acc[cb] += (columns 16*cb .. of the tile) . w, contracted over the tile's rows.
+// acc[cb] += (columns 16*cb .. of the tile) . w, contracted over the tile's rows.  The six products of a pair
+// of blocks are summed from zero and added to acc while the next pair's run: acc is rounded once per chunk of 32
+// rows, not six times (relative errors of O, head_dim 64, 900 tokens, 32/8 heads, 2.1 -> 1.2e-7).
 template <int HD, typename Work, typename Next>
 __device__ __forceinline__ void apply(f32x4 (&acc)[HD / 16], Pair (&ring)[kRing], const uint16_t* cols,
                                       const bf16x8 (&w)[kPlanes], Work work, Next next) {
+  f32x4 sum[2][2];
 #pragma unroll
   for (int i = 0; i < kPairs<HD>; ++i) {
     if (i + kAhead < kPairs<HD>) ring[(i + kAhead) % kRing] = col_pair<HD>(cols, i + kAhead);
     else next(ring[(i + kAhead) % kRing], i + kAhead - kPairs<HD>);
     const Pair& x = ring[i % kRing];
-    const int plane = 2 - i % 3, cb = 2 * (i / 3);
+    const int plane = 2 - i % 3, pair = i / 3;
+    f32x4(&c)[2] = sum[pair & 1];
+    if (plane == 2) c[0] = c[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int j = kPlanes - 1 - plane; j >= 0; --j)
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        acc[cb + b] = mfma16(x.a[b], w[j], acc[cb + b]);
-        work(12 * (i / 3) + (plane == 2 ? 0 : plane == 1 ? 2 : 6) + 2 * (kPlanes - 1 - plane - j) + b);
+        c[b] = mfma16(x.a[b], w[j], c[b]);
+        const int m = (plane == 2 ? 0 : plane == 1 ? 2 : 6) + 2 * (kPlanes - 1 - plane - j) + b;   // 0 .. 11
+        work(12 * pair + m);
+        if (pair > 0 && m >= 4) {   // (the previous pair's last products have ended by then)
+          const int e = m - 4;
+          acc[2 * pair - 2 + (e >> 2)][e & 3] += sum[(pair - 1) & 1][e >> 2][e & 3];
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
   }
+  constexpr int kLast = HD / 32 - 1;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) acc[2 * kLast + b] += sum[kLast & 1][b];
 }
 
 // The vector work that goes with products, in steps of about two instructions: twelve split a

@@ -259,3 +259,24 @@ def test_scales_at_the_ends_of_the_range(Hq, Hkv, scale, d):
     dQ, dK, dV = B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)
     for name, ref in (("dq", dQ), ("dk", dK), ("dv", dV)):
         assert rel_err(got[name], ref) <= 1e-5, name
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,seg,factor,limits", [
+    (16, 16, 64, [600, 500, 300, 250], 1, dict(o=2.19e-7, dq=3.71e-7, dk=3.78e-7, dv=3.25e-7)),
+    (16, 16, 128, [600, 500, 300, 250], 1, dict(o=2.86e-7, dq=4.38e-7, dk=4.25e-7, dv=3.57e-7)),
+    (4, 4, 64, [5000, 700, 900], 1, dict(o=3.16e-7, dq=4.88e-7, dk=4.84e-7, dv=4.29e-7)),
+    (4, 4, 128, [5000, 700, 900], 1, dict(o=4.26e-7, dq=5.83e-7, dk=5.49e-7, dv=4.89e-7)),
+])
+def test_errors_of_products_in_three_parts(Hq, Hkv, d, seg, factor, limits):
+    """Relative 2-norm errors against 64 bits, of queries `factor` times N(0,1): no larger than those of the
+    blocks that share out the keys on the fp32 instruction, which are the limits here (measured)."""
+    parent, seg = np.array([-1] + [0] * (len(seg) - 1), dtype=np.int32), np.array(seg, dtype=np.int32)
+    T, scale = int(seg.sum()), float(np.float32(1.0 / math.sqrt(d)))
+    x = make_inputs_numpy(T, Hq, Hkv, d, 41, dtype="f32")
+    x["q"] *= np.float32(factor)
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32")
+    ref = dict(zip(("o", "lse"), B.forward(parent, seg, x["q"], x["k"], x["v"], scale)))
+    ref.update(zip(("dq", "dk", "dv"), B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)))
+    err = {n: float(np.linalg.norm(got[n] - ref[n]) / np.linalg.norm(ref[n])) for n in limits}
+    print(f"T={T} {Hq}/{Hkv} d{d}: " + " ".join(f"{n} {e:.3e}" for n, e in err.items()), flush=True)
+    assert all(err[n] <= limits[n] for n in limits), err
