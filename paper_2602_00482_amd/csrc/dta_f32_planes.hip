@@ -476,34 +476,45 @@ struct Walk {
   __device__ __forceinline__ bool mine() const { return row_base + n16 < tile.t1; }
 };
 
-// The online softmax of a chunk: S becomes the probabilities relative to the running maximum m.  Both are
-// products of q and k, not scaled yet: only differences are multiplied by `scale2` (> 0, softmax_scale times log2 e),
-// so that its rounding does not grow with the scores, and LSE is one rounding from m.
-template <int DB>
-__device__ __forceinline__ void softmax_step(f32x4 (&S)[2], float& m, float& lsum, f32x4 (&O)[DB], float scale2) {
-  float mx = -INFINITY;
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[b][e]);
-  const float mnew = fmaxf(m, column_max4(mx));
-  const float mref = mnew == -INFINITY ? 0.f : mnew;
-  const float alpha = __builtin_amdgcn_exp2f((m - mref) * scale2);
-  m = mnew;
-  float ps = 0.f;
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      S[b][e] = __builtin_amdgcn_exp2f((S[b][e] - mref) * scale2);
-      ps += S[b][e];
-    }
-  lsum = fmaf(lsum, alpha, ps);
-  if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
-#pragma unroll
-    for (int b = 0; b < DB; ++b) O[b] *= alpha;
+// The online softmax of a chunk: S, products of q and k not scaled yet, becomes the probabilities
+// 2^(factor S - ref), relative to a reference that is the running maximum `m` scaled and rounded.  The factor is
+// |softmax_scale| log2 e in two parts, and LSE = ref ln 2 + ln(sum) takes ref as it is: neither the factor's rounding
+// (which LSE would show: all scores lie on one side of the maximum) nor that of large scores remains.
+struct Softmax {
+  float hi, lo;   // the factor; lo > 0, so that a score of -infinity stays one
+  float m = -INFINITY, ref = -INFINITY;
+  float sum = 0.f;   // this lane's share of the row's
+  __device__ __forceinline__ Softmax(float scale) {
+    const double factor = fabs((double)scale) * 1.4426950408889634;
+    hi = (float)factor;
+    if (hi >= factor) hi = __uint_as_float(__float_as_uint(hi) - 1);
+    lo = (float)(factor - hi);
   }
-}
+  template <int DB>
+  __device__ __forceinline__ void step(f32x4 (&S)[2], f32x4 (&O)[DB]) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[b][e]);
+    m = fmaxf(m, column_max4(mx));
+    const float next = m == -INFINITY ? 0.f : __fmul_rn(m, hi), alpha = __builtin_amdgcn_exp2f(ref - next);
+    ref = next;
+    float ps = 0.f;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        S[b][e] = __builtin_amdgcn_exp2f(fmaf(S[b][e], lo, fmaf(S[b][e], hi, -ref)));
+        ps += S[b][e];
+      }
+    sum = fmaf(sum, alpha, ps);
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+      for (int b = 0; b < DB; ++b) O[b] *= alpha;
+    }
+  }
+};
 
 // ---- forward: same walk as dta_f32_kernels.hip, 8 row tiles per block ------------------
 template <int HD>
@@ -525,8 +536,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
   for (int b = 0; b < DB; ++b) O[b] = f32x4{0.f, 0.f, 0.f, 0.f};
   // (a negative scale is a negative Q: the maximum is then that of the scaled scores, too)
-  const float sign = scale < 0.f ? -1.f : 1.f, scale2 = fabsf(scale) * kLog2e;
-  float m = -INFINITY, lsum = 0.f;   // lsum: this lane's share of the row sum
+  const float sign = scale < 0.f ? -1.f : 1.f;
+  Softmax softmax(scale);
   bool q_planes;   // (a row without planes spoils its own column only; it is worked out at the end)
   {
     OwnRows<HD> Q;
@@ -570,7 +581,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         sp.finish(sm, step + 1);
         go_on();
         if (wk.cur.masked()) wk.mask(S, wk.cur, kendS[buf], -INFINITY);
-        softmax_step<DB>(S, m, lsum, O, scale2);
+        softmax.step(S, O);
         Frag f[kPlanes];
 #pragma unroll
         for (int t = 0; t < 4; ++t) split_piece(S, f, t);
@@ -597,7 +608,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
       for (int b = 0; b < 2; ++b) S[b] *= sign;
       wk.mask_slow(S, wk.cur, kend, -INFINITY);
-      softmax_step<DB>(S, m, lsum, O, scale2);
+      softmax.step(S, O);
       slow_apply<HD>(O, wk.values(wk.cur), wk.kv_stride, wk.cur.n, S);
     }
     if (!wk.have_nxt) break;
@@ -605,7 +616,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     wk.have_nxt = wk.advance(wk.nxt);
   }
 done:
-  float lt = column_sum(lsum), m_e = m * fabsf(scale);   // (m_e: m of the scaled scores)
+  // (every score of the row may be -infinity: the sum is 0, and LSE -infinity)
+  float lt = column_sum(softmax.sum);
+  float lse_t = lt == 0.f ? -INFINITY : fmaf(softmax.ref, kLn2, fmaf(softmax.ref, kLn2Low, logf(lt)));
   if (__builtin_amdgcn_ballot_w64(!q_planes) != 0) {
     float m1 = -INFINITY, l1 = 0.f;
     scores_by_keys<HD>(wk.tile, segs, kend, wk.qrow, q + at * HD, wk.kbase, wk.kv_stride, scale, [&](int, float s) {
@@ -614,13 +627,12 @@ done:
       m1 = mn;
     });
     if (!q_planes) {
-      m_e = m1;
+      lse_t = m1 + logf(l1);
       lt = l1;
     }
   }
   const float inv = 1.f / lt;
-  if (wk.mine() && wk.lg == 0)   // (every score of the row may be -infinity: m is then, the sum is 0, and LSE -infinity)
-    lse[at] = q_planes ? fmaf(m, fabsf(scale), logf(lt)) : m_e + logf(lt);
+  if (wk.mine() && wk.lg == 0) lse[at] = lse_t;
   float t = 0.f;
 #pragma unroll
   for (int b = 0; b < DB; ++b) {
@@ -633,7 +645,7 @@ done:
   const bool spoilt = !q_planes | ((t != 0.f) & (lt - lt == 0.f));   // (NaN compares unequal)
   if (__builtin_amdgcn_ballot_w64(spoilt) != 0) {
     f32x4 acc[DB];
-    row_by_keys<HD>(wk.tile, segs, kend, wk.qrow, q + at * HD, wk.kbase, wk.vbase, wk.kv_stride, scale, m_e, inv, acc);
+    row_by_keys<HD>(wk.tile, segs, kend, wk.qrow, q + at * HD, wk.kbase, wk.vbase, wk.kv_stride, scale, lse_t, 1.f, acc);
     if (spoilt) {
 #pragma unroll
       for (int b = 0; b < DB; ++b) O[b] = acc[b];

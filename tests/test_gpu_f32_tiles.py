@@ -266,6 +266,12 @@ def test_scales_at_the_ends_of_the_range(Hq, Hkv, scale, d):
     (16, 16, 128, [600, 500, 300, 250], 1, dict(o=2.86e-7, dq=4.38e-7, dk=4.25e-7, dv=3.57e-7)),
     (4, 4, 64, [5000, 700, 900], 1, dict(o=3.16e-7, dq=4.88e-7, dk=4.84e-7, dv=4.29e-7)),
     (4, 4, 128, [5000, 700, 900], 1, dict(o=4.26e-7, dq=5.83e-7, dk=5.49e-7, dv=4.89e-7)),
+    # LSE, and the scores of large queries
+    (32, 8, 64, [300, 250, 200, 150], 1, dict(o=1.96e-7, lse=4.39e-8)),
+    (32, 8, 128, [300, 250, 200, 150], 1, dict(o=2.53e-7, lse=4.37e-8)),
+    (32, 8, 64, [300, 250, 200, 150], 30, dict(o=1.03e-6, lse=7.36e-8, dq=4.37e-6, dk=4.39e-6, dv=2.09e-6)),
+    (32, 8, 128, [300, 250, 200, 150], 30, dict(o=1.44e-6, lse=9.97e-8, dq=5.99e-6, dk=6.01e-6, dv=3.12e-6)),
+    (16, 16, 64, [600, 500, 300, 250], 100, dict(o=2.08e-6, lse=7.40e-8, dq=1.52e-5, dk=1.52e-5, dv=4.83e-6)),
 ])
 def test_errors_of_products_in_three_parts(Hq, Hkv, d, seg, factor, limits):
     """Relative 2-norm errors against 64 bits, of queries `factor` times N(0,1): no larger than those of the
