@@ -477,18 +477,21 @@ struct Walk {
 };
 
 // The online softmax of a chunk: S, products of q and k not scaled yet, becomes the probabilities
-// 2^(factor S - ref), relative to a reference that is the running maximum `m` scaled and rounded.  The factor is
-// |softmax_scale| log2 e in two parts, and LSE = ref ln 2 + ln(sum) takes ref as it is: neither the factor's rounding
-// (which LSE would show: all scores lie on one side of the maximum) nor that of large scores remains.
+// 2^((S - m) factor), m the running maximum.  The factor, |softmax_scale| log2 e, is a number in two parts: rounded to
+// one it would show in LSE (all scores lie on one side of the maximum).  Only differences are multiplied by it, which
+// keeps scores of any size in range, and LSE is one rounding from m |softmax_scale|.
 struct Softmax {
   float hi, lo;   // the factor; lo > 0, so that a score of -infinity stays one
-  float m = -INFINITY, ref = -INFINITY;
+  float m = -INFINITY;
   float sum = 0.f;   // this lane's share of the row's
   __device__ __forceinline__ Softmax(float scale) {
     const double factor = fabs((double)scale) * 1.4426950408889634;
     hi = (float)factor;
     if (hi >= factor) hi = __uint_as_float(__float_as_uint(hi) - 1);
     lo = (float)(factor - hi);
+  }
+  __device__ __forceinline__ float relative(float x) const {   // 2^(x factor)
+    return __builtin_amdgcn_exp2f(fmaf(x, lo, x * hi));
   }
   template <int DB>
   __device__ __forceinline__ void step(f32x4 (&S)[2], f32x4 (&O)[DB]) {
@@ -497,15 +500,15 @@ struct Softmax {
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e) mx = fmaxf(mx, S[b][e]);
-    m = fmaxf(m, column_max4(mx));
-    const float next = m == -INFINITY ? 0.f : __fmul_rn(m, hi), alpha = __builtin_amdgcn_exp2f(ref - next);
-    ref = next;
+    const float next = fmaxf(m, column_max4(mx)), ref = next == -INFINITY ? 0.f : next;
+    const float alpha = relative(m - ref);
+    m = next;
     float ps = 0.f;
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        S[b][e] = __builtin_amdgcn_exp2f(fmaf(S[b][e], lo, fmaf(S[b][e], hi, -ref)));
+        S[b][e] = relative(S[b][e] - ref);
         ps += S[b][e];
       }
     sum = fmaf(sum, alpha, ps);
@@ -616,9 +619,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     wk.have_nxt = wk.advance(wk.nxt);
   }
 done:
-  // (every score of the row may be -infinity: the sum is 0, and LSE -infinity)
   float lt = column_sum(softmax.sum);
-  float lse_t = lt == 0.f ? -INFINITY : fmaf(softmax.ref, kLn2, fmaf(softmax.ref, kLn2Low, logf(lt)));
+  float lse_t = fmaf(softmax.m, fabsf(scale), logf(lt));   // (-infinity if every score is)
   if (__builtin_amdgcn_ballot_w64(!q_planes) != 0) {
     float m1 = -INFINITY, l1 = 0.f;
     scores_by_keys<HD>(wk.tile, segs, kend, wk.qrow, q + at * HD, wk.kbase, wk.kv_stride, scale, [&](int, float s) {
