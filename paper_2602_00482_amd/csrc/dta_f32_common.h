@@ -26,56 +26,47 @@ __device__ __forceinline__ float column_max(float x) {
   return fmaxf(x, __shfl_xor(x, 32));
 }
 
-// The forward of single rows (query qrow of this lane's column), key by key: f(key, score) for every
-// key the row sees.  Called by whole waves.
-template <int HD, typename F>
-__device__ __forceinline__ void scores_by_keys(const QTile& tile, const KeySeg* segs, const int32_t* kend, int qrow,
-                                               const float* q_row, const float* kbase, size_t kv_stride, float scale, F f) {
-  constexpr int NB = HD / 16;
-  const int lg = (threadIdx.x >> 4) & 3;
-  f32x4 Qr[NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) Qr[j] = *reinterpret_cast<const f32x4*>(q_row + 4 * lg + 16 * j);
-  for (int si = tile.seg_begin; si <= tile.seg_end; ++si) {
-    const bool own = si == tile.seg_end;
-    const int start = own ? tile.t0 : segs[si].start, end = own ? tile.t1 : segs[si].end;
-    const bool all = !own && segs[si].full;
-#pragma unroll 1
-    for (int key = start; key < end; ++key) {
-      const float* k_row = kbase + (size_t)key * kv_stride + 4 * lg;
-      float s = 0.f;
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const f32x4 kx = *reinterpret_cast<const f32x4*>(k_row + 16 * j);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s = fmaf(kx[e], Qr[j][e], s);
-      }
-      s = column_sum(s) * scale;
-      if (all || (key <= qrow && qrow < kend[key])) f(key, s);
-    }
-  }
-}
-// acc = columns 16 * j + 4 * (lane group) .. + 3 of sum w v over the keys the row sees, with w = exp(s - m) * inv:
-// for rows that a V row they do not see has spoilt (a masked key's probability 0 times a value that
-// is not finite).
+// The forward of single rows (query qrow of this lane's column), key by key: acc = columns
+// 16 * j + 4 * (lane group) .. + 3 of sum w v over the keys the row sees, with w = exp(s - m) * inv.  For rows that a
+// V row they do not see has spoilt (a masked key's probability 0 times a value that is not finite).
+// Called by whole waves.
 template <int HD>
 __device__ __forceinline__ void row_by_keys(const QTile& tile, const KeySeg* segs, const int32_t* kend, int qrow,
                                             const float* q_row, const float* kbase, const float* vbase,
                                             size_t kv_stride, float scale, float m, float inv, f32x4 (&acc)[HD / 16]) {
   constexpr int NB = HD / 16;
   const int lg = (threadIdx.x >> 4) & 3;
+  f32x4 Qr[NB];
 #pragma unroll
-  for (int j = 0; j < NB; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  scores_by_keys<HD>(tile, segs, kend, qrow, q_row, kbase, kv_stride, scale, [&](int key, float s) {
-    const float w = expf(s - m) * inv;
-    const float* v_row = vbase + (size_t)key * kv_stride + 4 * lg;
+  for (int j = 0; j < NB; ++j) {
+    Qr[j] = *reinterpret_cast<const f32x4*>(q_row + 4 * lg + 16 * j);
+    acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int si = tile.seg_begin; si <= tile.seg_end; ++si) {
+    const bool own = si == tile.seg_end;
+    const int start = own ? tile.t0 : segs[si].start, end = own ? tile.t1 : segs[si].end;
+    const bool all = !own && segs[si].full;
+#pragma unroll 1
+    for (int key = start; key < end; ++key) {
+      const size_t at = (size_t)key * kv_stride + 4 * lg;
+      float s = 0.f;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const f32x4 vx = *reinterpret_cast<const f32x4*>(v_row + 16 * j);
+      for (int j = 0; j < NB; ++j) {
+        const f32x4 kx = *reinterpret_cast<const f32x4*>(kbase + at + 16 * j);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(w, vx[e], acc[j][e]);
+        for (int e = 0; e < 4; ++e) s = fmaf(kx[e], Qr[j][e], s);
+      }
+      s = column_sum(s) * scale;
+      if (!all && !(key <= qrow && qrow < kend[key])) continue;
+      const float w = expf(s - m) * inv;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const f32x4 vx = *reinterpret_cast<const f32x4*>(vbase + at + 16 * j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j][e] = fmaf(w, vx[e], acc[j][e]);
+      }
     }
-  });
+  }
 }
 
 // What the backward kernels read and write.

@@ -10,10 +10,12 @@
 // fp32 as in dta_f32_kernels.hip.
 //
 // bf16 has fp32's exponent range, so nothing has to be scaled (below 2^-110 the third part is
-// subnormal).  Numbers that bf16 rounds to infinity, infinities among them, have no such three
-// parts: from the first streamed chunk that holds one, a block goes on on the fp32 instruction
-// (slow_dot, slow_apply); so does a block of the backward kernels with such a row of its own, and the forward
-// works its own out by themselves.
+// subnormal).  Numbers from 2^40 on, infinities among them, do not take part: the six products of large ones
+// overflow with either sign, which adds up to NaN where the product is an infinity, and what bf16 rounds to infinity has no
+// parts at all.  (Three factors below 2^40, summed over head_dim, stay below 2^127.)  From the first streamed chunk that
+// holds one, a block goes on on the fp32 instruction (slow_dot, slow_apply); so does a block of the backward kernels with
+// such a row of its own, while a wave of the forward, whose other rows must not change, walks for them once more.
+// NaN may pass: its parts are NaN.
 //
 // A block is 8 waves, each with 16 query rows (dK/dV: 16 keys) as columns, their three planes in
 // registers.  The streamed rows, 32 per step, come as fp32 by direct global-to-LDS loads, every wave
@@ -43,7 +45,7 @@ namespace {
 constexpr int kThreads = 512, kWaves = 8;
 constexpr int kRows = 32;        // streamed rows per step
 constexpr int kPlanes = 3;
-constexpr float kNoPlanes = 3.38e38f;   // bf16's largest number is 3.39e38
+constexpr float kNoPlanes = 0x1p40f;   // numbers from here on are multiplied on the fp32 instruction
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -292,7 +294,8 @@ struct PairSplit {
   }
 };
 
-// The same on the fp32 instruction, from the tensors: streamed row r is at base + min(r, n - 1) * stride.
+// The same on the fp32 instruction, from the tensors: streamed row r is at base + min(r, n - 1) * stride.  The two
+// halves of head_dim are summed apart, as in dta_f32_kernels.hip.
 template <int HD>
 __device__ __forceinline__ void slow_dot(f32x4 (&S)[2], const float* base, size_t stride, int n, const float* own) {
   const int l = threadIdx.x & 63, n16 = l & 15, lg = l >> 4;
@@ -301,7 +304,12 @@ __device__ __forceinline__ void slow_dot(f32x4 (&S)[2], const float* base, size_
     const float* row = base + (size_t)min(16 * b + n16, n - 1) * stride + lg;
     S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (int j = 0; j < HD; j += 4) S[b] = mfma16_f32(row[j], own[j + lg], S[b]);
+    for (int half = 0; half < HD; half += HD / 2) {
+      f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int j = half; j < half + HD / 2; j += 4) c = mfma16_f32(row[j], own[j + lg], c);
+      S[b] += c;
+    }
   }
 }
 template <int HD>
@@ -541,7 +549,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   // (a negative scale is a negative Q: the maximum is then that of the scaled scores, too)
   const float sign = scale < 0.f ? -1.f : 1.f;
   Softmax softmax(scale);
-  bool q_planes;   // (a row without planes spoils its own column only; it is worked out at the end)
+  // the current chunk on the fp32 instruction
+  auto slow_step = [&](Softmax& sx, f32x4(&acc)[DB]) {
+    if (wk.unseen(wk.cur)) return;
+    f32x4 S[2];
+    slow_dot<HD>(S, wk.keys(wk.cur), wk.kv_stride, wk.cur.n, q + at * HD);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) S[b] *= sign;
+    wk.mask_slow(S, wk.cur, kend, -INFINITY);
+    sx.step(S, acc);
+    slow_apply<HD>(acc, wk.values(wk.cur), wk.kv_stride, wk.cur.n, S);
+  };
+  bool q_planes;   // (a row without planes spoils its own column only)
   {
     OwnRows<HD> Q;
     q_planes = Q.load(q + at * HD, sign);
@@ -605,35 +624,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
   // a chunk without planes: this one and what follows on the fp32 instruction
   for (;;) {
-    if (!wk.unseen(wk.cur)) {
-      f32x4 S[2];
-      slow_dot<HD>(S, wk.keys(wk.cur), wk.kv_stride, wk.cur.n, q + at * HD);
-#pragma unroll
-      for (int b = 0; b < 2; ++b) S[b] *= sign;
-      wk.mask_slow(S, wk.cur, kend, -INFINITY);
-      softmax.step(S, O);
-      slow_apply<HD>(O, wk.values(wk.cur), wk.kv_stride, wk.cur.n, S);
-    }
+    slow_step(softmax, O);
     if (!wk.have_nxt) break;
     wk.cur = wk.nxt;
     wk.have_nxt = wk.advance(wk.nxt);
   }
 done:
-  float lt = column_sum(softmax.sum);
-  float lse_t = fmaf(softmax.m, fabsf(scale), logf(lt));   // (-infinity if every score is)
-  if (__builtin_amdgcn_ballot_w64(!q_planes) != 0) {
-    float m1 = -INFINITY, l1 = 0.f;
-    scores_by_keys<HD>(wk.tile, segs, kend, wk.qrow, q + at * HD, wk.kbase, wk.kv_stride, scale, [&](int, float s) {
-      const float mn = fmaxf(m1, s), ref = mn == -INFINITY ? 0.f : mn;
-      l1 = fmaf(l1, expf(m1 - ref), expf(s - ref));
-      m1 = mn;
-    });
+  if (__builtin_amdgcn_ballot_w64(!q_planes) != 0) {   // rows without planes: the whole walk on the fp32 instruction
+    Softmax again(scale);
+    f32x4 acc[DB];
+#pragma unroll
+    for (int b = 0; b < DB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    wk.it.init(segs, wk.tile);
+    while (wk.advance(wk.cur)) slow_step(again, acc);
     if (!q_planes) {
-      lse_t = m1 + logf(l1);
-      lt = l1;
+      softmax = again;
+#pragma unroll
+      for (int b = 0; b < DB; ++b) O[b] = acc[b];
     }
   }
-  const float inv = 1.f / lt;
+  const float lt = column_sum(softmax.sum), inv = 1.f / lt;
+  const float lse_t = fmaf(softmax.m, fabsf(scale), logf(lt));   // (-infinity if every score is)
   if (wk.mine() && wk.lg == 0) lse[at] = lse_t;
   float t = 0.f;
 #pragma unroll
@@ -644,7 +655,7 @@ done:
   }
   // a row's output must not depend on keys it does not see, see row_by_keys
   t = column_sum(t);
-  const bool spoilt = !q_planes | ((t != 0.f) & (lt - lt == 0.f));   // (NaN compares unequal)
+  const bool spoilt = (t != 0.f) & (lt - lt == 0.f);   // (NaN compares unequal)
   if (__builtin_amdgcn_ballot_w64(spoilt) != 0) {
     f32x4 acc[DB];
     row_by_keys<HD>(wk.tile, segs, kend, wk.qrow, q + at * HD, wk.kbase, wk.vbase, wk.kv_stride, scale, lse_t, 1.f, acc);

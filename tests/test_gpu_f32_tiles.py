@@ -305,3 +305,29 @@ def test_scores_of_any_size(Hq, Hkv, factor, d):
     wrong = np.abs(got["o"] - O).max(axis=-1) > 1e-3
     print(f"rows that differ: {int(wrong.sum())} of {wrong.size}", flush=True)
     assert wrong.mean() <= 1e-3
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (112, 112), (96, 8)])
+def test_products_that_overflow(Hq, Hkv, d):
+    """Finite numbers whose product is -infinity in fp32: against every key of one query row (LSE -infinity, output
+    NaN, no other row touched), and against one key, which then has no weight in any row."""
+    parent, seg = np.array([-1, 0, 0], dtype=np.int32), np.array([170, 33, 64], dtype=np.int32)
+    T, scale = int(seg.sum()), 1.0 / math.sqrt(d)
+    x = make_inputs_numpy(T, Hq, Hkv, d, 53, dtype="f32")
+    k = x["k"].copy()
+    x["k"][:, :, 7] = -1.234567e30 * (1 + np.abs(k[:, :, 7]))
+    x["q"][:, :, 7] = 1.234567e-28
+    x["q"][150, :, 7] = 1.234567e30
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32", backward=False)
+    assert (got["lse"][150] == -np.inf).all() and np.isnan(got["o"][150]).all()
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    rest = np.arange(T) != 150
+    assert rel_err(got["o"][rest], O[rest]) <= 2e-5 and rel_err(got["lse"][rest], LSE[rest]) <= 1e-5
+    x["q"][:, :, 7] = 1.234567e20 * (1 + np.abs(k[:, :1, 7]))
+    x["k"][:, :, 7] = 0
+    x["k"][100, :, 7] = -1.3456e20
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32", backward=False)
+    x["k"][100, :, 7] = -1e30   # (so that in 64 bits, too, the key's weight is 0)
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    assert rel_err(got["o"], O) <= 1e-5 and rel_err(got["lse"], LSE) <= 1e-5
