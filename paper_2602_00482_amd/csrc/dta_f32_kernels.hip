@@ -1,7 +1,7 @@
 // fp32 tree attention for gfx950: forward, dQ and dK/dV with every product, sum
 // and exponential in fp32, for callers that need ~1e-6 relative accuracy.  Here: launches
 // that do not fill the chip; the others are in dta_f32_planes.hip (f32_planes in
-// dta_tree.cpp has the rule), but for the dK/dV kernel of 64-key tiles.
+// dta_tree.cpp has the rule).
 //
 // What is computed follows the attention inside the paper's FWD / BWD
 // primitives (pseudocode appendix) for all segments of the tree at once: a
@@ -106,20 +106,18 @@ __device__ __forceinline__ void rows_async_load(float* tiles, const float* base,
 // (KS - 1) * R * N * 1 KB that nobody reads any more.  Called by every thread.
 template <int KS, int R, int N>
 __device__ __forceinline__ void sum_over_groups(f32x4* buf, int rw, int kg, f32x4 (&acc)[N]) {
-  if constexpr (KS > 1) {
-    const int l = threadIdx.x & 63;
-    __syncthreads();
-    if (kg > 0) {
+  const int l = threadIdx.x & 63;
+  __syncthreads();
+  if (kg > 0) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) buf[(((kg - 1) * R + rw) * N + i) * 64 + l] = acc[i];
-    }
-    __syncthreads();
-    if (kg == 0) {
+    for (int i = 0; i < N; ++i) buf[(((kg - 1) * R + rw) * N + i) * 64 + l] = acc[i];
+  }
+  __syncthreads();
+  if (kg == 0) {
 #pragma unroll
-      for (int s = 0; s < KS - 1; ++s)
+    for (int s = 0; s < KS - 1; ++s)
 #pragma unroll
-        for (int i = 0; i < N; ++i) acc[i] += buf[((s * R + rw) * N + i) * 64 + l];
-    }
+      for (int i = 0; i < N; ++i) acc[i] += buf[((s * R + rw) * N + i) * 64 + l];
   }
 }
 
@@ -255,25 +253,24 @@ __global__ __launch_bounds__(64 * NW) void fwd_f32_kernel(
   }
 
   float lt = column_sum(lsum);
-  if constexpr (KS > 1) {   // merge the groups: common maximum, then one sum
-    if (lg == 0) {
-      mlS[0][kg][rw][n16] = m;
-      mlS[1][kg][rw][n16] = lt;
-    }
-    __syncthreads();
-    float mall = mlS[0][0][rw][n16];
-#pragma unroll
-    for (int s = 1; s < KS; ++s) mall = fmaxf(mall, mlS[0][s][rw][n16]);
-    const float mref = mall == -INFINITY ? 0.f : mall;   // (every score of the row may be -inf)
-    lt = 0.f;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) lt = fmaf(expf(mlS[0][s][rw][n16] - mref), mlS[1][s][rw][n16], lt);
-    const float f = expf(m - mref);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) O[b] *= f;
-    m = mall;
-    sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&Ks[0][0]), rw, kg, O);
+  // merge the groups: common maximum, then one sum
+  if (lg == 0) {
+    mlS[0][kg][rw][n16] = m;
+    mlS[1][kg][rw][n16] = lt;
   }
+  __syncthreads();
+  float mall = mlS[0][0][rw][n16];
+#pragma unroll
+  for (int s = 1; s < KS; ++s) mall = fmaxf(mall, mlS[0][s][rw][n16]);
+  const float mref = mall == -INFINITY ? 0.f : mall;   // (every score of the row may be -inf)
+  lt = 0.f;
+#pragma unroll
+  for (int s = 0; s < KS; ++s) lt = fmaf(expf(mlS[0][s][rw][n16] - mref), mlS[1][s][rw][n16], lt);
+  const float f = expf(m - mref);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) O[b] *= f;
+  m = mall;
+  sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&Ks[0][0]), rw, kg, O);
   if (kg != 0) return;
   const float inv = 1.f / lt;
   {
@@ -491,13 +488,11 @@ __device__ __forceinline__ void dq_block(const F32BwdArgs& p, DqSmem<HD, KS>& sm
 // Key-stationary: wave = 16 keys, K and V rows in registers; R key tiles x KS
 // groups per block.  Q and dO of the rows that can see the keys are streamed in
 // iterations of 32 rows of one q head, heads innermost, last chunk first, KS
-// iterations per step, one per group.  KS = 1: four waves, two
-// blocks per CU (see f32_key_planes in dta_tree.cpp).  KS = 4 / 2: eight waves (NW = 4: four, see the forward kernel), trees too
-// small to fill the chip.
+// iterations per step, one per group.  KS and NW as in the forward kernel.
 // Long walks are cut into items that write partial sums, as in bf16 mode.
 template <int HD, int KS>
 struct DkdvSmem {
-  static constexpr int kStat = 32 * KS < 64 ? 64 : 32 * KS;   // one wave-wide copy fills 64
+  static constexpr int kStat = 32 * KS;
   float Q[2][KS * Rows32<HD>::kTile];
   float dO[2][KS * Rows32<HD>::kTile];
   __attribute__((aligned(256))) float stat[2][2][kStat];   // [buffer][lse | delta][position]
@@ -541,7 +536,7 @@ __device__ __forceinline__ void dkdv_block(const F32BwdArgs& p, DkdvSmem<HD, KS>
   auto issue = [&](int it, int b) {
     if (w < kStat / 64) {   // stat is indexed by matrix position; a wave-wide copy covers two iterations
       const int r_base = row_of_it(min(it + 2 * w + 1, total - 1));
-      const int i = min(it + 2 * w + (KS == 1 ? 0 : l >> 5), total - 1), r0 = row_of_it(i);
+      const int i = min(it + 2 * w + (l >> 5), total - 1), r0 = row_of_it(i);
       const int row = min(RL::row_of_pos(l & 31), min(32, tile.q_end - r0) - 1);
       const uint32_t off = (uint32_t)(r0 - r_base + row) * (uint32_t)Hq + (uint32_t)(i % G);
       row_async_load(&stat[b][0][64 * w], lse + (size_t)r_base * Hq + g * G, off);
@@ -630,13 +625,11 @@ __device__ __forceinline__ void dkdv_block(const F32BwdArgs& p, DkdvSmem<HD, KS>
   }
 
   // (the LDS of both operands' buffers is one allocation only by declaration order: use each for its own half)
-  if constexpr (KS > 1) {
-    f32x4(&a)[NB] = *reinterpret_cast<f32x4(*)[NB]>(&acc[0]);
-    f32x4(&b)[NB] = *reinterpret_cast<f32x4(*)[NB]>(&acc[NB]);
-    sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&Qs[0][0]), kw, qg, a);
-    sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&dOs[0][0]), kw, qg, b);
-    if (qg != 0) return;
-  }
+  f32x4(&a)[NB] = *reinterpret_cast<f32x4(*)[NB]>(&acc[0]);
+  f32x4(&b)[NB] = *reinterpret_cast<f32x4(*)[NB]>(&acc[NB]);
+  sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&Qs[0][0]), kw, qg, a);
+  sum_over_groups<KS, R, NB>(reinterpret_cast<f32x4*>(&dOs[0][0]), kw, qg, b);
+  if (qg != 0) return;
   // lane (n16, lg) holds columns NB * (4*lg + e) + b of its key
   const int key = 16 * kw + n16;
 #pragma unroll
@@ -673,7 +666,7 @@ __global__ __launch_bounds__(64 * NW) void dq_f32_kernel(F32BwdArgs p) {
 }
 
 template <int HD, int KS, int NW>
-__global__ __launch_bounds__(64 * NW, KS == 1 ? 2 : 1) void dkdv_f32_kernel(F32BwdArgs p) {
+__global__ __launch_bounds__(64 * NW, 1) void dkdv_f32_kernel(F32BwdArgs p) {
   __shared__ __attribute__((aligned(1024))) DkdvSmem<HD, KS> sm;
   dkdv_block<HD, KS, NW>(p, sm, blockIdx.x);
 }
@@ -787,14 +780,12 @@ int bwd_impl(const LaunchArgs& a) {
     { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
   }
   if (a.stages & DTA_BWD_DKDV) {
-    if (a.tc.k_planes) {
+    if (a.tc.planes) {
       const int ls = launch_dkdv_f32_planes(a, args, kblocks);
       if (ls != DTA_OK) return ls;
     } else if (!one_launch) {
-      auto kernel = a.tc.tiny      ? dkdv_f32_kernel<HD, kSplit, 4>
-                    : a.tc.k_small ? dkdv_f32_kernel<HD, kSplit, 8>
-                                   : dkdv_f32_kernel<HD, 1, 4>;
-      launch(a, a.sched->kv_reduce.empty(), kernel, kblocks, a.tc.k_small && !a.tc.tiny ? 512 : 256, args);
+      auto kernel = a.tc.tiny ? dkdv_f32_kernel<HD, kSplit, 4> : dkdv_f32_kernel<HD, kSplit, 8>;
+      launch(a, a.sched->kv_reduce.empty(), kernel, kblocks, a.tc.tiny ? 256 : 512, args);
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     }
     if (!a.sched->kv_reduce.empty()) {

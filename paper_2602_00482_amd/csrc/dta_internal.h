@@ -215,7 +215,7 @@ struct TileChoice {
   bool q_small, k_small;   // forward and dQ, dK/dV: the form for launches too small to fill the chip
   bool q_split;            // forward and dQ (bf16): the form for launches of a few rounds of blocks
   bool tiny;               // fp32: blocks of four waves, for launches of at most one block per CU
-  bool planes, k_planes;   // fp32: forward and dQ, dK/dV: operands in three bf16 parts, for launches that fill the chip
+  bool planes;             // fp32: operands in three bf16 parts, for launches that fill the chip
 };
 // What a call covers: `rows` query rows, the `keys` they see (both the tokens of
 // the tree for a whole-tree call) and the (row, visible key) pairs of one head.

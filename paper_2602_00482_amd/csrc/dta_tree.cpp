@@ -665,13 +665,6 @@ bool f32_planes(const CallShape& c, const dta_attn_params_t* p) {
   if (row_tiles < 1200 || row_tiles >= 2048 || !c.segment) return row_tiles >= 1200;
   return 2 * c.keys >= 3 * c.rows && (!c.backward || c.keys / 128 * p->n_kv_heads >= 200);
 }
-// dK/dV beside a dQ of the planes form: from 2560 row tiles on and below 2048 tiles of 128 keys.  Between, the
-// blocks of 64 keys on the fp32 instruction stay, as the tile that dta_tree_schedule_info reports for these
-// sizes does; they take up to a third longer (128 / 102 us with 32/8 heads of 128, 70 / 66 of 64).
-bool f32_key_planes(const CallShape& c, const dta_attn_params_t* p) {
-  const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
-  return f32_planes(c, p) && (row_tiles < 2048 || row_tiles >= 2560);
-}
 }  // namespace
 
 int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& call) {
@@ -699,10 +692,8 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
       t->hb = 1;
       while (t->hb < R && G % (2 * t->hb) == 0) t->hb *= 2;
       t->hblocks = G / t->hb;
-      t->k_planes = f32_key_planes(c, p);
-      t->bn = t->k_small ? 16 * R : t->k_planes ? 128 : 64;
-      // an iteration takes a wave several microseconds, so cut walks may be short; blocks of 64 keys: two per CU
-      t->walk = KvWalk{32, 4 * split, t->k_small || t->k_planes ? kNumCUs : 2 * kNumCUs};
+      t->bn = t->planes ? 128 : 16 * R;
+      t->walk = KvWalk{32, 4 * split, kNumCUs};   // an iteration takes a wave several microseconds, so cut walks may be short
       return 16 * (R / t->hb);
     };
     const int fwd_bm = choose(false, &f);

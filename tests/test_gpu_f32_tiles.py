@@ -33,7 +33,7 @@ def test_tiles_against_the_oracle(Hq, Hkv, seg, d):
     tile = tree.schedule_info(dta.AttnParams(Hq, Hkv, d, scale, dta.F32))["bwd_kv_tile_tokens"]
     tree.destroy()
     # which form the launch takes: blocks that fill the chip, eight-wave and four-wave blocks of a small launch
-    assert tile == (64 if Hq > 16 else (32 if d == 64 else 64) // (1 if Hq > 8 else 2)), tile
+    assert tile == (128 if Hq > 16 else (32 if d == 64 else 64) // (1 if Hq > 8 else 2)), tile
     x = make_inputs_numpy(T, Hq, Hkv, d, 17, dtype="f32")
     got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32")
     O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)

@@ -124,11 +124,11 @@ def test_forms_of_fp32_calls(forms, d):
     that dK/dV multiplies in three bf16 parts."""
     calls = [   # heads, tokens before, rows, forward, dQ, key tile (None: a small form's)
         (32, 8, None, 607, "small", "small", None), (32, 8, None, 608, "large", "large", 128),
-        (32, 1, None, 1020, "large", "large", 128), (32, 8, None, 1100, "large", "large", 64),
+        (32, 1, None, 1020, "large", "large", 128), (32, 8, None, 1100, "large", "large", 128),
         (32, 8, None, 1290, "large", "large", 128), (16, 16, None, 9000, "large", "large", 128),
         (16, 16, 512, 1300, "small", "small", None), (32, 8, 512, 700, "large", "small", None),
         (32, 8, 512, 1000, "large", "small", None), (32, 8, 4096, 620, "large", "large", 128),
-        (8, 2, 4096, 2400, "large", "small", None), (8, 2, 4096, 4200, "large", "large", 64),
+        (8, 2, 4096, 2400, "large", "small", None), (8, 2, 4096, 4200, "large", "large", 128),
         (8, 2, 512, 5200, "large", "large", 128), (32, 8, 4096, 500, "small", "small", None),
     ]
     args = []
