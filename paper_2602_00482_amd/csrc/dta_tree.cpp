@@ -653,17 +653,24 @@ namespace {
 //   forward of a segment   rows after 512 keys, 1200: 134 / 154 (16/16, 1200 rows), 113 / 106 (32/8, 600 rows);
 //             1600: 282 / 327 (8/2, 3200 rows), 116 / 94 (64/8, 400 rows); 2000: 251 / 221, 400 / 396; after
 //             4096 keys, 1000: 349 / 397 (32/8), 1200: 638 / 404, 687 / 561 (8/2), 340 / 294 (16/16 heads of 64)
-//   backward of a segment (dK/dV walks are not cut: few 128-key tiles leave the chip empty)   after 512 keys, 1200:
-//             393 / 357 (16/16, 214 tiles; small all the same, as its forward is), 346 / 447 (32/8); 2000: 578 / 695 (32/8, 94 tiles), 2152 / 2481 (8/2, 70); after
-//             4096, 1200: 1730 / 1064, 1553 / 1137 (32/8, 293), 1567 / 1129 (64/8), 1775 / 1888 (8/2, 104)
+//   backward of a segment, whose dK/dV walks are not cut: with one block per CU up to 256 key tiles of 128 the planes
+//             form takes what its longest walk takes however many tiles there are, the small one the sum of its walks.  What
+//             decides is the number of key tiles that the average row sees, at any number of rows.  Small / planes: 60 to
+//             70 tiles 1276 / 1762 (8/2 heads of 64, 2060 row tiles), 2709 / 3870 (32/1), 591 / 730 (32/8 of 128); 79 to 94
+//             607 / 643, 1012 / 1034 (32/8, 3000), 5072 / 5384 (8/2 of 64, 6000), 4716 / 4535 (8/2 of 128, 4000 after 2048);
+//             102 to 114 -2 to +21 % for small; 126 1276 / 1005 (12/4 of 128, 3000); 159 2673 / 1656 (64/8 of 128, 4000), 1534 / 1021 (of 64)
 // (The planes' softmax multiplies by |softmax_scale| log2 e, which has to be a normal number: scales beyond 2^100 or
 // below 2^-100 stay on the fp32 instruction.)
 bool f32_planes(const CallShape& c, const dta_attn_params_t* p) {
   const float scale = std::fabs(p->softmax_scale);
   if (!(scale >= 0x1p-100f && scale <= 0x1p100f)) return false;
   const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
-  if (row_tiles < 1200 || row_tiles >= 2048 || !c.segment) return row_tiles >= 1200;
-  return 2 * c.keys >= 3 * c.rows && (!c.backward || c.keys / 128 * p->n_kv_heads >= 200);
+  if (row_tiles < 1200) return false;
+  if (!c.segment) return true;
+  // (a row sees the keys before the segment and half of its own rows' on average)
+  const int64_t seen = (2 * c.keys - c.rows) * p->n_kv_heads / 256;
+  if (c.backward && seen < 95) return false;
+  return row_tiles >= 2048 || 2 * c.keys >= 3 * c.rows;
 }
 }  // namespace
 

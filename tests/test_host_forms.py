@@ -129,7 +129,10 @@ def test_forms_of_fp32_calls(forms, d):
         (16, 16, 512, 1300, "small", "small", None), (32, 8, 512, 700, "large", "small", None),
         (32, 8, 512, 1000, "large", "small", None), (32, 8, 4096, 620, "large", "large", 128),
         (8, 2, 4096, 2400, "large", "small", None), (8, 2, 4096, 4200, "large", "large", 128),
-        (8, 2, 512, 5200, "large", "large", 128), (32, 8, 4096, 500, "small", "small", None),
+        (8, 2, 512, 5200, "large", "small", None), (32, 8, 4096, 500, "small", "small", None),
+        # segments whose average row sees 93, 97, 190 and 39 key tiles of 128
+        (32, 8, 512, 1960, "large", "small", None), (32, 8, 512, 2080, "large", "large", 128),
+        (8, 2, 8192, 8000, "large", "large", 128), (32, 1, 2048, 5900, "large", "small", None),
     ]
     args = []
     for Hq, Hkv, before, rows, *_ in calls:
