@@ -218,15 +218,17 @@ struct TileChoice {
   bool planes;             // fp32: operands in three bf16 parts, for launches that fill the chip
 };
 // What a call covers: `rows` query rows, the `keys` they see (both the tokens of
-// the tree for a whole-tree call) and the (row, visible key) pairs of one head.
+// the tree for a whole-tree call) and the (row, visible key) pairs of one head.  `path`: tokens of
+// a tree's longest root path (0 where it does not matter).
 struct CallShape {
   bool backward = true;
   bool segment = false;
-  int64_t rows = INT32_MAX, keys = INT32_MAX, pairs = INT64_MAX;
+  int64_t rows = INT32_MAX, keys = INT32_MAX, pairs = INT64_MAX, path = 0;
 };
 int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& call = CallShape());
 inline CallShape whole_tree(const dta_tree* tree, bool backward) {
-  return CallShape{backward, false, tree->info.n_tokens, tree->info.n_tokens, tree->info.unique_pairs};
+  return CallShape{backward,  false, tree->info.n_tokens, tree->info.n_tokens, tree->info.unique_pairs,
+                   tree->info.max_path_tokens};
 }
 int validate_params(const dta_attn_params_t* p);
 

@@ -650,9 +650,13 @@ namespace {
 //             1200: 51 + 150 / 47 + 124, 38 + 87 / 29 + 96, 26 + 75 / 21 + 67, 57 + 142 / 48 + 119, 38 + 95 / 29 + 106 (32/1);
 //             1600: 82 + 222 / 59 + 163, 50 + 146 / 32 + 118, 40 + 109 / 24 + 92, 80 + 220 / 59 + 154, 50 + 144 / 32 + 130;
 //             2000: 105 + 323 / 73 + 217, 65 + 207 / 41 + 150
+//   forward of a tree with few branches, whose longest walk is twice the average one: one segment, 1200 row tiles 52 / 71
+//             (16/16 heads of 64), 92 / 136 (8/2), 69 / 94 (12/4), 96 / 109 (16/16 of 128), 186 / 208 (8/2); 1600: 82 / 94, 151 / 179,
+//             53 / 50 (32/8), 136 / 143, 259 / 275 (8/2 of 128), 47 / 45 (64/8); 2000: 119 / 115, 223 / 223, 235 / 176
 //   forward of a segment   rows after 512 keys, 1200: 134 / 154 (16/16, 1200 rows), 113 / 106 (32/8, 600 rows);
 //             1600: 282 / 327 (8/2, 3200 rows), 116 / 94 (64/8, 400 rows); 2000: 251 / 221, 400 / 396; after
-//             4096 keys, 1000: 349 / 397 (32/8), 1200: 638 / 404, 687 / 561 (8/2), 340 / 294 (16/16 heads of 64)
+//             4096 keys, 1000: 349 / 397 (32/8), 1200: 638 / 404, 687 / 561 (8/2), 340 / 294 (16/16 heads of 64); 2400 rows
+//             after 2048, 8/2 heads of 64 234 / 253, 2900 270 / 281
 //   backward of a segment, whose dK/dV walks are not cut: with one block per CU up to 256 key tiles of 128 the planes
 //             form takes what its longest walk takes however many tiles there are, the small one the sum of its walks.  What
 //             decides is the number of key tiles that the average row sees, at any number of rows.  Small / planes: 60 to
@@ -666,11 +670,22 @@ bool f32_planes(const CallShape& c, const dta_attn_params_t* p) {
   if (!(scale >= 0x1p-100f && scale <= 0x1p100f)) return false;
   const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
   if (row_tiles < 1200) return false;
-  if (!c.segment) return true;
+  if (!c.segment) {
+    if (c.backward || row_tiles >= 2048 || c.path == 0) return true;
+    // One round of blocks: the planes form takes what its longest walk takes (1.85 us per 32 keys, 2.9 with heads of
+    // 128), the small one the sum of its walks.  A prompt with answers has walks of like length, a chain does not.
+    if (4 * c.path * c.rows < 7 * c.pairs) return p->head_dim == 64 || row_tiles >= 1250;
+    const double path = (double)c.path, pairs = (double)c.pairs * p->n_q_heads / 16e6;
+    return p->head_dim == 64 ? 5 + 0.058 * path < 12 + 54 * pairs : 6 + 0.09 * path < 10 + 100 * pairs;
+  }
   // (a row sees the keys before the segment and half of its own rows' on average)
   const int64_t seen = (2 * c.keys - c.rows) * p->n_kv_heads / 256;
   if (c.backward && seen < 95) return false;
-  return row_tiles >= 2048 || 2 * c.keys >= 3 * c.rows;
+  if (row_tiles >= 2048) return true;
+  // (heads of 64: the longest walk against their sum, as above)
+  const bool one_round = p->head_dim == 128 || c.keys >= 2 * c.rows ||
+                         5 + 0.055 * c.keys < 12 + 51e-6 * row_tiles * (c.keys - 0.5 * c.rows);
+  return one_round && 2 * c.keys >= 3 * c.rows;
 }
 }  // namespace
 

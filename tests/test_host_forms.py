@@ -17,7 +17,7 @@ CSRC = os.path.join(ROOT, "paper_2602_00482_amd", "csrc")
 
 @pytest.fixture(scope="module")
 def forms():
-    """forms(calls) -> [(q form, dK/dV form, dQ tile, key tile, forward tile where it differs)]"""
+    """forms(calls), with or without the longest path -> [(q form, dK/dV form, dQ tile, key tile, forward tile where it differs)]"""
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("no g++")
@@ -29,7 +29,7 @@ def forms():
     assert res.returncode == 0, res.stderr
 
     def run(calls):
-        text = "".join(" ".join(str(int(x)) for x in c) + "\n" for c in calls)
+        text = "".join(" ".join(str(int(x)) for x in (*c, 0)[:10]) + "\n" for c in calls)
         res = subprocess.run([out], input=text, capture_output=True, text=True, timeout=60)
         assert res.returncode == 0, res.stderr
         got = [l.split() for l in res.stdout.splitlines()]
@@ -45,7 +45,7 @@ def tree_call(parent, seg, Hq, Hkv, d, dtype, backward):
     info = tree.info()
     tree.destroy()
     T = info["n_tokens"]
-    return Hq, Hkv, d, dtype, backward, 0, T, T, info["unique_pairs"]
+    return Hq, Hkv, d, dtype, backward, 0, T, T, info["unique_pairs"], info["max_path_tokens"]
 
 
 def segment_call(Hq, Hkv, d, backward, before, rows):
@@ -143,6 +143,23 @@ def test_forms_of_fp32_calls(forms, d):
     for c, x, y in zip(calls, f, b):
         assert (x[0].replace("tiny", "small"), y[0].replace("tiny", "small")) == c[4:6], (c, x, y)
         assert y[3] == c[6] or (c[6] is None and y[3] < 128 and y[1] == "small"), (c, y)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,seg,small", [
+    (8, 2, 64, [2401], True), (8, 2, 64, [480, 360, 120, 288, 192, 240, 240, 336, 145], False), (8, 2, 64, [4800], False),
+    (16, 16, 64, [1601], True), (32, 8, 64, [651], True), (32, 8, 64, [1001], False), (16, 16, 128, [1200], True), (16, 16, 128, [2000], False),
+    (16, 16, 128, [260, 195, 65, 156, 104, 130, 130, 182, 79], False),
+])
+def test_form_of_an_fp32_trees_forward_follows_its_longest_walk(Hq, Hkv, d, seg, small):
+    """1200 row tiles and more: the forward of a tree without branches, which is as long as its longest walk, stays in
+    blocks that share out the keys until they are a round and a half; a prompt with answers does not."""
+    tree = dta.tree_build(np.array([-1] + [0] * (len(seg) - 1), dtype=np.int32), np.array(seg, dtype=np.int32))
+    info = tree.schedule_info(dta.AttnParams(Hq, Hkv, d, 0.1, dta.F32))
+    tree.destroy()
+    heads = min(8, Hq // Hkv)
+    large = 128 // heads   # tokens of a block of 8 row tiles
+    assert info["bwd_kv_tile_tokens"] == 128
+    assert (info["fwd_q_tile_tokens"] < large) == small, info
 
 
 def test_the_gpu_tests_reach_the_forms_they_name(forms):
