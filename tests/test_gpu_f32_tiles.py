@@ -331,3 +331,44 @@ def test_products_that_overflow(Hq, Hkv, d):
     x["k"][100, :, 7] = -1e30   # (so that in 64 bits, too, the key's weight is 0)
     O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
     assert rel_err(got["o"], O) <= 1e-5 and rel_err(got["lse"], LSE) <= 1e-5
+
+
+LARGE = np.float32(3.0e12)   # beyond 2^40: multiplied on the fp32 instruction
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,parent,seg,rows", [
+    (112, 112, [-1, 0, 0], [170, 33, 64], [100]),              # in the middle of a walk
+    (96, 8, [-1, 0, 0], [300, 333, 64], [12, 631]),            # in the first chunk, and in a leaf's last key tile
+    (32, 8, [-1, 0, 0, 0], [700, 300, 290, 310], [5, 650]),    # dK/dV walks that are cut into partial sums
+])
+@pytest.mark.parametrize("what", ["k", "v", "q", "do"])
+def test_backward_of_numbers_without_three_parts(what, Hq, Hkv, parent, seg, rows, d):
+    """One large number in some rows of a tensor, small ones in the same column of the tensor that it is multiplied
+    with.  dQ meets the rows of K and V while it streams them and those of Q and dO as its own, dK/dV the other way
+    round; in both the walk goes on on the fp32 instruction.  The large column of a gradient and the others
+    are compared on scales of their own."""
+    parent, seg = np.array(parent, dtype=np.int32), np.array(seg, dtype=np.int32)
+    T, scale, col = int(seg.sum()), 1.0 / math.sqrt(d), 9
+    x = make_inputs_numpy(T, Hq, Hkv, d, 59, dtype="f32")
+    other = {"k": "q", "q": "k", "v": "do", "do": "v"}[what]
+    x[what][rows, :, col] = LARGE
+    x[other][:, :, col] *= 1 / LARGE
+    p = dta.AttnParams(Hq, Hkv, d, scale, dta.F32)
+    tree = dta.tree_build(parent, seg)
+    info = tree.schedule_info(p)
+    tree.destroy()
+    assert info["bwd_kv_tile_tokens"] == 128
+    if len(seg) == 4:
+        assert info["bwd_work_items"] > T // 128 + len(seg)   # some walks are cut
+    got = run_hip(parent, seg, x, Hq, Hkv, d, scale, "f32")
+    ref = dict(zip(("o", "lse"), B.forward(parent, seg, x["q"], x["k"], x["v"], scale)))
+    ref.update(zip(("dq", "dk", "dv"), B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)))
+    rest = [i for i in range(d) if i != col]
+    for n, r in ref.items():
+        assert np.isfinite(got[n]).all(), n
+        if n == "lse":
+            assert rel_err(got[n], r) <= 1e-5, n
+        else:
+            assert rel_err(got[n][..., rest], r[..., rest]) <= 1e-5, n
+            assert rel_err(got[n][..., col], r[..., col]) <= 1e-5, (n, "large column")

@@ -219,3 +219,26 @@ def test_stages_one_by_one_give_the_bits_of_one_call(dtype, Hq, Hkv, d):
         for a, b in zip(ref, out):
             assert torch.equal(a, b), stages
     tree.destroy()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lens", [[40] * 40, [500, 640, 511]])   # chunks of 64 and of 128 keys
+def test_skipped_chunks_in_a_forward_that_draws_its_items(lens, d):
+    """A forward whose blocks draw their items from queues and whose waves leave out masked chunks: the bits
+    of the launch with a block per item, and the oracle's results for two heads."""
+    import torch
+    H, parent = 512, np.array([-1] * len(lens) if len(lens) > 3 else [-1, 0, 0], dtype=np.int32)
+    seg, scale = np.array(lens, dtype=np.int32), 1.0 / math.sqrt(d)
+    x = make_inputs_numpy(int(seg.sum()), 2, 2, d, 37, dtype="bf16")
+    q, k, v = (torch.from_numpy(x[n]).cuda().to(torch.bfloat16).repeat(1, H // 2, 1) for n in ("q", "k", "v"))
+    p = dta.AttnParams(H, H, d, scale, dta.BF16)
+    tree = dta.tree_build(parent, seg)
+    tiles = tree.schedule_info(p)["fwd_work_items"]
+    assert tiles * H >= 8 * 256
+    o, lse = dta.tree_attn_fwd(tree, p, q, k, v)
+    o2, lse2 = dta.tree_attn_fwd(tree, p, q, k, v, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    tree.destroy()
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
+    O, LSE = B.forward(parent, seg, x["q"], x["k"], x["v"], scale)
+    assert rel_err(o[:, -2:].double().cpu().numpy(), O) <= 1e-2 and rel_err(lse[:, -2:].double().cpu().numpy(), LSE) <= 1e-2
