@@ -9,12 +9,13 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 
 import numpy as np
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdta.so")
 _lib = None
-_torch_calls = None
+_torch_calls = None   # dta_torch, or False where it cannot be used
 
 F32, BF16 = 0, 1
 
@@ -142,13 +143,25 @@ def load_library():
 def _calls():
     """dta_torch.so: the attention calls on plain torch tensors, made without the
     interpreter between their parts.  Its functions return None where they do not
-    know an argument; the wrappers below then make the call, or raise the error."""
+    know an argument; the wrappers below then make the call, or raise the error.
+    They make every call (the same calls of libdta.so, a few us of host time each)
+    where the module is not there or was built for another torch or Python, which
+    it must not be used with: False then, with one warning."""
     global _torch_calls
     if _torch_calls is None:
-        import torch  # noqa: F401  (its libraries have to be there first)
         load_library()
-        from . import dta_torch
-        _torch_calls = dta_torch
+        from .build import torch_stamp
+        wanted = torch_stamp()   # (imports torch, whose libraries have to be there first)
+        try:
+            from . import dta_torch
+            built_for = getattr(dta_torch, "built_for", "another version")
+            problem = None if built_for == wanted else f"built for {built_for}, this is {wanted}"
+        except ImportError as e:
+            problem = str(e)
+        if problem:
+            warnings.warn(f"dta_torch.so cannot be used, calls take a few us longer on the host ({problem}); "
+                          "run `python -m paper_2602_00482_amd.build`", RuntimeWarning, stacklevel=3)
+        _torch_calls = False if problem else dta_torch
     return _torch_calls
 
 
@@ -274,8 +287,9 @@ def _shapes(T, params):
 def tree_attn_fwd(tree: Tree, params: AttnParams, q, k, v, o=None, lse=None, workspace=None):
     """dta_tree_attn_fwd on torch's current stream.  Returns (o, lse)."""
     h = _known(tree, params)
-    if h:
-        res = _calls().fwd(h, C.addressof(params), tree.n_tokens, q, k, v, o, lse, workspace)
+    calls = h and _calls()
+    if calls:
+        res = calls.fwd(h, C.addressof(params), tree.n_tokens, q, k, v, o, lse, workspace)
         if type(res) is tuple:
             return res
         if res is not None:
@@ -318,8 +332,9 @@ def tree_attn_bwd(tree: Tree, params: AttnParams, q, k, v, o, lse, d_o, dq=None,
     """dta_tree_attn_bwd (or dta_tree_attn_bwd_stages when `stages` selects a
     subset) on torch's current stream.  Returns (dq, dk, dv)."""
     h = stages == BWD_ALL and _known(tree, params)
-    if h:
-        res = _calls().bwd(h, C.addressof(params), tree.n_tokens, q, k, v, o, lse, d_o, dq, dk, dv, workspace)
+    calls = h and _calls()
+    if calls:
+        res = calls.bwd(h, C.addressof(params), tree.n_tokens, q, k, v, o, lse, d_o, dq, dk, dv, workspace)
         if type(res) is tuple:
             return res
         if res is not None:
@@ -387,8 +402,9 @@ def tree_attn_fwd_segment(tree: Tree, params: AttnParams, t_begin: int, t_end: i
     """dta_tree_attn_fwd_segment on torch's current stream: fills rows
     [t_begin, t_end) of the full-size o and lse."""
     h = _known(tree, params)
-    if h:
-        st = _calls().fwd_segment(h, C.addressof(params), tree.n_tokens, t_begin, t_end, q, k, v, o, lse)
+    calls = h and _calls()
+    if calls:
+        st = calls.fwd_segment(h, C.addressof(params), tree.n_tokens, t_begin, t_end, q, k, v, o, lse)
         if st is not None:
             return _check(st, "dta_tree_attn_fwd_segment")
     import torch
@@ -412,9 +428,10 @@ def tree_attn_bwd_segment(tree: Tree, params: AttnParams, t_begin: int, t_end: i
     """dta_tree_attn_bwd_segment on torch's current stream: writes rows
     [t_begin, t_end) of dq and adds into the fp32 accumulators dk_acc, dv_acc."""
     h = _known(tree, params)
-    if h:
-        st = _calls().bwd_segment(h, C.addressof(params), tree.n_tokens, t_begin, t_end, q, k, v, o, lse, d_o,
-                                  dq, dk_acc, dv_acc, workspace)
+    calls = h and _calls()
+    if calls:
+        st = calls.bwd_segment(h, C.addressof(params), tree.n_tokens, t_begin, t_end, q, k, v, o, lse, d_o,
+                               dq, dk_acc, dv_acc, workspace)
         if st is not None:
             return _check(st, "dta_tree_attn_bwd_segment")
     import torch

@@ -261,4 +261,9 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "dta_torch", nullptr, -1, metho
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_dta_torch() { return PyModule_Create(&module_def); }
+PyMODINIT_FUNC PyInit_dta_torch() {
+  PyObject* module = PyModule_Create(&module_def);
+  // the torch and Python it was compiled against: with others its tensors may be laid out otherwise
+  if (module && PyModule_AddStringConstant(module, "built_for", DTA_TORCH_BUILT_FOR) < 0) Py_CLEAR(module);
+  return module;
+}
