@@ -781,8 +781,11 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
     // Waves leave out masked chunks that none of their rows sees, with head_dim 64 where that is worth the branch, as
     // in the forward kernel.  Measured, without / with: two-answer pairs, 16/16 heads of 128 721 / 662 us, of 64 (pass of
     // dQ) 267 / 257; multi-turn agents, 32/8 heads of 128 7250 / 7220, of 64 4210 / 4250.  (Blocks of two groups lose 7 %.)
-    const bool skip = HD == 128 || (a.tc.hb <= 2 && 10 * a.sched->fwd_masked64 > 3 * a.sched->fwd_chunks64);
-    auto kernel = a.tc.q_split ? dq_bf16_kernel<HD, 2> : skip ? dq_bf16_kernel<HD, 1, true> : dq_bf16_kernel<HD, 1, HD == 128>;
+    auto kernel = a.tc.q_split ? dq_bf16_kernel<HD, 2> : dq_bf16_kernel<HD, 1, true>;
+    if constexpr (HD == 64) {
+      const bool skip = a.tc.hb <= 2 && 10 * a.sched->fwd_masked64 > 3 * a.sched->fwd_chunks64;
+      if (!a.tc.q_split && !skip) kernel = dq_bf16_kernel<64>;
+    }
     kernel<<<(unsigned)(draw ? qblocks + qblocks / 4 : qblocks), kDqThreads, 0, st>>>(
         a.sched->d_q_tiles, a.sched->d_segs, a.d_kend, (const uint16_t*)a.q, (const uint16_t*)a.k,
         (const uint16_t*)a.v, (const uint16_t*)a.d_o, a.lse_in,

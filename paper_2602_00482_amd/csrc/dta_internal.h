@@ -190,10 +190,10 @@ struct KvWalk {
 
 // Key of a whole-tree schedule in dta_tree::schedules.
 inline uint64_t schedule_key(int bm, int bn, int hkv, int group, const KvWalk& kw) {
-  // (query tiles are 16 to 256 tokens, multiples of 16)
+  // (every field of kw; query tiles are 16 to 256 tokens, multiples of 16, key tiles up to 256, `resident` 256 or 512)
   return ((uint64_t)(kw.min_piece / 4) << 60) | ((uint64_t)(kw.fwd_bm / 16) << 54) | ((uint64_t)(bm / 16) << 48) |
-         ((uint64_t)kw.key_steps << 46) | ((uint64_t)(kw.q_rows / 32) << 44) |
-         ((uint64_t)bn << 32) | ((uint64_t)hkv << 16) | (uint64_t)group;
+         ((uint64_t)kw.queues << 47) | ((uint64_t)kw.key_steps << 46) | ((uint64_t)(kw.q_rows / 32) << 44) |
+         ((uint64_t)(kw.resident / 256) << 42) | ((uint64_t)bn << 32) | ((uint64_t)hkv << 16) | (uint64_t)group;
 }
 // Host: build (or fetch) the schedule for tile sizes (bm, bn).
 Schedule& get_schedule(dta_tree* tree, int bm, int bn, int hkv, int group, const KvWalk& kw = KvWalk());
