@@ -185,7 +185,11 @@ int dta_tree_attn_prepare(dta_tree_t* tree, const dta_attn_params_t* params);
  * device memory for the tree's metadata and waits for its upload (see the general
  * rules above); later calls with the same configuration only enqueue.
  * bf16 mode multiplies in bf16 on the matrix cores and accumulates / does the
- * softmax in fp32; fp32 mode is fp32 throughout.
+ * softmax in fp32.  fp32 mode is fp32 throughout: products either on the fp32 matrix
+ * instruction or, in launches that fill the chip, of all 24 bits of both factors in
+ * three parts each on the bf16 one (no further from 64 bits).  There, and in the backward
+ * pass, numbers below 2^-110 in magnitude are held to 2^-134, and probabilities below
+ * 2^-126 count as 0.
  */
 int dta_tree_attn_fwd(dta_tree_t* tree, const dta_attn_params_t* params, const void* q,
                       const void* k, const void* v, void* o, float* lse, void* workspace,
@@ -202,6 +206,7 @@ int dta_tree_attn_fwd(dta_tree_t* tree, const dta_attn_params_t* params, const v
  *   dk[k,g] = scale * sum_{h in group g} sum_{t : k in anc(t)} ds_tk q_t
  *   dv[k,g] =         sum_{h in group g} sum_{t : k in anc(t)} p_tk d_o_t
  *   q,k,v,o,d_o : device inputs as in forward; lse : device [T,Hq] fp32 from forward
+ *        on the same q, k and scale (with another one's, probabilities may overflow)
  *   dq : device [T,Hq,d] out;  dk, dv : device [T,Hkv,d] out.  All three are
  *        OVERWRITTEN (each element written exactly once, no atomics).
  *   workspace : device, >= dta_tree_attn_workspace_bytes(tree, params, 1)

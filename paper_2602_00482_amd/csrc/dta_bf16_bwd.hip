@@ -779,7 +779,7 @@ int launch_bwd_bf16_hd(const LaunchArgs& a) {
       { int ls = launch_status(__func__); if (ls != DTA_OK) return ls; }
     }
     // Waves leave out masked chunks that none of their rows sees, with head_dim 64 where that is worth the branch, as
-    // in the forward kernel.  Measured, without / with: two-answer pairs, 16/16 heads of 128 721 / 662 us, of 64 (pass of
+    // in the forward kernel.  Measured, without / with: two-answer pairs, 16/16 heads of 128 673 / 643 us, of 64 (pass of
     // dQ) 267 / 257; multi-turn agents, 32/8 heads of 128 7250 / 7220, of 64 4210 / 4250.  (Blocks of two groups lose 7 %.)
     auto kernel = a.tc.q_split ? dq_bf16_kernel<HD, 2> : dq_bf16_kernel<HD, 1, true>;
     if constexpr (HD == 64) {

@@ -1,16 +1,16 @@
 // fp32 tree attention for launches that fill the chip: forward, dQ and dK/dV with every
 // product on the bf16 matrix instruction, whose rate is 16 times the fp32 one's.
 //
-// An fp32 number is the sum of three bf16 numbers (planes) of 8 bits each: x = x1 + x2 + x3 with
-// x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2, each subtraction exact.  A product
-// x y is x1 y1 + x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1; what is left out is below 2^-26 |x y|,
-// less than the rounding of one fp32 addition, and the matrix instruction adds products
-// that are exact in fp32 accumulators.  Six bf16 products of 16x16x32 take 96 cycles where the
-// fp32 instruction takes 256.  Softmax, exponentials and everything between the products is
-// fp32 as in dta_f32_kernels.hip.
+// An fp32 number is the sum of three bf16 numbers (planes) of 8 bits each (the split that Henry, Tang and Heinecke
+// describe in "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", 2019):
+// x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2, each subtraction exact.  A product
+// x y is x1 y1 + x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1; x2 y3, x3 y2 and x3 y3 are left out, together up to
+// 2^-24 |x y| (what rounding one product to fp32 costs; 2^-26 and less for most).  The matrix instruction adds
+// exact products in fp32 accumulators.  Six bf16 products of 16x16x32 take 96 cycles where the
+// fp32 instruction takes 256.  Softmax, exponentials and everything between the products is fp32.
 //
-// bf16 has fp32's exponent range, so nothing has to be scaled (below 2^-110 the third part is
-// subnormal).  Numbers from 2^40 on, infinities among them, do not take part: the six products of large ones
+// bf16 has fp32's exponent range, so nothing has to be scaled.  Below 2^-110 the third part is subnormal, and a number
+// is held to 2^-134; probabilities below 2^-126 count as 0.  Numbers from 2^40 on, infinities among them, do not take part: the six products of large ones
 // overflow with either sign, which adds up to NaN where the product is an infinity, and what bf16 rounds to infinity has no
 // parts at all.  (Three factors below 2^40, summed over head_dim, stay below 2^127.)  From the first streamed chunk that
 // holds one, a block goes on on the fp32 instruction (slow_dot, slow_apply); so does a block of the backward kernels with
@@ -24,15 +24,16 @@
 // after next.  One split then serves eight waves, and one barrier a step is enough.
 //
 // What bounds the kernels is the issue of vector instructions beside the products: per product of the
-// forward 4 (the split of the streamed rows 1.4, softmax and the split of P the rest), dQ and
-// dK/dV 2.5, of which two go under a product for free where they alternate with it; the matrix pipe is
-// busy 40 % (forward), 46 % (dQ) and 57 % (dK/dV) of the time at 2.2 GHz.  Larger blocks would
+// forward 4.6 (the split of the streamed rows 1.4, softmax, the split of P and the sums of O the rest), dQ 3.0 and
+// dK/dV 2.4, of which two go under a product for free where they alternate with it; the matrix pipe is
+// busy 39 % (forward), 45 % (dQ) and 55 % (dK/dV) of the time at 2.2 GHz.  Larger blocks would
 // share a split among more rows, but 16 more columns per wave do not fit in the registers of dQ and dK/dV.
-// Measured on MI355X, products on the fp32 instruction before, and now:
-//   4862 tokens (a prompt with 16 answers), 32/8 heads of 128: forward 376 -> 289 us, dQ 540 -> 380,
-//     dK/dV 655 -> 421, reduce 14.5 -> 9
-//   9000 row tiles of 16, 16/16 heads of 128, one prompt with 8 answers: forward 1348 -> 932 us, backward 4427 -> 2612
-//   relative 2-norm errors against 64 bits on the first: O 3.8 -> 3.1e-7, dQ 5.1 -> 4.1e-7, dK 6.9 -> 6.1e-7, dV 6.6 -> 5.9e-7
+// Measured on MI355X, products on the fp32 instruction before, and now (kernel trace, medians):
+//   4862 tokens (a prompt with 16 answers), 32/8 heads of 128: forward 386 -> 300 us, dQ 554 -> 385,
+//     dK/dV 669 -> 435, reduce 14.6 -> 8.1; of 64: forward 223 -> 192, dQ 297 -> 233, dK/dV 365 -> 269
+//   8898 tokens (a prompt with 8 answers), 16/16 heads of 128: forward 1362 -> 1011 us, dQ 1995 -> 1221, dK/dV 2331 -> 1401
+//   relative 2-norm errors against 64 bits, 4546 tokens, 32/8 heads of 128: O 3.87 -> 1.65e-7, LSE 4.3 -> 4.0e-8, dQ 5.1 -> 3.2e-7,
+//     dK 6.8 -> 3.5e-7, dV 6.4 -> 3.3e-7; 6600 tokens, 4/4 heads of 64: O 3.16 -> 1.66e-7, dQ 4.9 -> 3.6e-7, dK 4.8 -> 3.6e-7
 #include <hip/hip_runtime.h>
 
 #include "dta_f32_common.h"
@@ -65,8 +66,8 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t (&p)[kPlanes])
   }
 }
 
-// e^x to fp32 accuracy for the arguments of a softmax (not above 88), without the range handling
-// of expf: 2^t with t = x log2 e rounded, times 1 + (x - t ln 2).  0 below -87; the
+// e^x to fp32 accuracy for the arguments of a softmax (not above 88; LSE has to be the forward's), without the range
+// handling of expf: 2^t with t = x log2 e rounded, times 1 + (x - t ln 2).  0 below -87; the
 // correction is NaN for x = -infinity, where the maximum drops it.  NaN stays.
 constexpr float kLn2Low = -1.9046543e-9f;   // ln 2 = kLn2 + kLn2Low
 __device__ __forceinline__ float exp_f32(float x) {
@@ -238,7 +239,7 @@ __device__ __forceinline__ void dot(f32x4 (&S)[2], Pair (&ring)[kRing], const ui
 
 // acc[cb] += (columns 16*cb .. of the tile) . w, contracted over the tile's rows.  The six products of a pair
 // of blocks are summed from zero and added to acc while the next pair's run: acc is rounded once per chunk of 32
-// rows, not six times (relative errors of O, head_dim 64, 900 tokens, 32/8 heads, 2.1 -> 1.2e-7).
+// rows, not six times: relative errors of O, 900 tokens, 32/8 heads of 64, 2.1 -> 1.2e-7, for 2 % of the time.
 template <int HD, typename Work, typename Next>
 __device__ __forceinline__ void apply(f32x4 (&acc)[HD / 16], Pair (&ring)[kRing], const uint16_t* cols,
                                       const bf16x8 (&w)[kPlanes], Work work, Next next) {

@@ -645,21 +645,22 @@ namespace {
 // share out the keys (small, dta_f32_kernels.hip), or on the bf16 one with operands in three
 // parts (planes, dta_f32_planes.hip), whose blocks of 8 row tiles of 16 and 128-key tiles need a
 // launch that fills the chip.  Measured on MI355X, in us, small / planes:
-//   trees (a prompt with 8 answers), forward and backward   1000 row tiles: 38 + 124 / 46 + 120 (16/16 heads of
-//             128), 25 + 83 / 29 + 77 (32/8), 19 + 56 / 21 + 66 (64/8), 42 + 116 / 43 + 107 (8/2 heads of 64);
-//             1200: 51 + 150 / 47 + 124, 38 + 87 / 29 + 96, 26 + 75 / 21 + 67, 57 + 142 / 48 + 119, 38 + 95 / 29 + 106 (32/1);
-//             1600: 82 + 222 / 59 + 163, 50 + 146 / 32 + 118, 40 + 109 / 24 + 92, 80 + 220 / 59 + 154, 50 + 144 / 32 + 130;
-//             2000: 105 + 323 / 73 + 217, 65 + 207 / 41 + 150
-//   forward of a tree with few branches, whose longest walk is twice the average one: one segment, 1200 row tiles 52 / 71
-//             (16/16 heads of 64), 92 / 136 (8/2), 69 / 94 (12/4), 96 / 109 (16/16 of 128), 186 / 208 (8/2); 1600: 82 / 94, 151 / 179,
-//             53 / 50 (32/8), 136 / 143, 259 / 275 (8/2 of 128), 47 / 45 (64/8); 2000: 119 / 115, 223 / 223, 235 / 176
-//   forward of a segment   rows after 512 keys, 1200: 134 / 154 (16/16, 1200 rows), 113 / 106 (32/8, 600 rows);
-//             1600: 282 / 327 (8/2, 3200 rows), 116 / 94 (64/8, 400 rows); 2000: 251 / 221, 400 / 396; after
-//             4096 keys, 1000: 349 / 397 (32/8), 1200: 638 / 404, 687 / 561 (8/2), 340 / 294 (16/16 heads of 64); 2400 rows
-//             after 2048, 8/2 heads of 64 234 / 253, 2900 270 / 281
+//   trees (a prompt with 8 answers), forward + backward, heads of 128   1000 row tiles: 39 + 121 / 50 + 125 (16/16),
+//             24 + 81 / 29 + 76 (32/8), 18 + 53 / 20 + 64 (64/8), 63 + 187 / 74 + 180 (8/2); 1200: 50 + 142 / 56 + 134,
+//             36 + 92 / 32 + 99, 25 + 73 / 23 + 69, 80 + 242 / 85 + 206, 36 + 96 / 32 + 108 (32/1); 1600: 77 + 224 / 65 + 171,
+//             50 + 137 / 35 + 123, 38 + 106 / 27 + 95, 146 + 352 / 107 + 271; 2000: 111 + 323 / 81 + 227, 65 + 204 / 45 + 154,
+//             45 + 143 / 30 + 108; of 64   1000: 29 + 82 / 34 + 78, 22 + 56 / 19 + 50, 20 + 42 / 13 + 43, 41 + 114 / 49 + 114;
+//             1200: 37 + 100 / 38 + 86, 29 + 64 / 21 + 65, 25 + 50 / 15 + 47, 56 + 141 / 57 + 130
+//   forward of a tree with few branches, whose longest walk is twice the average one: one segment, 1200 row tiles 52 / 74
+//             (16/16 heads of 64), 91 / 142 (8/2), 68 / 98 (12/4), 96 / 112 (16/16 of 128), 185 / 216 (8/2); 1600: 82 / 98, 149 / 188,
+//             52 / 52 (32/8), 135 / 148, 257 / 285 (8/2 of 128), 47 / 46 (64/8); 2000: 119 / 121, 222 / 234, 233 / 183
+//   forward of a segment, heads of 128   after 512 keys, 1200: 134 / 157 (16/16, 1200 rows), 112 / 107 (32/8, 600 rows);
+//             1800: 221 / 211, 155 / 134, 338 / 367 (8/2, 3600 rows); after 2048, 1000: 197 / 233 (32/8), 1200: 337 / 241,
+//             388 / 396 (8/2), 351 / 291 (16/16); of 64   after 512, 1200: 91 / 104, 72 / 70; after 2048, 1200: 178 / 159 (32/8),
+//             198 / 192 (16/16), 207 / 214 (12/4, 1600 rows), 233 / 260 (8/2, 2400 rows); 1450: 269 / 288 (8/2, 2900 rows)
 //   backward of a segment, whose dK/dV walks are not cut: with one block per CU up to 256 key tiles of 128 the planes
 //             form takes what its longest walk takes however many tiles there are, the small one the sum of its walks.  What
-//             decides is the number of key tiles that the average row sees, at any number of rows.  Small / planes: 60 to
+//             decides is the number of key tiles that the average row sees, at any number of rows: 60 to
 //             70 tiles 1276 / 1762 (8/2 heads of 64, 2060 row tiles), 2709 / 3870 (32/1), 591 / 730 (32/8 of 128); 79 to 94
 //             607 / 643, 1012 / 1034 (32/8, 3000), 5072 / 5384 (8/2 of 64, 6000), 4716 / 4535 (8/2 of 128, 4000 after 2048);
 //             102 to 114 -2 to +21 % for small; 126 1276 / 1005 (12/4 of 128, 3000); 159 2673 / 1656 (64/8 of 128, 4000), 1534 / 1021 (of 64)
