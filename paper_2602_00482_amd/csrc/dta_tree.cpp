@@ -664,6 +664,9 @@ namespace {
 //             70 tiles 1276 / 1762 (8/2 heads of 64, 2060 row tiles), 2709 / 3870 (32/1), 591 / 730 (32/8 of 128); 79 to 94
 //             607 / 643, 1012 / 1034 (32/8, 3000), 5072 / 5384 (8/2 of 64, 6000), 4716 / 4535 (8/2 of 128, 4000 after 2048);
 //             102 to 114 -2 to +21 % for small; 126 1276 / 1005 (12/4 of 128, 3000); 159 2673 / 1656 (64/8 of 128, 4000), 1534 / 1021 (of 64)
+// One form for both directions: what the backward recomputes from an LSE of the other form's scores, whose roundings are
+// others, is further from 64 bits: dV of queries 3 / 8 / 30 times N(0,1), one segment of 1300 tokens, 16/16 heads of 64, 5.3 / 8.6 / 22e-7
+// small, 4.1 / 7.2 / 21e-7 planes, 7.2 / 21 / 80e-7 small forward and planes backward (N(0,1): 3.1, 2.5, 2.6e-7).
 // (The planes' softmax multiplies by |softmax_scale| log2 e, which has to be a normal number: scales beyond 2^100 or
 // below 2^-100 stay on the fp32 instruction.)
 bool f32_planes(const CallShape& c, const dta_attn_params_t* p) {
@@ -672,16 +675,20 @@ bool f32_planes(const CallShape& c, const dta_attn_params_t* p) {
   const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
   if (row_tiles < 1200) return false;
   if (!c.segment) {
-    if (c.backward || row_tiles >= 2048 || c.path == 0) return true;
+    if (row_tiles >= 2048 || c.path == 0) return true;
     // One round of blocks: the planes form takes what its longest walk takes (1.85 us per 32 keys, 2.9 with heads of
-    // 128), the small one the sum of its walks.  A prompt with answers has walks of like length, a chain does not.
+    // 128), the small one the sum of its walks.  A prompt with answers has walks of like length, a chain does not.  (The
+    // backward gains more: a tenth more of the forward's time, a twentieth with heads of 128, is allowed for.)
     if (4 * c.path * c.rows < 7 * c.pairs) return p->head_dim == 64 || row_tiles >= 1250;
     const double path = (double)c.path, pairs = (double)c.pairs * p->n_q_heads / 16e6;
-    return p->head_dim == 64 ? 5 + 0.058 * path < 12 + 54 * pairs : 6 + 0.09 * path < 10 + 100 * pairs;
+    return p->head_dim == 64 ? 5 + 0.058 * path < 1.1 * (12 + 54 * pairs) : 6 + 0.09 * path < 1.05 * (10 + 100 * pairs);
   }
+  // (From 3500 row tiles on the small form's forward would take up to 1.4 times what it took on the fp32 instruction in
+  // blocks that fill the chip, below no longer.)
+  if (row_tiles >= 3500) return true;
   // (a row sees the keys before the segment and half of its own rows' on average)
   const int64_t seen = (2 * c.keys - c.rows) * p->n_kv_heads / 256;
-  if (c.backward && seen < 95) return false;
+  if (seen < 95) return false;
   if (row_tiles >= 2048) return true;
   // (heads of 64: the longest walk against their sum, as above)
   const bool one_round = p->head_dim == 128 || c.keys >= 2 * c.rows ||
@@ -701,31 +708,21 @@ int choose_tiles(const dta_attn_params_t* p, TileChoice* out, const CallShape& c
     // in us: 256 row tiles of 16, head_dim 128, 32/8 heads 35 / 53, 16/16 34 / 51; 512: 43 / 56,
     // 56 / 63; head_dim 64, 8/2 heads, 256: 32 / 37.  Above, a CU gets two such blocks one after
     // the other: 16/16 heads of 64, 256 row and 256 key blocks in one launch, 29 / 23.
-    TileChoice f{}, b{};
-    auto choose = [&](bool backward, TileChoice* t) {
-      CallShape c = call;
-      c.backward = backward;
-      t->planes = f32_planes(c, p);
-      t->q_small = t->k_small = !t->planes;
-      const int split = t->planes ? 1 : p->head_dim == 64 ? 4 : 2;
-      const int64_t row_tiles = c.rows / 16 * p->n_q_heads;
-      const int64_t row_blocks = row_tiles * split / 4, key_blocks = c.keys / 16 * p->n_kv_heads * split / 4;
-      t->tiny = t->q_small && row_blocks <= kNumCUs && (p->head_dim == 128 || row_blocks + key_blocks <= kNumCUs * 4 / 3);
-      const int R = (t->tiny ? 4 : 8) / split;
-      t->hb = 1;
-      while (t->hb < R && G % (2 * t->hb) == 0) t->hb *= 2;
-      t->hblocks = G / t->hb;
-      t->bn = t->planes ? 128 : 16 * R;
-      t->walk = KvWalk{32, 4 * split, kNumCUs};   // an iteration takes a wave several microseconds, so cut walks may be short
-      return 16 * (R / t->hb);
-    };
-    const int fwd_bm = choose(false, &f);
-    b.bm = choose(true, &b);
-    b.walk.fwd_bm = fwd_bm == b.bm ? 0 : fwd_bm;
-    f.bm = b.bm;
-    f.bn = b.bn;
-    f.walk = b.walk;
-    *out = call.backward ? b : f;
+    TileChoice t{};
+    t.planes = f32_planes(call, p);
+    t.q_small = t.k_small = !t.planes;
+    const int split = t.planes ? 1 : p->head_dim == 64 ? 4 : 2;
+    const int64_t row_tiles = call.rows / 16 * p->n_q_heads;
+    const int64_t row_blocks = row_tiles * split / 4, key_blocks = call.keys / 16 * p->n_kv_heads * split / 4;
+    t.tiny = t.q_small && row_blocks <= kNumCUs && (p->head_dim == 128 || row_blocks + key_blocks <= kNumCUs * 4 / 3);
+    const int R = (t.tiny ? 4 : 8) / split;
+    t.hb = 1;
+    while (t.hb < R && G % (2 * t.hb) == 0) t.hb *= 2;
+    t.hblocks = G / t.hb;
+    t.bm = 16 * (R / t.hb);
+    t.bn = t.planes ? 128 : 16 * R;
+    t.walk = KvWalk{32, 4 * split, kNumCUs};   // an iteration takes a wave several microseconds, so cut walks may be short
+    *out = t;
   } else {
     // eight waves per block: hb q heads of the group x (R/hb) 32-row query blocks
     TileChoice f{}, b{};

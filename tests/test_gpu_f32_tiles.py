@@ -264,7 +264,7 @@ def test_scales_at_the_ends_of_the_range(Hq, Hkv, scale, d):
 @pytest.mark.parametrize("Hq,Hkv,d,seg,factor,limits", [
     (16, 16, 64, [600, 500, 300, 250], 1, dict(o=2.19e-7, dq=3.71e-7, dk=3.78e-7, dv=3.25e-7)),
     (16, 16, 128, [600, 500, 300, 250], 1, dict(o=2.86e-7, dq=4.38e-7, dk=4.25e-7, dv=3.57e-7)),
-    (4, 4, 64, [5000, 700, 900], 1, dict(o=3.16e-7, dq=4.88e-7, dk=4.84e-7, dv=4.29e-7)),
+    (8, 8, 64, [5000, 700, 900], 1, dict(o=3.16e-7, dq=4.88e-7, dk=4.84e-7, dv=4.29e-7)),   # limits: 4/4 heads
     (4, 4, 128, [5000, 700, 900], 1, dict(o=4.26e-7, dq=5.83e-7, dk=5.49e-7, dv=4.89e-7)),
     # LSE, and the scores of large queries
     (32, 8, 64, [300, 250, 200, 150], 1, dict(o=1.96e-7, lse=4.39e-8)),
@@ -372,3 +372,38 @@ def test_backward_of_numbers_without_three_parts(what, Hq, Hkv, parent, seg, row
         else:
             assert rel_err(got[n][..., rest], r[..., rest]) <= 1e-5, n
             assert rel_err(got[n][..., col], r[..., col]) <= 1e-5, (n, "large column")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,before,rows,limits", [
+    (32, 8, 64, 512, 1000, dict(o=6.30e-7, lse=6.25e-8, dq=1.32e-6, dk=1.32e-6, dv=8.87e-7)),
+    (32, 8, 128, 512, 1000, dict(o=8.67e-7, lse=8.30e-8, dq=1.78e-6, dk=1.79e-6, dv=1.18e-6)),
+    (32, 1, 64, 100, 1100, dict(o=6.29e-7, lse=6.28e-8, dq=1.36e-6, dk=1.75e-6, dv=1.33e-6)),
+    (8, 2, 128, 512, 5200, dict(o=1.06e-6, lse=7.95e-8, dq=2.03e-6, dk=2.09e-6, dv=1.47e-6)),
+])
+def test_errors_of_segment_calls(Hq, Hkv, d, before, rows, limits):
+    """Relative 2-norm errors against 64 bits of pushes and pops with queries of 8 times N(0,1), whose scores
+    a backward call has to round as the forward did: no larger than in the fp32 kernels that fill the chip or
+    share out the keys on the fp32 instruction (measured)."""
+    import torch
+    parent, seg = np.array([-1, 0], dtype=np.int32), np.array([before, rows], dtype=np.int32)
+    T, scale = before + rows, float(np.float32(1.0 / math.sqrt(d)))
+    x = make_inputs_numpy(T, Hq, Hkv, d, 41, dtype="f32")
+    x["q"] *= np.float32(8)
+    t = {n: torch.from_numpy(a).cuda() for n, a in x.items()}
+    p = dta.AttnParams(Hq, Hkv, d, scale, dta.F32)
+    tree = dta.tree_build(parent, seg)
+    o, lse, dq = torch.zeros_like(t["q"]), torch.zeros((T, Hq), device="cuda"), torch.zeros_like(t["q"])
+    dk, dv = (torch.zeros((T, Hkv, d), device="cuda") for _ in range(2))
+    ws = torch.empty(dta.workspace_bytes(tree, p, True), dtype=torch.uint8, device="cuda")
+    for a, b in ((0, before), (before, T)):
+        dta.tree_attn_fwd_segment(tree, p, a, b, t["q"], t["k"], t["v"], o, lse)
+    for a, b in ((before, T), (0, before)):
+        dta.tree_attn_bwd_segment(tree, p, a, b, t["q"], t["k"], t["v"], o, lse, t["do"], dq, dk, dv, ws)
+    torch.cuda.synchronize()
+    tree.destroy()
+    ref = dict(zip(("o", "lse"), B.forward(parent, seg, x["q"], x["k"], x["v"], scale)))
+    ref.update(zip(("dq", "dk", "dv"), B.backward(parent, seg, x["q"], x["k"], x["v"], x["do"], scale)))
+    err = {n: float(np.linalg.norm(a.double().cpu().numpy() - ref[n]) / np.linalg.norm(ref[n]))
+           for n, a in zip(("o", "lse", "dq", "dk", "dv"), (o, lse, dq, dk, dv))}
+    print(" ".join(f"{n} {e:.3e}" for n, e in err.items()), flush=True)
+    assert all(err[n] <= limits[n] for n in limits), err

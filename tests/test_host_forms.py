@@ -120,29 +120,26 @@ def test_one_schedule_serves_both_directions(forms, segment, d):
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_forms_of_fp32_calls(forms, d):
-    """Trees (before = None) and segments on both sides of the measured crossings; key tiles of 128 say
-    that dK/dV multiplies in three bf16 parts."""
-    calls = [   # heads, tokens before, rows, forward, dQ, key tile (None: a small form's)
-        (32, 8, None, 607, "small", "small", None), (32, 8, None, 608, "large", "large", 128),
-        (32, 1, None, 1020, "large", "large", 128), (32, 8, None, 1100, "large", "large", 128),
-        (32, 8, None, 1290, "large", "large", 128), (16, 16, None, 9000, "large", "large", 128),
-        (16, 16, 512, 1300, "small", "small", None), (32, 8, 512, 700, "large", "small", None),
-        (32, 8, 512, 1000, "large", "small", None), (32, 8, 4096, 620, "large", "large", 128),
-        (8, 2, 4096, 2400, "large", "small", None), (8, 2, 4096, 4200, "large", "large", 128),
-        (8, 2, 512, 5200, "large", "small", None), (32, 8, 4096, 500, "small", "small", None),
-        # segments whose average row sees 93, 97, 190 and 39 key tiles of 128
-        (32, 8, 512, 1960, "large", "small", None), (32, 8, 512, 2080, "large", "large", 128),
-        (8, 2, 8192, 8000, "large", "large", 128), (32, 1, 2048, 5900, "large", "small", None),
+    """Trees (before = None) and segments on both sides of the measured crossings; both directions take
+    one form, and key tiles of 128 say that dK/dV multiplies in three bf16 parts."""
+    calls = [   # heads, tokens before, rows, form
+        (32, 8, None, 607, "small"), (32, 8, None, 608, "large"), (32, 1, None, 1020, "large"),
+        (32, 8, None, 1100, "large"), (32, 8, None, 1290, "large"), (16, 16, None, 9000, "large"),
+        (16, 16, 512, 1300, "small"), (32, 8, 4096, 620, "large"), (32, 8, 4096, 500, "small"),
+        # segments whose average row sees 53, 64, 82, 97, 93, 97, 190 and 39 key tiles of 128
+        (32, 8, 512, 700, "small"), (32, 8, 512, 1000, "small"), (8, 2, 4096, 2400, "small"), (8, 2, 4096, 4200, "large"),
+        (32, 8, 1100, 800, "small"), (32, 8, 1160, 800, "large"), (8, 2, 8192, 8000, "large"), (32, 1, 2048, 1700, "small"),
+        (32, 1, 2048, 1800, "large"), (8, 2, 512, 5200, "small"), (8, 2, 512, 7100, "large"),   # 3500 row tiles
     ]
     args = []
-    for Hq, Hkv, before, rows, *_ in calls:
+    for Hq, Hkv, before, rows, _ in calls:
         keys = rows + (before or 0)
         args.append((Hq, Hkv, d, dta.F32, 0, int(before is not None), rows, keys, 1))
     f = forms(args)
     b = forms([a[:4] + (1,) + a[5:] for a in args])
     for c, x, y in zip(calls, f, b):
-        assert (x[0].replace("tiny", "small"), y[0].replace("tiny", "small")) == c[4:6], (c, x, y)
-        assert y[3] == c[6] or (c[6] is None and y[3] < 128 and y[1] == "small"), (c, y)
+        assert x == y, (c, x, y)
+        assert (x[0].replace("tiny", "small"), x[3] == 128) == (c[4], c[4] == "large"), (c, x)
 
 
 @pytest.mark.parametrize("Hq,Hkv,d,seg,small", [
@@ -150,16 +147,13 @@ def test_forms_of_fp32_calls(forms, d):
     (16, 16, 64, [1601], True), (32, 8, 64, [651], True), (32, 8, 64, [1001], False), (16, 16, 128, [1200], True), (16, 16, 128, [2000], False),
     (16, 16, 128, [260, 195, 65, 156, 104, 130, 130, 182, 79], False),
 ])
-def test_form_of_an_fp32_trees_forward_follows_its_longest_walk(Hq, Hkv, d, seg, small):
-    """1200 row tiles and more: the forward of a tree without branches, which is as long as its longest walk, stays in
+def test_form_of_an_fp32_tree_follows_its_longest_walk(Hq, Hkv, d, seg, small):
+    """1200 row tiles and more: a tree without branches, whose forward is as long as its longest walk, stays in
     blocks that share out the keys until they are a round and a half; a prompt with answers does not."""
     tree = dta.tree_build(np.array([-1] + [0] * (len(seg) - 1), dtype=np.int32), np.array(seg, dtype=np.int32))
     info = tree.schedule_info(dta.AttnParams(Hq, Hkv, d, 0.1, dta.F32))
     tree.destroy()
-    heads = min(8, Hq // Hkv)
-    large = 128 // heads   # tokens of a block of 8 row tiles
-    assert info["bwd_kv_tile_tokens"] == 128
-    assert (info["fwd_q_tile_tokens"] < large) == small, info
+    assert (info["bwd_kv_tile_tokens"] < 128) == small, info
 
 
 def test_the_gpu_tests_reach_the_forms_they_name(forms):
